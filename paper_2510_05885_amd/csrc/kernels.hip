@@ -154,17 +154,153 @@ __device__ __forceinline__ void wave_fence() {
     __asm__ volatile("" ::: "memory");
 }
 
+// Value of lane 16 * (lane / 16) + U of each 16-lane row (DPP row_newbcast).
+template <int U>
+__device__ __forceinline__ double rowbcast(double v) {
+    const long long b = __builtin_bit_cast(long long, v);
+    const long long r = __builtin_amdgcn_update_dpp(b, b, 0x150 + U, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, r);
+}
+template <int U>
+__device__ __forceinline__ float rowbcast(float v) {
+    const int b = __builtin_bit_cast(int, v);
+    const int r = __builtin_amdgcn_update_dpp(b, b, 0x150 + U, 0xf, 0xf, true);
+    return __builtin_bit_cast(float, r);
+}
+template <typename T>
+__device__ __forceinline__ T rowbcast_n(T v, int u) {   // u: a compile-time constant after unrolling
+    switch (u) {
+        case 0: return rowbcast<0>(v);   case 1: return rowbcast<1>(v);   case 2: return rowbcast<2>(v);
+        case 3: return rowbcast<3>(v);   case 4: return rowbcast<4>(v);   case 5: return rowbcast<5>(v);
+        case 6: return rowbcast<6>(v);   case 7: return rowbcast<7>(v);   case 8: return rowbcast<8>(v);
+        case 9: return rowbcast<9>(v);   case 10: return rowbcast<10>(v); case 11: return rowbcast<11>(v);
+        case 12: return rowbcast<12>(v); case 13: return rowbcast<13>(v); case 14: return rowbcast<14>(v);
+        default: return rowbcast<15>(v);
+    }
+}
+
+// The pivots of one 16-column sub-panel, all above the static-pivot threshold:
+// right-looking LDL^T of the 16 x 16 diagonal block with, for kExt, one more
+// row per lane below it.  rp: row lane % 16 of the diagonal block, the same in
+// each 16-lane row of the wave, so that the pivot and the multipliers of the
+// other columns come from lane t and u of the lane's own row by DPP (one
+// instruction, against two readlanes through scalar registers); x: the lane's
+// own row below.  On return both hold L, and dk the pivot of row lane % 16.
+// The next pivot's column is updated first, so that its reciprocal runs under
+// the other columns' updates.  The chain was bound by the issue of ~45
+// instructions per pivot (290 cycles, against ~65 of dependent latency); the
+// threshold test is left to the caller, once for all 16 pivots.
+// Pivots t >= bw are skipped.
+template <typename T, bool kExt>
+__device__ __forceinline__ void pivots16(T (&rp)[16], T (&x)[16], T& dk, int bw, int li) {
+    T d = rowbcast_n(rp[0], 0);
+    T inv = fast_rcp(d);
+    dk = T(1);
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+        if (t >= bw) continue;   // uniform
+        const T dt = d;
+        const T l = rp[t] * inv;
+        const T lx = kExt ? x[t] * inv : T(0);
+        if (t + 1 < 16) {
+            const T c = rowbcast_n(rp[t], t + 1);
+            rp[t + 1] -= l * c;
+            if (kExt) x[t + 1] -= lx * c;
+            d = rowbcast_n(rp[t + 1], t + 1);
+            inv = fast_rcp(d);
+        }
+#pragma unroll
+        for (int u = t + 2; u < 16; ++u) {
+            const T c = rowbcast_n(rp[t], u);
+            rp[u] -= l * c;
+            if (kExt) x[u] -= lx * c;
+        }
+        dk = li == t ? dt : dk;
+        rp[t] = l;
+        if (kExt) x[t] = lx;
+    }
+}
+
+// Whether every pivot dk of a sub-panel's first bw (lane % 16 < bw) is finite
+// and at or above the larger threshold, so that the static-pivot rule of
+// Sec. 3.1 keeps them all; and their counts (positive, negative, zero).
+template <typename T>
+__device__ __forceinline__ bool pivots_plain(T dk, const PivThr<T>& thr, int bw, int lane, unsigned int* n3) {
+    const double a = fabs(to_d(dk));
+    const bool in = lane < bw;
+    const bool ok = a >= thr.p && a >= thr.n && isfinite(a);
+    if (__ballot(in && !ok) != 0ULL) return false;
+    n3[0] = __popcll(__ballot(in && to_d(dk) > 0.0));
+    n3[1] = __popcll(__ballot(in && to_d(dk) < 0.0));
+    n3[2] = __popcll(__ballot(in && to_d(dk) == 0.0));
+    return true;
+}
+
 // Partial LDL^T of the leading p columns of an f x f lower-triangular matrix
 // held in LDS (column-major, leading dimension lda), with the static-pivot
 // rule of Sec. 3.1.  Blocked by 16 columns: wave 0 factors each 16-column
-// sub-panel over all rows below it (one row per lane, no workgroup barrier),
-// then the four waves apply the rank-16 update to the trailing lower matrix
-// on MFMA.  On return A holds L (unit lower, strictly below the diagonal) in
+// sub-panel with the 64 rows below its diagonal block, wave 1 (which repeats
+// the diagonal block) the rows beyond those, then the four waves apply the
+// rank-16 update to the trailing lower matrix on MFMA.  A sub-panel with a
+// pivot below its threshold is done again by wave 0 alone, pivot by pivot.
+// On return A holds L (unit lower, strictly below the diagonal) in
 // its first p columns, d_k on the diagonal and in dv[k], and the Schur
 // complement in the trailing (f - p) x (f - p) part.  sgn[k] is the block sign
 // of pivot k.  Lane 0 of wave 0 accumulates the pivot counts into cnt[4].
 // kTwoRows: f may exceed 64 + (sub-panel start), so a lane holds two rows.
 // Must be called by all 256 threads; ends with a barrier.
+template <typename T>
+__device__ __forceinline__ void store_subpanel(T* A, int lda, int kb, int bw, int lane, int row, int f,
+                                               const T (&rp)[16], const T (&x)[16], T dk, bool diag) {
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+        if (t >= bw) continue;   // uniform
+        if (diag && lane < 16 && lane >= t && kb + lane < f) A[(kb + lane) + (kb + t) * lda] = lane == t ? dk : rp[t];
+        if (row < f) A[row + (kb + t) * lda] = x[t];
+    }
+}
+
+// A sub-panel with a pivot that the static-pivot rule replaces (or a
+// non-finite one), by one wave straight in LDS, pivot by pivot: columns kb ..
+// kb + bw of the rows kb .. f - 1 of A.  Bit t of neg: pivot t takes the
+// negative sign.  Each entry takes the operations of pivots16 in the same
+// order.  Rolled on purpose: it is rare, and must not set the register budget
+// of the kernels around it.  Counts pivots t < bcount.
+template <typename T>
+__device__ __forceinline__ void subpanel_by_pivot(T* A, int lda, int f, int kb, int bw, int bcount, unsigned int neg,
+                                                  T* dv, const PivThr<T>& thr, int lane, unsigned int* cnt,
+                                                  bool& bad_any) {
+#pragma unroll 1
+    for (int t = 0; t < bw; ++t) {
+        T* col = A + (kb + t) * lda;
+        bool pert, bad;
+        const int sg = (neg >> t & 1u) ? -1 : 1;
+        const T draw = col[kb + t];
+        const T inv0 = fast_rcp(draw);
+        const T dk = static_pivot(draw, thr, sg, pert, bad);
+        const T inv = pert ? thr.inv(sg) : inv0;
+#pragma unroll 1
+        for (int i = kb + t + 1 + lane; i < f; i += 64) {
+            const T l = col[i] * inv;
+#pragma unroll 1
+            for (int u = t + 1; u < bw && kb + u <= i; ++u) A[i + (kb + u) * lda] -= l * col[kb + u];
+        }
+        wave_fence();   // every row has taken the unscaled column
+#pragma unroll 1
+        for (int i = kb + t + 1 + lane; i < f; i += 64) col[i] *= inv;
+        if (lane == 0) {
+            col[kb + t] = dk;
+            dv[kb + t] = dk;
+            if (t < bcount) {
+                const double dd = to_d(dk);
+                cnt[0] += dd > 0.0; cnt[1] += dd < 0.0; cnt[2] += dd == 0.0; cnt[3] += pert;
+                bad_any |= bad;
+            }
+        }
+        wave_fence();
+    }
+}
+
 template <typename T, bool kTwoRows>
 __device__ void lds_partial_ldlt(T* A, int lda, int f, int p, T* dv, const int8_t* sgn, const PivThr<T>& thr,
                                  unsigned int* cnt, bool& bad_out) {
@@ -173,57 +309,35 @@ __device__ void lds_partial_ldlt(T* A, int lda, int f, int p, T* dv, const int8_
     bool bad_any = false;
     for (int kb = 0; kb < p; kb += 16) {
         const int bw = min(16, p - kb);
-        if (wave == 0) {
-            // Rows kb + lane and kb + lane + 64 of the sub-panel, in registers.
-            // Slots above a row's diagonal are scratch: they take the same
-            // unpredicated updates as the rest, are never read for a later
-            // pivot, and are not written back.
-            const int i0 = kb + lane, i1 = kb + lane + 64;
-            T r0[16], r1[16];
+        // wave 0: rows kb + 16 + lane below the diagonal block; wave 1: the 64 after
+        const bool act = wave == 0 || (kTwoRows && wave == 1 && kb + 80 < f);
+        const int row = kb + 16 + 64 * wave + lane;
+        T rp[16], x[16], dk = T(0);
+        unsigned int n3[3];
+        bool plain = true;
+        if (act) {
+            // a short sub-panel (bw < 16): the rows between it and row kb + 16
+            // are in the diagonal block's lanes lr >= bw
 #pragma unroll
             for (int t = 0; t < 16; ++t) {
-                r0[t] = (t < bw && i0 < f && t <= lane) ? A[i0 + (kb + t) * lda] : T(0);
-                r1[t] = (kTwoRows && t < bw && i1 < f) ? A[i1 + (kb + t) * lda] : T(0);
+                rp[t] = (t < bw && kb + lr < f && t <= lr) ? A[(kb + lr) + (kb + t) * lda] : T(0);
+                x[t] = (t < bw && row < f) ? A[row + (kb + t) * lda] : T(0);
             }
-            T mydk = T(0);
-            unsigned int np = 0, nn = 0, nz = 0, npt = 0;
-            bool anybad = false;
-#pragma unroll
-            for (int t = 0; t < 16; ++t) {
-                if (t >= bw) continue;   // uniform; keeps the loop fully unrolled
-                bool pert, bad;
-                const T draw = bcast(r0[t], t);
-                const T inv0 = fast_rcp(draw);
-                const int sg = sgn[kb + t];
-                const T dk = static_pivot(draw, thr, sg, pert, bad);
-                const T inv = pert ? thr.inv(sg) : inv0;
-                T ck[16];
-#pragma unroll
-                for (int u = t + 1; u < 16; ++u) ck[u] = (u < bw) ? bcast(r0[t], u) : T(0);
-                const T l0 = r0[t] * inv;
-#pragma unroll
-                for (int u = t + 1; u < 16; ++u) r0[u] -= l0 * ck[u];
-                r0[t] = (lane == t) ? dk : l0;
-                if (kTwoRows) {
-                    const T l1 = r1[t] * inv;
-#pragma unroll
-                    for (int u = t + 1; u < 16; ++u) r1[u] -= l1 * ck[u];
-                    r1[t] = l1;
+        }
+        if (kTwoRows) __syncthreads();   // wave 1 has read the diagonal block that wave 0 overwrites
+        if (act) {
+            pivots16<T, true>(rp, x, dk, bw, lr);
+            plain = pivots_plain(dk, thr, bw, lane, n3);
+            if (plain) {
+                store_subpanel(A, lda, kb, bw, lane, row, f, rp, x, dk, wave == 0);
+                if (wave == 0) {
+                    if (lane < bw) dv[kb + lane] = dk;
+                    if (lane == 0)
+                        for (int k = 0; k < 3; ++k) cnt[k] += n3[k];
                 }
-                mydk = (lane == t) ? dk : mydk;
-                const double dd = to_d(dk);
-                np += dd > 0.0; nn += dd < 0.0; nz += dd == 0.0; npt += pert;
-                anybad |= bad;
-            }
-#pragma unroll
-            for (int t = 0; t < 16; ++t) {
-                if (t < bw && i0 < f && t <= lane) A[i0 + (kb + t) * lda] = r0[t];
-                if (kTwoRows && t < bw && i1 < f) A[i1 + (kb + t) * lda] = r1[t];
-            }
-            if (lane < bw) dv[kb + lane] = mydk;
-            if (lane == 0) {
-                cnt[0] += np; cnt[1] += nn; cnt[2] += nz; cnt[3] += npt;
-                bad_any |= anybad;
+            } else if (wave == 0) {
+                const unsigned int neg = (unsigned int)__ballot(lane < bw && sgn[kb + min(lane, bw - 1)] < 0);
+                subpanel_by_pivot(A, lda, f, kb, bw, bw, neg, dv, thr, lane, cnt, bad_any);
             }
         }
         __syncthreads();
@@ -259,40 +373,17 @@ __device__ void lds_partial_ldlt(T* A, int lda, int f, int p, T* dv, const int8_
     bad_out = bad_any;
 }
 
-// Value of lane 16 * (lane / 16) + U of each 16-lane row (DPP row_newbcast).
-template <int U>
-__device__ __forceinline__ double rowbcast(double v) {
-    const long long b = __builtin_bit_cast(long long, v);
-    const long long r = __builtin_amdgcn_update_dpp(b, b, 0x150 + U, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, r);
-}
-template <int U>
-__device__ __forceinline__ float rowbcast(float v) {
-    const int b = __builtin_bit_cast(int, v);
-    const int r = __builtin_amdgcn_update_dpp(b, b, 0x150 + U, 0xf, 0xf, true);
-    return __builtin_bit_cast(float, r);
-}
-template <typename T>
-__device__ __forceinline__ T rowbcast_n(T v, int u) {   // u: a compile-time constant after unrolling
-    switch (u) {
-        case 0: return rowbcast<0>(v);   case 1: return rowbcast<1>(v);   case 2: return rowbcast<2>(v);
-        case 3: return rowbcast<3>(v);   case 4: return rowbcast<4>(v);   case 5: return rowbcast<5>(v);
-        case 6: return rowbcast<6>(v);   case 7: return rowbcast<7>(v);   case 8: return rowbcast<8>(v);
-        case 9: return rowbcast<9>(v);   case 10: return rowbcast<10>(v); case 11: return rowbcast<11>(v);
-        case 12: return rowbcast<12>(v); case 13: return rowbcast<13>(v); case 14: return rowbcast<14>(v);
-        default: return rowbcast<15>(v);
-    }
-}
-
 // LDL^T of one kPanel x kPanel diagonal block held in LDS (column-major,
 // leading dimension kPanel + 1, lower triangle), with the static-pivot rule of
 // Sec. 3.1 for its first w pivots.  The caller pads the block beyond w with
 // the identity and zeroes the upper triangle, so every size is a compile-time
-// constant: wave 0 factors each 16-column sub-panel in registers (lane = row,
-// readlane broadcasts), then the four waves apply its rank-16 update to the
+// constant: wave 0 factors each 16-column sub-panel in registers (pivots16;
+// pivot by pivot where one falls below its threshold), then the four waves
+// apply its rank-16 update to the
 // trailing lower block on MFMA.  Bit c of negmask set = pivot c takes the
-// negative sign.  On return: L strictly below the diagonal, d on the diagonal
-// and in dv; lane 0 of wave 0 has added the counts of the first w pivots to
+// negative sign.  Sub-panels past w are the identity already and are skipped.
+// On return: L strictly below the diagonal, d on the diagonal
+// and in dv (its first w entries); lane 0 of wave 0 has added the counts of the first w pivots to
 // cnt[4].  Called by all 256 threads; ends with a barrier.
 template <typename T>
 __device__ __forceinline__ void diag_ldlt64(T* B, T* dv, unsigned long long negmask, int w, const PivThr<T>& thr,
@@ -301,55 +392,34 @@ __device__ __forceinline__ void diag_ldlt64(T* B, T* dv, unsigned long long negm
     const int wave = tid >> 6, lane = tid & 63;
     const int lr = lane & 15, lk = lane >> 4;
     bool bad_any = false;
-#pragma unroll
-    for (int kb = 0; kb < kPanel; kb += 16) {
+#pragma unroll 1
+    for (int kb = 0; kb < w; kb += 16) {
         if (wave == 0) {
-            // Row `lane`, columns kb..kb+15.  Entries above a row's diagonal are
-            // scratch: they take the same updates, are never read as a pivot or
-            // a multiplier of a lower row, and are not stored.
-            T r[16];
-#pragma unroll
-            for (int t = 0; t < 16; ++t) r[t] = B[lane + (kb + t) * LB];
-            T mydk = T(0);
-            unsigned int np = 0, nn = 0, nz = 0, npt = 0;
-            bool anybad = false;
+            const int row = kb + 16 + lane;
+            const int rowc = min(row, kPanel - 1);
+            T rp[16], x[16], dk;
 #pragma unroll
             for (int t = 0; t < 16; ++t) {
-                const int c = kb + t;
-                bool pert, bd;
-                // The reciprocal starts from the raw pivot; the static-pivot
-                // rule (rarely taken) replaces both afterwards, so its test is
-                // off the dependent chain.
-                const T draw = bcast(r[t], c);
-                const T inv0 = fast_rcp(draw);
-                const int sg = ((negmask >> c) & 1ULL) ? -1 : 1;
-                const T dk = static_pivot(draw, thr, sg, pert, bd);
-                const T inv = pert ? thr.inv(sg) : inv0;
-                const T l = r[t] * inv;
-#pragma unroll
-                for (int u = t + 1; u < 16; ++u) r[u] -= l * bcast(r[t], kb + u);
-                r[t] = (lane == c) ? dk : l;
-                mydk = (lane == c) ? dk : mydk;
-                if (c < w) {
-                    const double dd = to_d(dk);
-                    np += dd > 0.0; nn += dd < 0.0; nz += dd == 0.0; npt += pert;
-                    anybad |= bd;
-                }
+                rp[t] = B[(kb + lr) + (kb + t) * LB];
+                x[t] = B[rowc + (kb + t) * LB];
             }
-#pragma unroll
-            for (int t = 0; t < 16; ++t)
-                if (lane >= kb + t) B[lane + (kb + t) * LB] = r[t];
-            if (lane >= kb && lane < kb + 16) dv[lane] = mydk;
-            if (lane == 0) {
-                cnt[0] += np; cnt[1] += nn; cnt[2] += nz; cnt[3] += npt;
-                bad_any |= anybad;
+            pivots16<T, true>(rp, x, dk, 16, lr);
+            unsigned int n3[3];
+            if (pivots_plain(dk, thr, min(16, w - kb), lane, n3)) {
+                store_subpanel(B, LB, kb, 16, lane, row, kPanel, rp, x, dk, true);
+                if (lane < 16) dv[kb + lane] = dk;
+                if (lane == 0)
+                    for (int k = 0; k < 3; ++k) cnt[k] += n3[k];
+            } else {
+                subpanel_by_pivot(B, LB, kPanel, kb, 16, w - kb, (unsigned int)(negmask >> kb) & 0xffffu, dv, thr, lane,
+                                  cnt, bad_any);
             }
         }
         __syncthreads();
-        if (kb + 16 < kPanel) {
+        if (kb + 16 < w) {
             // trailing lower block of order kPanel - kb - 16, in 16 x 16 tiles
             const int r0 = kb + 16;
-            const int nt = (kPanel - r0) / 16;
+            const int nt = (w - r0 + 15) / 16;
             const int ntiles = nt * (nt + 1) / 2;
             for (int tix = wave; tix < ntiles; tix += 4) {
                 int tj = 0, rem = tix;
