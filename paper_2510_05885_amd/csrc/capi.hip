@@ -89,9 +89,9 @@ struct ncl_kkt_s {
     DevPlan d{};
     int64_t nnzF = 0;
     // schedule arrays (device)
-    int *small_list = nullptr, *level_list = nullptr, *large_asm = nullptr, *large_panel = nullptr,
-        *large_upd = nullptr, *large_diag = nullptr, *solve_p = nullptr, *solve_seg = nullptr, *solve_s = nullptr,
+    int *small_list = nullptr, *level_list = nullptr, *large_asm = nullptr, *solve_p = nullptr, *solve_seg = nullptr, *solve_s = nullptr,
         *fsolve_p = nullptr;
+    LargeTask *large_panel = nullptr, *large_upd = nullptr, *large_diag = nullptr;
     int *chunk_row0 = nullptr, *chunk_rows = nullptr, *sys_chunk_ptr = nullptr;
     int nchunks = 0;
     // numeric state
@@ -237,6 +237,11 @@ void setup_device(ncl_kkt_s* h) {
     d.row_sys = upload(h, P.row_sys);
     d.row_sign = upload(h, P.row_sign);
     d.perm = upload(h, P.perm);
+    {
+        std::vector<int8_t> ps(P.N);
+        for (int64_t k = 0; k < P.N; ++k) ps[k] = P.row_sign[P.perm[k]];
+        d.piv_sign = upload(h, ps);
+    }
     d.sn_first = upload(h, P.sn_first);
     d.sn_rowptr = upload(h, P.sn_rowptr);
     d.sn_rows = upload(h, P.sn_rows);
@@ -270,7 +275,23 @@ void setup_device(ncl_kkt_s* h) {
     h->small_list = upload(h, P.small_list);
     h->level_list = upload(h, P.level_list);
     h->large_asm = upload(h, P.large_asm);
-    h->large_diag = upload(h, P.large_diag);
+    {
+        // tasks of `width` ints (front, panel, then first row, column) as records
+        auto records = [&](const std::vector<int>& v, int width) {
+            std::vector<LargeTask> r(v.size() / width);
+            for (size_t t = 0; t < r.size(); ++t) {
+                const int* tk = v.data() + t * width;
+                const int s = tk[0];
+                r[t] = LargeTask{P.sn_first[s], P.sn_first[s + 1] - P.sn_first[s],
+                                 (int)(P.sn_rowptr[s + 1] - P.sn_rowptr[s]), tk[1], width > 2 ? tk[2] : 0,
+                                 width > 3 ? tk[3] : 0, P.sn_sys[s], s, P.L_off[s], P.M_off[s]};
+            }
+            return r;
+        };
+        h->large_diag = upload(h, records(P.large_diag, 2));
+        h->large_panel = upload(h, records(P.large_panel, 3));
+        h->large_upd = upload(h, records(P.large_upd, 4));
+    }
     {
         // every sweep task with its panel's and its front's fields (kTaskRec
         // ints): the backward tasks (with the panel each finishes) and the
@@ -304,8 +325,6 @@ void setup_device(ncl_kkt_s* h) {
     }
     h->solve_seg = upload(h, P.solve_seg);
     h->solve_s = upload(h, P.solve_s);
-    h->large_panel = upload(h, P.large_panel);
-    h->large_upd = upload(h, P.large_upd);
     // row chunks (<= 256 rows, never straddling two systems)
     std::vector<int> c0, cn, scp(1, 0);
     for (int s = 0; s < P.S; ++s) {
@@ -573,21 +592,21 @@ void factor_fronts(ncl_kkt_s* h, T* F, T* D, T* Mb, hipStream_t st) {
                 const size_t nsteps = ls.panel_first.size();
                 {
                     Span sp(h, st, TM_DIAG, h->tm.on ? diag_flops(P, ls, 0) : 0.0, 6);
-                    launch_large_diag<T>(d, h->large_diag + 2 * ls.diag_first[0], (int)ls.diag_count[0], F, D, Mb,
+                    launch_large_diag<T>(d, h->large_diag + ls.diag_first[0], (int)ls.diag_count[0], F, D, Mb,
                                          st);
                 }
                 for (size_t k = 0; k < nsteps; ++k) {
                     {
                         Span sp(h, st, TM_PANEL, h->tm.on ? panel_flops(P, ls, k) : 0.0, 5);
-                        launch_large_panel<T>(d, h->large_panel + 3 * ls.panel_first[k], (int)ls.panel_count[k], F, D,
+                        launch_large_panel<T>(h->large_panel + ls.panel_first[k], (int)ls.panel_count[k], F, D,
                                               Mb, st);
                     }
                     const int nd = k + 1 < nsteps ? (int)ls.diag_count[k + 1] : 0;
-                    const int* dt = nd > 0 ? h->large_diag + 2 * ls.diag_first[k + 1] : nullptr;
+                    const LargeTask* dt = nd > 0 ? h->large_diag + ls.diag_first[k + 1] : nullptr;
                     {
                         Span sp(h, st, TM_UPD, ls.upd_flops[k] + (h->tm.on && nd > 0 ? diag_flops(P, ls, k + 1) : 0.0),
                                 1);
-                        launch_large_dstep<T>(d, dt, nd, h->large_upd + 4 * ls.upd_first[k], (int)ls.upd_count[k], F,
+                        launch_large_dstep<T>(d, dt, nd, h->large_upd + ls.upd_first[k], (int)ls.upd_count[k], F,
                                               D, Mb, st);
                     }
                 }

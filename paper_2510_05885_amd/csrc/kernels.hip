@@ -39,14 +39,12 @@ __device__ __forceinline__ double to_d(float x) { return (double)x; }
 
 // Static-pivot thresholds of one system (Sec. 3.1): p for pivots of the
 // primal block, n for pivots of the dual block (equal unless the thresholds
-// are block-scaled), with the reciprocals of the replacement pivots +p, -n.
+// are block-scaled); inv: the reciprocal of the replacement pivot +p or -n.
 template <typename T>
 struct PivThr {
     double p, n;
-    T inv_p, inv_n;
-    __device__ PivThr(const DevPlan& d, int sys)
-        : p(d.sys_thr[2 * sys]), n(d.sys_thr[2 * sys + 1]), inv_p(T(1) / (T)p), inv_n(-(T(1) / (T)n)) {}
-    __device__ __forceinline__ T inv(int sign) const { return sign > 0 ? inv_p : inv_n; }
+    __device__ PivThr(const DevPlan& d, int sys) : p(d.sys_thr[2 * sys]), n(d.sys_thr[2 * sys + 1]) {}
+    __device__ __forceinline__ T inv(int sign) const { return sign > 0 ? T(1) / (T)p : -(T(1) / (T)n); }
 };
 
 // Static-pivot rule (Sec. 3.1): returns the pivot to use; flags perturbation.
@@ -81,31 +79,16 @@ __device__ __forceinline__ void count_pivot(unsigned long long* in4, double d, b
 // B[l / 16][l % 16].  Result item r of lane l is D[row(l / 16, r)][l % 16];
 // the row order differs between the f64 and f32 instructions (checked on
 // gfx950 with a one-hot probe).
-template <typename T> struct Mfma;
 //
-// run_chained: for an MFMA whose result is read by the very next instruction
-// that touches it (the next MFMA of a single-accumulator chain, as SrcC or as
-// an operand, or the read-out).  On gfx950 such a dependency needs more
-// separation than the compiler inserts: without the 16 wait states below,
-// about 3% of the factorizations of a 500k-order system differed from run to
-// run, always in one accumulator register pair of one wave, while with them
-// every repeat was bitwise identical.  Chains whose consecutive MFMAs write
-// different accumulators (the interleaved 64x64 tile update) need only pad()
-// before their read-out.
-__device__ __forceinline__ void mfma_pad() {
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_nop 15");
-    __builtin_amdgcn_sched_barrier(0);
-}
+// The compiler inserts the wait states of dependent MFMAs itself (none between
+// the links of a chain on one accumulator, 19 before an f64 result is read).
+// Chains once carried 16 more each, against a difference from run to run that
+// was the panel solve's (see panel_body).
+template <typename T> struct Mfma;
 template <> struct Mfma<double> {
     typedef f64x4 acc_t;
     static __device__ __forceinline__ acc_t run(double a, double b, acc_t c) {
         return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-    }
-    static __device__ __forceinline__ acc_t run_chained(double a, double b, acc_t c) {
-        acc_t r = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-        mfma_pad();
-        return r;
     }
     static __device__ __forceinline__ int row(int lk, int r) { return 4 * r + lk; }
 };
@@ -113,11 +96,6 @@ template <> struct Mfma<float> {
     typedef f32x4 acc_t;
     static __device__ __forceinline__ acc_t run(float a, float b, acc_t c) {
         return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-    static __device__ __forceinline__ acc_t run_chained(float a, float b, acc_t c) {
-        acc_t r = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-        mfma_pad();
-        return r;
     }
     static __device__ __forceinline__ int row(int lk, int r) { return 4 * lk + r; }
 };
@@ -219,6 +197,11 @@ __device__ __forceinline__ void pivots16(T (&rp)[16], T (&x)[16], T& dk, int bw,
         rp[t] = l;
         if (kExt) x[t] = lx;
     }
+    // x is updated here, not where the caller comes to use it: that would hold
+    // all 120 broadcasts in registers until then
+    if (kExt)
+#pragma unroll
+        for (int t = 0; t < 16; ++t) asm volatile("" : "+v"(x[t]));
 }
 
 // Whether every pivot dk of a sub-panel's first bw (lane % 16 < bw) is finite
@@ -361,7 +344,7 @@ __device__ void lds_partial_ldlt(T* A, int lda, int f, int p, T* dv, const int8_
             }
             typename Mfma<T>::acc_t acc = {0, 0, 0, 0};
 #pragma unroll
-            for (int st = 0; st < 4; ++st) acc = Mfma<T>::run_chained(av[st], bv[st], acc);
+            for (int st = 0; st < 4; ++st) acc = Mfma<T>::run(av[st], bv[st], acc);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int gi = i0 + Mfma<T>::row(lk, r), gj = j0 + lr;
@@ -373,154 +356,190 @@ __device__ void lds_partial_ldlt(T* A, int lda, int f, int p, T* dv, const int8_
     bad_out = bad_any;
 }
 
-// LDL^T of one kPanel x kPanel diagonal block held in LDS (column-major,
-// leading dimension kPanel + 1, lower triangle), with the static-pivot rule of
-// Sec. 3.1 for its first w pivots.  The caller pads the block beyond w with
-// the identity and zeroes the upper triangle, so every size is a compile-time
-// constant: wave 0 factors each 16-column sub-panel in registers (pivots16;
-// pivot by pivot where one falls below its threshold), then the four waves
-// apply its rank-16 update to the
-// trailing lower block on MFMA.  Bit c of negmask set = pivot c takes the
-// negative sign.  Sub-panels past w are the identity already and are skipped.
-// On return: L strictly below the diagonal, d on the diagonal
-// and in dv (its first w entries); lane 0 of wave 0 has added the counts of the first w pivots to
-// cnt[4].  Called by all 256 threads; ends with a barrier.
+// ---- one diagonal block of a large front ---------------------------------
+// LDL^T of a kPanel x kPanel diagonal block and Z = L^-1, by the workgroup.
+// The block's ten lower 16 x 16 tiles stay in MFMA accumulators (three a wave)
+// and only the next 16-column sub-panel goes through LDS, where wave 0 factors
+// it; meanwhile waves 1..3 apply the previous sub-panel to the tiles beyond
+// and build the block row of Z that it completes.  The block was a chain of
+// LDS round trips: with every tile in LDS and Z formed afterwards it took
+// 10 us + 4.4 us a block (order 20k), of which the pivots themselves are 3.8.
+// Tiles are held transposed (lane % 16 = row), so that a column's entries are
+// contiguous over lanes in LDS and in the front.
+constexpr int kDiagLd = 80;   // leading dimension of the LDS block: 16 mod 32 doubles, so that the
+                              // four 16-row column pieces an operand load takes lie in different banks
+
+// The tiles of a wave: slot t of wave v is block row ti, block column tj.
+// Wave 0 has (0,0) only, wave 1 (1,0), (1,1), (3,3), waves 2 and 3 their block
+// row's first three.
+__device__ __forceinline__ int diag_ti(int wave, int t) { return wave == 1 && t == 2 ? 3 : wave; }
+__device__ __forceinline__ int diag_tj(int wave, int t) { return wave == 1 && t == 2 ? 3 : t; }
+__device__ __forceinline__ bool diag_has(int wave, int t) { return wave > 0 || t == 0; }
+
+// Z[u][t] of the LDS block: strictly lower entries are stored transposed in
+// the strictly upper triangle.
 template <typename T>
-__device__ __forceinline__ void diag_ldlt64(T* B, T* dv, unsigned long long negmask, int w, const PivThr<T>& thr,
+__device__ __forceinline__ T zget(const T* B, int u, int t) {
+    return u > t ? B[t + u * kDiagLd] : (u == t ? T(1) : T(0));
+}
+
+// acc (a tile at block (ti, tj), transposed) -= L_ti D L_tj^T of sub-panel q.
+template <typename T>
+__device__ __forceinline__ void diag_apply(typename Mfma<T>::acc_t& acc, const T* B, const T* dv, int q, int ti,
+                                           int tj, int lr, int lk) {
+    T a[4], b[4];
+#pragma unroll
+    for (int st = 0; st < 4; ++st) {
+        const int t = 16 * q + 4 * st + lk;
+        a[st] = B[(16 * tj + lr) + t * kDiagLd] * -dv[t];
+        b[st] = B[(16 * ti + lr) + t * kDiagLd];
+    }
+#pragma unroll
+    for (int st = 0; st < 4; ++st) acc = Mfma<T>::run(a[st], b[st], acc);
+}
+
+// Z_qq = L_qq^-1 of a 16 x 16 unit lower block by one wave: lane (g, j) builds
+// column j (the same in each 16-lane row) and holds row j of L_qq, whose
+// entries come from lane i of its row.  Waves that need Z_qq at the same time
+// each do this and write the same values.
+template <typename T>
+__device__ __forceinline__ void diag_inv16(T* B, int q, int lane) {
+    const int o = 16 * q, j = lane & 15;
+    T lrow[16], z[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+        const T x = B[(o + j) + (o + u) * kDiagLd];
+        lrow[u] = u < j ? x : T(0);
+        z[u] = (u == j) ? T(1) : T(0);
+    }
+#pragma unroll
+    for (int i = 1; i < 16; ++i) {
+        // Tie row i's broadcasts to z[i-1]: otherwise all 120 of them are
+        // issued up front and held in registers.
+#pragma unroll
+        for (int u = 0; u < i; ++u) asm volatile("" : "+v"(lrow[u]) : "v"(z[i - 1]));
+#pragma unroll
+        for (int u = 0; u < i; ++u) z[i] = __builtin_fma(-rowbcast_n(lrow[u], i), z[u], z[i]);
+    }
+    wave_fence();
+    if (lane < 16) {
+#pragma unroll
+        for (int i = 1; i < 16; ++i)
+            if (i > j) B[(o + j) + (o + i) * kDiagLd] = z[i];
+    }
+    wave_fence();
+}
+
+// Column j of Z's block row i, first half: S = sum_{k = j}^{i - 1} L_ik Z_kj.
+template <typename T>
+__device__ __forceinline__ void diag_zsum(typename Mfma<T>::acc_t& S, const T* B, int i, int j, int lr, int lk) {
+    S = typename Mfma<T>::acc_t{0, 0, 0, 0};
+    for (int k = j; k < i; ++k) {
+        T la[4], zb[4];
+#pragma unroll
+        for (int st = 0; st < 4; ++st) {
+            const int kk = 16 * k + Mfma<T>::row(lk, st);
+            la[st] = B[(16 * i + lr) + kk * kDiagLd];
+            zb[st] = zget(B, kk, 16 * j + lr);
+        }
+#pragma unroll
+        for (int st = 0; st < 4; ++st) S = Mfma<T>::run(la[st], zb[st], S);
+    }
+}
+
+// ... second half: Z_ij = -Z_ii S.
+template <typename T>
+__device__ __forceinline__ void diag_zrow(const typename Mfma<T>::acc_t& S, T* B, int i, int j, int lr, int lk) {
+    typename Mfma<T>::acc_t R = {0, 0, 0, 0};
+    T zi[4];
+#pragma unroll
+    for (int st = 0; st < 4; ++st) zi[st] = zget(B, 16 * i + lr, 16 * i + Mfma<T>::row(lk, st));
+#pragma unroll
+    for (int st = 0; st < 4; ++st) R = Mfma<T>::run(zi[st], S[st], R);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) B[(16 * j + lr) + (16 * i + Mfma<T>::row(lk, r)) * kDiagLd] = -R[r];
+    wave_fence();
+}
+
+// Factors the block whose tiles are in acc (first w pivots; entries beyond are
+// taken as the identity), leaving L strictly below the diagonal of B, Z
+// transposed above it (rows past the last sub-panel unwritten) and the pivots
+// in dv.  Bit c of negmask: pivot c takes the negative sign; lane 0 of wave 0
+// adds the counts of the w pivots to cnt[4].  Called by all 256 threads; B is
+// free on entry; ends with a barrier.
+template <typename T>
+__device__ __forceinline__ void diag_factor(typename Mfma<T>::acc_t (&acc)[3], T* B, T* dv,
+                                            unsigned long long negmask, int w, const PivThr<T>& thr,
                                             unsigned int* cnt, bool& bad_out, int tid) {
-    constexpr int LB = kPanel + 1;
-    const int wave = tid >> 6, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int lr = lane & 15, lk = lane >> 4;
+    const int nq = (w + 15) >> 4;
     bool bad_any = false;
+    typename Mfma<T>::acc_t S = {0, 0, 0, 0};
+    // side work of waves 1..3 once sub-panel i is factored: the diagonal block
+    // of Z, and block (i, wave - 1) from the sum formed before
+    auto zstep = [&](int i) {
+        if (wave <= i + 1) diag_inv16<T>(B, i, lane);
+        if (wave <= i) diag_zrow<T>(S, B, i, wave - 1, lr, lk);
+    };
 #pragma unroll 1
-    for (int kb = 0; kb < w; kb += 16) {
+    for (int q = 0; q < nq; ++q) {
+        const int kb = 16 * q;
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            if (!diag_has(wave, t) || diag_tj(wave, t) != q) continue;   // uniform
+            const int row = 16 * diag_ti(wave, t) + lr;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int col = kb + Mfma<T>::row(lk, r);
+                B[row + col * kDiagLd] = row < w && col < w ? acc[t][r] : (row == col ? T(1) : T(0));
+            }
+        }
+        __syncthreads();
         if (wave == 0) {
             const int row = kb + 16 + lane;
             const int rowc = min(row, kPanel - 1);
             T rp[16], x[16], dk;
 #pragma unroll
             for (int t = 0; t < 16; ++t) {
-                rp[t] = B[(kb + lr) + (kb + t) * LB];
-                x[t] = B[rowc + (kb + t) * LB];
+                rp[t] = B[(kb + lr) + (kb + t) * kDiagLd];
+                x[t] = B[rowc + (kb + t) * kDiagLd];
             }
             pivots16<T, true>(rp, x, dk, 16, lr);
             unsigned int n3[3];
             if (pivots_plain(dk, thr, min(16, w - kb), lane, n3)) {
-                store_subpanel(B, LB, kb, 16, lane, row, kPanel, rp, x, dk, true);
-                if (lane < 16) dv[kb + lane] = dk;
+                // the diagonal block's upper triangle takes scratch values: it
+                // is written as Z before it is read
+                if (row < kPanel)
+#pragma unroll
+                    for (int t = 0; t < 16; ++t) B[row + (kb + t) * kDiagLd] = x[t];
+                if (lane < 16) {
+#pragma unroll
+                    for (int t = 0; t < 16; ++t) B[(kb + lane) + (kb + t) * kDiagLd] = rp[t];
+                    dv[kb + lane] = dk;
+                }
                 if (lane == 0)
                     for (int k = 0; k < 3; ++k) cnt[k] += n3[k];
             } else {
-                subpanel_by_pivot(B, LB, kPanel, kb, 16, w - kb, (unsigned int)(negmask >> kb) & 0xffffu, dv, thr, lane,
-                                  cnt, bad_any);
+                subpanel_by_pivot(B, kDiagLd, kPanel, kb, 16, w - kb, (unsigned int)(negmask >> kb) & 0xffffu, dv,
+                                  thr, lane, cnt, bad_any);
             }
+        } else if (q > 0) {
+#pragma unroll
+            for (int t = 0; t < 3; ++t)
+                if (diag_tj(wave, t) > q) diag_apply<T>(acc[t], B, dv, q - 1, diag_ti(wave, t), diag_tj(wave, t), lr, lk);
+            zstep(q - 1);
+            if (wave <= q) diag_zsum<T>(S, B, q, wave - 1, lr, lk);
         }
         __syncthreads();
-        if (kb + 16 < w) {
-            // trailing lower block of order kPanel - kb - 16, in 16 x 16 tiles
-            const int r0 = kb + 16;
-            const int nt = (w - r0 + 15) / 16;
-            const int ntiles = nt * (nt + 1) / 2;
-            for (int tix = wave; tix < ntiles; tix += 4) {
-                int tj = 0, rem = tix;
-                while (rem >= nt - tj) { rem -= nt - tj; ++tj; }
-                const int ti = tj + rem;
-                const int i0 = r0 + 16 * ti, j0 = r0 + 16 * tj;
-                T av[4], bv[4];   // operands first: see panel_body
 #pragma unroll
-                for (int st = 0; st < 4; ++st) {
-                    const int t = kb + 4 * st + lk;
-                    av[st] = B[(i0 + lr) + t * LB];
-                    bv[st] = B[(j0 + lr) + t * LB] * dv[t];
-                }
-                typename Mfma<T>::acc_t acc = {0, 0, 0, 0};
-#pragma unroll
-                for (int st = 0; st < 4; ++st) acc = Mfma<T>::run_chained(av[st], bv[st], acc);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int gi = i0 + Mfma<T>::row(lk, r), gj = j0 + lr;
-                    if (gi >= gj) B[gi + gj * LB] -= acc[r];
-                }
-            }
-            __syncthreads();
-        }
+        for (int t = 0; t < 3; ++t)
+            if (diag_has(wave, t) && diag_tj(wave, t) == q + 1)
+                diag_apply<T>(acc[t], B, dv, q, diag_ti(wave, t), q + 1, lr, lk);
     }
-    bad_out = bad_any;
-}
-
-// Inverse Z = L^-1 of the unit lower triangle of a factored kPanel x kPanel
-// block in LDS (L strictly below the diagonal of B, column-major, leading
-// dimension kPanel + 1).  Z is unit lower triangular; its strictly lower part
-// is stored transposed in the strictly upper triangle of B (Z[u][t] at
-// B[t + u * LB], u > t).  By 16 x 16 blocks: Z_qq = L_qq^-1 by substitution
-// (wave q, lane j builds column j), then for distance 1..3 the blocks below,
-// Z_iq = -Z_ii (sum_{k=q}^{i-1} L_ik Z_kq), on MFMA.  Called by all 256
-// threads; ends with a barrier.
-template <typename T>
-__device__ __forceinline__ T zget(const T* B, int u, int t) {   // Z[u][t]
-    constexpr int LB = kPanel + 1;
-    return u > t ? B[t + u * LB] : (u == t ? T(1) : T(0));
-}
-
-template <typename T>
-__device__ __forceinline__ void tri_inv64(T* B, int tid) {
-    constexpr int LB = kPanel + 1;
-    const int wave = tid >> 6, lane = tid & 63;
-    const int lr = lane & 15, lk = lane >> 4;
-    {
-        // wave q: lane (g, j) builds column j of Z_qq (same in each 16-lane
-        // row) and holds row j of L_qq; L[i][u] comes from lane i of its row.
-        const int o = 16 * wave, j = lr;
-        T lrow[16], z[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            lrow[u] = u < j ? B[(o + j) + (o + u) * LB] : T(0);
-            z[u] = (u == j) ? T(1) : T(0);
-        }
-#pragma unroll
-        for (int i = 1; i < 16; ++i) {
-            // Tie row i's broadcasts to z[i-1]: otherwise all 120 of them are
-            // issued up front and held in registers.
-#pragma unroll
-            for (int u = 0; u < i; ++u) asm volatile("" : "+v"(lrow[u]) : "v"(z[i - 1]));
-#pragma unroll
-            for (int u = 0; u < i; ++u) z[i] = __builtin_fma(-rowbcast_n(lrow[u], i), z[u], z[i]);
-        }
-        if (lane < 16) {
-#pragma unroll
-            for (int i = 1; i < 16; ++i)
-                if (i > j) B[(o + j) + (o + i) * LB] = z[i];
-        }
-    }
+    if (wave > 0) zstep(nq - 1);
     __syncthreads();
-    typedef typename Mfma<T>::acc_t acc_t;
-#pragma unroll
-    for (int dist = 1; dist < 4; ++dist) {
-        const int q = wave, i = q + dist;
-        if (i < 4) {
-            acc_t S = {0, 0, 0, 0};
-            for (int k = q; k < i; ++k) {
-                T la[4], zb[4];   // operands first: see panel_body
-#pragma unroll
-                for (int st = 0; st < 4; ++st) {
-                    const int kk = Mfma<T>::row(lk, st);
-                    la[st] = B[(16 * i + lr) + (16 * k + kk) * LB];
-                    zb[st] = zget(B, 16 * k + kk, 16 * q + lr);
-                }
-#pragma unroll
-                for (int st = 0; st < 4; ++st) S = Mfma<T>::run_chained(la[st], zb[st], S);
-            }
-            T zi[4];
-#pragma unroll
-            for (int st = 0; st < 4; ++st) zi[st] = zget(B, 16 * i + lr, 16 * i + Mfma<T>::row(lk, st));
-            acc_t R = {0, 0, 0, 0};
-#pragma unroll
-            for (int st = 0; st < 4; ++st) R = Mfma<T>::run_chained(zi[st], S[st], R);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) B[(16 * q + lr) + (16 * i + Mfma<T>::row(lk, r)) * LB] = -R[r];
-        }
-        __syncthreads();
-    }
+    bad_out = bad_any;
 }
 
 // Workgroups are dealt to the 8 XCDs round-robin (workgroup b runs on XCD
@@ -954,46 +973,30 @@ __global__ __launch_bounds__(256) void k_large_asm(DevPlan d, int64_t task0, int
 }
 
 // Writes the factored diagonal block of a panel (in LDS: L strictly below the
-// diagonal, Z = L^-1 transposed strictly above it, column-major with leading
-// dimension kPanel + 1; dv = pivots) to its consumers: D, the front's L
+// diagonal, Z = L^-1 transposed strictly above it, dv = pivots) to its
+// consumers: D, the front's L
 // (strictly lower part of the block), and Zg = Z (column-major, kPanel x
 // kPanel, unit diagonal, identity beyond w) for the panel solves.
 template <typename T>
-__device__ void publish_diag(T* A, int f, int k0, int w, const T* Bf, const T* dv, T* D, int first, T* Zg, int tid) {
-    constexpr int LB = kPanel + 1;
+__device__ __forceinline__ void publish_diag(T* A, int f, int k0, int w, const T* B, const T* dv, T* D, int first,
+                                             T* Zg, int tid) {
     if (tid < w) D[first + k0 + tid] = dv[tid];
-    for (int idx = tid; idx < kPanel * kPanel; idx += 256) {
+#pragma unroll
+    for (int it = 0; it < kPanel * kPanel / 256; ++it) {
+        const int idx = tid + 256 * it;
         const int u = idx & (kPanel - 1), t = idx / kPanel;   // row u, column t
-        if (u < w && t < u) A[(k0 + u) + (int64_t)(k0 + t) * f] = Bf[u + t * LB];
-        Zg[idx] = zget(Bf, u, t);
+        if (u < w && t < u) A[(k0 + u) + (int64_t)(k0 + t) * f] = B[u + t * kDiagLd];
+        Zg[idx] = u < w ? zget(B, u, t) : (u == t ? T(1) : T(0));
     }
-}
-
-// Pads the diagonal block beyond its w pivots with the identity and zeroes
-// its upper triangle (entries with u < w and t < w on or below the diagonal
-// are left to the caller).
-template <typename T>
-__device__ __forceinline__ void pad_diag(T* Bf, int w, int tid) {
-    constexpr int LB = kPanel + 1;
-    for (int idx = tid; idx < kPanel * kPanel; idx += 256) {
-        const int u = idx & (kPanel - 1), t = idx / kPanel;
-        if (u < t) Bf[u + t * LB] = T(0);
-        else if (u >= w) Bf[u + t * LB] = (u == t) ? T(1) : T(0);
-    }
-}
-
-__device__ __forceinline__ unsigned long long neg_mask(const DevPlan& d, int first, int k0, int w, int tid) {
-    const int lane = tid & 63;
-    const bool neg = lane < w && d.row_sign[d.perm[first + k0 + lane]] < 0;
-    return __ballot(neg);
 }
 
 // C - L_I D_k L_J^T for the 64x64 tile at rows i0, columns j0 of front A
 // (ld f), with panel k = columns [k0, k0 + w): four waves, each a 32x32
 // quadrant as 2x2 blocks of 16x16 (v_mfma 16x16x4).  The accumulators start
-// from C (prefetched with the operands, clamped addresses) and the B operand
-// is negated, so the result is the updated tile.  acc[bi][bj][r] holds entry
-// (i0 + wr + 16 bi + row(lk, r), j0 + wc + 16 bj + lr).
+// from C (prefetched with the operands, clamped addresses) and one operand
+// is negated, so the result is the updated tile.  Blocks are held transposed
+// (lane % 16 = row): C is read and written 16 rows of a column at a time.
+// acc[bi][bj][r] holds entry (i0 + wr + 16 bi + lr, j0 + wc + 16 bj + row(lk, r)).
 template <typename T>
 __device__ __forceinline__ void tile_update(const T* __restrict__ A, int f, int k0, int w, int i0, int j0,
                                             const T* __restrict__ Dk, typename Mfma<T>::acc_t (&acc)[2][2], int tid) {
@@ -1001,16 +1004,16 @@ __device__ __forceinline__ void tile_update(const T* __restrict__ A, int f, int 
     const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
     const int lr = lane & 15, lk = lane >> 4;
 #pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
+    for (int bi = 0; bi < 2; ++bi) {
+        const int gi = min(i0 + wr + 16 * bi + lr, f - 1);
 #pragma unroll
-        for (int bj = 0; bj < 2; ++bj) {
-            const int gj = min(j0 + wc + 16 * bj + lr, f - 1);
+        for (int bj = 0; bj < 2; ++bj)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int gi = min(i0 + wr + 16 * bi + Mfma<T>::row(lk, r), f - 1);
+                const int gj = min(j0 + wc + 16 * bj + Mfma<T>::row(lk, r), f - 1);
                 acc[bi][bj][r] = A[gi + (int64_t)gj * f];
             }
-        }
+    }
     constexpr int KS = kPanel / 4;
     T av[KS][2], bv[KS][2];
 #pragma unroll
@@ -1034,8 +1037,7 @@ __device__ __forceinline__ void tile_update(const T* __restrict__ A, int f, int 
 #pragma unroll
         for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-            for (int bj = 0; bj < 2; ++bj) acc[bi][bj] = Mfma<T>::run(av[ks][bi], bv[ks][bj], acc[bi][bj]);
-    mfma_pad();   // before the read-out of the last accumulator written
+            for (int bj = 0; bj < 2; ++bj) acc[bi][bj] = Mfma<T>::run(bv[ks][bj], av[ks][bi], acc[bi][bj]);
 }
 
 // One workgroup per (large front, panel k0): bring the panel's diagonal block
@@ -1047,75 +1049,81 @@ __device__ __forceinline__ void tile_update(const T* __restrict__ A, int f, int 
 // belong to the panel rows below it / the contribution block and are written
 // back to the front.
 template <typename T>
-__device__ __forceinline__ void diag_body(const DevPlan& d, int s, int k0, T* F, T* D, T* Zbuf, int tid) {
-    const int first = d.sn_first[s];
-    const int p = d.sn_first[s + 1] - first;
-    const int f = (int)(d.sn_rowptr[s + 1] - d.sn_rowptr[s]);
+__device__ __forceinline__ void diag_body(const DevPlan& d, const LargeTask* tk, T* F, T* D, T* Zbuf, int tid) {
+    const int first = tk->first, p = tk->p, f = tk->f, k0 = tk->k0;
     const int w = min(kPanel, p - k0);
-    T* __restrict__ A = F + d.L_off[s];
-    constexpr int LB = kPanel + 1;
-    __shared__ T Bf[kPanel * LB];
+    T* __restrict__ A = F + tk->L_off;
+    __shared__ T B[kPanel * kDiagLd];
     __shared__ T dv[kPanel];
-    constexpr int kIt = kPanel * kPanel / 256;   // staging: all loads first, then the LDS stores
-    if (k0 == 0) {
-        T cv[kIt];
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int lr = lane & 15, lk = lane >> 4;
+    __builtin_amdgcn_s_setprio(3);   // the launch waits for this chain, not for the tiles beside it
+    const int8_t sg = lane < w ? d.piv_sign[first + k0 + lane] : 1;
+    const PivThr<T> thr(d, tk->sys);
+    typename Mfma<T>::acc_t acc[3];
 #pragma unroll
-        for (int it = 0; it < kIt; ++it) {
-            const int idx = tid + 256 * it, u = idx & (kPanel - 1), t = idx / kPanel;
-            cv[it] = A[min(u, w - 1) + (int64_t)min(t, w - 1) * f];
-        }
+    for (int t = 0; t < 3; ++t) {
+        if (!diag_has(wave, t)) continue;   // uniform
+        const int gi = min(k0 + 16 * diag_ti(wave, t) + lr, f - 1);
 #pragma unroll
-        for (int it = 0; it < kIt; ++it) {
-            const int idx = tid + 256 * it, u = idx & (kPanel - 1), t = idx / kPanel;
-            if (u < w && t <= u) Bf[u + t * LB] = cv[it];
+        for (int r = 0; r < 4; ++r) {
+            const int gj = min(k0 + 16 * diag_tj(wave, t) + Mfma<T>::row(lk, r), f - 1);
+            acc[t][r] = A[gi + (int64_t)gj * f];
         }
-    } else {
+    }
+    if (k0 > 0) {
         // The block's own update by the previous panel (columns kp = k0 - 64
-        // .. k0, all 64 wide), with the operands read from the front as for a
-        // trailing-update tile, the result into the block.
+        // .. k0, all 64 wide): its 64 rows of L staged in B.
         const int kp = k0 - kPanel;
         const int nr = min(kPanel, f - k0);
-        typename Mfma<T>::acc_t acc[2][2];
-        tile_update<T>(A, f, kp, kPanel, k0, k0, D + first + kp, acc, tid);
-        const int wave = tid >> 6, lane = tid & 63;
-        const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
-        const int lr = lane & 15, lk = lane >> 4;
+        {
+            constexpr int kIt = kPanel * kPanel / 256;   // all loads first, then the LDS stores
+            T lv[kIt];
+            const T* __restrict__ src = A + min(k0 + lane, f - 1);
 #pragma unroll
-        for (int bi = 0; bi < 2; ++bi)
+            for (int it = 0; it < kIt; ++it) lv[it] = src[(int64_t)(kp + 4 * it + wave) * f];
+            const T dl = wave == 0 ? D[first + kp + lane] : T(0);
 #pragma unroll
-            for (int bj = 0; bj < 2; ++bj)
+            for (int it = 0; it < kIt; ++it) B[lane + (4 * it + wave) * kDiagLd] = lane < nr ? lv[it] : T(0);
+            if (wave == 0) dv[lane] = dl;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int t = 0; t < 3; ++t)
+                if (diag_has(wave, t))
+                    diag_apply<T>(acc[t], B, dv, q, diag_ti(wave, t), diag_tj(wave, t), lr, lk);
+        if (w < kPanel) {
+#pragma unroll
+            for (int t = 0; t < 3; ++t) {
+                if (!diag_has(wave, t)) continue;
+                const int li = 16 * diag_ti(wave, t) + lr;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int li = wr + bi * 16 + Mfma<T>::row(lk, r), lj = wc + bj * 16 + lr;
-                    if (li < lj || li >= nr) continue;
-                    const T v = acc[bi][bj][r];
-                    if (li < w) Bf[li + lj * LB] = v;
-                    else A[(k0 + li) + (int64_t)(k0 + lj) * f] = v;   // rows past the last pivot
+                    const int lj = 16 * diag_tj(wave, t) + Mfma<T>::row(lk, r);
+                    if (li >= w && li >= lj && li < nr) A[(k0 + li) + (int64_t)(k0 + lj) * f] = acc[t][r];
                 }
-        __syncthreads();   // pad_diag below overwrites rows past the last pivot
+            }
+        }
+        __syncthreads();   // the staged rows have been read
     }
-    pad_diag<T>(Bf, w, tid);
-    const unsigned long long negmask = neg_mask(d, first, k0, w, tid);
-    __syncthreads();
-    const int sys = d.sn_sys[s];
     unsigned int cnt[4] = {0, 0, 0, 0};
     bool bad = false;
-    diag_ldlt64<T>(Bf, dv, negmask, w, PivThr<T>(d, sys), cnt, bad, tid);
-    tri_inv64<T>(Bf, tid);
+    diag_factor<T>(acc, B, dv, __ballot(sg < 0), w, thr, cnt, bad, tid);
     if (tid == 0) {
-        add_inertia(d, sys, cnt, s + k0);
+        add_inertia(d, tk->sys, cnt, tk->s + k0);
         if (bad) atomicOr(d.nonfinite, kNonfiniteFactor);
     }
-    publish_diag<T>(A, f, k0, w, Bf, dv, D, first, Zbuf + d.M_off[s] + (int64_t)(k0 / kPanel) * (kPanel * kPanel),
-                    tid);
+    publish_diag<T>(A, f, k0, w, B, dv, D, first, Zbuf + tk->M_off + (int64_t)(k0 / kPanel) * (kPanel * kPanel), tid);
 }
 
 // The first panels' diagonal blocks of a level (later ones run in
 // k_large_dstep beside the previous panel's trailing update).
 template <typename T>
-__global__ __launch_bounds__(256) void k_large_diag(DevPlan d, const int* __restrict__ tasks, T* __restrict__ F,
+__global__ __launch_bounds__(256, 2) void k_large_diag(DevPlan d, const LargeTask* __restrict__ tasks, T* __restrict__ F,
                                                     T* __restrict__ D, T* __restrict__ Zbuf) {
-    diag_body<T>(d, tasks[2 * blockIdx.x], tasks[2 * blockIdx.x + 1], F, D, Zbuf, threadIdx.x);
+    diag_body<T>(d, tasks + blockIdx.x, F, D, Zbuf, threadIdx.x);
 }
 
 // One workgroup per (front, panel, 32-row block) below the panel's diagonal
@@ -1126,14 +1134,11 @@ __global__ __launch_bounds__(256) void k_large_diag(DevPlan d, const int* __rest
 // and the output column blocks J = w >> 1 and 3 - (w >> 1); Z is lower
 // triangular, so block J contracts over k < 16 (J + 1) only.
 template <typename T>
-__device__ __forceinline__ void panel_body(const DevPlan& d, int s, int k0, int r0, T* F, const T* D,
-                                           const T* Zbuf, int tid) {
-    const int first = d.sn_first[s];
-    const int p = d.sn_first[s + 1] - first;
-    const int f = (int)(d.sn_rowptr[s + 1] - d.sn_rowptr[s]);
+__device__ __forceinline__ void panel_body(const LargeTask* tk, T* F, const T* D, const T* Zbuf, int tid) {
+    const int first = tk->first, p = tk->p, f = tk->f, k0 = tk->k0, r0 = tk->a;
     const int w = min(kPanel, p - k0);
-    T* __restrict__ A = F + d.L_off[s];
-    const T* __restrict__ Zt = Zbuf + d.M_off[s] + (int64_t)(k0 / kPanel) * (kPanel * kPanel);
+    T* __restrict__ A = F + tk->L_off;
+    const T* __restrict__ Zt = Zbuf + tk->M_off + (int64_t)(k0 / kPanel) * (kPanel * kPanel);
     const int wave = tid >> 6, lane = tid & 63;
     const int lr = lane & 15, lk = lane >> 4;
     const int rb = r0 + 16 * (wave & 1);
@@ -1149,9 +1154,7 @@ __device__ __forceinline__ void panel_body(const DevPlan& d, int s, int k0, int 
         }
     typedef typename Mfma<T>::acc_t acc_t;
     // Z operands of both output blocks (blocks K <= J only: Z is lower
-    // triangular), loaded before the padded MFMA chains (the padding's
-    // scheduling barriers would otherwise hold each load next to its MFMA and
-    // serialize the round trips)
+    // triangular), loaded before the MFMA chains
     T zo[2][4][4];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -1177,7 +1180,7 @@ __device__ __forceinline__ void panel_body(const DevPlan& d, int s, int k0, int 
         for (int K = 0; K < 4; ++K) {
             if (K > J) continue;   // uniform
 #pragma unroll
-            for (int st = 0; st < 4; ++st) acc = Mfma<T>::run_chained(a[K][st], zo[h][K][st], acc);
+            for (int st = 0; st < 4; ++st) acc = Mfma<T>::run(a[K][st], zo[h][K][st], acc);
         }
         const int col = 16 * J + lr;
         if (col < w) {
@@ -1196,23 +1199,19 @@ __device__ __forceinline__ void panel_body(const DevPlan& d, int s, int k0, int 
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_large_panel(DevPlan d, const int* __restrict__ tasks, T* __restrict__ F,
+__global__ __launch_bounds__(256) void k_large_panel(const LargeTask* __restrict__ tasks, T* __restrict__ F,
                                                      const T* __restrict__ D, const T* __restrict__ Zbuf) {
-    panel_body<T>(d, tasks[3 * blockIdx.x], tasks[3 * blockIdx.x + 1], tasks[3 * blockIdx.x + 2], F, D, Zbuf,
-                  threadIdx.x);
+    panel_body<T>(tasks + blockIdx.x, F, D, Zbuf, threadIdx.x);
 }
 
 // Trailing update of one 64x64 lower tile: C -= L_I D_k L_J^T on MFMA, with
 // the operands read straight from the front (no LDS).  The next panel's
 // diagonal tile is not in the task list: its diagonal-block workgroup updates it.
 template <typename T>
-__device__ __forceinline__ void update_body(const DevPlan& d, int s, int k0, int i0, int j0, T* F, const T* D,
-                                            int tid) {
-    const int first = d.sn_first[s];
-    const int p = d.sn_first[s + 1] - first;
-    const int f = (int)(d.sn_rowptr[s + 1] - d.sn_rowptr[s]);
+__device__ __forceinline__ void update_body(const LargeTask* tk, T* F, const T* D, int tid) {
+    const int first = tk->first, p = tk->p, f = tk->f, k0 = tk->k0, i0 = tk->a, j0 = tk->b;
     const int w = min(kPanel, p - k0);
-    T* __restrict__ A = F + d.L_off[s];
+    T* __restrict__ A = F + tk->L_off;
     typename Mfma<T>::acc_t acc[2][2];
     tile_update<T>(A, f, k0, w, i0, j0, D + first + k0, acc, tid);
     const int wave = tid >> 6, lane = tid & 63;
@@ -1224,7 +1223,7 @@ __device__ __forceinline__ void update_body(const DevPlan& d, int s, int k0, int
         for (int bj = 0; bj < 2; ++bj)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int gi = i0 + wr + bi * 16 + Mfma<T>::row(lk, r), gj = j0 + wc + bj * 16 + lr;
+                const int gi = i0 + wr + bi * 16 + lr, gj = j0 + wc + bj * 16 + Mfma<T>::row(lk, r);
                 if (gi < f && gj < f && gi >= gj) A[gi + (int64_t)gj * f] = acc[bi][bj][r];
             }
 }
@@ -1234,17 +1233,13 @@ __device__ __forceinline__ void update_body(const DevPlan& d, int s, int k0, int
 // blocks (their own update read from the front, like a tile), workgroups from nd8 = nd rounded up to a
 // multiple of 8 take the update tiles with the XCD-contiguous mapping.
 template <typename T>
-__global__ __launch_bounds__(256) void k_large_dstep(DevPlan d, const int* __restrict__ dtasks, int nd,
-                                                     const int* __restrict__ utasks, int nu, T* __restrict__ F,
+__global__ __launch_bounds__(256, 2) void k_large_dstep(DevPlan d, const LargeTask* __restrict__ dtasks, int nd,
+                                                     const LargeTask* __restrict__ utasks, int nu, T* __restrict__ F,
                                                      T* __restrict__ D, T* __restrict__ Zbuf) {
     const int nd8 = (nd + 7) & ~7;
     const int b = blockIdx.x;
-    if (b < nd) {
-        diag_body<T>(d, dtasks[2 * b], dtasks[2 * b + 1], F, D, Zbuf, threadIdx.x);
-    } else if (b >= nd8) {
-        const int* tk = utasks + 4 * xcd_task(b - nd8, nu);
-        update_body<T>(d, tk[0], tk[1], tk[2], tk[3], F, D, threadIdx.x);
-    }
+    if (b < nd) diag_body<T>(d, dtasks + b, F, D, Zbuf, threadIdx.x);
+    else if (b >= nd8) update_body<T>(utasks + xcd_task(b - nd8, nu), F, D, threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -2416,25 +2411,24 @@ void launch_large_asm(const DevPlan& d, int64_t first, int count, int fmax, cons
 }
 
 template <typename T>
-void launch_large_diag(const DevPlan& d, const int* tasks, int count, T* F, T* D, T* M, hipStream_t st) {
+void launch_large_diag(const DevPlan& d, const LargeTask* tasks, int count, T* F, T* D, T* M, hipStream_t st) {
     if (count <= 0) return;
     launch(k_large_diag<T>, dim3(count), dim3(256), 0, st, d, tasks, F, D, M);
 }
 
 template <typename T>
-void launch_large_panel(const DevPlan& d, const int* tasks, int count, T* F, const T* D, const T* M, hipStream_t st) {
+void launch_large_panel(const LargeTask* tasks, int count, T* F, const T* D, const T* M, hipStream_t st) {
     if (count <= 0) return;
-    launch(k_large_panel<T>, dim3(count), dim3(256), 0, st, d, tasks, F, D, M);
+    launch(k_large_panel<T>, dim3(count), dim3(256), 0, st, tasks, F, D, M);
 }
 
 template <typename T>
-void launch_large_dstep(const DevPlan& d, const int* dtasks, int nd, const int* utasks, int nu, T* F, T* D, T* M,
-                        hipStream_t st) {
+void launch_large_dstep(const DevPlan& d, const LargeTask* dtasks, int nd, const LargeTask* utasks, int nu, T* F,
+                        T* D, T* M, hipStream_t st) {
     if (nd <= 0 && nu <= 0) return;
     const int nd8 = (nd + 7) & ~7;
     launch(k_large_dstep<T>, dim3(nd8 + nu), dim3(256), 0, st, d, dtasks, nd, utasks, nu, F, D, M);
 }
-
 
 template <typename T>
 void launch_permute_in(const DevPlan& d, const double* B, int64_t ldb, int nrhs, T* Y, hipStream_t st) {
@@ -2555,9 +2549,10 @@ hipError_t configure_kernels(int max_dynamic_lds) {
 #define NCL_INSTANTIATE(T)                                                                                         \
     template void launch_small_fronts<T>(const DevPlan&, const int*, int, int, const double*, T*, T*, hipStream_t); \
     template void launch_large_asm<T>(const DevPlan&, int64_t, int, int, const double*, T*, hipStream_t);          \
-    template void launch_large_diag<T>(const DevPlan&, const int*, int, T*, T*, T*, hipStream_t);                \
-    template void launch_large_panel<T>(const DevPlan&, const int*, int, T*, const T*, const T*, hipStream_t);     \
-    template void launch_large_dstep<T>(const DevPlan&, const int*, int, const int*, int, T*, T*, T*, hipStream_t); \
+    template void launch_large_diag<T>(const DevPlan&, const LargeTask*, int, T*, T*, T*, hipStream_t);          \
+    template void launch_large_panel<T>(const LargeTask*, int, T*, const T*, const T*, hipStream_t);               \
+    template void launch_large_dstep<T>(const DevPlan&, const LargeTask*, int, const LargeTask*, int, T*, T*, T*,  \
+                                        hipStream_t);                                                              \
     template void launch_permute_in<T>(const DevPlan&, const double*, int64_t, int, T*, hipStream_t);              \
     template void launch_permute_out<T>(const DevPlan&, const T*, int, double*, int64_t, hipStream_t);             \
     template void launch_fwd_S<T>(const DevPlan&, const int*, int, const T*, const T*, T*, T*, int, hipStream_t);  \

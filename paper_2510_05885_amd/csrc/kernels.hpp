@@ -32,6 +32,14 @@ constexpr int kResWidth = 6;         // residual figures per (row chunk, column)
 constexpr size_t kAsmLdsMax = 96 * 1024;  // large-front column assembly staged in LDS (4 columns per
                                            // workgroup) up to this size
 
+// A large-front task (diagonal block, 32 panel rows or update tile) with its
+// front's fields, so that one load brings all of it: pivots first .. first + p,
+// order f, panel k0, a = first panel row or tile row, b = tile column.
+struct LargeTask {
+    int first, p, f, k0, a, b, sys, s;
+    int64_t L_off, M_off;
+};
+
 // Device copies of the plan (all device pointers), passed by value.
 struct DevPlan {
     int64_t N;
@@ -52,6 +60,7 @@ struct DevPlan {
     const int* row_sys;
     const int8_t* row_sign;
     const int* perm;
+    const int8_t* piv_sign;    // row_sign in pivot order
     // supernodes
     const int* sn_first;
     const int64_t* sn_rowptr;
@@ -147,14 +156,14 @@ void launch_small_fronts(const DevPlan& d, const int* list, int count, int fmax,
 template <typename T>
 void launch_large_asm(const DevPlan& d, int64_t first, int count, int fmax, const double* K, T* F, hipStream_t st);
 template <typename T>
-void launch_large_diag(const DevPlan& d, const int* tasks, int count, T* F, T* D, T* M, hipStream_t st);
+void launch_large_diag(const DevPlan& d, const LargeTask* tasks, int count, T* F, T* D, T* M, hipStream_t st);
 template <typename T>
-void launch_large_panel(const DevPlan& d, const int* tasks, int count, T* F, const T* D, const T* M, hipStream_t st);
+void launch_large_panel(const LargeTask* tasks, int count, T* F, const T* D, const T* M, hipStream_t st);
 // Panel k's trailing update (utasks) and panel k+1's diagonal blocks (dtasks)
 // in one launch.
 template <typename T>
-void launch_large_dstep(const DevPlan& d, const int* dtasks, int nd, const int* utasks, int nu, T* F, T* D, T* M,
-                        hipStream_t st);
+void launch_large_dstep(const DevPlan& d, const LargeTask* dtasks, int nd, const LargeTask* utasks, int nu, T* F,
+                        T* D, T* M, hipStream_t st);
 
 // ---- solves -----------------------------------------------------------------
 template <typename T>
