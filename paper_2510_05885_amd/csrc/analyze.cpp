@@ -710,7 +710,10 @@ int build_plan(Plan& P, int form, const std::vector<SysInput>& sys, int ordering
                 int64_t fa = P.sn_rowptr[a + 1] - P.sn_rowptr[a], fb = P.sn_rowptr[b + 1] - P.sn_rowptr[b];
                 return fa != fb ? fa > fb : a < b;
             });
-            // batches by front-size class (32-wide), each launch sized for its largest front
+            // batches by front-size class (32-wide), each launch sized for its
+            // largest front; a level with no more small fronts than the GPU has
+            // CUs is one batch, since each launch then costs its own latency
+            const bool one = small.size() <= 256;
             size_t k = 0;
             while (k < small.size()) {
                 LevelBatch b;
@@ -720,9 +723,11 @@ int build_plan(Plan& P, int form, const std::vector<SysInput>& sys, int ordering
                 int cls = (f0 + 31) / 32;
                 b.fmax = f0;
                 while (k < small.size()) {
-                    int fk = (int)(P.sn_rowptr[small[k] + 1] - P.sn_rowptr[small[k]]);
-                    if ((fk + 31) / 32 != cls) break;
-                    P.small_list.push_back(small[k]);
+                    const int s = small[k];
+                    int fk = (int)(P.sn_rowptr[s + 1] - P.sn_rowptr[s]);
+                    if (!one && (fk + 31) / 32 != cls) break;
+                    b.strip = std::max(b.strip, front_strip(fk, P.sn_first[s + 1] - P.sn_first[s]));
+                    P.small_list.push_back(s);
                     ++k;
                 }
                 b.count = (int64_t)P.small_list.size() - b.first;

@@ -89,7 +89,9 @@ struct ncl_kkt_s {
     DevPlan d{};
     int64_t nnzF = 0;
     // schedule arrays (device)
-    int *small_list = nullptr, *level_list = nullptr, *large_asm = nullptr, *solve_p = nullptr, *solve_seg = nullptr, *solve_s = nullptr,
+    FrontTask* small_tasks = nullptr;
+    FrontPlan fp{};
+    int *level_list = nullptr, *large_asm = nullptr, *solve_p = nullptr, *solve_seg = nullptr, *solve_s = nullptr,
         *fsolve_p = nullptr;
     LargeTask *large_panel = nullptr, *large_upd = nullptr, *large_diag = nullptr;
     int *chunk_row0 = nullptr, *chunk_rows = nullptr, *sys_chunk_ptr = nullptr;
@@ -131,9 +133,6 @@ struct ncl_kkt_s {
     // second stream: a level's small fronts run beside its large-front chain
     hipStream_t aux_stream = nullptr;
     std::vector<hipEvent_t> lvl_ev;   // 2 per level: fork, join
-    // fourth stream: a level's small-front batches split over two streams
-    hipStream_t aux2_stream = nullptr;
-    std::vector<hipEvent_t> sb_ev;    // 2 per level: fork, join of the second batch stream
     hipGraphExec_t g_factor[2] = {nullptr, nullptr};
     hipGraphExec_t g_sweep[2][kNrhsMax + 1] = {};
 };
@@ -272,7 +271,37 @@ void setup_device(ncl_kkt_s* h) {
     d.asm_seg_cb = upload(h, P.asm_seg_cb);
     d.asm_seg_rel = upload(h, P.asm_seg_rel);
     d.asm_seg_bc = upload(h, P.asm_seg_bc);
-    h->small_list = upload(h, P.small_list);
+    {
+        // small fronts as records, with their children's row maps and the
+        // places of their K entries
+        std::vector<FrontTask> ft;
+        std::vector<KidMap> km;
+        std::vector<uint8_t> map;
+        std::vector<int> rc(P.kent_pos.size(), 0);
+        for (int s : P.small_list) {
+            const int f = (int)(P.sn_rowptr[s + 1] - P.sn_rowptr[s]);
+            const int64_t k0 = P.kent_ptr[s], k1 = P.kent_ptr[s + 1];
+            for (int64_t e = k0; e < k1; ++e) rc[e] = P.kent_pos[e] % f + 256 * (P.kent_pos[e] / f);
+            FrontTask t{P.sn_first[s], P.sn_first[s + 1] - P.sn_first[s], f, P.sn_sys[s], s, (int)km.size(), 0,
+                        (int)(k1 - k0), P.L_off[s], P.CB_off[s], k0, P.CB_ld[s], 0};
+            for (int k = P.child_ptr[s]; k < P.child_ptr[s + 1]; ++k) {
+                const int ch = P.child_list[k];
+                const int64_t r0 = P.rel_ptr[ch], cc = P.rel_ptr[ch + 1] - r0;
+                if (cc == 0) continue;
+                km.push_back(KidMap{P.CB_off[ch], P.CB_ld[ch], (int)map.size()});
+                map.resize(map.size() + f, 255);
+                for (int64_t a = 0; a < cc; ++a) map[km.back().map_off + P.rel[r0 + a]] = (uint8_t)a;
+                ++t.nkid;
+            }
+            ft.push_back(t);
+        }
+        h->small_tasks = upload(h, ft);
+        h->fp.kids = upload(h, km);
+        h->fp.kid_map = upload(h, map);
+        h->fp.kent_rc = upload(h, rc);
+        h->fp.kent_csr = d.kent_csr;
+        h->fp.piv_sign = d.piv_sign;
+    }
     h->level_list = upload(h, P.level_list);
     h->large_asm = upload(h, P.large_asm);
     {
@@ -353,6 +382,9 @@ void setup_device(ncl_kkt_s* h) {
     d.inertia = h->inertia;
     d.inertia_part = h->inertia_part;
     d.nonfinite = h->nonfinite;
+    h->fp.sys_thr = h->thr;
+    h->fp.inertia_part = h->inertia_part;
+    h->fp.nonfinite = h->nonfinite;
     h->F64 = dalloc<double>(h, P.factor_elems);
     h->D64 = dalloc<double>(h, P.N);
     h->M64 = dalloc<double>(h, P.M_elems);
@@ -414,9 +446,6 @@ void setup_device(ncl_kkt_s* h) {
     HIPCHK(hipStreamCreateWithFlags(&h->aux_stream, hipStreamNonBlocking));
     h->lvl_ev.assign(2 * (size_t)std::max(P.nlevels, 1), nullptr);
     for (auto& e : h->lvl_ev) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    HIPCHK(hipStreamCreateWithFlags(&h->aux2_stream, hipStreamNonBlocking));
-    h->sb_ev.assign(2 * (size_t)std::max(P.nlevels, 1), nullptr);
-    for (auto& e : h->sb_ev) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     {
         int lds = 0;
         HIPCHK(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, h->device));
@@ -539,33 +568,22 @@ void factor_fronts(ncl_kkt_s* h, T* F, T* D, T* Mb, hipStream_t st) {
     launch_zero_u64(h->inertia_part, 4 * (int64_t)P.S * kInertiaSlots, st);
     size_t sb = 0, lb = 0;
     for (int l = 0; l < P.nlevels; ++l) {
-        // Fronts of one level are independent: when the level has both kinds,
-        // its small fronts go to the second stream (forked after the previous
-        // level, joined before the next one).
-        const bool has_small = sb < P.small_batches.size() && P.small_batches[sb].level == l;
+        // Fronts of one level are independent: when the level has large fronts and
+        // more small ones than fill the GPU once, the small ones go to the second
+        // stream (forked after the previous level, joined before the next one).
+        // Fewer take less than the fork and the join (about 10 us each way, against 15 us).
+        int64_t nsmall = 0;
+        for (size_t i = sb; i < P.small_batches.size() && P.small_batches[i].level == l; ++i)
+            nsmall += P.small_batches[i].count;
         const bool has_large = lb < P.large_steps.size() && P.large_steps[lb].level == l;
-        const bool fork = has_small && has_large;
+        const bool fork = nsmall > 256 && has_large;
         hipStream_t ss = fork ? h->aux_stream : st;
         if (fork) {
             HIPCHK(hipEventRecord(h->lvl_ev[2 * l], st));
             HIPCHK(hipStreamWaitEvent(ss, h->lvl_ev[2 * l], 0));
         }
-        // The level's batches (one per front-size class, each a launch) are
-        // independent: split them over two streams, each batch to the one
-        // with less estimated work (a latency floor plus count x fmax^2).
-        size_t nbl = 0;
-        while (sb + nbl < P.small_batches.size() && P.small_batches[sb + nbl].level == l) ++nbl;
-        const bool split = nbl >= 2;
-        if (split) {
-            HIPCHK(hipEventRecord(h->sb_ev[2 * l], st));
-            HIPCHK(hipStreamWaitEvent(h->aux2_stream, h->sb_ev[2 * l], 0));
-        }
-        double work[2] = {0.0, 0.0};
         while (sb < P.small_batches.size() && P.small_batches[sb].level == l) {
             const LevelBatch& b = P.small_batches[sb++];
-            const int side = split && work[1] < work[0] ? 1 : 0;
-            work[side] += 40.0 + (double)b.count * b.fmax * b.fmax / 2e5;
-            hipStream_t bs = side ? h->aux2_stream : ss;
             double fl = 0.0;
             if (h->tm.on)
                 for (int64_t k = b.first; k < b.first + b.count; ++k) {
@@ -576,10 +594,9 @@ void factor_fronts(ncl_kkt_s* h, T* F, T* D, T* Mb, hipStream_t st) {
                     for (int t = 0; t < p; ++t) { double r = f - t - 1; ff += r + r * (r + 1.0); }
                     fl += ff * P.sn_flop_ratio[s];
                 }
-            Span sp(h, bs, TM_SMALL, fl, 2);
-            launch_small_fronts<T>(d, h->small_list + b.first, (int)b.count, b.fmax, h->K, F, D, bs);
+            Span sp(h, ss, TM_SMALL, fl, 2);
+            launch_fronts<T>(h->fp, h->small_tasks + b.first, (int)b.count, b.fmax, b.strip, h->K, F, D, ss);
         }
-        if (split) HIPCHK(hipEventRecord(h->sb_ev[2 * l + 1], h->aux2_stream));
         if (lb < P.large_steps.size() && P.large_steps[lb].level == l) {
             const LargeStep& ls = P.large_steps[lb++];
             {
@@ -616,7 +633,6 @@ void factor_fronts(ncl_kkt_s* h, T* F, T* D, T* Mb, hipStream_t st) {
             HIPCHK(hipEventRecord(h->lvl_ev[2 * l + 1], ss));
             HIPCHK(hipStreamWaitEvent(st, h->lvl_ev[2 * l + 1], 0));
         }
-        if (split) HIPCHK(hipStreamWaitEvent(st, h->sb_ev[2 * l + 1], 0));
     }
     launch_reduce_inertia(d, P.S, st);
 }
@@ -1315,8 +1331,6 @@ void ncl_kkt_destroy(ncl_kkt_t h) {
             for (auto& g : row) if (g) (void)hipGraphExecDestroy(g);
         if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
         if (h->aux_stream) (void)hipStreamDestroy(h->aux_stream);
-        if (h->aux2_stream) (void)hipStreamDestroy(h->aux2_stream);
-        for (auto& e : h->sb_ev) if (e) (void)hipEventDestroy(e);
         for (auto& e : h->lvl_ev) if (e) (void)hipEventDestroy(e);
     }
     delete h;

@@ -43,7 +43,7 @@ __device__ __forceinline__ double to_d(float x) { return (double)x; }
 template <typename T>
 struct PivThr {
     double p, n;
-    __device__ PivThr(const DevPlan& d, int sys) : p(d.sys_thr[2 * sys]), n(d.sys_thr[2 * sys + 1]) {}
+    __device__ PivThr(const double* sys_thr, int sys) : p(sys_thr[2 * sys]), n(sys_thr[2 * sys + 1]) {}
     __device__ __forceinline__ T inv(int sign) const { return sign > 0 ? T(1) / (T)p : -(T(1) / (T)n); }
 };
 
@@ -62,17 +62,10 @@ __device__ __forceinline__ T static_pivot(T d, const PivThr<T>& th, int sign, bo
 
 // Adds a workgroup's pivot counts to one of the system's partial counters
 // (many fronts finish at once; one shared counter would serialize them).
-__device__ __forceinline__ void add_inertia(const DevPlan& d, int sys, const unsigned int* cnt, int slot) {
-    unsigned long long* in4 = d.inertia_part + 4 * ((int64_t)sys * kInertiaSlots + (slot & (kInertiaSlots - 1)));
+__device__ __forceinline__ void add_inertia(unsigned long long* part, int sys, const unsigned int* cnt, int slot) {
+    unsigned long long* in4 = part + 4 * ((int64_t)sys * kInertiaSlots + (slot & (kInertiaSlots - 1)));
     for (int k = 0; k < 4; ++k)
         if (cnt[k]) atomicAdd(&in4[k], (unsigned long long)cnt[k]);
-}
-
-__device__ __forceinline__ void count_pivot(unsigned long long* in4, double d, bool pert) {
-    if (d > 0.0) atomicAdd(&in4[0], 1ULL);
-    else if (d < 0.0) atomicAdd(&in4[1], 1ULL);
-    else atomicAdd(&in4[2], 1ULL);
-    if (pert) atomicAdd(&in4[3], 1ULL);
 }
 
 // 16x16x4 MFMA wrappers.  Operands: lane l holds A[l % 16][l / 16] and
@@ -219,30 +212,6 @@ __device__ __forceinline__ bool pivots_plain(T dk, const PivThr<T>& thr, int bw,
     return true;
 }
 
-// Partial LDL^T of the leading p columns of an f x f lower-triangular matrix
-// held in LDS (column-major, leading dimension lda), with the static-pivot
-// rule of Sec. 3.1.  Blocked by 16 columns: wave 0 factors each 16-column
-// sub-panel with the 64 rows below its diagonal block, wave 1 (which repeats
-// the diagonal block) the rows beyond those, then the four waves apply the
-// rank-16 update to the trailing lower matrix on MFMA.  A sub-panel with a
-// pivot below its threshold is done again by wave 0 alone, pivot by pivot.
-// On return A holds L (unit lower, strictly below the diagonal) in
-// its first p columns, d_k on the diagonal and in dv[k], and the Schur
-// complement in the trailing (f - p) x (f - p) part.  sgn[k] is the block sign
-// of pivot k.  Lane 0 of wave 0 accumulates the pivot counts into cnt[4].
-// kTwoRows: f may exceed 64 + (sub-panel start), so a lane holds two rows.
-// Must be called by all 256 threads; ends with a barrier.
-template <typename T>
-__device__ __forceinline__ void store_subpanel(T* A, int lda, int kb, int bw, int lane, int row, int f,
-                                               const T (&rp)[16], const T (&x)[16], T dk, bool diag) {
-#pragma unroll
-    for (int t = 0; t < 16; ++t) {
-        if (t >= bw) continue;   // uniform
-        if (diag && lane < 16 && lane >= t && kb + lane < f) A[(kb + lane) + (kb + t) * lda] = lane == t ? dk : rp[t];
-        if (row < f) A[row + (kb + t) * lda] = x[t];
-    }
-}
-
 // A sub-panel with a pivot that the static-pivot rule replaces (or a
 // non-finite one), by one wave straight in LDS, pivot by pivot: columns kb ..
 // kb + bw of the rows kb .. f - 1 of A.  Bit t of neg: pivot t takes the
@@ -284,78 +253,6 @@ __device__ __forceinline__ void subpanel_by_pivot(T* A, int lda, int f, int kb, 
     }
 }
 
-template <typename T, bool kTwoRows>
-__device__ void lds_partial_ldlt(T* A, int lda, int f, int p, T* dv, const int8_t* sgn, const PivThr<T>& thr,
-                                 unsigned int* cnt, bool& bad_out) {
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int lr = lane & 15, lk = lane >> 4;
-    bool bad_any = false;
-    for (int kb = 0; kb < p; kb += 16) {
-        const int bw = min(16, p - kb);
-        // wave 0: rows kb + 16 + lane below the diagonal block; wave 1: the 64 after
-        const bool act = wave == 0 || (kTwoRows && wave == 1 && kb + 80 < f);
-        const int row = kb + 16 + 64 * wave + lane;
-        T rp[16], x[16], dk = T(0);
-        unsigned int n3[3];
-        bool plain = true;
-        if (act) {
-            // a short sub-panel (bw < 16): the rows between it and row kb + 16
-            // are in the diagonal block's lanes lr >= bw
-#pragma unroll
-            for (int t = 0; t < 16; ++t) {
-                rp[t] = (t < bw && kb + lr < f && t <= lr) ? A[(kb + lr) + (kb + t) * lda] : T(0);
-                x[t] = (t < bw && row < f) ? A[row + (kb + t) * lda] : T(0);
-            }
-        }
-        if (kTwoRows) __syncthreads();   // wave 1 has read the diagonal block that wave 0 overwrites
-        if (act) {
-            pivots16<T, true>(rp, x, dk, bw, lr);
-            plain = pivots_plain(dk, thr, bw, lane, n3);
-            if (plain) {
-                store_subpanel(A, lda, kb, bw, lane, row, f, rp, x, dk, wave == 0);
-                if (wave == 0) {
-                    if (lane < bw) dv[kb + lane] = dk;
-                    if (lane == 0)
-                        for (int k = 0; k < 3; ++k) cnt[k] += n3[k];
-                }
-            } else if (wave == 0) {
-                const unsigned int neg = (unsigned int)__ballot(lane < bw && sgn[kb + min(lane, bw - 1)] < 0);
-                subpanel_by_pivot(A, lda, f, kb, bw, bw, neg, dv, thr, lane, cnt, bad_any);
-            }
-        }
-        __syncthreads();
-        // trailing update on MFMA: C -= L_panel D L_panel^T for rows/cols >= r0
-        const int r0 = kb + bw;
-        const int nt = (f - r0 + 15) / 16;
-        const int ntiles = nt * (nt + 1) / 2;
-        for (int tix = wave; tix < ntiles; tix += 4) {
-            int tj = 0, rem = tix;
-            while (rem >= nt - tj) { rem -= nt - tj; ++tj; }
-            const int ti = tj + rem;
-            const int i0 = r0 + 16 * ti, j0 = r0 + 16 * tj;
-            T av[4], bv[4];   // operands first: see panel_body
-#pragma unroll
-            for (int st = 0; st < 4; ++st) {
-                const int tt = 4 * st + lk;
-                const bool tv = tt < bw;
-                const int t = kb + tt;
-                av[st] = (tv && i0 + lr < f) ? A[(i0 + lr) + t * lda] : T(0);
-                bv[st] = (tv && j0 + lr < f) ? A[(j0 + lr) + t * lda] * dv[tv ? t : 0] : T(0);
-            }
-            typename Mfma<T>::acc_t acc = {0, 0, 0, 0};
-#pragma unroll
-            for (int st = 0; st < 4; ++st) acc = Mfma<T>::run(av[st], bv[st], acc);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int gi = i0 + Mfma<T>::row(lk, r), gj = j0 + lr;
-                if (gi < f && gj < f && gi >= gj) A[gi + gj * lda] -= acc[r];
-            }
-        }
-        __syncthreads();
-    }
-    bad_out = bad_any;
-}
-
 // ---- one diagonal block of a large front ---------------------------------
 // LDL^T of a kPanel x kPanel diagonal block and Z = L^-1, by the workgroup.
 // The block's ten lower 16 x 16 tiles stay in MFMA accumulators (three a wave)
@@ -383,16 +280,17 @@ __device__ __forceinline__ T zget(const T* B, int u, int t) {
     return u > t ? B[t + u * kDiagLd] : (u == t ? T(1) : T(0));
 }
 
-// acc (a tile at block (ti, tj), transposed) -= L_ti D L_tj^T of sub-panel q.
+// acc (a tile at block (ti, tj), transposed) -= L_ti D L_tj^T of sub-panel q,
+// L in LDS with leading dimension ld.
 template <typename T>
-__device__ __forceinline__ void diag_apply(typename Mfma<T>::acc_t& acc, const T* B, const T* dv, int q, int ti,
+__device__ __forceinline__ void diag_apply(typename Mfma<T>::acc_t& acc, const T* B, int ld, const T* dv, int q, int ti,
                                            int tj, int lr, int lk) {
     T a[4], b[4];
 #pragma unroll
     for (int st = 0; st < 4; ++st) {
         const int t = 16 * q + 4 * st + lk;
-        a[st] = B[(16 * tj + lr) + t * kDiagLd] * -dv[t];
-        b[st] = B[(16 * ti + lr) + t * kDiagLd];
+        a[st] = B[(16 * tj + lr) + t * ld] * -dv[t];
+        b[st] = B[(16 * ti + lr) + t * ld];
     }
 #pragma unroll
     for (int st = 0; st < 4; ++st) acc = Mfma<T>::run(a[st], b[st], acc);
@@ -403,12 +301,12 @@ __device__ __forceinline__ void diag_apply(typename Mfma<T>::acc_t& acc, const T
 // entries come from lane i of its row.  Waves that need Z_qq at the same time
 // each do this and write the same values.
 template <typename T>
-__device__ __forceinline__ void diag_inv16(T* B, int q, int lane) {
+__device__ __forceinline__ void diag_inv16(T* B, int ld, int q, int lane) {
     const int o = 16 * q, j = lane & 15;
     T lrow[16], z[16];
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
-        const T x = B[(o + j) + (o + u) * kDiagLd];
+        const T x = B[(o + j) + (o + u) * ld];
         lrow[u] = u < j ? x : T(0);
         z[u] = (u == j) ? T(1) : T(0);
     }
@@ -425,7 +323,7 @@ __device__ __forceinline__ void diag_inv16(T* B, int q, int lane) {
     if (lane < 16) {
 #pragma unroll
         for (int i = 1; i < 16; ++i)
-            if (i > j) B[(o + j) + (o + i) * kDiagLd] = z[i];
+            if (i > j) B[(o + j) + (o + i) * ld] = z[i];
     }
     wave_fence();
 }
@@ -479,7 +377,7 @@ __device__ __forceinline__ void diag_factor(typename Mfma<T>::acc_t (&acc)[3], T
     // side work of waves 1..3 once sub-panel i is factored: the diagonal block
     // of Z, and block (i, wave - 1) from the sum formed before
     auto zstep = [&](int i) {
-        if (wave <= i + 1) diag_inv16<T>(B, i, lane);
+        if (wave <= i + 1) diag_inv16<T>(B, kDiagLd, i, lane);
         if (wave <= i) diag_zrow<T>(S, B, i, wave - 1, lr, lk);
     };
 #pragma unroll 1
@@ -527,7 +425,7 @@ __device__ __forceinline__ void diag_factor(typename Mfma<T>::acc_t (&acc)[3], T
         } else if (q > 0) {
 #pragma unroll
             for (int t = 0; t < 3; ++t)
-                if (diag_tj(wave, t) > q) diag_apply<T>(acc[t], B, dv, q - 1, diag_ti(wave, t), diag_tj(wave, t), lr, lk);
+                if (diag_tj(wave, t) > q) diag_apply<T>(acc[t], B, kDiagLd, dv, q - 1, diag_ti(wave, t), diag_tj(wave, t), lr, lk);
             zstep(q - 1);
             if (wave <= q) diag_zsum<T>(S, B, q, wave - 1, lr, lk);
         }
@@ -535,7 +433,7 @@ __device__ __forceinline__ void diag_factor(typename Mfma<T>::acc_t (&acc)[3], T
 #pragma unroll
         for (int t = 0; t < 3; ++t)
             if (diag_has(wave, t) && diag_tj(wave, t) == q + 1)
-                diag_apply<T>(acc[t], B, dv, q, diag_ti(wave, t), q + 1, lr, lk);
+                diag_apply<T>(acc[t], B, kDiagLd, dv, q, diag_ti(wave, t), q + 1, lr, lk);
     }
     if (wave > 0) zstep(nq - 1);
     __syncthreads();
@@ -681,220 +579,234 @@ __global__ void k_thresholds(int S, const double* norms3, double eps, int mode, 
 }
 
 // ---------------------------------------------------------------------------
-// small fronts: one workgroup per front, front in LDS (column-major, ld = f)
+// small fronts (order up to kSmallMax)
 // ---------------------------------------------------------------------------
-// One front s (f <= kSmallMax) factored by the whole workgroup in LDS (A: f x f
-// of T); `slot` spreads the inertia atomics.  Ends with the write-out (no
-// trailing barrier).
-template <typename T, bool kTwoRows>
-__device__ __forceinline__ void small_front_body(const DevPlan& d, int s, int slot, const double* __restrict__ K,
-                                                 T* __restrict__ F, T* __restrict__ D, T* A) {
-    __shared__ T dv[kSmallMax];
-    __shared__ int8_t sgn[kSmallMax];
-    const int first = d.sn_first[s];
-    const int p = d.sn_first[s + 1] - first;
-    const int f = (int)(d.sn_rowptr[s + 1] - d.sn_rowptr[s]);
-    const int c = f - p;
-    const int tid = threadIdx.x;
-    const int ti = tid & 63, tj = tid >> 6;
+// One front by NW waves: one for orders up to 64, four for those up to 128.
+// The front's lower 16 x 16 tiles are MFMA accumulators (held transposed, lane
+// % 16 = row): the children's contribution blocks are gathered straight into
+// them through byte maps (front row -> child row), and what is left in them
+// after the last pivot is the front's own contribution block.  Only the pivot
+// columns live in LDS (a strip of 16-column sub-panels, leading dimension
+// front_ld): K's entries are scattered there, a sub-panel's tiles are added
+// when its turn comes, wave 0 eliminates it (wave 1 takes the rows more than
+// 64 below its diagonal block), and the other waves apply the previous one
+// meanwhile.
+// The whole front in LDS, as before, took 128 KB at order 128 (one workgroup a
+// CU) and pulled the children one after the other through LDS with two
+// barriers each: 36..45 us for a lone front of order 65..128, 20 us for
+// one of 33..64 (order 20k).  Bound by latency: about six dependent trips to
+// memory, then the pivots (1.2 us per 16).
+// Z_qq = L_qq^-1 of each 16-column sub-panel goes, transposed, into the
+// strictly upper triangle of its diagonal block, for the solves.
+constexpr int kKidBatch = 4;   // children whose maps are in LDS at a time
 
-    // The front's first K entries (position and value, two per thread) are
-    // loaded before the LDS zero-fill, so their latency overlaps it.
-    const int64_t ke0 = d.kent_ptr[s], ke1 = d.kent_ptr[s + 1];
-    int kpos[2];
-    T kval[2];
+// Leading dimension of the strip: 16 mod 32 elements, see kDiagLd.
+__host__ __device__ constexpr int front_ld(int nt) { return 16 * (nt | 1); }
+
+// Tile idx of the lower triangle of NT x NT tiles, column by column.
+template <int NT>
+__device__ __forceinline__ int tile_col(int idx) {
+    int c = 0;
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int64_t e = ke0 + tid + 256 * u;
-        if (e < ke1) {
-            kpos[u] = d.kent_pos[e];
-            kval[u] = (T)K[d.kent_csr[e]];
-        }
+    for (int j = 1; j < NT; ++j) c += idx >= j * NT - j * (j - 1) / 2;
+    return c;
+}
+template <int NT>
+__device__ __forceinline__ int tile_row(int idx) {
+    const int c = tile_col<NT>(idx);
+    return c + idx - (c * NT - c * (c - 1) / 2);
+}
+
+template <int NW>
+__device__ __forceinline__ void front_sync() {
+    if (NW > 1) __syncthreads();
+    else wave_fence();
+}
+
+template <typename T, int NT, int NW>
+__global__ __launch_bounds__(64 * NW, NW > 1 ? 2 : 1) void k_front(FrontPlan d, const FrontTask* __restrict__ tasks,
+                                                               const double* __restrict__ K, T* __restrict__ F,
+                                                               T* __restrict__ D) {
+    constexpr int kThreads = 64 * NW, kTiles = NT * (NT + 1) / 2, kSlots = (kTiles + NW - 1) / NW, kRows = 16 * NT;
+    constexpr int kE = NW > 1 ? 2 : NT;   // K entries a thread holds from the start
+    typedef typename Mfma<T>::acc_t acc_t;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    T* S = reinterpret_cast<T*>(smem_raw);
+    __shared__ T dv[kRows];
+    __shared__ __align__(4) uint8_t mrow[kKidBatch][kRows], mcol[kKidBatch][kRows];
+    const FrontTask* tk = tasks + blockIdx.x;
+    const int first = tk->first, p = tk->p, f = tk->f, nkid = tk->nkid, kid0 = tk->kid0, kn = tk->kn;
+    const int nt = (f + 15) >> 4, nq = (p + 15) >> 4, ld = front_ld(nt), rows = 16 * nt;
+    const int tid = threadIdx.x, lane = tid & 63, wave = NW > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0;
+    const int lr = lane & 15, lk = lane >> 4;
+    const int64_t* __restrict__ kc = d.kent_csr + tk->k0;
+    const int* __restrict__ krc = d.kent_rc + tk->k0;
+    // K entries: places and values, in flight over the fill of the strip
+    int rc[kE];
+    T kv[kE];
+#pragma unroll
+    for (int u = 0; u < kE; ++u) {
+        const int e = tid + kThreads * u;
+        const int ec = min(e, kn - 1);
+        rc[u] = krc[ec];
+        kv[u] = (T)K[kc[ec]];
     }
-    for (int t = tid; t < f * f; t += 256) A[t] = T(0);
-    __syncthreads();
+    const PivThr<T> thr(d.sys_thr, tk->sys);
+    // the maps of children kid .. kid + kKidBatch - 1; columns in the order in
+    // which a lane's accumulator items take them
+    auto load_maps = [&](int kid) {
+        constexpr int kN = kKidBatch * kRows;
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-        if (ke0 + tid + 256 * u < ke1) A[kpos[u]] = kval[u];
-    for (int64_t e = ke0 + tid + 512; e < ke1; e += 256) A[d.kent_pos[e]] = (T)K[d.kent_csr[e]];
-    __syncthreads();
-    // extend-add: pull every child's contribution block, children in order.
-    // Entry (a, b) of the child's lower CB is element idx = a + 128 b of a
-    // 128-row grid (cc <= f <= 128); 8 loads per thread are issued before
-    // their LDS adds.
-    static_assert(kSmallMax == 128, "the extend-add grid assumes 128 rows");
-    __shared__ int rl[kSmallMax];
-    for (int k = d.child_ptr[s]; k < d.child_ptr[s + 1]; ++k) {
-        const int ch = d.child_list[k];
-        const int fc = (int)(d.sn_rowptr[ch + 1] - d.sn_rowptr[ch]);
-        const int cc = fc - (d.sn_first[ch + 1] - d.sn_first[ch]);
-        const T* __restrict__ CB = F + d.CB_off[ch];
-        const int ld = d.CB_ld[ch];
-        const int* __restrict__ r = d.rel + d.rel_ptr[ch];
-        const int n2 = kSmallMax * cc;
-        // the first batch of the child's entries is loaded before the
-        // barrier that publishes its row map, so both round trips overlap
-        T v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int idx = tid + 256 * u;
-            const int a = min(idx & (kSmallMax - 1), cc - 1), b = min(idx >> 7, cc - 1);
-            v[u] = cc > 0 ? CB[a + (int64_t)b * ld] : T(0);
+        for (int i0 = 0; i0 < kN; i0 += kThreads) {
+            const int i = i0 + tid, k = i / kRows, m = i % kRows;
+            uint8_t v = 255;
+            if (i < kN && kid + k < nkid && m < f) v = d.kid_map[d.kids[kid0 + kid + k].map_off + m];
+            if (i < kN) {
+                mrow[k][m] = v;
+                const int r = m & 15;
+                mcol[k][(m & ~15) + (sizeof(T) == 8 ? 4 * (r & 3) + (r >> 2) : r)] = v;
+            }
         }
-        if (tid < cc) rl[tid] = r[tid];
-        __syncthreads();
-        for (int base = 0; base < n2; base += 256 * 8) {
-            if (base > 0) {
+    };
+    load_maps(0);
+    for (int i = tid; i < ld * 16 * nq; i += kThreads) S[i] = T(0);
+    front_sync<NW>();
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int idx = base + tid + 256 * u;
-                    const int a = min(idx & (kSmallMax - 1), cc - 1), b = min(idx >> 7, cc - 1);
-                    v[u] = CB[a + (int64_t)b * ld];
+    for (int u = 0; u < kE; ++u)
+        if (tid + kThreads * u < kn) S[(rc[u] & 255) + (rc[u] >> 8) * ld] = kv[u];
+    for (int e = tid + kThreads * kE; e < kn; e += kThreads) S[(krc[e] & 255) + (krc[e] >> 8) * ld] = (T)K[kc[e]];
+    acc_t acc[kSlots];
+#pragma unroll
+    for (int t = 0; t < kSlots; ++t) acc[t] = acc_t{0, 0, 0, 0};
+    for (int kb = 0; kb < nkid; kb += kKidBatch) {
+        if (kb > 0) {
+            front_sync<NW>();
+            load_maps(kb);
+            front_sync<NW>();
+        }
+        const int kn2 = min(kKidBatch, nkid - kb);
+        for (int k = 0; k < kn2; ++k) {
+            const KidMap km = d.kids[kid0 + kb + k];
+            const T* __restrict__ CB = F + km.CB_off;
+            T v[kSlots][4];
+            unsigned long long ok = 0;
+#pragma unroll
+            for (int t = 0; t < kSlots; ++t) {
+                const int idx = NW * t + wave;
+                const int a = (int8_t)mrow[k][16 * tile_row<NT>(idx) + lr];   // -1: none
+                const unsigned int b4 = *reinterpret_cast<const unsigned int*>(&mcol[k][16 * tile_col<NT>(idx) + 4 * lk]);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int b = (int)(b4 >> (8 * r) & 255u);                // 255: none
+                    const bool in = a >= b;
+                    const unsigned int off = in ? (unsigned int)a + __umul24((unsigned int)b, (unsigned int)km.ld) : 0u;
+                    v[t][r] = CB[off];
+                    ok |= (unsigned long long)in << (4 * t + r);
                 }
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int idx = base + tid + 256 * u;
-                const int a = idx & (kSmallMax - 1), b = idx >> 7;
-                if (idx < n2 && a < cc && a >= b) A[rl[a] + rl[b] * f] += v[u];
-            }
+            for (int t = 0; t < kSlots; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[t][r] += (ok >> (4 * t + r) & 1ULL) ? v[t][r] : T(0);
         }
-        __syncthreads();
     }
-    // partial LDL^T of the p pivot columns (blocked, MFMA trailing updates)
-    const int sys = d.sn_sys[s];
-    for (int k = tid; k < p; k += 256) sgn[k] = d.row_sign[d.perm[first + k]];
-    __syncthreads();
     unsigned int cnt[4] = {0, 0, 0, 0};
     bool bad = false;
-    lds_partial_ldlt<T, kTwoRows>(A, f, f, p, dv, sgn, PivThr<T>(d, sys), cnt, bad);
+#pragma unroll 1
+    for (int q = 0; q < nq; ++q) {
+        const int kb = 16 * q, bw = min(16, p - kb);
+#pragma unroll
+        for (int t = 0; t < kSlots; ++t) {
+            const int idx = NW * t + wave, ti = tile_row<NT>(idx);
+            if (tile_col<NT>(idx) != q || ti >= nt) continue;   // uniform
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int c = Mfma<T>::row(lk, r);
+                if (c < bw) S[(16 * ti + lr) + (kb + c) * ld] += acc[t][r];
+            }
+        }
+        front_sync<NW>();
+        const bool two = NT > 4 && kb + 80 < rows;   // rows beyond the 64 that wave 0 takes
+        const int row = kb + 16 + 64 * wave + lane, rowc = min(row, rows - 1);
+        const bool act = wave == 0 || (wave == 1 && two);
+        T rp[16], x[16], dk = T(0);
+        if (act) {
+#pragma unroll
+            for (int t = 0; t < 16; ++t) {
+                rp[t] = S[(kb + lr) + (kb + t) * ld];
+                x[t] = S[rowc + (kb + t) * ld];
+            }
+        }
+        if (NW > 1 && two) __syncthreads();   // wave 1 has read the diagonal block that wave 0 overwrites
+        if (act) {
+            pivots16<T, true>(rp, x, dk, bw, lr);
+            unsigned int n3[3];
+            if (pivots_plain(dk, thr, bw, lane, n3)) {
+#pragma unroll
+                for (int t = 0; t < 16; ++t) {
+                    if (t >= bw) continue;   // uniform: columns past the last pivot stay zero
+                    if (row < rows) S[row + (kb + t) * ld] = x[t];
+                    if (wave == 0 && lane < 16) S[(kb + lane) + (kb + t) * ld] = rp[t];
+                }
+                if (wave == 0) {
+                    if (lane < 16) dv[kb + lane] = lane < bw ? dk : T(0);
+                    if (lane == 0)
+                        for (int k = 0; k < 3; ++k) cnt[k] += n3[k];
+                }
+            } else if (wave == 0) {
+                const int8_t sg = lane < bw ? d.piv_sign[first + kb + lane] : 1;
+                if (lane < 16) dv[kb + lane] = T(0);
+                wave_fence();
+                subpanel_by_pivot(S, ld, f, kb, bw, bw, (unsigned int)__ballot(sg < 0), dv, thr, lane, cnt, bad);
+            }
+        }
+        if (q > 0) {
+#pragma unroll
+            for (int t = 0; t < kSlots; ++t) {
+                const int idx = NW * t + wave, ti = tile_row<NT>(idx), tj = tile_col<NT>(idx);
+                if (tj > q && ti < nt) diag_apply<T>(acc[t], S, ld, dv, q - 1, ti, tj, lr, lk);
+            }
+            if (wave == NW - 1) diag_inv16<T>(S, ld, q - 1, lane);
+        }
+        front_sync<NW>();
+        if (q + 1 < nq) {
+#pragma unroll
+            for (int t = 0; t < kSlots; ++t) {
+                const int idx = NW * t + wave, ti = tile_row<NT>(idx);
+                if (tile_col<NT>(idx) == q + 1 && ti < nt) diag_apply<T>(acc[t], S, ld, dv, q, ti, q + 1, lr, lk);
+            }
+        }
+    }
+    // the last sub-panel, also on its own block column where that holds columns
+    // past the last pivot
+    if (f > p) {
+        const int tj0 = p >> 4;
+        const int64_t ldc = tk->CB_ld;
+        T* __restrict__ CB = F + tk->CB_off;
+#pragma unroll
+        for (int t = 0; t < kSlots; ++t) {
+            const int idx = NW * t + wave, ti = tile_row<NT>(idx), tj = tile_col<NT>(idx);
+            if (tj < tj0 || ti >= nt) continue;   // uniform
+            diag_apply<T>(acc[t], S, ld, dv, nq - 1, ti, tj, lr, lk);
+            const int i = 16 * ti + lr;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int j = 16 * tj + Mfma<T>::row(lk, r);
+                if (j >= p && i >= j && i < f) CB[(i - p) + (j - p) * ldc] = acc[t][r];
+            }
+        }
+    }
+    if (wave == NW - 1) diag_inv16<T>(S, ld, nq - 1, lane);
     if (tid == 0) {
-        add_inertia(d, sys, cnt, slot);
+        add_inertia(d.inertia_part, tk->sys, cnt, tk->s);
         if (bad) atomicOr(d.nonfinite, kNonfiniteFactor);
     }
-    for (int k = tid; k < p; k += 256) D[first + k] = dv[k];
-    // write L (f x p, ld f) and the contribution block (c x c, ld CB_ld)
-    T* __restrict__ L = F + d.L_off[s];
-    for (int j = tj; j < p; j += 4)
-        for (int i = j + ti; i < f; i += 64) L[i + (int64_t)j * f] = A[i + j * f];
-    if (c > 0) {
-        T* __restrict__ CB = F + d.CB_off[s];
-        const int ld = d.CB_ld[s];
-        for (int b = tj; b < c; b += 4)
-            for (int a = b + ti; a < c; a += 64) CB[a + (int64_t)b * ld] = A[(p + a) + (p + b) * f];
-    }
-}
-
-template <typename T, bool kTwoRows>
-__global__ __launch_bounds__(256) void k_small_fronts(DevPlan d, const int* __restrict__ list,
-                                                      const double* __restrict__ K, T* __restrict__ F,
-                                                      T* __restrict__ D) {
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    small_front_body<T, kTwoRows>(d, list[blockIdx.x], blockIdx.x, K, F, D, reinterpret_cast<T*>(smem_raw));
-}
-
-// Fronts of order f <= kTinyMax: one wave per front, four fronts per
-// workgroup, no workgroup barrier.  The wave assembles its front in an LDS
-// slice (K entries, then the children's contribution blocks one after the
-// other), loads row `lane` into registers and eliminates the p pivots right-
-// looking with readlane broadcasts (static pivoting of Sec. 3.1), then writes
-// L, D and the contribution block like k_small_fronts.
-constexpr int kTinyMax = 32;
-
-template <typename T>
-__global__ __launch_bounds__(256) void k_tiny_fronts(DevPlan d, const int* __restrict__ list, int count,
-                                                     const double* __restrict__ K, T* __restrict__ F,
-                                                     T* __restrict__ D) {
-    constexpr int LD = kTinyMax;
-    __shared__ T Aall[4][kTinyMax * kTinyMax];
-    __shared__ int rlall[4][kTinyMax];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int q = 4 * blockIdx.x + wave;
-    if (q >= count) return;
-    T* A = Aall[wave];
-    int* rl = rlall[wave];
-    const int s = list[q];
-    const int first = d.sn_first[s];
-    const int p = d.sn_first[s + 1] - first;
-    const int f = (int)(d.sn_rowptr[s + 1] - d.sn_rowptr[s]);
-    const int c = f - p;
-    for (int t = lane; t < kTinyMax * kTinyMax; t += 64) A[t] = T(0);
-    wave_fence();
-    // K entries come with local positions for leading dimension f
-    for (int64_t e = d.kent_ptr[s] + lane; e < d.kent_ptr[s + 1]; e += 64) {
-        const int pos = d.kent_pos[e];
-        A[pos % f + (pos / f) * LD] = (T)K[d.kent_csr[e]];
-    }
-    wave_fence();
-    for (int k = d.child_ptr[s]; k < d.child_ptr[s + 1]; ++k) {
-        const int ch = d.child_list[k];
-        const int fc = (int)(d.sn_rowptr[ch + 1] - d.sn_rowptr[ch]);
-        const int cc = fc - (d.sn_first[ch + 1] - d.sn_first[ch]);
-        if (cc <= 0) continue;   // uniform
-        const T* __restrict__ CB = F + d.CB_off[ch];
-        const int ld = d.CB_ld[ch];
-        if (lane < cc) rl[lane] = d.rel[d.rel_ptr[ch] + lane];
-        wave_fence();
-        T v[kTinyMax * kTinyMax / 64];
-#pragma unroll
-        for (int u = 0; u < kTinyMax * kTinyMax / 64; ++u) {
-            const int idx = lane + 64 * u, a = min(idx % kTinyMax, cc - 1), b = min(idx / kTinyMax, cc - 1);
-            v[u] = CB[a + (int64_t)b * ld];
-        }
-#pragma unroll
-        for (int u = 0; u < kTinyMax * kTinyMax / 64; ++u) {
-            const int idx = lane + 64 * u, a = idx % kTinyMax, b = idx / kTinyMax;
-            if (a < cc && b < cc && a >= b) A[rl[a] + rl[b] * LD] += v[u];
-        }
-        wave_fence();
-    }
-    // row `lane` of the front (lanes >= f hold zeros and are never stored)
-    T r[kTinyMax];
-#pragma unroll
-    for (int j = 0; j < kTinyMax; ++j) r[j] = A[(lane & (kTinyMax - 1)) + j * LD];
-    const bool neg = lane < p && d.row_sign[d.perm[first + lane]] < 0;
-    const unsigned long long negmask = __ballot(neg);
-    const int sys = d.sn_sys[s];
-    const PivThr<T> thr(d, sys);
-    unsigned int np = 0, nn = 0, nz = 0, npt = 0;
-    bool anybad = false;
-#pragma unroll
-    for (int k = 0; k < kTinyMax; ++k) {
-        if (k < p) {   // uniform
-            bool pert, bd;
-            const T draw = bcast(r[k], k);
-            const T inv0 = fast_rcp(draw);
-            const int sg = ((negmask >> k) & 1ULL) ? -1 : 1;
-            const T dk = static_pivot(draw, thr, sg, pert, bd);
-            const T inv = pert ? thr.inv(sg) : inv0;
-            const T l = r[k] * inv;
-#pragma unroll
-            for (int j = k + 1; j < kTinyMax; ++j) r[j] -= l * bcast(r[k], j);
-            r[k] = (lane == k) ? dk : l;
-            const double dd = to_d(dk);
-            np += dd > 0.0; nn += dd < 0.0; nz += dd == 0.0; npt += pert;
-            anybad |= bd;
-        }
-    }
-    if (lane == 0) {
-        const unsigned int cnt[4] = {np, nn, nz, npt};
-        add_inertia(d, sys, cnt, q);
-        if (anybad) atomicOr(d.nonfinite, kNonfiniteFactor);
-    }
-    T* __restrict__ L = F + d.L_off[s];
-    T* __restrict__ CBo = F + d.CB_off[s];
-    const int ldo = d.CB_ld[s];
-#pragma unroll
-    for (int j = 0; j < kTinyMax; ++j) {
-        if (lane < f && lane >= j) {
-            if (j < p) L[lane + (int64_t)j * f] = r[j];
-            else if (c > 0) CBo[(lane - p) + (int64_t)(j - p) * ldo] = r[j];
-        }
-    }
-    T mine = T(0);
-#pragma unroll
-    for (int j = 0; j < kTinyMax; ++j) mine = (lane == j) ? r[j] : mine;
-    if (lane < p) D[first + lane] = mine;
+    for (int k = tid; k < p; k += kThreads) D[first + k] = dv[k];
+    front_sync<NW>();
+    // L with Z^T above it: column j from the top of its diagonal block
+    T* __restrict__ L = F + tk->L_off;
+    for (int j = wave; j < p; j += NW)
+        for (int i = (j & ~15) + lane; i < f; i += 64) L[i + (int64_t)j * f] = S[i + j * ld];
 }
 
 // ---------------------------------------------------------------------------
@@ -1059,7 +971,7 @@ __device__ __forceinline__ void diag_body(const DevPlan& d, const LargeTask* tk,
     const int lr = lane & 15, lk = lane >> 4;
     __builtin_amdgcn_s_setprio(3);   // the launch waits for this chain, not for the tiles beside it
     const int8_t sg = lane < w ? d.piv_sign[first + k0 + lane] : 1;
-    const PivThr<T> thr(d, tk->sys);
+    const PivThr<T> thr(d.sys_thr, tk->sys);
     typename Mfma<T>::acc_t acc[3];
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
@@ -1093,7 +1005,7 @@ __device__ __forceinline__ void diag_body(const DevPlan& d, const LargeTask* tk,
 #pragma unroll
             for (int t = 0; t < 3; ++t)
                 if (diag_has(wave, t))
-                    diag_apply<T>(acc[t], B, dv, q, diag_ti(wave, t), diag_tj(wave, t), lr, lk);
+                    diag_apply<T>(acc[t], B, kDiagLd, dv, q, diag_ti(wave, t), diag_tj(wave, t), lr, lk);
         if (w < kPanel) {
 #pragma unroll
             for (int t = 0; t < 3; ++t) {
@@ -1112,7 +1024,7 @@ __device__ __forceinline__ void diag_body(const DevPlan& d, const LargeTask* tk,
     bool bad = false;
     diag_factor<T>(acc, B, dv, __ballot(sg < 0), w, thr, cnt, bad, tid);
     if (tid == 0) {
-        add_inertia(d, tk->sys, cnt, tk->s + k0);
+        add_inertia(d.inertia_part, tk->sys, cnt, tk->s + k0);
         if (bad) atomicOr(d.nonfinite, kNonfiniteFactor);
     }
     publish_diag<T>(A, f, k0, w, B, dv, D, first, Zbuf + tk->M_off + (int64_t)(k0 / kPanel) * (kPanel * kPanel), tid);
@@ -2385,18 +2297,14 @@ void launch_thresholds(int S, const double* norms3, double eps, int mode, const 
 }
 
 template <typename T>
-void launch_small_fronts(const DevPlan& d, const int* list, int count, int fmax, const double* K, T* F, T* D,
-                         hipStream_t st) {
+void launch_fronts(const FrontPlan& d, const FrontTask* tasks, int count, int fmax, int strip, const double* K, T* F,
+                   T* D, hipStream_t st) {
     if (count <= 0) return;
-    if (fmax <= kTinyMax) {
-        launch(k_tiny_fronts<T>, dim3((count + 3) / 4), dim3(256), 0, st, d, list, count, K, F, D);
-        return;
-    }
-    const size_t lds = (size_t)fmax * fmax * sizeof(T);
-    if (fmax <= 64)
-        launch(k_small_fronts<T, false>, dim3(count), dim3(256), lds, st, d, list, K, F, D);
-    else
-        launch(k_small_fronts<T, true>, dim3(count), dim3(256), lds, st, d, list, K, F, D);
+    const uint32_t lds = (uint32_t)(strip * sizeof(T));
+    if (fmax <= 32) launch(k_front<T, 2, 1>, dim3(count), dim3(64), lds, st, d, tasks, K, F, D);
+    else if (fmax <= 64) launch(k_front<T, 4, 1>, dim3(count), dim3(64), lds, st, d, tasks, K, F, D);
+    else if (fmax <= 96) launch(k_front<T, 6, 4>, dim3(count), dim3(256), lds, st, d, tasks, K, F, D);
+    else launch(k_front<T, 8, 4>, dim3(count), dim3(256), lds, st, d, tasks, K, F, D);
 }
 
 template <typename T>
@@ -2528,8 +2436,8 @@ void launch_adjoint(const DevPlan& d, int64_t nnzW, const int* W_row, const int*
 // (gfx950 has 160 KiB per workgroup).
 hipError_t configure_kernels(int max_dynamic_lds) {
     hipError_t e = hipSuccess, r;
-    const void* fns[] = {(const void*)k_small_fronts<double, true>, (const void*)k_small_fronts<float, true>,
-                         (const void*)k_small_fronts<double, false>, (const void*)k_small_fronts<float, false>,
+    const void* fns[] = {(const void*)k_front<double, 6, 4>, (const void*)k_front<double, 8, 4>,
+                         (const void*)k_front<float, 6, 4>, (const void*)k_front<float, 8, 4>,
                          (const void*)k_fwd_P<double, kNrhsMax>, (const void*)k_fwd_P<float, kNrhsMax>,
                          (const void*)k_bwd_P<double, kNrhsMax>, (const void*)k_bwd_P<float, kNrhsMax>,
                          (const void*)k_fwd_S<double>, (const void*)k_fwd_S<float>,
@@ -2547,7 +2455,8 @@ hipError_t configure_kernels(int max_dynamic_lds) {
 }
 
 #define NCL_INSTANTIATE(T)                                                                                         \
-    template void launch_small_fronts<T>(const DevPlan&, const int*, int, int, const double*, T*, T*, hipStream_t); \
+    template void launch_fronts<T>(const FrontPlan&, const FrontTask*, int, int, int, const double*, T*, T*,       \
+                                   hipStream_t);                                                                   \
     template void launch_large_asm<T>(const DevPlan&, int64_t, int, int, const double*, T*, hipStream_t);          \
     template void launch_large_diag<T>(const DevPlan&, const LargeTask*, int, T*, T*, T*, hipStream_t);          \
     template void launch_large_panel<T>(const LargeTask*, int, T*, const T*, const T*, hipStream_t);               \

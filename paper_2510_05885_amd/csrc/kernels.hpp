@@ -40,6 +40,31 @@ struct LargeTask {
     int64_t L_off, M_off;
 };
 
+// A small front: pivots first .. first + p, order f, its children's maps
+// (kids kid0 .. kid0 + nkid) and its K entries (k0 .. k0 + kn of kent_csr / kent_rc).
+struct FrontTask {
+    int first, p, f, sys, s, kid0, nkid, kn;
+    int64_t L_off, CB_off, k0;
+    int CB_ld, pad;
+};
+// A child of a small front: its contribution block and its map, one byte per
+// row of the parent: the contribution row that lands there, 255 for none.
+struct KidMap {
+    int64_t CB_off;
+    int ld, map_off;
+};
+// What the small-front kernels read of the plan.
+struct FrontPlan {
+    const KidMap* kids;
+    const uint8_t* kid_map;
+    const int64_t* kent_csr;
+    const int* kent_rc;        // front row + 256 * front column of each K entry (small fronts)
+    const int8_t* piv_sign;
+    const double* sys_thr;
+    unsigned long long* inertia_part;
+    int* nonfinite;
+};
+
 // Device copies of the plan (all device pointers), passed by value.
 struct DevPlan {
     int64_t N;
@@ -150,9 +175,11 @@ void launch_thresholds(int S, const double* norms3, double eps, int mode, const 
                        double* kinf, double* thr, int* nonfinite, hipStream_t st);
 
 // ---- numeric factorization (T = double or float) --------------------------
+// One launch of small fronts of order up to fmax; strip: elements of LDS for
+// the pivot columns of the largest (front_strip).
 template <typename T>
-void launch_small_fronts(const DevPlan& d, const int* list, int count, int fmax, const double* K, T* F, T* D,
-                         hipStream_t st);
+void launch_fronts(const FrontPlan& d, const FrontTask* tasks, int count, int fmax, int strip, const double* K, T* F,
+                   T* D, hipStream_t st);
 template <typename T>
 void launch_large_asm(const DevPlan& d, int64_t first, int count, int fmax, const double* K, T* F, hipStream_t st);
 template <typename T>

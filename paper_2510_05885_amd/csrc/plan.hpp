@@ -22,9 +22,15 @@ struct PlanConfig {
     double relax_big_zeros = 0.2;  // panels anyway) may carry up to this fraction of zeros
 };
 
+// LDS elements that the pivot columns of a small front of order f with p pivots
+// take: whole 16-column sub-panels, leading dimension an odd multiple of 16
+// that covers f.
+inline int front_strip(int f, int p) { return 16 * (((f + 15) / 16) | 1) * 16 * ((p + 15) / 16); }
+
 struct LevelBatch {            // one launch of the small-front kernel
     int level = 0;
-    int fmax = 0;              // largest front in the batch (sets LDS size)
+    int fmax = 0;              // largest front in the batch
+    int strip = 0;             // LDS elements of the pivot columns, see front_strip()
     int64_t first = 0, count = 0;  // range in Plan::small_list
 };
 
