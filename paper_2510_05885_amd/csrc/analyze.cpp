@@ -689,12 +689,16 @@ int build_plan(Plan& P, int form, const std::vector<SysInput>& sys, int ordering
         }
         P.U_elems = std::max<int64_t>(uoff, 32);
         P.M_off.assign(nsn, -1);   // -1: small front (no panel inverses)
+        P.P_off.assign(nsn, 0);
         int64_t moff = 0;
         for (int s = 0; s < nsn; ++s) {
             if (!P.sn_large[s]) continue;
             const int64_t p = P.sn_first[s + 1] - P.sn_first[s];
             P.M_off[s] = moff;
-            moff += ((p + cfg.panel - 1) / cfg.panel) * (int64_t)cfg.panel * cfg.panel;
+            // one block per panel, then P and P^T per pair of panels
+            const int64_t npan = (p + cfg.panel - 1) / cfg.panel, blk = (int64_t)cfg.panel * cfg.panel;
+            P.P_off[s] = moff + npan * blk;
+            moff += (npan + 2 * (npan / 2)) * blk;
         }
         P.M_elems = std::max<int64_t>(moff, 32);
 
@@ -800,196 +804,149 @@ int build_plan(Plan& P, int form, const std::vector<SysInput>& sys, int ordering
         }
         // ---------------- solve schedule -----------------------------------
         {
-            const int PW = 64;   // kPanel
-            // rows per task: the panel's columns are taken 16 at a time by the
-            // four waves, the rest of the workgroup takes more rows
-            auto task_rows = [](int w) { return 64 * (4 / ((w + 15) / 16)); };
-            // entries [a0, a1) of child ch's update vector landing in parent rows [lo, hi)
-            auto child_range = [&](int ch, int lo, int hi, int& a0, int& a1) {
-                const int* r = P.rel.data() + P.rel_ptr[ch];
-                const int cc = (int)(P.rel_ptr[ch + 1] - P.rel_ptr[ch]);
-                a0 = (int)(std::lower_bound(r, r + cc, lo) - r);
-                a1 = (int)(std::lower_bound(r, r + cc, hi) - r);
-            };
-            for (int s = 0; s < nsn; ++s)
-                for (int64_t q = P.rel_ptr[s] + 1; q < P.rel_ptr[s + 1]; ++q)
-                    if (P.rel[q] <= P.rel[q - 1]) throw AnalyzeError(-4, "internal: update-vector map not increasing");
-            std::vector<std::vector<int>> sn_pids(nsn);   // panels of each front, in column order
-            std::vector<int64_t> pan_task0;               // first task of each panel
-            for (int l = 0; l < P.nlevels; ++l) {
-                int maxj = 0;
-                for (int k = P.level_ptr[l]; k < P.level_ptr[l + 1]; ++k) {
-                    int s = P.level_list[k];
-                    int p = P.sn_first[s + 1] - P.sn_first[s];
-                    maxj = std::max(maxj, (p + PW - 1) / PW);
+            const int PW = cfg.panel;
+            // gather tables: row i of front s takes the update-vector entries
+            // gather[gat[s] + k f + i], k = 0 .. gk[s] - 1, in the children's order
+            std::vector<int64_t> gat(nsn, 0);
+            std::vector<int> gk(nsn, 0), depth;
+            if (P.U_elems >= (int64_t)1 << 31) throw AnalyzeError(-3, "update vectors beyond 2^31 entries");
+            for (int s = 0; s < nsn; ++s) {
+                const int f = (int)(P.sn_rowptr[s + 1] - P.sn_rowptr[s]);
+                depth.assign(f, 0);
+                for (int k = P.child_ptr[s]; k < P.child_ptr[s + 1]; ++k) {
+                    const int ch = P.child_list[k];
+                    for (int64_t q = P.rel_ptr[ch]; q < P.rel_ptr[ch + 1]; ++q) gk[s] = std::max(gk[s], ++depth[P.rel[q]]);
                 }
-                for (int j = 0; j < maxj; ++j) {
+                gat[s] = (int64_t)P.gather.size();
+                P.gather.resize(P.gather.size() + (size_t)gk[s] * f, -1);
+                std::fill(depth.begin(), depth.end(), 0);
+                for (int k = P.child_ptr[s]; k < P.child_ptr[s + 1]; ++k) {
+                    const int ch = P.child_list[k];
+                    for (int64_t q = P.rel_ptr[ch], a = 0; q < P.rel_ptr[ch + 1]; ++q, ++a) {
+                        const int i = P.rel[q];
+                        P.gather[gat[s] + (int64_t)depth[i]++ * f + i] = (int)(P.U_off[ch] + a);
+                    }
+                }
+            }
+            auto pivots = [&](int s) { return P.sn_first[s + 1] - P.sn_first[s]; };
+            auto order = [&](int s) { return (int)(P.sn_rowptr[s + 1] - P.sn_rowptr[s]); };
+            // a pair's task without its rows
+            auto pair_task = [&](int s, int c0) {
+                PanelTask t{};
+                t.first = P.sn_first[s]; t.p = pivots(s); t.f = order(s);
+                t.c0 = c0;
+                t.w1 = std::min(PW, t.p - c0);
+                t.w2 = std::min(PW, t.p - c0 - t.w1);
+                t.L_off = P.L_off[s]; t.U_off = P.U_off[s]; t.M_off = P.M_off[s]; t.rows_off = P.sn_rowptr[s];
+                t.P_off = t.w2 > 0 ? P.P_off[s] + (int64_t)(c0 / (2 * PW)) * 2 * PW * PW : 0;
+                t.gat = gat[s]; t.gk = c0 == 0 ? gk[s] : 0;
+                t.ntask = std::max(1, (t.f - c0 - t.w1 - t.w2 + 63) / 64);
+                return t;
+            };
+            auto pair_bytes = [&](const PanelTask& t, int s) {
+                double e = 0.0;
+                for (int j = t.c0; j < t.c0 + t.w1 + t.w2; ++j) e += t.f - j;
+                return 8.0 * e * P.sn_nnz_ratio[s];
+            };
+            std::vector<std::vector<SolveStep>> back(P.nlevels);
+            for (int l = 0; l < P.nlevels; ++l) {
+                int npair = 0;
+                SolveStep sm;
+                sm.s_first = (int64_t)P.solve_small.size();
+                for (int k = P.level_ptr[l]; k < P.level_ptr[l + 1]; ++k) {
+                    const int s = P.level_list[k], p = pivots(s), f = order(s);
+                    if (P.sn_large[s]) {
+                        npair = std::max(npair, (p + 2 * PW - 1) / (2 * PW));
+                        for (int c0 = 0; c0 + PW < p; c0 += 2 * PW)
+                            P.pairs.push_back(PairTask{f, c0, std::min(PW, p - c0 - PW), 0, P.L_off[s],
+                                                       P.M_off[s] + (int64_t)(c0 / PW) * PW * PW,
+                                                       P.P_off[s] + (int64_t)(c0 / (2 * PW)) * 2 * PW * PW});
+                    } else {
+                        P.solve_small.push_back(SmallTask{P.sn_first[s], p, f, gk[s], P.L_off[s], P.U_off[s],
+                                                          P.sn_rowptr[s], gat[s]});
+                        sm.bytes += 8.0 * ((double)p * f - (double)p * (p - 1) / 2.0) * P.sn_nnz_ratio[s];
+                    }
+                }
+                sm.s_count = (int64_t)P.solve_small.size() - sm.s_first;
+                const int nstep = std::max(npair, 1);
+                std::vector<int> slot_of;   // the previous step's first slot of each front (backward)
+                std::vector<int> large;
+                for (int k = P.level_ptr[l]; k < P.level_ptr[l + 1]; ++k)
+                    if (P.sn_large[P.level_list[k]]) large.push_back(P.level_list[k]);
+                for (int j = 0; j < nstep; ++j) {
                     SolveStep st;
-                    st.level = l; st.j = j;
-                    st.p_first = (int64_t)P.solve_p.size() / 6;
-                    st.s_first = (int64_t)P.solve_s.size();
+                    st.level = l; st.k = j;
+                    if (j == 0) { st.s_first = sm.s_first; st.s_count = sm.s_count; st.bytes = sm.bytes; }
+                    st.p_first = (int64_t)P.fwd_tasks.size();
+                    for (int s : large) {
+                        if (j * 2 * PW >= pivots(s)) continue;
+                        PanelTask t = pair_task(s, j * 2 * PW);
+                        st.bytes += pair_bytes(t, s);
+                        for (int i = 0; i < t.ntask; ++i) {
+                            t.index = i;
+                            t.r0 = std::min(t.f, t.c0 + t.w1 + t.w2 + 64 * i);
+                            t.r1 = std::min(t.f, t.r0 + 64);
+                            P.fwd_tasks.push_back(t);
+                        }
+                    }
+                    st.p_count = (int64_t)P.fwd_tasks.size() - st.p_first;
+                    P.fwd_steps.push_back(st);
+                }
+                // backward: pairs from the last; every front's slots of a step are
+                // consecutive, and the next step's first two tasks read them
+                slot_of.assign(large.size(), 0);
+                for (int j = nstep - 1; j >= -1; --j) {
+                    SolveStep st;
+                    st.level = l; st.k = j;
+                    if (j == nstep - 1) { st.s_first = sm.s_first; st.s_count = sm.s_count; st.bytes = sm.bytes; }
+                    st.p_first = (int64_t)P.bwd_tasks.size();
                     int slot = 0;
-                    for (int k = P.level_ptr[l]; k < P.level_ptr[l + 1]; ++k) {
-                        int s = P.level_list[k];
-                        const int p = P.sn_first[s + 1] - P.sn_first[s];
-                        const int f = (int)(P.sn_rowptr[s + 1] - P.sn_rowptr[s]);
-                        const int c0 = j * PW;
-                        if (c0 >= p) continue;
-                        const int w = std::min(PW, p - c0);
-                        const int below = f - c0 - w;
-                        st.fwd_bytes += 8.0 * ((double)w * (w + 1) / 2.0 + (double)below * w) * P.sn_nnz_ratio[s];
-                        if (!P.sn_large[s] && p <= 64 && f <= 128) {
-                            P.solve_s.push_back(s);
+                    for (size_t a = 0; a < large.size(); ++a) {
+                        const int s = large[a];
+                        // the pair of the step before, if its tasks left sums
+                        PanelTask fin{};
+                        if ((j + 1) * 2 * PW < pivots(s)) {
+                            fin = pair_task(s, (j + 1) * 2 * PW);
+                            if (fin.ntask == 1) fin.ntask = 0;
+                        }
+                        auto finishes = [&](PanelTask& t, int which) {
+                            t.fc0 = fin.c0; t.fw1 = fin.w1; t.fw2 = fin.w2; t.fP_off = fin.P_off;
+                            t.fslot0 = slot_of[a]; t.fntask = fin.ntask; t.which = which;
+                        };
+                        const int nfin = fin.ntask == 0 ? 0 : (fin.w2 > 0 ? 2 : 1);
+                        if (j < 0) {
+                            for (int i = 0; i < nfin; ++i) {
+                                PanelTask t = fin;
+                                t.index = -1;
+                                t.r0 = t.r1 = t.f;
+                                finishes(t, i);
+                                P.bwd_tasks.push_back(t);
+                            }
                             continue;
                         }
-                        const int pid = (int)(P.solve_pan.size() / 7);
-                        sn_pids[s].push_back(pid);
-                        pan_task0.push_back((int64_t)P.solve_p.size() / 6);
-                        const int GR = task_rows(w);
-                        if (!P.sn_large[s] && below > 64)
-                            throw AnalyzeError(-4, "internal: LDS-path front with more than 64 rows below a panel");
-                        const int ntask = std::max(1, (below + GR - 1) / GR);
-                        const int seg0 = (int)(P.solve_seg.size() / 3);
-                        if (c0 == 0)
-                            for (int q = P.child_ptr[s]; q < P.child_ptr[s + 1]; ++q) {
-                                int a0, a1;
-                                child_range(P.child_list[q], 0, w, a0, a1);
-                                if (a1 > a0) { P.solve_seg.push_back(P.child_list[q]); P.solve_seg.push_back(a0); P.solve_seg.push_back(a1); }
-                            }
-                        const int nseg = (int)(P.solve_seg.size() / 3) - seg0;
-                        for (int v : {s, c0, w, slot, ntask, seg0, nseg}) P.solve_pan.push_back(v);
-                        for (int t = 0; t < ntask; ++t) {
-                            const int r0 = below > 0 ? c0 + w + t * GR : f;
-                            const int r1 = below > 0 ? std::min(f, r0 + GR) : f;
-                            const int tseg0 = (int)(P.solve_seg.size() / 3);
-                            if (c0 == 0 && r1 > r0)
-                                for (int q = P.child_ptr[s]; q < P.child_ptr[s + 1]; ++q) {
-                                    int a0, a1;
-                                    child_range(P.child_list[q], r0, r1, a0, a1);
-                                    if (a1 > a0) { P.solve_seg.push_back(P.child_list[q]); P.solve_seg.push_back(a0); P.solve_seg.push_back(a1); }
-                                }
-                            const int tnseg = (int)(P.solve_seg.size() / 3) - tseg0;
-                            for (int v : {pid, r0, r1, t, tseg0, tnseg}) P.solve_p.push_back(v);
+                        if (j * 2 * PW >= pivots(s)) continue;
+                        PanelTask t = pair_task(s, j * 2 * PW);
+                        if (nfin > t.ntask) throw AnalyzeError(-4, "internal: a panel pair has too few tasks to finish the next");
+                        st.bytes += pair_bytes(t, s);
+                        t.slot0 = slot;
+                        for (int i = 0; i < t.ntask; ++i) {
+                            PanelTask u = t;
+                            u.index = i;
+                            u.r0 = std::min(t.f, t.c0 + t.w1 + t.w2 + 64 * i);
+                            u.r1 = std::min(t.f, u.r0 + 64);
+                            if (i < nfin) finishes(u, i);
+                            P.bwd_tasks.push_back(u);
                         }
-                        slot += ntask;
+                        slot_of[a] = slot;
+                        slot += t.ntask;
                     }
-                    st.p_count = (int64_t)P.solve_p.size() / 6 - st.p_first;
-                    st.s_count = (int64_t)P.solve_s.size() - st.s_first;
+                    st.p_count = (int64_t)P.bwd_tasks.size() - st.p_first;
                     P.solve_max_slots = std::max<int64_t>(P.solve_max_slots, slot);
-                    P.solve_steps.push_back(st);
+                    if (st.p_count > 0 || st.s_count > 0) back[l].push_back(st);
                 }
             }
-            // Backward: a panel swept by several tasks is finished (its x from
-            // the tasks' sums) by the first task of the front's previous panel,
-            // whose rows start with it; a front's first panel by a finish-only
-            // record launched after its level's last step.
-            const int64_t nreg = (int64_t)P.solve_p.size() / 6;
-            P.solve_fin.assign(4 * (size_t)nreg, 0);
-            auto fin_fields = [&](int pid, int* out) {
-                const int* pn = P.solve_pan.data() + 7 * (size_t)pid;
-                out[0] = pn[1]; out[1] = pn[2]; out[2] = pn[3]; out[3] = pn[4];
-            };
-            for (int s = 0; s < nsn; ++s) {
-                const std::vector<int>& pids = sn_pids[s];
-                for (size_t j = 0; j + 1 < pids.size(); ++j) {
-                    if (P.solve_pan[7 * (size_t)pids[j + 1] + 4] <= 1) continue;
-                    if (!P.sn_large[s]) throw AnalyzeError(-4, "internal: multi-task panel in an LDS-path front");
-                    const int64_t t0 = pan_task0[pids[j]];
-                    if (P.solve_p[6 * t0 + 3] != 0 || P.solve_p[6 * t0 + 1] != P.solve_pan[7 * (size_t)pids[j + 1] + 1] ||
-                        P.solve_pan[7 * (size_t)pids[j] + 4] <= 1)
-                        throw AnalyzeError(-4, "internal: first task of a panel does not start at the next panel");
-                    fin_fields(pids[j + 1], P.solve_fin.data() + 4 * t0);
-                }
-            }
-            for (SolveStep& st : P.solve_steps) {
-                if (st.j != 0) continue;
-                st.f_first = (int64_t)P.solve_p.size() / 6;
-                for (int k = P.level_ptr[st.level]; k < P.level_ptr[st.level + 1]; ++k) {
-                    const int s = P.level_list[k];
-                    if (sn_pids[s].empty()) continue;
-                    const int pid = sn_pids[s][0];
-                    if (P.solve_pan[7 * (size_t)pid + 4] <= 1) continue;
-                    const int f = (int)(P.sn_rowptr[s + 1] - P.sn_rowptr[s]);
-                    for (int v : {pid, f, f, -1, 0, 0}) P.solve_p.push_back(v);
-                    int fin[4];
-                    fin_fields(pid, fin);
-                    for (int v : fin) P.solve_fin.push_back(v);
-                }
-                st.f_count = (int64_t)P.solve_p.size() / 6 - st.f_first;
-            }
-            // Forward: a large front's panels are taken two at a time (2k and
-            // 2k + 1 in step k of its level): its tasks own the rows below the
-            // second panel, 64 each, and form both panels' y themselves.  Other
-            // fronts keep one panel per step.  Tasks refer to the first
-            // panel's record; solve_fx holds (w of the second panel or 0, its
-            // pivot rows' contribution segments (first, count), 0).
-            {
-                std::vector<int64_t> s_first_of(P.nlevels, 0), s_count_of(P.nlevels, 0);
-                for (const SolveStep& st : P.solve_steps)
-                    if (st.j == 0) { s_first_of[st.level] = st.s_first; s_count_of[st.level] = st.s_count; }
-                for (int l = 0; l < P.nlevels; ++l) {
-                    int maxk = 0;
-                    for (int k = P.level_ptr[l]; k < P.level_ptr[l + 1]; ++k) {
-                        const int s = P.level_list[k];
-                        const int np = (int)sn_pids[s].size();
-                        maxk = std::max(maxk, P.sn_large[s] ? (np + 1) / 2 : np);
-                    }
-                    if (s_count_of[l] > 0) maxk = std::max(maxk, 1);
-                    for (int kk = 0; kk < maxk; ++kk) {
-                        SolveStep st;
-                        st.level = l; st.j = kk;
-                        st.p_first = (int64_t)P.fsolve_p.size() / 6;
-                        if (kk == 0) { st.s_first = s_first_of[l]; st.s_count = s_count_of[l]; }
-                        for (int k = P.level_ptr[l]; k < P.level_ptr[l + 1]; ++k) {
-                            const int s = P.level_list[k];
-                            const std::vector<int>& pids = sn_pids[s];
-                            const bool lg = P.sn_large[s] != 0;
-                            const size_t j = lg ? 2 * (size_t)kk : (size_t)kk;
-                            if (j >= pids.size()) continue;
-                            const int pid = pids[j];
-                            const int* pn = P.solve_pan.data() + 7 * (size_t)pid;
-                            const int c0 = pn[1], w = pn[2];
-                            const int f = (int)(P.sn_rowptr[s + 1] - P.sn_rowptr[s]);
-                            const int w2 = (lg && j + 1 < pids.size()) ? P.solve_pan[7 * (size_t)pids[j + 1] + 2] : 0;
-                            if (w2 > 0 && w != PW) throw AnalyzeError(-4, "internal: paired panel narrower than 64");
-                            auto bytes = [&](int cc, int ww) {
-                                const int below = f - cc - ww;
-                                return 8.0 * ((double)ww * (ww + 1) / 2.0 + (double)below * ww) * P.sn_nnz_ratio[s];
-                            };
-                            st.fwd_bytes += bytes(c0, w) + (w2 > 0 ? bytes(c0 + w, w2) : 0.0);
-                            const int rs = c0 + w + w2;                 // first row below the step's panels
-                            const int below = f - rs;
-                            const int GR = w2 > 0 ? 64 : task_rows(w);
-                            const int ntask = std::max(1, (below + GR - 1) / GR);
-                            int s2seg0 = (int)(P.solve_seg.size() / 3), s2nseg = 0;
-                            if (w2 > 0 && c0 == 0) {
-                                for (int q = P.child_ptr[s]; q < P.child_ptr[s + 1]; ++q) {
-                                    int a0, a1;
-                                    child_range(P.child_list[q], w, w + w2, a0, a1);
-                                    if (a1 > a0) { P.solve_seg.push_back(P.child_list[q]); P.solve_seg.push_back(a0); P.solve_seg.push_back(a1); }
-                                }
-                                s2nseg = (int)(P.solve_seg.size() / 3) - s2seg0;
-                            }
-                            for (int t = 0; t < ntask; ++t) {
-                                const int r0 = below > 0 ? rs + t * GR : f;
-                                const int r1 = below > 0 ? std::min(f, r0 + GR) : f;
-                                const int tseg0 = (int)(P.solve_seg.size() / 3);
-                                if (c0 == 0 && r1 > r0)
-                                    for (int q = P.child_ptr[s]; q < P.child_ptr[s + 1]; ++q) {
-                                        int a0, a1;
-                                        child_range(P.child_list[q], r0, r1, a0, a1);
-                                        if (a1 > a0) { P.solve_seg.push_back(P.child_list[q]); P.solve_seg.push_back(a0); P.solve_seg.push_back(a1); }
-                                    }
-                                const int tnseg = (int)(P.solve_seg.size() / 3) - tseg0;
-                                for (int v : {pid, r0, r1, t, tseg0, tnseg}) P.fsolve_p.push_back(v);
-                                for (int v : {w2, s2seg0, s2nseg, 0}) P.fsolve_x.push_back(v);
-                            }
-                        }
-                        st.p_count = (int64_t)P.fsolve_p.size() / 6 - st.p_first;
-                        P.fsolve_steps.push_back(st);
-                    }
-                }
-            }
+            for (int l = P.nlevels - 1; l >= 0; --l)
+                P.bwd_steps.insert(P.bwd_steps.end(), back[l].begin(), back[l].end());
         }
     } catch (const AnalyzeError& e) {
         err = e.what();

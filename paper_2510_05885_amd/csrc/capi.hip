@@ -91,8 +91,10 @@ struct ncl_kkt_s {
     // schedule arrays (device)
     FrontTask* small_tasks = nullptr;
     FrontPlan fp{};
-    int *level_list = nullptr, *large_asm = nullptr, *solve_p = nullptr, *solve_seg = nullptr, *solve_s = nullptr,
-        *fsolve_p = nullptr;
+    int *level_list = nullptr, *large_asm = nullptr, *gather = nullptr;
+    PanelTask *fwd_tasks = nullptr, *bwd_tasks = nullptr;
+    SmallTask* solve_small = nullptr;
+    PairTask* pairs = nullptr;
     LargeTask *large_panel = nullptr, *large_upd = nullptr, *large_diag = nullptr;
     int *chunk_row0 = nullptr, *chunk_rows = nullptr, *sys_chunk_ptr = nullptr;
     int nchunks = 0;
@@ -134,7 +136,7 @@ struct ncl_kkt_s {
     hipStream_t aux_stream = nullptr;
     std::vector<hipEvent_t> lvl_ev;   // 2 per level: fork, join
     hipGraphExec_t g_factor[2] = {nullptr, nullptr};
-    hipGraphExec_t g_sweep[2][kNrhsMax + 1] = {};
+    hipGraphExec_t g_sweep[2][2] = {};   // one column, several
 };
 
 namespace {
@@ -260,10 +262,6 @@ void setup_device(ncl_kkt_s* h) {
     d.L_off = upload(h, P.L_off);
     d.CB_off = upload(h, P.CB_off);
     d.CB_ld = upload(h, P.CB_ld);
-    std::vector<int64_t> uo(P.U_off);
-    for (auto& x : uo) x *= kNrhsMax;
-    d.U_off = upload(h, uo);
-    d.M_off = upload(h, P.M_off);
     d.asm_col = upload(h, P.asm_col);
     d.asm_fj = upload(h, P.asm_fj);
     d.asm_kr = upload(h, P.asm_kr);
@@ -321,39 +319,11 @@ void setup_device(ncl_kkt_s* h) {
         h->large_panel = upload(h, records(P.large_panel, 3));
         h->large_upd = upload(h, records(P.large_upd, 4));
     }
-    {
-        // every sweep task with its panel's and its front's fields (kTaskRec
-        // ints): the backward tasks (with the panel each finishes) and the
-        // forward ones (with their second panel)
-        auto records = [&](const std::vector<int>& tasks, const std::vector<int>* fin,
-                           const std::vector<int>* fx) {
-            const size_t nt = tasks.size() / kPTaskInts;
-            std::vector<int> rec(std::max<size_t>(nt, 1) * kTaskRec, 0);
-            for (size_t t = 0; t < nt; ++t) {
-                int* r = rec.data() + t * kTaskRec;
-                const int* tk = tasks.data() + t * kPTaskInts;
-                const int* pn = P.solve_pan.data() + (size_t)tk[0] * kPanInts;
-                const int s = pn[0];
-                for (int i = 0; i < kPTaskInts; ++i) r[i] = tk[i];
-                for (int i = 0; i < kPanInts; ++i) r[kPTaskInts + i] = pn[i];
-                r[13] = P.sn_first[s];
-                r[14] = P.sn_first[s + 1] - P.sn_first[s];
-                r[15] = (int)(P.sn_rowptr[s + 1] - P.sn_rowptr[s]);
-                // U_off as on the device: room for kNrhsMax columns per front
-                const int64_t v64[4] = {P.L_off[s], P.U_off[s] * kNrhsMax, P.M_off[s], P.sn_rowptr[s]};
-                std::memcpy(r + kTaskRec64, v64, sizeof(v64));
-                for (int i = 0; i < 4; ++i) {
-                    if (fin) r[kTaskRec64 + 8 + i] = (*fin)[4 * t + i];
-                    if (fx) r[kTaskRec64 + 12 + i] = (*fx)[4 * t + i];
-                }
-            }
-            return rec;
-        };
-        h->solve_p = upload(h, records(P.solve_p, &P.solve_fin, nullptr));
-        h->fsolve_p = upload(h, records(P.fsolve_p, nullptr, &P.fsolve_x));
-    }
-    h->solve_seg = upload(h, P.solve_seg);
-    h->solve_s = upload(h, P.solve_s);
+    h->fwd_tasks = upload(h, P.fwd_tasks);
+    h->bwd_tasks = upload(h, P.bwd_tasks);
+    h->solve_small = upload(h, P.solve_small);
+    h->pairs = upload(h, P.pairs);
+    h->gather = upload(h, P.gather);
     // row chunks (<= 256 rows, never straddling two systems)
     std::vector<int> c0, cn, scp(1, 0);
     for (int s = 0; s < P.S; ++s) {
@@ -388,16 +358,16 @@ void setup_device(ncl_kkt_s* h) {
     h->F64 = dalloc<double>(h, P.factor_elems);
     h->D64 = dalloc<double>(h, P.N);
     h->M64 = dalloc<double>(h, P.M_elems);
-    h->Y64 = dalloc<double>(h, 2 * P.N * kNrhsMax);   // right-hand side, then the pivots' y / x
+    h->Y64 = dalloc<double>(h, 3 * P.N * kNrhsMax);   // right-hand side, the pivots' y, their x
     h->U64 = dalloc<double>(h, P.U_elems * kNrhsMax);
-    h->P64 = dalloc<double>(h, 2 * std::max<int64_t>(P.solve_max_slots, 1) * kPanel * kNrhsMax);
+    h->P64 = dalloc<double>(h, 4 * std::max<int64_t>(P.solve_max_slots, 1) * kPanel * kNrhsMax);
     if (h->opt.precision == NCL_FP32_IR) {
         h->F32 = dalloc<float>(h, P.factor_elems);
         h->D32 = dalloc<float>(h, P.N);
         h->M32 = dalloc<float>(h, P.M_elems);
-        h->Y32 = dalloc<float>(h, 2 * P.N * kNrhsMax);
+        h->Y32 = dalloc<float>(h, 3 * P.N * kNrhsMax);
         h->U32 = dalloc<float>(h, P.U_elems * kNrhsMax);
-        h->P32 = dalloc<float>(h, 2 * std::max<int64_t>(P.solve_max_slots, 1) * kPanel * kNrhsMax);
+        h->P32 = dalloc<float>(h, 4 * std::max<int64_t>(P.solve_max_slots, 1) * kPanel * kNrhsMax);
     }
     h->R = dalloc<double>(h, P.N * kNrhsMax);
     h->DX = dalloc<double>(h, P.N * kNrhsMax);
@@ -634,6 +604,7 @@ void factor_fronts(ncl_kkt_s* h, T* F, T* D, T* Mb, hipStream_t st) {
             HIPCHK(hipStreamWaitEvent(st, h->lvl_ev[2 * l + 1], 0));
         }
     }
+    launch_pair_inverse<T>(h->pairs, (int)P.pairs.size(), F, Mb, st);
     launch_reduce_inertia(d, P.S, st);
 }
 
@@ -760,88 +731,22 @@ int factor_impl(ncl_kkt_s* h, const double* W, const double* Sigma, const double
 // ----- solve -------------------------------------------------------------------
 template <typename T>
 void sweeps(ncl_kkt_s* h, int nrhs, const T* F, const T* Z, const T* D, T* Y, T* U, T* partial, hipStream_t st) {
-    Plan& P = h->P;
-    const DevPlan& d = h->d;
-    T* Y2 = Y + P.N * kNrhsMax;
-    const std::vector<SolveStep>& S = P.solve_steps;
-    const std::vector<SolveStep>& FS = P.fsolve_steps;
-    // Steps of one level are independent between the one-wave fronts and the
-    // panel tasks: when a level has both, the one-wave fronts go to the second
-    // stream, forked at the level's first step and joined after its last.
-    auto level_end = [&](const std::vector<SolveStep>& V, size_t i) {
-        size_t e = i;
-        while (e < V.size() && V[e].level == V[i].level) ++e;
-        return e;
-    };
-    auto has_panels = [&](const std::vector<SolveStep>& V, size_t i0, size_t i1) {
-        for (size_t i = i0; i < i1; ++i)
-            if (V[i].p_count > 0) return true;
-        return false;
-    };
-    for (size_t i0 = 0; i0 < FS.size();) {
-        const size_t i1 = level_end(FS, i0);
-        const int l = FS[i0].level;
-        const bool fork = FS[i0].s_count > 0 && has_panels(FS, i0, i1);
-        hipStream_t ss = fork ? h->aux_stream : st;
-        if (fork) {
-            HIPCHK(hipEventRecord(h->lvl_ev[2 * l], st));
-            HIPCHK(hipStreamWaitEvent(ss, h->lvl_ev[2 * l], 0));
-        }
-        for (size_t i = i0; i < i1; ++i) {
-            const SolveStep& ss_ = FS[i];
-            if (ss_.s_count > 0) {
-                Span sp(h, ss, TM_SOLVE, 0.0, 0);
-                launch_fwd_S<T>(d, h->solve_s + ss_.s_first, (int)ss_.s_count, F, Y, Y2, U, nrhs, ss);
-            }
-            if (ss_.p_count > 0) {
-                Span sp(h, st, TM_SOLVE, ss_.fwd_bytes * sizeof(T) / 8.0, 4);
-                launch_fwd_P<T>(d, h->fsolve_p + kTaskRec * ss_.p_first, (int)ss_.p_count, h->solve_seg, F, Z, Y,
-                                Y2, U, nrhs, st);
-            }
-        }
-        if (fork) {
-            HIPCHK(hipEventRecord(h->lvl_ev[2 * l + 1], ss));
-            HIPCHK(hipStreamWaitEvent(st, h->lvl_ev[2 * l + 1], 0));
-        }
-        i0 = i1;
+    const Plan& P = h->P;
+    const bool many = nrhs > 1;
+    const int64_t len = P.N * (many ? kNrhsMax : 1);
+    T *Y2 = Y + len, *X = Y2 + len;
+    for (const SolveStep& s : P.fwd_steps) {
+        Span sp(h, st, TM_SOLVE, s.bytes * sizeof(T) / 8.0, 4);
+        launch_fwd<T>(many, h->fwd_tasks + s.p_first, (int)s.p_count, h->solve_small + s.s_first, (int)s.s_count,
+                      h->gather, F, Z, Y, Y2, U, st);
     }
-    // backward: levels from the top down, steps of a level in reverse.  The
-    // tasks' sums of panel j go to partial half j & 1 and are read by the
-    // next launch (panel j - 1, or the level's finish-only records).
-    const int64_t half = std::max<int64_t>(P.solve_max_slots, 1) * kPanel * kNrhsMax;
+    // the sums of pair step k go to partial half k & 1 and are read by the next launch
+    const int64_t half = std::max<int64_t>(P.solve_max_slots, 1) * 2 * kPanel * kNrhsMax;
     T* const pbuf[2] = {partial, partial + half};
-    std::vector<size_t> starts;
-    for (size_t i0 = 0; i0 < S.size(); i0 = level_end(S, i0)) starts.push_back(i0);
-    for (auto it = starts.rbegin(); it != starts.rend(); ++it) {
-        const size_t i0 = *it, i1 = level_end(S, i0);
-        const int l = S[i0].level;
-        const bool fork = S[i0].s_count > 0 && has_panels(S, i0, i1);
-        hipStream_t ss = fork ? h->aux_stream : st;
-        if (fork) {
-            HIPCHK(hipEventRecord(h->lvl_ev[2 * l], st));
-            HIPCHK(hipStreamWaitEvent(ss, h->lvl_ev[2 * l], 0));
-        }
-        for (size_t i = i1; i-- > i0;) {
-            const SolveStep& ss_ = S[i];
-            if (ss_.p_count > 0) {
-                Span sp(h, st, TM_SOLVE, ss_.fwd_bytes * sizeof(T) / 8.0, 4);
-                launch_bwd_P<T>(d, h->solve_p + kTaskRec * ss_.p_first, (int)ss_.p_count, F, Z, D, Y2,
-                                pbuf[ss_.j & 1], pbuf[(ss_.j + 1) & 1], nrhs, st);
-            }
-            if (ss_.s_count > 0) {
-                Span sp(h, ss, TM_SOLVE, 0.0, 0);
-                launch_bwd_S<T>(d, h->solve_s + ss_.s_first, (int)ss_.s_count, F, D, Y2, nrhs, ss);
-            }
-        }
-        if (S[i0].f_count > 0) {
-            Span sp(h, st, TM_SOLVE, 0.0, 0);
-            launch_bwd_P<T>(d, h->solve_p + kTaskRec * S[i0].f_first, (int)S[i0].f_count, F, Z, D, Y2, pbuf[1],
-                            pbuf[0], nrhs, st);
-        }
-        if (fork) {
-            HIPCHK(hipEventRecord(h->lvl_ev[2 * l + 1], ss));
-            HIPCHK(hipStreamWaitEvent(st, h->lvl_ev[2 * l + 1], 0));
-        }
+    for (const SolveStep& s : P.bwd_steps) {
+        Span sp(h, st, TM_SOLVE, s.bytes * sizeof(T) / 8.0, 4);
+        launch_bwd<T>(many, h->bwd_tasks + s.p_first, (int)s.p_count, h->solve_small + s.s_first, (int)s.s_count,
+                      h->d.sn_rows, F, Z, D, Y2, X, pbuf[s.k & 1], pbuf[(s.k + 1) & 1], st);
     }
 }
 
@@ -854,7 +759,7 @@ void solve_once(ncl_kkt_s* h, const double* B, int64_t ldb, double* X, int64_t l
     if (!h->opt.use_graphs || h->tm.on) {
         sweeps<T>(h, nrhs, F, Z, D, Y, U, partial, st);
     } else {
-        hipGraphExec_t& ge = h->g_sweep[pr][nrhs];
+        hipGraphExec_t& ge = h->g_sweep[pr][nrhs > 1];
         if (!ge) {
             hipGraph_t g = nullptr;
             HIPCHK(hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal));
@@ -866,7 +771,7 @@ void solve_once(ncl_kkt_s* h, const double* B, int64_t ldb, double* X, int64_t l
         }
         HIPCHK(hipGraphLaunch(ge, st));
     }
-    launch_permute_out<T>(d, Y + h->P.N * kNrhsMax, nrhs, X, ldx, st);
+    launch_permute_out<T>(d, Y + 2 * h->P.N * (nrhs > 1 ? kNrhsMax : 1), nrhs, X, ldx, st);
 }
 
 void solve_with_factor(ncl_kkt_s* h, const double* B, int64_t ldb, double* X, int64_t ldx, int nrhs, hipStream_t st) {

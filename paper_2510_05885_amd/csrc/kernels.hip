@@ -888,7 +888,8 @@ __global__ __launch_bounds__(256) void k_large_asm(DevPlan d, int64_t task0, int
 // diagonal, Z = L^-1 transposed strictly above it, dv = pivots) to its
 // consumers: D, the front's L
 // (strictly lower part of the block), and Zg = Z (column-major, kPanel x
-// kPanel, unit diagonal, identity beyond w) for the panel solves.
+// kPanel, unit diagonal, identity beyond w) for the panel solves and the
+// sweeps, with Z^T in its strictly upper triangle.
 template <typename T>
 __device__ __forceinline__ void publish_diag(T* A, int f, int k0, int w, const T* B, const T* dv, T* D, int first,
                                              T* Zg, int tid) {
@@ -898,7 +899,8 @@ __device__ __forceinline__ void publish_diag(T* A, int f, int k0, int w, const T
         const int idx = tid + 256 * it;
         const int u = idx & (kPanel - 1), t = idx / kPanel;   // row u, column t
         if (u < w && t < u) A[(k0 + u) + (int64_t)(k0 + t) * f] = B[u + t * kDiagLd];
-        Zg[idx] = u < w ? zget(B, u, t) : (u == t ? T(1) : T(0));
+        const int lo = max(u, t), hi = min(u, t);
+        Zg[idx] = u == t ? T(1) : (lo < w ? B[hi + lo * kDiagLd] : T(0));
     }
 }
 
@@ -1075,7 +1077,10 @@ __device__ __forceinline__ void panel_body(const LargeTask* tk, T* F, const T* D
         for (int K = 0; K < 4; ++K) {
             if (K > J) continue;   // uniform
 #pragma unroll
-            for (int st = 0; st < 4; ++st) zo[h][K][st] = Zt[(16 * K + Mfma<T>::row(lk, st)) * kPanel + 16 * J + lr];
+            for (int st = 0; st < 4; ++st) {
+                const T z = Zt[(16 * K + Mfma<T>::row(lk, st)) * kPanel + 16 * J + lr];
+                zo[h][K][st] = K < J || Mfma<T>::row(lk, st) <= lr ? z : T(0);   // Z^T lies above the diagonal
+            }
         }
     }
     // The results overwrite A[rows, panel] in place, and the two waves that
@@ -1157,732 +1162,911 @@ __global__ __launch_bounds__(256, 2) void k_large_dstep(DevPlan d, const LargeTa
 // ---------------------------------------------------------------------------
 // solves
 // ---------------------------------------------------------------------------
-template <typename T>
+// Vectors in pivot order, `ld` values per row: 1 for one right-hand side,
+// kNrhsMax (unused columns zero) for several, so that a row's columns are
+// contiguous and a 16-row, 16-column piece is one MFMA operand.
+//   Y   the right-hand side, updated in place for rows not yet solved
+//   Y2  the pivots' y after the forward sweep
+//   X   the pivots' x after the backward sweep
+//   U   the fronts' update vectors (rows below the pivots)
+template <typename T, int LD>
 __global__ void k_permute_in(DevPlan d, const double* __restrict__ B, int64_t ldb, int nrhs, T* __restrict__ Y) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t k = i / LD;
+    const int q = (int)(i % LD);
     if (k >= d.N) return;
-    const int src = d.perm[k];
-    for (int q = 0; q < nrhs; ++q) Y[k + q * d.N] = (T)B[src + q * ldb];
+    Y[i] = q < nrhs ? (T)B[d.perm[k] + q * ldb] : T(0);
 }
 
+template <typename T, int LD>
+__global__ void k_permute_out(DevPlan d, const T* __restrict__ X, int nrhs, double* __restrict__ Xo, int64_t ldx) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t k = i / LD;
+    const int q = (int)(i % LD);
+    if (k >= d.N || q >= nrhs) return;
+    Xo[d.perm[k] + q * ldx] = to_d(X[i]);
+}
+
+// One launch per step of a level holds the tasks of its large fronts (one
+// workgroup each) and, in the level's first step, its small fronts (one wave
+// each).  A large front's panels are taken two at a time, columns
+// [c0, c0 + w1) and [c0 + w1, c0 + w1 + w2) (w1 = 64 when w2 > 0), through
+//   G1, G2  the inverses Z = L_kk^-1 of their diagonal blocks (unit lower,
+//           with Z^T in the strictly upper triangle) and
+//   P       = -Z2 L21 Z1, the coupling block of the pair's inverse (and P^T),
+// so that every result is one product with what the launch starts from:
+//   forward:  y1 = Z1 b1, y2 = Z2 b2 + P b1, rows below -= L1 y1 + L2 y2
+//   backward: v = y / d - L^T x (rows below), x2 = Z2^T v2, x1 = Z1^T v1 + P^T v2
+// The rows below are split into tasks of 64.
+//   forward:  every task forms the pair's y itself; task 0 stores it.
+//   backward: a pair with one task is finished by it.  The tasks of any other
+//     leave their sums in pw (slot0 + task), and the next launch on the stream
+//     finishes it: the front's previous pair's tasks 0 and 1, whose rows begin
+//     with the two panels, or, for a front's first pair, two records of their
+//     own after the level's last step.  No task waits for another of its launch.
+// Children's update vectors come through a table: row i of the front takes
+// U[gat[k f + i]], k = 0 .. gk - 1 in the children's order (-1: none).
+// The sweeps are bound by the latency of their chain of launches; panel by
+// panel, with the one-wave fronts forked to a second stream, a forward step
+// took 10 us, a backward one 6 and the fork and join 9 (order 20k).
+
+// Values of a pair's pivots and of the task's rows before the step.
 template <typename T>
-__global__ void k_permute_out(DevPlan d, const T* __restrict__ Y, int nrhs, double* __restrict__ X, int64_t ldx) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= d.N) return;
-    const int dst = d.perm[k];
-    for (int q = 0; q < nrhs; ++q) X[dst + q * ldx] = to_d(Y[k + q * d.N]);
+__device__ __forceinline__ T gather1(const T* __restrict__ U, const int* __restrict__ gat, int f, int gk, int i, T v) {
+    for (int k0 = 0; k0 < gk; k0 += 4) {
+        int o[4];
+        T u[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) o[k] = k0 + k < gk ? gat[(k0 + k) * f + i] : -1;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) u[k] = U[max(o[k], 0)];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v += o[k] >= 0 ? u[k] : T(0);
+    }
+    return v;
 }
 
-// ---- sweeps of the fronts outside the one-wave path ----------------------
-// One launch per panel step of a level.  Panel = pivot columns [c0, c0 + w),
-// w <= kPanel, of front s.  Its triangle is applied through the inverse
-// Z = L_kk^-1 that the factorization published (a GEMV, no dependent chain)
-// for large fronts, by one-wave substitution otherwise.  The rows below the
-// panel are split into tasks, one workgroup each, of solve_task_rows(w) rows:
-// the panel's columns are taken 16 at a time, so a narrow panel gives each
-// wave more rows instead of leaving waves idle.
-//   forward: every task recomputes y = Z b of its panel (b = the pivots' right-
-//     hand side, plus the children's update vectors at the first panel),
-//     subtracts L[rows, panel] y from its own rows and writes them back; task 0
-//     also stores y.  No task reads what another task of the launch writes: the
-//     pivots' results go to a second vector Y2 (y after the forward sweep, x
-//     after the backward one), the right-hand side stays in Y.
-//   backward: every task forms the partial sums L[rows, panel]^T x of its rows
-//     (x of rows below the panel is final when it starts).  A one-task panel
-//     forms v = y / d - sum and x = Z^T v itself; otherwise the sums are left
-//     for the next launch, where the task whose rows begin with the panel's
-//     pivots (or a finish-only record) adds them in task order and forms x.
-// Panel table (kPanInts ints): s, c0, w, first partial slot, tasks, first and
-// count of the pivot rows' contribution segments.  Task (kPTaskInts ints):
-// panel, rows [r0, r1) (r0 == r1 = f for a panel with nothing below), index
-// within the panel, first and count of its rows' segments.  Segment (3 ints):
-// child, entries [a0, a1) of its update vector that land in the rows.
-// NR: columns of the right-hand side the kernel is built for (1, or up to
-// kNrhsMax).
-
-// acc[q] += sum_{k < n} M[row + (col0 + k) * f] v[k + q * ldv], q < nrhs,
-// in chunks of kDotChunk operands loaded before use.
-constexpr int kDotChunk = 32;
+// ---- one right-hand side ----------------------------------------------------
 template <typename T>
-__device__ __forceinline__ void row_dot(const T* __restrict__ M, int64_t f, int row, int col0, int n, const T* v,
-                                        int ldv, int nrhs, T* acc) {
-    for (int kc = 0; kc < n; kc += kDotChunk) {
-        T lv[kDotChunk];
-#pragma unroll
-        for (int k = 0; k < kDotChunk; ++k) lv[k] = (kc + k < n) ? M[row + (int64_t)(col0 + kc + k) * f] : T(0);
-        const bool tail = kc + kDotChunk > n;
-#pragma unroll
-        for (int q = 0; q < kNrhsMax; ++q) {
-            if (q >= nrhs) continue;   // uniform
-            const T* vq = v + kc + q * ldv;
-            T a0 = T(0), a1 = T(0);
-            if (!tail) {
-#pragma unroll
-                for (int k = 0; k < kDotChunk; k += 2) { a0 += lv[k] * vq[k]; a1 += lv[k + 1] * vq[k + 1]; }
-            } else {
-#pragma unroll
-                for (int k = 0; k < kDotChunk; k += 2) {
-                    a0 += (kc + k < n) ? lv[k] * vq[k] : T(0);
-                    a1 += (kc + k + 1 < n) ? lv[k + 1] * vq[k + 1] : T(0);
-                }
-            }
-            acc[q] += a0 + a1;
-        }
-    }
-}
-
-// Small fronts: the sub-block's unit lower triangle staged in Ld (64 x 65),
-// then one wave substitutes (forward: rows; backward: transposed); v has
-// leading dimension vld.
-template <typename T, bool kBackward>
-__device__ __forceinline__ void chain_solve64(const T* __restrict__ L, int f, int c, int ws, T* Ld, T* v, int vld,
-                                              int nrhs) {
-    const int tid = threadIdx.x, lane = tid & 63;
-    {
-        T lv[16];   // all loads first, then the LDS stores
-#pragma unroll
-        for (int it = 0; it < 16; ++it) {
-            const int idx = tid + 256 * it, a = idx & 63, b = idx >> 6;
-            lv[it] = L[(c + min(a, ws - 1)) + (int64_t)(c + min(b, ws - 1)) * f];
-        }
-#pragma unroll
-        for (int it = 0; it < 16; ++it) {
-            const int idx = tid + 256 * it, a = idx & 63, b = idx >> 6;
-            if (a < ws && b < a) Ld[a * 65 + b] = lv[it];
-        }
-    }
-    __syncthreads();
-    if (tid < 64) {
-        // the row (forward) or column (backward) of the triangle is read from
-        // LDS at each step: a register copy would set the register budget of
-        // every kernel that contains this path
-        for (int q = 0; q < nrhs; ++q) {
-            T val = lane < ws ? v[lane + q * vld] : T(0);
-            if (!kBackward) {
-#pragma unroll 8
-                for (int k = 0; k < 63; ++k) {
-                    const T l = (k < lane && lane < ws) ? Ld[lane * 65 + k] : T(0);
-                    val -= l * bcast(val, k);
-                }
-            } else {
-#pragma unroll 8
-                for (int k = 63; k > 0; --k) {
-                    const T l = (lane < k && k < ws) ? Ld[k * 65 + lane] : T(0);
-                    val -= l * bcast(val, k);
-                }
-            }
-            if (lane < ws) v[lane + q * vld] = val;
-        }
-    }
-    __syncthreads();
-}
-
-// dst[r - base] += the children's update-vector entries of segments
-// [g0, g0 + gn).  The entries of all segments are loaded at once (256 per
-// round, one per thread, held in registers), then added segment by segment:
-// two children may add to one row, and the order stays the children's.
-template <typename T, int NR>
-__device__ __forceinline__ void add_segments(const DevPlan& d, const T* __restrict__ U, const int* __restrict__ segs,
-                                             int g0, int gn, int base, T* dst, int ld, int nrhs) {
-    int total = 0;
-    for (int g = g0; g < g0 + gn; ++g) total += segs[3 * g + 2] - segs[3 * g + 1];
-    for (int e0 = 0; e0 < total; e0 += 256) {
-        const int e = e0 + (int)threadIdx.x;
-        int mine = -1, row = 0;
-        T val[NR];
-        if (e < total) {
-            int g = g0, acc = 0;
-            for (;; ++g) {
-                const int len = segs[3 * g + 2] - segs[3 * g + 1];
-                if (e < acc + len) break;
-                acc += len;
-            }
-            const int ch = segs[3 * g], a = segs[3 * g + 1] + (e - acc);
-            const int cc = (int)(d.sn_rowptr[ch + 1] - d.sn_rowptr[ch]) - (d.sn_first[ch + 1] - d.sn_first[ch]);
-            const T* __restrict__ Uc = U + d.U_off[ch] + a;
-            row = d.rel[d.rel_ptr[ch] + a] - base;
-#pragma unroll
-            for (int q = 0; q < NR; ++q)
-                if (q < nrhs) val[q] = Uc[(int64_t)q * cc];
-            mine = g;
-        }
-        for (int g = g0; g < g0 + gn; ++g) {
-            if (mine == g)
-#pragma unroll
-                for (int q = 0; q < NR; ++q)
-                    if (q < nrhs) dst[row + q * ld] += val[q];
-            __syncthreads();
-        }
-    }
-}
-
-// Forward sweep step, one workgroup per task.  With a second panel (w2 > 0,
-// large fronts, w = 64) the task owns 64 rows below both panels and forms
-// both y itself: y = Z b of the first, the second's b minus L[its pivots,
-// first panel] y, y2 = Z2 b2, then its rows -= L[rows, first] y and
-// -= L[rows, second] y2.  Every product and sum is the one a step per
-// panel would form (the second panel's b as the first panel's task 0
-// would update it), in the same order.
-template <typename T, int NR>
-__global__ __launch_bounds__(256) void k_fwd_P(DevPlan d, const int* __restrict__ tasks,
-                                               const int* __restrict__ segs, const T* __restrict__ F,
-                                               const T* __restrict__ Zbuf, T* __restrict__ Y, T* __restrict__ Y2,
-                                               T* __restrict__ U, int nrhs) {
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    T* v = reinterpret_cast<T*>(smem_raw);        // kPanel x nrhs: b of the pivots, then y
-    T* rw = v + kPanel * nrhs;                    // kSolveRowsMax x nrhs: the task's rows
-    T* part = rw + kSolveRowsMax * nrhs;          // 256 x nrhs
-    T* Ld = part + 256 * nrhs;                    // 64 x 65
-    T* v2 = Ld + 64 * 65;                         // kPanel x nrhs: the second panel's b, then y
-    const int* tk = tasks + kTaskRec * blockIdx.x;
-    const int64_t* tk64 = reinterpret_cast<const int64_t*>(tk + kTaskRec64);
-    const int c0 = tk[7], w = tk[8];
-    const int r0 = tk[1], nr = tk[2] - tk[1], chunk = tk[3];
-    const int first = tk[13], p = tk[14], f = tk[15];
-    const int w2 = tk[kTaskRec64 + 12];
-    const int c02 = c0 + kPanel;
-    const int c = f - p;
-    const T* __restrict__ L = F + tk64[0];
-    T* __restrict__ Us = U + tk64[1];
-    const int64_t moff = tk64[2];
+__device__ __forceinline__ void fwd_panels1(const PanelTask* tk, const T* __restrict__ F, const T* __restrict__ Zbuf,
+                                            const int* __restrict__ gatab, T* __restrict__ Y, T* __restrict__ Y2,
+                                            T* __restrict__ U) {
+    __shared__ T v[128], y[128], rw[64], part[2][256];
+    const int first = tk->first, p = tk->p, f = tk->f, c0 = tk->c0, w1 = tk->w1, w2 = tk->w2;
+    const int r0 = tk->r0, nr = tk->r1 - r0;
     const int tid = threadIdx.x, lane = tid & 63, q4 = tid >> 6;
-    const int64_t N = d.N;
-    const bool large = moff >= 0;
-    const bool pair = w2 > 0;
-    // wave q4: row group q4 / nwc (64 rows, lane = row), columns 16 (q4 % nwc) + [0, 16)
-    const int nwc = (w + 15) >> 4, ng = 4 / nwc;
-    const int rgrp = q4 / nwc, k0 = 16 * (q4 - rgrp * nwc);
-    const int myrow = 64 * rgrp + lane;           // row of the task (valid if < nr)
-    const int nwc2 = (w2 + 15) >> 4;              // second panel: wave q4 takes its columns 16 q4 + [0, 16)
-    // Operands that depend on nothing computed here are loaded first, so
-    // their latency overlaps the right-hand side's: Z[lane][16 q4 + j] (large
-    // fronts) and this thread's slice of L[rows, panel]; with a second panel
-    // also its Z, its slice of L[rows, second panel] and of the block
-    // L[second panel's pivots, first panel].
-    T z[16], lv[16], z2[16], lv2[16], lb[16];
-    if (large) {
-        const T* __restrict__ Zb = Zbuf + moff + (int64_t)(c0 / kPanel) * (kPanel * kPanel);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) z[j] = (lane < w && 16 * q4 + j < w) ? Zb[(16 * q4 + j) * kPanel + lane] : T(0);
+    const T* __restrict__ L = F + tk->L_off;
+    const T* __restrict__ G1 = Zbuf + tk->M_off + (int64_t)(c0 / kPanel) * (kPanel * kPanel);
+    const T* __restrict__ G2 = G1 + kPanel * kPanel;
+    const T* __restrict__ Pm = Zbuf + tk->P_off;
+    T* __restrict__ Us = U + tk->U_off;
+    // right-hand side: the pair's pivots, then the task's rows
+    if (tid < 192) {
+        const int gi = tid < 128 ? c0 + tid : r0 + tid - 128;
+        const bool in = tid < 128 ? tid < w1 + w2 : tid - 128 < nr;
+        T b = T(0);
+        if (in) {
+            if (gi < p) b = Y[first + gi];
+            else if (c0 > 0) b = Us[gi - p];
+            if (tk->gk > 0) b = gather1(U, gatab + tk->gat, f, tk->gk, gi, b);
+        }
+        (tid < 128 ? v[tid] : rw[tid - 128]) = b;
     }
-    {
-        const bool rv = rgrp < ng && myrow < nr;
-        const int64_t row = r0 + (rv ? myrow : 0);
+    T z1[16], z2[16], pm[16], l1[16], l2[16];
+    const bool rv = lane < nr;
+    const T* __restrict__ Lr = L + r0 + (rv ? lane : 0);
 #pragma unroll
-        for (int j = 0; j < 16; ++j) lv[j] = (rv && k0 + j < w) ? L[row + (int64_t)(c0 + k0 + j) * f] : T(0);
+    for (int j = 0; j < 16; ++j) {
+        const int k = 16 * q4 + j;
+        z1[j] = G1[k * kPanel + lane];
+        l1[j] = (rv && k < w1) ? Lr[(int64_t)(c0 + k) * f] : T(0);
     }
-    if (pair) {
-        const T* __restrict__ Zb = Zbuf + moff + (int64_t)(c02 / kPanel) * (kPanel * kPanel);
-        const bool rv = lane < nr;
-        const int64_t row = r0 + (rv ? lane : 0);
+    if (w2 > 0) {
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
-            const int kk = 16 * q4 + j;
-            z2[j] = (lane < w2 && kk < w2) ? Zb[kk * kPanel + lane] : T(0);
-            lv2[j] = (rv && kk < w2) ? L[row + (int64_t)(c02 + kk) * f] : T(0);
-            lb[j] = lane < w2 ? L[(c02 + lane) + (int64_t)(c0 + kk) * f] : T(0);
+            const int k = 16 * q4 + j;
+            pm[j] = Pm[k * kPanel + lane];
+            z2[j] = G2[k * kPanel + lane];
+            l2[j] = (rv && k < w2) ? Lr[(int64_t)(c0 + kPanel + k) * f] : T(0);
         }
-    }
-    for (int q = 0; q < nrhs; ++q) {
-        if (tid < kPanel) {
-            v[tid + q * kPanel] = tid < w ? Y[first + c0 + tid + q * N] : T(0);
-            if (pair) v2[tid + q * kPanel] = tid < w2 ? Y[first + c02 + tid + q * N] : T(0);
-        }
-        const int gi = r0 + tid;
-        T val = T(0);
-        if (tid < nr) val = gi < p ? Y[first + gi + q * N] : (c0 == 0 ? T(0) : Us[(gi - p) + (int64_t)q * c]);
-        rw[tid + q * kSolveRowsMax] = val;
     }
     __syncthreads();
-    if (c0 == 0) {
-        add_segments<T, NR>(d, U, segs, tk[11], tk[12], 0, v, kPanel, nrhs);
-        if (pair) add_segments<T, NR>(d, U, segs, tk[kTaskRec64 + 13], tk[kTaskRec64 + 14], c02, v2, kPanel, nrhs);
-        add_segments<T, NR>(d, U, segs, tk[4], tk[5], r0, rw, kSolveRowsMax, nrhs);
-    }
-    if (large) {
-        // y = Z b: the 4 waves split the contraction, partial sums meet in part
-        for (int q = 0; q < nrhs; ++q) {
-            const T* vq = v + 16 * q4 + q * kPanel;
-            T acc = T(0);
+    {
+        const T* v1 = v + 16 * q4;
+        T a1 = T(0);
 #pragma unroll
-            for (int j = 0; j < 16; ++j) acc += z[j] * vq[j];
-            part[(q4 * 64 + lane) * nrhs + q] = acc;
+        for (int j = 0; j < 16; ++j) a1 += (16 * q4 + j <= lane ? z1[j] : T(0)) * v1[j];
+        part[0][tid] = a1;
+        if (w2 > 0) {
+            T a2 = T(0);
+#pragma unroll
+            for (int j = 0; j < 16; ++j) a2 += pm[j] * v1[j] + (16 * q4 + j <= lane ? z2[j] : T(0)) * v1[64 + j];
+            part[1][tid] = a2;
         }
-        __syncthreads();
-        if (tid < w)
-            for (int q = 0; q < nrhs; ++q) {
-                const T* pp = part + tid * nrhs + q;
-                v[tid + q * kPanel] = (pp[0] + pp[64 * nrhs]) + (pp[128 * nrhs] + pp[192 * nrhs]);
-            }
-        __syncthreads();
-    } else {
-        chain_solve64<T, false>(L, f, c0, w, Ld, v, kPanel, nrhs);
-    }
-    if (chunk == 0)
-        for (int q = 0; q < nrhs; ++q)
-            if (tid < w) Y2[first + c0 + tid + q * N] = v[tid + q * kPanel];
-    if (pair) {
-        // the second panel's b -= L[its pivots, first panel] y (wave q4: columns
-        // 16 q4 + [0, 16), lane = pivot), then y2 = Z2 b
-        for (int q = 0; q < nrhs; ++q) {
-            const T* vq = v + 16 * q4 + q * kPanel;
-            T acc = T(0);
-#pragma unroll
-            for (int j = 0; j < 16; ++j) acc += lb[j] * vq[j];
-            part[(q4 * 64 + lane) * nrhs + q] = acc;
-        }
-        __syncthreads();
-        if (tid < w2)
-            for (int q = 0; q < nrhs; ++q) {
-                const T* pp = part + tid * nrhs + q;
-                T sum = pp[0];
-                for (int k = 1; k < 4; ++k) sum += pp[k * 64 * nrhs];
-                v2[tid + q * kPanel] -= sum;
-            }
-        __syncthreads();
-        for (int q = 0; q < nrhs; ++q) {
-            const T* vq = v2 + 16 * q4 + q * kPanel;
-            T acc = T(0);
-#pragma unroll
-            for (int j = 0; j < 16; ++j) acc += z2[j] * vq[j];
-            part[(q4 * 64 + lane) * nrhs + q] = acc;
-        }
-        __syncthreads();
-        if (tid < w2)
-            for (int q = 0; q < nrhs; ++q) {
-                const T* pp = part + tid * nrhs + q;
-                const T y2 = (pp[0] + pp[64 * nrhs]) + (pp[128 * nrhs] + pp[192 * nrhs]);
-                v2[tid + q * kPanel] = y2;
-                if (chunk == 0) Y2[first + c02 + tid + q * N] = y2;
-            }
-        __syncthreads();
-    }
-    if (nr == 0) return;
-    // rows: y_i -= L[i, panel] y
-#pragma unroll
-    for (int q = 0; q < NR; ++q) {
-        if (q >= nrhs) continue;
-        const T* vq = v + k0 + q * kPanel;
-        T acc = T(0);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) acc += lv[j] * vq[j];
-        part[(q4 * 64 + lane) * nrhs + q] = acc;
     }
     __syncthreads();
-    if (!pair) {
-        if (tid < nr) {
-            const int gi = r0 + tid, g = tid >> 6, l = tid & 63;
-            for (int q = 0; q < nrhs; ++q) {
-                const T* pp = part + ((g * nwc) * 64 + l) * nrhs + q;
-                T sum = pp[0];
-                for (int k = 1; k < nwc; ++k) sum += pp[k * 64 * nrhs];
-                const T val = rw[tid + q * kSolveRowsMax] - sum;
-                if (gi < p) Y[first + gi + q * N] = val;
-                else Us[(gi - p) + (int64_t)q * c] = val;
-            }
-        }
-        return;
+    if (tid < w1 + w2) {
+        const T* pp = part[tid >> 6] + (tid & 63);
+        const T s = (pp[0] + pp[64]) + (pp[128] + pp[192]);
+        y[tid] = s;
+        if (tk->index == 0) Y2[first + c0 + tid] = s;
+    } else if (tid < 128) {
+        y[tid] = T(0);
     }
-    // two panels: the first panel's update of the rows, then the second's
-    if (tid < nr)
-        for (int q = 0; q < nrhs; ++q) {
-            const T* pp = part + tid * nrhs + q;
-            T sum = pp[0];
-            for (int k = 1; k < 4; ++k) sum += pp[k * 64 * nrhs];
-            rw[tid + q * kSolveRowsMax] -= sum;
-        }
+    if (nr == 0) return;   // the whole workgroup
     __syncthreads();
+    {
+        const T* y1 = y + 16 * q4;
+        T a = T(0);
 #pragma unroll
-    for (int q = 0; q < NR; ++q) {
-        if (q >= nrhs) continue;
-        const T* vq = v2 + 16 * q4 + q * kPanel;
-        T acc = T(0);
+        for (int j = 0; j < 16; ++j) a += l1[j] * y1[j];
+        if (w2 > 0) {
+            T b = T(0);
 #pragma unroll
-        for (int j = 0; j < 16; ++j) acc += lv2[j] * vq[j];
-        part[(q4 * 64 + lane) * nrhs + q] = acc;
+            for (int j = 0; j < 16; ++j) b += l2[j] * y1[64 + j];
+            a += b;
+        }
+        part[0][tid] = a;
     }
     __syncthreads();
     if (tid < nr) {
+        const T* pp = part[0] + tid;
+        const T val = rw[tid] - ((pp[0] + pp[64]) + (pp[128] + pp[192]));
         const int gi = r0 + tid;
-        for (int q = 0; q < nrhs; ++q) {
-            const T* pp = part + tid * nrhs + q;
-            T sum = pp[0];
-            for (int k = 1; k < nwc2; ++k) sum += pp[k * 64 * nrhs];
-            const T val = rw[tid + q * kSolveRowsMax] - sum;
-            if (gi < p) Y[first + gi + q * N] = val;
-            else Us[(gi - p) + (int64_t)q * c] = val;
-        }
+        if (gi < p) Y[first + gi] = val;
+        else Us[gi - p] = val;
     }
 }
 
-// x of a panel's xw pivots from the sums over its rows below (v, kPanel x
-// nrhs in LDS): v = y / d - sums, then x = Z^T v with Z = L_kk^-1 (this
-// thread's share in zv, staged transposed in Ld; wave q4 takes rows
-// 16 q4 .. 16 q4 + 15).  x goes to Y2p (the panel's first pivot) and, when
-// xs is given, to the task's rows from xoff.
-template <typename T, int NR>
-__device__ __forceinline__ void bwd_panel_x(T* v, T* part, T* Ld, const T (&zv)[kPanel * kPanel / 256],
-                                            const T (&yv)[NR], T dinv, int xw, int nrhs, T* __restrict__ Y2p,
-                                            int64_t N, T* xs, int xoff, int tid) {
-    const int lane = tid & 63, q4 = tid >> 6;
-    if (tid < kPanel) {
+// A small front by one wave: lane = row and (kHi: order above 64) row + 64; column by column, the
+// pivot's y (readlane) times its column of L.
+template <typename T, bool kHi>
+__device__ __forceinline__ void fwd_front1(const SmallTask* tk, const T* __restrict__ F, const int* __restrict__ gatab,
+                                           const T* __restrict__ Y, T* __restrict__ Y2, T* __restrict__ U, int lane) {
+    const int first = tk->first, p = tk->p, f = tk->f, gk = tk->gk;
+    const T* __restrict__ L = F + tk->L_off;
+    T* __restrict__ Us = U + tk->U_off;
+    const int* __restrict__ gat = gatab + tk->gat;
+    const int i0 = min(lane, f - 1), i1 = min(lane + 64, f - 1);
+    constexpr int kC = 16;
+    T l0[kC], l1[kC];
+    auto load = [&](int kb) {
 #pragma unroll
-        for (int q = 0; q < NR; ++q) {
-            if (q >= nrhs) continue;
-            v[tid + q * kPanel] = tid < xw ? yv[q] * dinv - v[tid + q * kPanel] : T(0);
+        for (int t = 0; t < kC; ++t) {
+            const T* __restrict__ c = L + (int64_t)min(kb + t, p - 1) * f;
+            l0[t] = c[i0];
+            if (kHi) l1[t] = c[i1];
+        }
+    };
+    load(0);
+    T v0 = lane < p ? Y[first + lane] : T(0);
+    T v1 = kHi && lane + 64 < p ? Y[first + lane + 64] : T(0);
+    if (gk > 0) {
+        v0 = gather1(U, gat, f, gk, i0, v0);
+        if (kHi) v1 = gather1(U, gat, f, gk, i1, v1);
+    }
+    for (int kb = 0; kb < p; kb += kC) {
+        if (kb > 0) load(kb);
+#pragma unroll
+        for (int t = 0; t < kC; ++t) {
+            const int k = kb + t;
+            if (k >= p) continue;   // uniform
+            const T yk = !kHi || k < 64 ? bcast(v0, k) : bcast(v1, k - 64);
+            v0 -= (lane > k ? l0[t] : T(0)) * yk;
+            if (kHi) v1 -= (lane + 64 > k ? l1[t] : T(0)) * yk;
         }
     }
-#pragma unroll
-    for (int it = 0; it < kPanel * kPanel / 256; ++it) {
-        const int idx = tid + 256 * it;
-        Ld[(idx & 63) + (idx >> 6) * 65] = zv[it];
+    if (lane < p) Y2[first + lane] = v0;
+    else if (lane < f) Us[lane - p] = v0;
+    if (kHi) {
+        if (lane + 64 < p) Y2[first + lane + 64] = v1;
+        else if (lane + 64 < f) Us[lane + 64 - p] = v1;
     }
-    __syncthreads();
-    for (int q = 0; q < nrhs; ++q) {
-        const T* vq = v + 16 * q4 + q * kPanel;
-        T acc = T(0);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) acc += Ld[(16 * q4 + j) + lane * 65] * vq[j];
-        part[(q4 * 64 + lane) * nrhs + q] = acc;
-    }
-    __syncthreads();
-    if (tid < xw)
-        for (int q = 0; q < nrhs; ++q) {
-            const T* pp = part + tid * nrhs + q;
-            const T x = (pp[0] + pp[64 * nrhs]) + (pp[128 * nrhs] + pp[192 * nrhs]);
-            Y2p[tid + q * N] = x;
-            if (xs) xs[xoff + tid + q * kSolveRowsMax] = x;
-        }
 }
 
-// Backward sweep step, one workgroup per task (rows r0..r1 below a panel):
-// the task's sums L[rows, panel]^T x[rows] (a large front keeps L^T in its
-// upper triangle).  A panel with one task is finished by it.  A panel with
-// several leaves their sums in pw (slots slot0 + index) and is finished in
-// the next launch -- ordered on the same stream, so plain loads see the sums
-// -- by the first task of the front's previous panel, whose rows start with
-// this panel's pivots and which needs their x first, or, for a front's first
-// panel, by a finish-only record (index -1) after the level's last step.
-// Each panel's sums are added in task order per wave (wave q4: tasks q4,
-// q4 + 4, ...), then the four waves' totals.
-template <typename T, int NR>
-__global__ __launch_bounds__(256) void k_bwd_P(DevPlan d, const int* __restrict__ tasks,
-                                               const T* __restrict__ F, const T* __restrict__ Zbuf,
-                                               const T* __restrict__ D, T* __restrict__ Y2, T* __restrict__ pw,
-                                               const T* __restrict__ pr, int nrhs) {
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    T* xs = reinterpret_cast<T*>(smem_raw);       // kSolveRowsMax x nrhs: x of the task's rows
-    T* v = xs + kSolveRowsMax * nrhs;             // kPanel x nrhs
-    T* part = v + kPanel * nrhs;                  // 256 x nrhs
-    T* Ld = part + 256 * nrhs;                    // 64 x 65
-    const int* tk = tasks + kTaskRec * blockIdx.x;
-    const int64_t* tk64 = reinterpret_cast<const int64_t*>(tk + kTaskRec64);
-    const int c0 = tk[7], w = tk[8], slot0 = tk[9], ntask = tk[10];
-    const int r0 = tk[1], nr = tk[2] - tk[1], chunk = tk[3];
-    const int first = tk[13], p = tk[14], f = tk[15];
-    const int fc0 = tk[kTaskRec64 + 8], fw = tk[kTaskRec64 + 9];
-    const int fslot0 = tk[kTaskRec64 + 10], fntask = tk[kTaskRec64 + 11];
-    const T* __restrict__ L = F + tk64[0];
-    const int64_t moff = tk64[2];
-    const int* __restrict__ rows = d.sn_rows + tk64[3];
-    const bool large = moff >= 0;
-    const bool own = chunk >= 0;              // else a finish-only record
-    const bool fin = fntask > 0;              // finishes panel fc0 before its own sums
-    const bool self = own && ntask == 1;      // finishes its own panel
-    const int xc0 = fin ? fc0 : c0;           // the panel it finishes (xw pivots, 0: none)
-    const int xw = fin ? fw : (self ? w : 0);
+// np panel tasks, one workgroup each, then ns small fronts, four a workgroup.
+template <typename T>
+__global__ __launch_bounds__(256, 2) void k_fwd1(const PanelTask* __restrict__ pt, int np,
+                                                 const SmallTask* __restrict__ st, int ns, const int* __restrict__ gat,
+                                                 const T* __restrict__ F, const T* __restrict__ Zbuf,
+                                                 T* __restrict__ Y, T* __restrict__ Y2, T* __restrict__ U) {
+    const int b = blockIdx.x;
+    if (b < np) {
+        fwd_panels1<T>(pt + b, F, Zbuf, gat, Y, Y2, U);
+    } else {
+        const int t = 4 * (b - np) + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        if (t >= ns) return;
+        if (st[t].f > 64) fwd_front1<T, true>(st + t, F, gat, Y, Y2, U, threadIdx.x & 63);
+        else fwd_front1<T, false>(st + t, F, gat, Y, Y2, U, threadIdx.x & 63);
+    }
+}
+
+// One panel of a pair from v = y / d - sums (v: 128 in LDS): x1 = Z1^T v1 +
+// P^T v2, or x2 = Z2^T v2.  The operands come loaded (wave q4 takes rows
+// 16 q4 .. 16 q4 + 15); the waves' shares go to part.
+template <typename T>
+struct PairOps {
+    T z[16], pt[16];
+    __device__ __forceinline__ void load(const T* __restrict__ G, const T* __restrict__ PT, bool with_p, int lane,
+                                         int q4) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int u = 16 * q4 + j;
+            z[j] = u >= lane ? G[u * kPanel + lane] : T(0);   // Z^T is upper
+            pt[j] = with_p ? PT[u * kPanel + lane] : T(0);
+        }
+    }
+    __device__ __forceinline__ void apply(const T* v, int half, T* part, int lane, int q4) const {
+        const T* vq = v + 16 * q4;
+        T a = T(0);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) a += z[j] * vq[64 * half + j] + pt[j] * vq[64 + j];
+        part[64 * q4 + lane] = a;
+    }
+};
+
+template <typename T>
+__device__ __forceinline__ void bwd_panels1(const PanelTask* tk, const int* __restrict__ rows, const T* __restrict__ F,
+                                            const T* __restrict__ Zbuf, const T* __restrict__ D,
+                                            const T* __restrict__ Y2, T* __restrict__ X, T* __restrict__ pw,
+                                            const T* __restrict__ pr) {
+    __shared__ T v[128], xs[64], part[2][256];
+    const int first = tk->first, p = tk->p, f = tk->f, c0 = tk->c0, w = tk->w1 + tk->w2;
+    const int r0 = tk->r0, nr = tk->r1 - r0;
     const int tid = threadIdx.x, lane = tid & 63, q4 = tid >> 6;
-    const int64_t N = d.N;
-    // thread = (panel column t, row group rg): columns in slots of 16, the
-    // row groups take rows rg, rg + nrg, ... (at most 16 per thread)
-    const int W16 = 16 * ((w + 15) >> 4), nrg = 256 / W16;
-    const int t = tid % W16, rg = tid / W16;
-    const bool tact = own && t < w && rg < nrg;
-    // Loads that depend on nothing computed here first: this thread's L^T
-    // operands, and Z, 1 / d and y of the panel it finishes.
-    T lv[16], zv[kPanel * kPanel / 256];
-    if (large) {
-        const T* __restrict__ lt = L + (c0 + (tact ? t : 0)) + (int64_t)r0 * f;
+    const bool own = tk->index >= 0;                 // else a finish-only record
+    const bool fin = tk->fntask > 0, self = own && tk->ntask == 1;
+    const int xc0 = fin ? tk->fc0 : c0, xw1 = fin ? tk->fw1 : tk->w1, xw2 = fin ? tk->fw2 : tk->w2;
+    const int which = fin ? tk->which : 0;           // the panel it finishes first
+    const T* __restrict__ A = F + tk->L_off;
+    // L^T operands (a large front keeps L^T above its diagonal): one panel: 64
+    // columns in four groups of 16 rows, two: 128 in two of 32
+    const bool two = tk->w2 > 0;
+    const int cols = two ? 128 : 64, col = tid & (cols - 1), rg = tid / cols, nrg = two ? 2 : 4, rpg = 64 / nrg;
+    T lv[32];
+    {
+        const bool cv = own && col < w;
+        const T* __restrict__ src = A + c0 + (cv ? col : 0) + (int64_t)(r0 + rpg * rg) * f;
+        const int n = cv ? nr - rpg * rg : 0;
 #pragma unroll
-        for (int m = 0; m < 16; ++m) {
-            const int i = rg + nrg * m;
-            lv[m] = (tact && i < nr) ? lt[(int64_t)i * f] : T(0);
+        for (int m = 0; m < 16; ++m) lv[m] = m < n ? src[(int64_t)m * f] : T(0);
+        if (two)
+#pragma unroll
+            for (int m = 16; m < 32; ++m) lv[m] = m < n ? src[(int64_t)m * f] : T(0);
+    }
+    PairOps<T> ops;
+    const T* __restrict__ G1 = Zbuf + tk->M_off + (int64_t)(xc0 / kPanel) * (kPanel * kPanel);
+    if (fin || self)
+        ops.load(G1 + which * kPanel * kPanel, Zbuf + (fin ? tk->fP_off : tk->P_off) + kPanel * kPanel,
+                 which == 0 && xw2 > 0, lane, q4);
+    T yd = T(0);   // y / d of the pair to finish
+    if (tid < xw1 + xw2 && (fin || self)) yd = Y2[first + xc0 + tid] * (T(1) / D[first + xc0 + tid]);
+    if (own && tid < 64) {
+        const int gi = r0 + tid;
+        xs[tid] = tid >= nr ? T(0) : X[gi < p ? first + gi : rows[tk->rows_off + gi]];
+    }
+    if (fin) {
+        // the sums of the pair's tasks: column tid & 127, tasks of one parity
+        const int c = tid & 127, g1 = tid >> 7;
+        T a = T(0);
+        const T* __restrict__ src = pr + (int64_t)tk->fslot0 * 128 + c;
+        for (int g0 = g1; g0 < tk->fntask; g0 += 16) {
+            T u[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) u[k] = g0 + 2 * k < tk->fntask ? src[(int64_t)(g0 + 2 * k) * 128] : T(0);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) a += u[k];
         }
-        const T* __restrict__ Zb = Zbuf + moff + (int64_t)(xc0 / kPanel) * (kPanel * kPanel);
-#pragma unroll
-        for (int it = 0; it < kPanel * kPanel / 256; ++it) {
-            const int idx = tid + 256 * it;
-            zv[it] = ((idx & 63) < xw && (idx >> 6) < xw) ? Zb[idx] : T(0);
+        part[0][tid] = a;
+        __syncthreads();
+        if (tid < 128) v[tid] = tid < xw1 + xw2 ? yd - (part[0][tid] + part[0][tid + 128]) : T(0);
+        __syncthreads();
+        ops.apply(v, which, part[0], lane, q4);
+        __syncthreads();
+        const T* pp = part[0] + lane;
+        if (tid < (which ? xw2 : xw1)) {
+            const T x = (pp[0] + pp[64]) + (pp[128] + pp[192]);
+            const int gi = xc0 + 64 * which + tid;
+            X[first + gi] = x;
+            if (own) xs[gi - r0] = x;
         }
     }
-    const T dinv = tid < xw ? T(1) / D[first + xc0 + tid] : T(0);
-    T yv[NR];
+    if (!own) return;   // the whole workgroup
+    __syncthreads();
+    {
+        const T* xr = xs + rpg * rg;
+        T a = T(0), b = T(0);
 #pragma unroll
-    for (int q = 0; q < NR; ++q) yv[q] = (q < nrhs && tid < xw) ? Y2[first + xc0 + tid + q * N] : T(0);
-    if (own)
-        for (int q = 0; q < nrhs; ++q) {
-            const int gi = r0 + tid;
-            xs[tid + q * kSolveRowsMax] = tid >= nr ? T(0) : gi < p ? Y2[first + gi + q * N] : Y2[rows[gi] + q * N];
+        for (int m = 0; m < 16; ++m) a += lv[m] * xr[m];
+        if (two)
+#pragma unroll
+            for (int m = 16; m < 32; ++m) b += lv[m] * xr[m];
+        part[0][tid] = a + b;
+    }
+    __syncthreads();
+    if (tid < cols) {
+        const T* pp = part[0] + tid;
+        const T s = two ? pp[0] + pp[128] : (pp[0] + pp[64]) + (pp[128] + pp[192]);
+        if (!self) pw[(int64_t)(tk->slot0 + tk->index) * 128 + tid] = s;
+        else v[tid] = tid < w ? yd - s : T(0);
+    }
+    if (!self) return;
+    if (!two && tid >= 64 && tid < 128) v[tid] = T(0);
+    __syncthreads();
+    ops.apply(v, 0, part[0], lane, q4);
+    if (two) {
+        ops.load(G1 + kPanel * kPanel, nullptr, false, lane, q4);
+        ops.apply(v, 1, part[1], lane, q4);
+    }
+    __syncthreads();
+    if (tid < w) {
+        const T* pp = part[tid >> 6] + lane;
+        X[first + c0 + tid] = (pp[0] + pp[64]) + (pp[128] + pp[192]);
+    }
+}
+
+// A small front by one wave, its 16-column sub-panels from the last: lane =
+// (column, row group g of four), the groups' sums meet by lane exchange, and
+// the sub-panel's x = Z_qq^T v (Z^T is stored above L's diagonal).
+template <typename T>
+__device__ __forceinline__ void bwd_front1(const SmallTask* tk, const int* __restrict__ rows, const T* __restrict__ F,
+                                           const T* __restrict__ D, const T* __restrict__ Y2, T* __restrict__ X,
+                                           T* xs, int lane) {
+    const int first = tk->first, p = tk->p, f = tk->f;
+    const T* __restrict__ L = F + tk->L_off;
+    const int t = lane & 15, g = lane >> 4;
+    for (int i = p + lane; i < f; i += 64) xs[i] = X[rows[tk->rows_off + i]];
+    wave_fence();
+    for (int kb = (p - 1) & ~15; kb >= 0; kb -= 16) {
+        const int bw = min(16, p - kb), c = kb + min(t, bw - 1), base = kb + bw;
+        const T* __restrict__ Lc = L + (int64_t)c * f;
+        T z[16];
+#pragma unroll
+        for (int u = 1; u < 16; ++u) {
+            const T x = L[c + (int64_t)(kb + min(u, bw - 1)) * f];
+            z[u] = u > t && u < bw ? x : T(0);
         }
-    if (!large && own && nr > 0) {
-        // column-major L only: stage L[rows, panel] as Ld[i + 65 t] (coalesced
-        // reads); such fronts have at most 64 rows below a panel (analysis)
-        for (int idx = tid; idx < 64 * kPanel; idx += 256) {
-            const int i = idx & 63, tt = idx >> 6;
-            Ld[i + 65 * tt] = (i < nr && tt < w) ? L[(r0 + i) + (int64_t)(c0 + tt) * f] : T(0);
+        const T yd = Y2[first + c] * (T(1) / D[first + c]);
+        // rows base + 4 m + g: four lanes of a column read consecutive rows
+        T acc = T(0);
+        for (int m0 = base; m0 < f; m0 += 64) {
+            T l[16];
+#pragma unroll
+            for (int m = 0; m < 16; ++m) l[m] = Lc[min(m0 + 4 * m + g, f - 1)];
+#pragma unroll
+            for (int m = 0; m < 16; ++m) {
+                const int i = m0 + 4 * m + g;
+                acc += i < f ? l[m] * xs[i] : T(0);
+            }
+        }
+        acc += __shfl_xor(acc, 16);
+        acc += __shfl_xor(acc, 32);
+        const T v = yd - acc;
+        T x = v;
+#pragma unroll
+        for (int u = 1; u < 16; ++u) x += z[u] * rowbcast_n(v, u);
+        if (lane < bw) {
+            xs[kb + lane] = x;
+            X[first + kb + lane] = x;
+        }
+        wave_fence();
+    }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256, 2) void k_bwd1(const PanelTask* __restrict__ pt, int np,
+                                                 const SmallTask* __restrict__ st, int ns, const int* __restrict__ rows,
+                                                 const T* __restrict__ F, const T* __restrict__ Zbuf,
+                                                 const T* __restrict__ D, const T* __restrict__ Y2, T* __restrict__ X,
+                                                 T* __restrict__ pw, const T* __restrict__ pr) {
+    const int b = blockIdx.x;
+    if (b < np) {
+        bwd_panels1<T>(pt + b, rows, F, Zbuf, D, Y2, X, pw, pr);
+    } else {
+        __shared__ T xs[4][kSmallMax];
+        const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), t = 4 * (b - np) + wave;
+        if (t < ns) bwd_front1<T>(st + t, rows, F, D, Y2, X, xs[wave], threadIdx.x & 63);
+    }
+}
+
+// ---- several right-hand sides (up to kNrhsMax, on MFMA) ----------------------
+// A 16-row piece of a vector is one accumulator: item r of a lane is row
+// row(lk, r), column lr.  Such a piece is also the second operand of a product
+// whose contraction takes rows row(lk, st) in step st.
+template <typename T>
+__device__ __forceinline__ typename Mfma<T>::acc_t rows16(const T* V, int lr, int lk) {   // V: row-major, 16 a row
+    typename Mfma<T>::acc_t a;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) a[r] = V[Mfma<T>::row(lk, r) * kNrhsMax + lr];
+    return a;
+}
+
+// Adds the children's update vectors to rows i0 .. i0 + 15 (those < iend) of a front.
+template <typename T>
+__device__ __forceinline__ void gather16(typename Mfma<T>::acc_t& a, const T* __restrict__ U,
+                                         const int* __restrict__ gat, int f, int gk, int i0, int iend, int lr, int lk) {
+    for (int k = 0; k < gk; ++k) {
+        int o[4];
+        T u[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = i0 + Mfma<T>::row(lk, r);
+            o[r] = i < iend ? gat[k * f + i] : -1;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) u[r] = U[(int64_t)max(o[r], 0) * kNrhsMax + lr];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) a[r] += o[r] >= 0 ? u[r] : T(0);
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ void fwd_panels16(const PanelTask* tk, const T* __restrict__ F, const T* __restrict__ Zbuf,
+                                             const int* __restrict__ gatab, T* __restrict__ Y, T* __restrict__ Y2,
+                                             T* __restrict__ U) {
+    typedef typename Mfma<T>::acc_t acc_t;
+    __shared__ T b[128 * kNrhsMax], y[128 * kNrhsMax];
+    const int first = tk->first, p = tk->p, f = tk->f, c0 = tk->c0, w1 = tk->w1, w2 = tk->w2, w = w1 + w2;
+    const int r0 = tk->r0, r1 = tk->r1, gk = tk->gk;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lr = lane & 15, lk = lane >> 4;
+    const T* __restrict__ L = F + tk->L_off;
+    const T* __restrict__ G1 = Zbuf + tk->M_off + (int64_t)(c0 / kPanel) * (kPanel * kPanel);
+    const T* __restrict__ Pm = Zbuf + tk->P_off;
+    T* __restrict__ Us = U + tk->U_off * kNrhsMax;
+    const int* __restrict__ gat = gatab + tk->gat;
+    const int i0 = r0 + 16 * wave;   // the wave's 16 rows
+    const bool act = i0 < r1;        // uniform
+    // the pair's right-hand side: rows 16 wave and 64 + 16 wave
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int l0 = 64 * h + 16 * wave;
+        acc_t a = {0, 0, 0, 0};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = l0 + Mfma<T>::row(lk, r);
+            if (i < w) a[r] = Y[(int64_t)(first + c0 + i) * kNrhsMax + lr];
+        }
+        if (gk > 0) gather16<T>(a, U, gat, f, gk, c0 + l0, c0 + w, lr, lk);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) b[(l0 + Mfma<T>::row(lk, r)) * kNrhsMax + lr] = a[r];
+    }
+    acc_t a = {0, 0, 0, 0};
+    if (act) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = i0 + Mfma<T>::row(lk, r);
+            if (i < r1) {
+                if (i < p) a[r] = Y[(int64_t)(first + i) * kNrhsMax + lr];
+                else if (c0 > 0) a[r] = Us[(int64_t)(i - p) * kNrhsMax + lr];
+            }
+        }
+        if (gk > 0) gather16<T>(a, U, gat, f, gk, i0, r1, lr, lk);
+    }
+    // L of the wave's rows, in flight over the first products
+    T l1[4][4];
+    const T* __restrict__ Lr = L + min(i0 + lr, f - 1);
+    const bool rv = i0 + lr < r1;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+        for (int st = 0; st < 4; ++st) {
+            const int k = 16 * kk + Mfma<T>::row(lk, st);
+            l1[kk][st] = rv && k < w1 ? -Lr[(int64_t)(c0 + k) * f] : T(0);
+        }
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if (h == 1 && w2 == 0) break;   // uniform
+        const T* __restrict__ G = G1 + h * kPanel * kPanel;
+        acc_t s = {0, 0, 0, 0};
+#pragma unroll 1
+        for (int kk = 0; kk <= wave; ++kk) {
+            T z[4];
+#pragma unroll
+            for (int st = 0; st < 4; ++st) {
+                const int k = 16 * kk + Mfma<T>::row(lk, st);
+                const T x = G[k * kPanel + 16 * wave + lr];
+                z[st] = k <= 16 * wave + lr ? x : T(0);
+            }
+            const acc_t bb = rows16<T>(b + (64 * h + 16 * kk) * kNrhsMax, lr, lk);
+#pragma unroll
+            for (int st = 0; st < 4; ++st) s = Mfma<T>::run(z[st], bb[st], s);
+        }
+        if (h == 1)
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                T z[4];
+#pragma unroll
+                for (int st = 0; st < 4; ++st) z[st] = Pm[(16 * kk + Mfma<T>::row(lk, st)) * kPanel + 16 * wave + lr];
+                const acc_t bb = rows16<T>(b + 16 * kk * kNrhsMax, lr, lk);
+#pragma unroll
+                for (int st = 0; st < 4; ++st) s = Mfma<T>::run(z[st], bb[st], s);
+            }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 64 * h + 16 * wave + Mfma<T>::row(lk, r);
+            y[i * kNrhsMax + lr] = s[r];
+            if (tk->index == 0 && i < w) Y2[(int64_t)(first + c0 + i) * kNrhsMax + lr] = s[r];
+        }
+    }
+    __syncthreads();
+    if (!act) return;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+        const acc_t yy = rows16<T>(y + 16 * kk * kNrhsMax, lr, lk);
+#pragma unroll
+        for (int st = 0; st < 4; ++st) a = Mfma<T>::run(l1[kk][st], yy[st], a);
+    }
+    if (w2 > 0) {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+            T l2[4];
+#pragma unroll
+            for (int st = 0; st < 4; ++st) {
+                const int k = 16 * kk + Mfma<T>::row(lk, st);
+                l2[st] = rv && k < w2 ? -Lr[(int64_t)(c0 + kPanel + k) * f] : T(0);
+            }
+            const acc_t yy = rows16<T>(y + (64 + 16 * kk) * kNrhsMax, lr, lk);
+#pragma unroll
+            for (int st = 0; st < 4; ++st) a = Mfma<T>::run(l2[st], yy[st], a);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = i0 + Mfma<T>::row(lk, r);
+        if (i >= r1) continue;
+        if (i < p) Y[(int64_t)(first + i) * kNrhsMax + lr] = a[r];
+        else Us[(int64_t)(i - p) * kNrhsMax + lr] = a[r];
+    }
+}
+
+// A small front of order up to 16 NT by one wave, all of it in registers.
+template <typename T, int NT>
+__device__ __forceinline__ void fwd_front16(const SmallTask* tk, const T* __restrict__ F, const int* __restrict__ gatab,
+                                            const T* __restrict__ Y, T* __restrict__ Y2, T* __restrict__ U, int lane) {
+    typedef typename Mfma<T>::acc_t acc_t;
+    const int first = tk->first, p = tk->p, f = tk->f, gk = tk->gk;
+    const int lr = lane & 15, lk = lane >> 4;
+    const T* __restrict__ L = F + tk->L_off;
+    T* __restrict__ Us = U + tk->U_off * kNrhsMax;
+    acc_t a[NT];
+#pragma unroll
+    for (int ti = 0; ti < NT; ++ti) {
+        a[ti] = acc_t{0, 0, 0, 0};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 16 * ti + Mfma<T>::row(lk, r);
+            if (i < p) a[ti][r] = Y[(int64_t)(first + i) * kNrhsMax + lr];
+        }
+        if (gk > 0) gather16<T>(a[ti], U, gatab + tk->gat, f, gk, 16 * ti, f, lr, lk);
+    }
+#pragma unroll
+    for (int q = 0; q < NT; ++q) {
+        const int kb = 16 * q, bw = min(16, p - kb);
+        if (bw <= 0) break;   // uniform
+        // y = Z_qq b, on the sub-panel's pivots only
+        T z[4];
+#pragma unroll
+        for (int st = 0; st < 4; ++st) {
+            const int k = Mfma<T>::row(lk, st);
+            const T x = L[(kb + min(k, bw - 1)) + (int64_t)(kb + min(lr, bw - 1)) * f];
+            z[st] = lr < bw && k <= lr ? (k == lr ? T(1) : x) : T(0);
+        }
+        acc_t y = {0, 0, 0, 0};
+#pragma unroll
+        for (int st = 0; st < 4; ++st) y = Mfma<T>::run(z[st], a[q][st], y);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = Mfma<T>::row(lk, r);
+            if (i < bw) Y2[(int64_t)(first + kb + i) * kNrhsMax + lr] = y[r];
+        }
+#pragma unroll
+        for (int ti = q; ti < NT; ++ti) {
+            T l[4];
+            const int i = 16 * ti + lr;
+            const T* __restrict__ Li = L + min(i, f - 1);
+#pragma unroll
+            for (int st = 0; st < 4; ++st) {
+                const int k = Mfma<T>::row(lk, st);
+                const T x = Li[(int64_t)(kb + min(k, bw - 1)) * f];
+                l[st] = k < bw && i < f && i >= kb + bw ? -x : T(0);
+            }
+#pragma unroll
+            for (int st = 0; st < 4; ++st) a[ti] = Mfma<T>::run(l[st], y[st], a[ti]);
+        }
+    }
+#pragma unroll
+    for (int ti = 0; ti < NT; ++ti) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 16 * ti + Mfma<T>::row(lk, r);
+            if (i >= p && i < f) Us[(int64_t)(i - p) * kNrhsMax + lr] = a[ti][r];
+        }
+    }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256, 2) void k_fwd16(const PanelTask* __restrict__ pt, int np,
+                                                  const SmallTask* __restrict__ st, int ns,
+                                                  const int* __restrict__ gat, const T* __restrict__ F,
+                                                  const T* __restrict__ Zbuf, T* __restrict__ Y, T* __restrict__ Y2,
+                                                  T* __restrict__ U) {
+    const int b = blockIdx.x;
+    if (b < np) {
+        fwd_panels16<T>(pt + b, F, Zbuf, gat, Y, Y2, U);
+    } else {
+        const int t = 4 * (b - np) + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        if (t >= ns) return;
+        const int lane = threadIdx.x & 63;
+        if (st[t].f <= 32) fwd_front16<T, 2>(st + t, F, gat, Y, Y2, U, lane);
+        else if (st[t].f <= 64) fwd_front16<T, 4>(st + t, F, gat, Y, Y2, U, lane);
+        else fwd_front16<T, 8>(st + t, F, gat, Y, Y2, U, lane);
+    }
+}
+
+// x pieces of a pair from v (128 x 16 in LDS): wave w forms rows 16 w .. of
+// x1 = Z1^T v1 + P^T v2 and of x2 = Z2^T v2.
+template <typename T>
+__device__ __forceinline__ void pair_x16(const T* __restrict__ G1, const T* __restrict__ PT, const T* v, bool do1,
+                                         bool do2, int xw1, int xw2, T* __restrict__ Xp, T* xs, int xoff, int wave,
+                                         int lr, int lk) {
+    typedef typename Mfma<T>::acc_t acc_t;
+    for (int h = 0; h < 2; ++h) {
+        if (!(h ? do2 && xw2 > 0 : do1)) continue;   // uniform
+        const T* __restrict__ G = G1 + h * kPanel * kPanel;
+        acc_t s = {0, 0, 0, 0};
+#pragma unroll 1
+        for (int kk = wave; kk < 4; ++kk) {
+            T z[4];
+#pragma unroll
+            for (int st = 0; st < 4; ++st) {
+                const int u = 16 * kk + Mfma<T>::row(lk, st);
+                const T x = G[u * kPanel + 16 * wave + lr];   // (Z^T)[t][u] above the diagonal
+                z[st] = u >= 16 * wave + lr ? x : T(0);
+            }
+            const acc_t vv = rows16<T>(v + (64 * h + 16 * kk) * kNrhsMax, lr, lk);
+#pragma unroll
+            for (int st = 0; st < 4; ++st) s = Mfma<T>::run(z[st], vv[st], s);
+        }
+        if (h == 0 && xw2 > 0)
+            for (int kk = 0; kk < 4; ++kk) {
+                T z[4];
+#pragma unroll
+                for (int st = 0; st < 4; ++st) z[st] = PT[(16 * kk + Mfma<T>::row(lk, st)) * kPanel + 16 * wave + lr];
+                const acc_t vv = rows16<T>(v + (64 + 16 * kk) * kNrhsMax, lr, lk);
+#pragma unroll
+                for (int st = 0; st < 4; ++st) s = Mfma<T>::run(z[st], vv[st], s);
+            }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 16 * wave + Mfma<T>::row(lk, r);
+            if (i >= (h ? xw2 : xw1)) continue;
+            Xp[(int64_t)(64 * h + i) * kNrhsMax + lr] = s[r];
+            if (xs) xs[(xoff + 64 * h + i) * kNrhsMax + lr] = s[r];
+        }
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ void bwd_panels16(const PanelTask* tk, const int* __restrict__ rows, const T* __restrict__ F,
+                                             const T* __restrict__ Zbuf, const T* __restrict__ D,
+                                             const T* __restrict__ Y2, T* __restrict__ X, T* __restrict__ pw,
+                                             const T* __restrict__ pr) {
+    typedef typename Mfma<T>::acc_t acc_t;
+    __shared__ T v[128 * kNrhsMax], xs[64 * kNrhsMax];
+    const int first = tk->first, p = tk->p, f = tk->f, c0 = tk->c0, w = tk->w1 + tk->w2;
+    const int r0 = tk->r0, nr = tk->r1 - r0;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lr = lane & 15, lk = lane >> 4;
+    const bool own = tk->index >= 0, fin = tk->fntask > 0, self = own && tk->ntask == 1;
+    const int xc0 = fin ? tk->fc0 : c0, xw1 = fin ? tk->fw1 : tk->w1, xw2 = fin ? tk->fw2 : tk->w2;
+    const T* __restrict__ A = F + tk->L_off;
+    const T* __restrict__ G1 = Zbuf + tk->M_off + (int64_t)(xc0 / kPanel) * (kPanel * kPanel);
+    const T* __restrict__ PT = Zbuf + (fin ? tk->fP_off : tk->P_off) + kPanel * kPanel;
+    if (own) {
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const int i = (tid >> 4) + 16 * it, gi = r0 + i;
+            xs[i * kNrhsMax + (tid & 15)] =
+                i < nr ? X[(int64_t)(gi < p ? first + gi : rows[tk->rows_off + gi]) * kNrhsMax + (tid & 15)] : T(0);
         }
     }
     if (fin) {
-        T acc2[NR];
+        // v = y / d - sum over the pair's tasks, eight entries a thread
+        T a[8];
 #pragma unroll
-        for (int q = 0; q < NR; ++q) acc2[q] = T(0);
-        for (int g0 = q4; g0 < fntask; g0 += 32) {
-            T pv[8];
+        for (int k = 0; k < 8; ++k) a[k] = T(0);
+        const T* __restrict__ src = pr + (int64_t)tk->fslot0 * (128 * kNrhsMax) + tid;
+        for (int g = 0; g < tk->fntask; ++g)
 #pragma unroll
-            for (int q = 0; q < NR; ++q) {
-                if (q >= nrhs) continue;
+            for (int k = 0; k < 8; ++k) a[k] += src[(int64_t)g * (128 * kNrhsMax) + 256 * k];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int g = g0 + 4 * u;
-                    pv[u] = g < fntask ? pr[((int64_t)(fslot0 + g) * kPanel + lane) * kNrhsMax + q] : T(0);
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) acc2[q] += pv[u];
-            }
+        for (int k = 0; k < 8; ++k) {
+            const int e = tid + 256 * k, i = e >> 4;
+            v[e] = i < xw1 + xw2
+                       ? Y2[(int64_t)(first + xc0) * kNrhsMax + e] * (T(1) / D[first + xc0 + i]) - a[k] : T(0);
         }
-#pragma unroll
-        for (int q = 0; q < NR; ++q)
-            if (q < nrhs) part[(q4 * 64 + lane) * nrhs + q] = acc2[q];
         __syncthreads();
-        if (tid < kPanel)
-            for (int q = 0; q < nrhs; ++q) {
-                const T* pp = part + tid * nrhs + q;
-                v[tid + q * kPanel] = (pp[0] + pp[64 * nrhs]) + (pp[128 * nrhs] + pp[192 * nrhs]);
-            }
-        __syncthreads();
-        bwd_panel_x<T, NR>(v, part, Ld, zv, yv, dinv, fw, nrhs, Y2 + first + fc0, N, own ? xs : nullptr,
-                           fc0 - r0, tid);
+        pair_x16<T>(G1, PT, v, tk->which == 0, tk->which == 1, xw1, xw2, X + (int64_t)(first + xc0) * kNrhsMax,
+                    own ? xs : nullptr, xc0 - r0, wave, lr, lk);
     }
-    if (!own) return;
+    if (!own) return;   // the whole workgroup
     __syncthreads();
-    // partial sums over the task's rows
+    // the sums: wave w takes columns 16 w and 64 + 16 w
 #pragma unroll
-    for (int q = 0; q < NR; ++q) {
-        if (q >= nrhs) continue;
-        T a = T(0);
-        if (large) {
+    for (int h = 0; h < 2; ++h) {
+        if (h == 1 && tk->w2 == 0) break;   // uniform
+        const int cl = 64 * h + 16 * wave + lr;
+        const T* __restrict__ src = A + c0 + min(cl, w - 1);
+        acc_t s = {0, 0, 0, 0};
 #pragma unroll
-            for (int m = 0; m < 16; ++m) {
-                const int i = rg + nrg * m;
-                a += lv[m] * xs[min(i, kSolveRowsMax - 1) + q * kSolveRowsMax];
+        for (int kk = 0; kk < 4; ++kk) {
+            T l[4];
+#pragma unroll
+            for (int st = 0; st < 4; ++st) {
+                const int i = 16 * kk + Mfma<T>::row(lk, st);
+                const T x = src[(int64_t)min(r0 + i, f - 1) * f];
+                l[st] = i < nr && cl < w ? x : T(0);
             }
-        } else if (tact) {
-            for (int m = 0; m < 16; ++m) {
-                const int i = rg + nrg * m;
-                if (i < 64) a += Ld[i + 65 * t] * xs[i + q * kSolveRowsMax];
+            const acc_t xx = rows16<T>(xs + 16 * kk * kNrhsMax, lr, lk);
+#pragma unroll
+            for (int st = 0; st < 4; ++st) s = Mfma<T>::run(l[st], xx[st], s);
+        }
+        if (!self) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                pw[((int64_t)(tk->slot0 + tk->index) * 128 + 64 * h + 16 * wave + Mfma<T>::row(lk, r)) * kNrhsMax + lr] =
+                    s[r];
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int i = 64 * h + 16 * wave + Mfma<T>::row(lk, r);
+                v[i * kNrhsMax + lr] = i < w ? Y2[(int64_t)(first + c0 + i) * kNrhsMax + lr] * (T(1) / D[first + c0 + i]) - s[r]
+                                             : T(0);
             }
         }
-        part[tid * nrhs + q] = tact ? a : T(0);
     }
+    if (!self) return;
     __syncthreads();
-    // this task's sum per panel column
-    if (tid < kPanel)
-        for (int q = 0; q < nrhs; ++q) {
-            T sum = T(0);
-            if (tid < w)
-                for (int g = 0; g < nrg; ++g) sum += part[(g * W16 + tid) * nrhs + q];
-            v[tid + q * kPanel] = sum;
+    pair_x16<T>(G1, PT, v, true, true, xw1, xw2, X + (int64_t)(first + c0) * kNrhsMax, nullptr, 0, wave, lr, lk);
+}
+
+template <typename T, int NT>
+__device__ __forceinline__ void bwd_front16(const SmallTask* tk, const int* __restrict__ rows, const T* __restrict__ F,
+                                            const T* __restrict__ D, const T* __restrict__ Y2, T* __restrict__ X,
+                                            int lane) {
+    typedef typename Mfma<T>::acc_t acc_t;
+    const int first = tk->first, p = tk->p, f = tk->f;
+    const int lr = lane & 15, lk = lane >> 4;
+    const T* __restrict__ L = F + tk->L_off;
+    acc_t x[NT];
+#pragma unroll
+    for (int ti = 0; ti < NT; ++ti) {
+        x[ti] = acc_t{0, 0, 0, 0};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 16 * ti + Mfma<T>::row(lk, r);
+            if (i >= p && i < f) x[ti][r] = X[(int64_t)rows[tk->rows_off + i] * kNrhsMax + lr];
         }
-    __syncthreads();
-    if (ntask > 1) {
-        if (tid < kPanel)
-            for (int q = 0; q < nrhs; ++q)
-                pw[((int64_t)(slot0 + chunk) * kPanel + tid) * kNrhsMax + q] = v[tid + q * kPanel];
-        return;
     }
-    if (large) {
-        bwd_panel_x<T, NR>(v, part, Ld, zv, yv, dinv, w, nrhs, Y2 + first + c0, N, nullptr, 0, tid);
+#pragma unroll
+    for (int q = NT - 1; q >= 0; --q) {
+        const int kb = 16 * q, bw = min(16, p - kb);
+        if (bw <= 0) continue;   // uniform
+        acc_t s = {0, 0, 0, 0};
+        const T* __restrict__ Lc = L + (int64_t)(kb + min(lr, bw - 1)) * f;
+#pragma unroll
+        for (int ti = q; ti < NT; ++ti) {
+            T l[4];
+#pragma unroll
+            for (int st = 0; st < 4; ++st) {
+                const int i = 16 * ti + Mfma<T>::row(lk, st);
+                const T e = Lc[min(i, f - 1)];
+                l[st] = lr < bw && i < f && i >= kb + bw ? e : T(0);
+            }
+#pragma unroll
+            for (int st = 0; st < 4; ++st) s = Mfma<T>::run(l[st], x[ti][st], s);
+        }
+        acc_t v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = kb + min(Mfma<T>::row(lk, r), bw - 1);
+            v[r] = Y2[(int64_t)(first + i) * kNrhsMax + lr] * (T(1) / D[first + i]) - s[r];
+        }
+        T z[4];
+#pragma unroll
+        for (int st = 0; st < 4; ++st) {
+            const int u = Mfma<T>::row(lk, st);
+            const T e = L[(kb + min(lr, bw - 1)) + (int64_t)(kb + min(u, bw - 1)) * f];
+            z[st] = lr < bw && u < bw && u >= lr ? (u == lr ? T(1) : e) : T(0);
+        }
+        acc_t xq = {0, 0, 0, 0};
+#pragma unroll
+        for (int st = 0; st < 4; ++st) xq = Mfma<T>::run(z[st], v[st], xq);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = Mfma<T>::row(lk, r);
+            if (i < bw) {
+                X[(int64_t)(first + kb + i) * kNrhsMax + lr] = xq[r];
+                x[q][r] = xq[r];
+            }
+        }
+    }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256, 2) void k_bwd16(const PanelTask* __restrict__ pt, int np,
+                                                  const SmallTask* __restrict__ st, int ns,
+                                                  const int* __restrict__ rows, const T* __restrict__ F,
+                                                  const T* __restrict__ Zbuf, const T* __restrict__ D,
+                                                  const T* __restrict__ Y2, T* __restrict__ X, T* __restrict__ pw,
+                                                  const T* __restrict__ pr) {
+    const int b = blockIdx.x;
+    if (b < np) {
+        bwd_panels16<T>(pt + b, rows, F, Zbuf, D, Y2, X, pw, pr);
     } else {
-        if (tid < kPanel) {
-#pragma unroll
-            for (int q = 0; q < NR; ++q) {
-                if (q >= nrhs) continue;
-                v[tid + q * kPanel] = tid < w ? yv[q] * dinv - v[tid + q * kPanel] : T(0);
-            }
-        }
-        __syncthreads();
-        chain_solve64<T, true>(L, f, c0, w, Ld, v, kPanel, nrhs);
-        for (int q = 0; q < nrhs; ++q)
-            if (tid < w) Y2[first + c0 + tid + q * N] = v[tid + q * kPanel];
+        const int t = 4 * (b - np) + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        if (t >= ns) return;
+        const int lane = threadIdx.x & 63;
+        if (st[t].f <= 32) bwd_front16<T, 2>(st + t, rows, F, D, Y2, X, lane);
+        else if (st[t].f <= 64) bwd_front16<T, 4>(st + t, rows, F, D, Y2, X, lane);
+        else bwd_front16<T, 8>(st + t, rows, F, D, Y2, X, lane);
     }
 }
 
-// Fronts with p <= 64 pivots and f <= kSmallRows rows (L is f x p, ld f).  Each
-// wave keeps its front's right-hand-side rows in LDS (ld kSmallRows) and
-// synchronizes only with itself; a workgroup carries four fronts.
-constexpr int kSmallRows = 128;
-
-// Forward: pull the children's update vectors, substitute the p pivots (lane =
-// pivot row, readlane broadcasts), apply them to the rows below, write back.
+// P = -Z2 L21 Z1 and P^T of one panel pair (64 x 64 each, column-major), by the
+// workgroup: wave w forms columns 16 w .. 16 w + 15 of L21 Z1, keeps them as the second
+// operand, and multiplies by -Z2.  One launch after the factorization, for all pairs.
 template <typename T>
-__global__ __launch_bounds__(256, 4) void k_fwd_S(DevPlan d, const int* __restrict__ fronts, int count,
-                                               const T* __restrict__ F, const T* __restrict__ Y, T* __restrict__ Y2,
-                                               T* __restrict__ U, int nrhs) {
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int task = blockIdx.x * 4 + wv;
-    if (task >= count) return;   // whole wave; no workgroup barrier below
-    T* ys = reinterpret_cast<T*>(smem_raw) + wv * kSmallRows * nrhs;
-    const int s = fronts[task];
-    const int first = d.sn_first[s];
-    const int p = d.sn_first[s + 1] - first;
-    const int f = (int)(d.sn_rowptr[s + 1] - d.sn_rowptr[s]);
-    const int c = f - p;
-    const T* __restrict__ L = F + d.L_off[s];
-    T* __restrict__ Us = U + d.U_off[s];
-    const int64_t N = d.N;
-    for (int q = 0; q < nrhs; ++q)
-        for (int i = lane; i < f; i += 64) ys[i + q * kSmallRows] = i < p ? Y[first + i + q * N] : T(0);
-    wave_fence();
-    for (int k = d.child_ptr[s]; k < d.child_ptr[s + 1]; ++k) {
-        const int ch = d.child_list[k];
-        const int cc = (int)(d.sn_rowptr[ch + 1] - d.sn_rowptr[ch]) - (d.sn_first[ch + 1] - d.sn_first[ch]);
-        const T* __restrict__ Uc = U + d.U_off[ch];
-        const int* __restrict__ r = d.rel + d.rel_ptr[ch];
-        for (int q = 0; q < nrhs; ++q)
-            for (int a = lane; a < cc; a += 64) ys[r[a] + q * kSmallRows] += Uc[a + (int64_t)q * cc];
-        wave_fence();
-    }
-    // substitution in two 32-column chunks (most small fronts need one)
-    const int lr = min(lane, f - 1);
-    for (int kc = 0; kc < p; kc += 32) {
-        T lrow[32];
+__global__ __launch_bounds__(256) void k_pair_inverse(const PairTask* __restrict__ tasks, const T* __restrict__ F,
+                                                      T* __restrict__ Zbuf) {
+    typedef typename Mfma<T>::acc_t acc_t;
+    const PairTask* tk = tasks + blockIdx.x;
+    const int f = tk->f, c0 = tk->c0, w2 = tk->w2;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int lr = lane & 15, lk = lane >> 4;
+    const T* __restrict__ A = F + tk->L_off + (c0 + kPanel) + (int64_t)c0 * f;   // L21
+    const T* __restrict__ G1 = Zbuf + tk->M_off;
+    const T* __restrict__ G2 = G1 + kPanel * kPanel;
+    acc_t m[4];   // rows 16 i .. of L21 Z1, columns 16 wave ..
 #pragma unroll
-        for (int k = 0; k < 32; ++k) {
-            if (kc + k < p) {
-                const T x = L[lr + (int64_t)(kc + k) * f];
-                lrow[k] = (kc + k < lane && lane < p) ? x : T(0);
-            } else {
-                lrow[k] = T(0);
+    for (int i = 0; i < 4; ++i) m[i] = acc_t{0, 0, 0, 0};
+    for (int kk = wave; kk < 4; ++kk) {   // Z1 is lower: rows k >= its column
+#pragma unroll
+        for (int st = 0; st < 4; ++st) {
+            const int k = 16 * kk + Mfma<T>::row(lk, st), c = 16 * wave + lr;
+            const T zx = G1[c * kPanel + k];
+            const T z = k >= c ? zx : T(0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int r = 16 * i + lr;
+                const T l = r < w2 ? A[r + (int64_t)k * f] : T(0);
+                m[i] = Mfma<T>::run(l, z, m[i]);
             }
         }
-        for (int q = 0; q < nrhs; ++q) {
-            T val = lane < p ? ys[lane + q * kSmallRows] : T(0);
-#pragma unroll
-            for (int k = 0; k < 32; ++k)
-                if (kc + k + 1 < p) val -= lrow[k] * bcast(val, kc + k);
-            if (lane < p) ys[lane + q * kSmallRows] = val;
-        }
-        wave_fence();
     }
-    for (int i0 = p; i0 < f; i0 += 64) {
-        const int i = i0 + lane;
-        const int ic = min(i, f - 1);
-        T acc[kNrhsMax];
+    T* __restrict__ P = Zbuf + tk->P_off;
+    T* __restrict__ PT = P + kPanel * kPanel;
 #pragma unroll
-        for (int q = 0; q < kNrhsMax; ++q) acc[q] = T(0);
-        for (int kc = 0; kc < p; kc += 32) {
-            T lv[32];
+    for (int i = 0; i < 4; ++i) {
+        acc_t s = {0, 0, 0, 0};
 #pragma unroll
-            for (int k = 0; k < 32; ++k) lv[k] = (kc + k < p) ? L[ic + (int64_t)(kc + k) * f] : T(0);
+        for (int kk = 0; kk <= i; ++kk) {
 #pragma unroll
-            for (int q = 0; q < kNrhsMax; ++q) {
-                if (q >= nrhs) continue;
-                const T* yq = ys + kc + q * kSmallRows;
-                T a = T(0);
-#pragma unroll
-                for (int k = 0; k < 32; ++k)
-                    if (kc + k < p) a += lv[k] * yq[k];
-                acc[q] += a;
+            for (int st = 0; st < 4; ++st) {
+                const int k = 16 * kk + Mfma<T>::row(lk, st), r = 16 * i + lr;
+                const T zx = G2[k * kPanel + r];
+                s = Mfma<T>::run(r >= k ? -zx : T(0), m[kk][st], s);
             }
         }
 #pragma unroll
-        for (int q = 0; q < kNrhsMax; ++q)
-            if (q < nrhs && i < f) ys[i + q * kSmallRows] -= acc[q];
-    }
-    wave_fence();
-    for (int q = 0; q < nrhs; ++q)
-        for (int i = lane; i < f; i += 64) {
-            const T v = ys[i + q * kSmallRows];
-            if (i < p) Y2[first + i + q * N] = v;
-            else Us[(i - p) + (int64_t)q * c] = v;
-        }
-}
-
-// Backward: gather x of the rows below, v_t = y_t / d_t - sum_i L[i][t] x_i
-// (lane = pivot column t, its column read contiguously), then the transposed
-// substitution from the last pivot up (readlane broadcasts).
-template <typename T>
-__global__ __launch_bounds__(256, 4) void k_bwd_S(DevPlan d, const int* __restrict__ fronts, int count,
-                                               const T* __restrict__ F, const T* __restrict__ D,
-                                               T* __restrict__ Y2, int nrhs) {
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int task = blockIdx.x * 4 + wv;
-    if (task >= count) return;   // whole wave; no workgroup barrier below
-    T* xs = reinterpret_cast<T*>(smem_raw) + wv * kSmallRows * nrhs;
-    const int s = fronts[task];
-    const int first = d.sn_first[s];
-    const int p = d.sn_first[s + 1] - first;
-    const int64_t rb = d.sn_rowptr[s];
-    const int f = (int)(d.sn_rowptr[s + 1] - rb);
-    const T* __restrict__ L = F + d.L_off[s];
-    const int* __restrict__ rows = d.sn_rows + rb;
-    const int64_t N = d.N;
-    for (int q = 0; q < nrhs; ++q)
-        for (int i = lane; i < f; i += 64)
-            xs[i + q * kSmallRows] = i < p ? Y2[first + i + q * N] : Y2[rows[i] + q * N];
-    wave_fence();
-    const int t = lane;
-    const bool tv = t < p;
-    const T* __restrict__ col = L + (int64_t)min(t, p - 1) * f;
-    T acc[kNrhsMax];
-#pragma unroll
-    for (int q = 0; q < kNrhsMax; ++q) acc[q] = T(0);
-    for (int i0 = p; i0 < f; i0 += 32) {
-        T lv[32];
-#pragma unroll
-        for (int k = 0; k < 32; ++k) lv[k] = (i0 + k < f) ? col[i0 + k] : T(0);
-#pragma unroll
-        for (int q = 0; q < kNrhsMax; ++q) {
-            if (q >= nrhs) continue;
-            const T* xq = xs + i0 + q * kSmallRows;
-            T a = T(0);
-#pragma unroll
-            for (int k = 0; k < 32; ++k)
-                if (i0 + k < f) a += lv[k] * xq[k];
-            acc[q] += a;
+        for (int r = 0; r < 4; ++r) {
+            const int u = 16 * i + Mfma<T>::row(lk, r), c = 16 * wave + lr;
+            P[u + c * kPanel] = s[r];
+            PT[c + u * kPanel] = s[r];
         }
     }
-    // v_t into xs[t], then the transposed substitution in 32-row chunks from
-    // the last pivot up (x_k final at lane k when chunk k is reached)
-    const T dinv = T(1) / D[first + min(t, p - 1)];
-#pragma unroll
-    for (int q = 0; q < kNrhsMax; ++q)
-        if (q < nrhs && tv) xs[t + q * kSmallRows] = xs[t + q * kSmallRows] * dinv - acc[q];
-    wave_fence();
-    for (int kc = ((p - 1) / 32) * 32; kc >= 0; kc -= 32) {
-        T lcol[32];
-#pragma unroll
-        for (int k = 0; k < 32; ++k) {
-            if (kc + k < p) {
-                const T x = col[kc + k];
-                lcol[k] = (tv && kc + k > t) ? x : T(0);
-            } else {
-                lcol[k] = T(0);
-            }
-        }
-        for (int q = 0; q < nrhs; ++q) {
-            T val = tv ? xs[t + q * kSmallRows] : T(0);
-#pragma unroll
-            for (int k = 31; k >= 0; --k)
-                if (kc + k < p && kc + k > 0) val -= lcol[k] * bcast(val, kc + k);
-            if (tv) xs[t + q * kSmallRows] = val;
-        }
-        wave_fence();
-    }
-    for (int q = 0; q < nrhs; ++q)
-        if (tv) Y2[first + t + q * N] = xs[t + q * kSmallRows];
 }
 
 // ---------------------------------------------------------------------------
@@ -2339,51 +2523,43 @@ void launch_large_dstep(const DevPlan& d, const LargeTask* dtasks, int nd, const
 }
 
 template <typename T>
+void launch_pair_inverse(const PairTask* tasks, int count, const T* F, T* M, hipStream_t st) {
+    if (count > 0) launch(k_pair_inverse<T>, dim3(count), dim3(256), 0, st, tasks, F, M);
+}
+
+template <typename T>
 void launch_permute_in(const DevPlan& d, const double* B, int64_t ldb, int nrhs, T* Y, hipStream_t st) {
-    launch(k_permute_in<T>, dim3(blocks_for(d.N, 256)), dim3(256), 0, st, d, B, ldb, nrhs, Y);
-}
-
-template <typename T>
-void launch_permute_out(const DevPlan& d, const T* Y, int nrhs, double* X, int64_t ldx, hipStream_t st) {
-    launch(k_permute_out<T>, dim3(blocks_for(d.N, 256)), dim3(256), 0, st, d, Y, nrhs, X, ldx);
-}
-
-template <typename T>
-void launch_fwd_S(const DevPlan& d, const int* fronts, int count, const T* F, const T* Y, T* Y2, T* U, int nrhs,
-                  hipStream_t st) {
-    if (count <= 0) return;
-    const size_t lds = (size_t)4 * kSmallRows * nrhs * sizeof(T);
-    launch(k_fwd_S<T>, dim3((count + 3) / 4), dim3(256), lds, st, d, fronts, count, F, Y, Y2, U, nrhs);
-}
-
-template <typename T>
-void launch_bwd_S(const DevPlan& d, const int* fronts, int count, const T* F, const T* D, T* Y2, int nrhs,
-                  hipStream_t st) {
-    if (count <= 0) return;
-    const size_t lds = (size_t)4 * kSmallRows * nrhs * sizeof(T);
-    launch(k_bwd_S<T>, dim3((count + 3) / 4), dim3(256), lds, st, d, fronts, count, F, D, Y2, nrhs);
-}
-
-template <typename T>
-void launch_fwd_P(const DevPlan& d, const int* tasks, int count, const int* segs, const T* F,
-                  const T* Z, T* Y, T* Y2, T* U, int nrhs, hipStream_t st) {
-    if (count <= 0) return;
-    const size_t lds = (size_t)((2 * kPanel + kSolveRowsMax + 256) * nrhs + 64 * 65) * sizeof(T);
     if (nrhs == 1)
-        launch(k_fwd_P<T, 1>, dim3(count), dim3(256), lds, st, d, tasks, segs, F, Z, Y, Y2, U, nrhs);
+        launch(k_permute_in<T, 1>, dim3(blocks_for(d.N, 256)), dim3(256), 0, st, d, B, ldb, nrhs, Y);
     else
-        launch(k_fwd_P<T, kNrhsMax>, dim3(count), dim3(256), lds, st, d, tasks, segs, F, Z, Y, Y2, U, nrhs);
+        launch(k_permute_in<T, kNrhsMax>, dim3(blocks_for(d.N * kNrhsMax, 256)), dim3(256), 0, st, d, B, ldb, nrhs, Y);
 }
 
 template <typename T>
-void launch_bwd_P(const DevPlan& d, const int* tasks, int count, const T* F, const T* Z,
-                  const T* D, T* Y2, T* pw, const T* pr, int nrhs, hipStream_t st) {
-    if (count <= 0) return;
-    const size_t lds = (size_t)((kPanel + kSolveRowsMax + 256) * nrhs + 64 * 65) * sizeof(T);
+void launch_permute_out(const DevPlan& d, const T* X, int nrhs, double* Xo, int64_t ldx, hipStream_t st) {
     if (nrhs == 1)
-        launch(k_bwd_P<T, 1>, dim3(count), dim3(256), lds, st, d, tasks, F, Z, D, Y2, pw, pr, nrhs);
+        launch(k_permute_out<T, 1>, dim3(blocks_for(d.N, 256)), dim3(256), 0, st, d, X, nrhs, Xo, ldx);
     else
-        launch(k_bwd_P<T, kNrhsMax>, dim3(count), dim3(256), lds, st, d, tasks, F, Z, D, Y2, pw, pr, nrhs);
+        launch(k_permute_out<T, kNrhsMax>, dim3(blocks_for(d.N * kNrhsMax, 256)), dim3(256), 0, st, d, X, nrhs, Xo,
+               ldx);
+}
+
+template <typename T>
+void launch_fwd(bool many, const PanelTask* pt, int np, const SmallTask* sm, int ns, const int* gat, const T* F,
+                const T* Z, T* Y, T* Y2, T* U, hipStream_t st) {
+    const int grid = np + (ns + 3) / 4;
+    if (grid <= 0) return;
+    if (many) launch(k_fwd16<T>, dim3(grid), dim3(256), 0, st, pt, np, sm, ns, gat, F, Z, Y, Y2, U);
+    else launch(k_fwd1<T>, dim3(grid), dim3(256), 0, st, pt, np, sm, ns, gat, F, Z, Y, Y2, U);
+}
+
+template <typename T>
+void launch_bwd(bool many, const PanelTask* pt, int np, const SmallTask* sm, int ns, const int* rows, const T* F,
+                const T* Z, const T* D, const T* Y2, T* X, T* pw, const T* pr, hipStream_t st) {
+    const int grid = np + (ns + 3) / 4;
+    if (grid <= 0) return;
+    if (many) launch(k_bwd16<T>, dim3(grid), dim3(256), 0, st, pt, np, sm, ns, rows, F, Z, D, Y2, X, pw, pr);
+    else launch(k_bwd1<T>, dim3(grid), dim3(256), 0, st, pt, np, sm, ns, rows, F, Z, D, Y2, X, pw, pr);
 }
 
 void launch_residual(const DevPlan& d, const double* K, const double* B, int64_t ldb, const double* X, int64_t ldx,
@@ -2438,11 +2614,7 @@ hipError_t configure_kernels(int max_dynamic_lds) {
     hipError_t e = hipSuccess, r;
     const void* fns[] = {(const void*)k_front<double, 6, 4>, (const void*)k_front<double, 8, 4>,
                          (const void*)k_front<float, 6, 4>, (const void*)k_front<float, 8, 4>,
-                         (const void*)k_fwd_P<double, kNrhsMax>, (const void*)k_fwd_P<float, kNrhsMax>,
-                         (const void*)k_bwd_P<double, kNrhsMax>, (const void*)k_bwd_P<float, kNrhsMax>,
-                         (const void*)k_fwd_S<double>, (const void*)k_fwd_S<float>,
-                         (const void*)k_large_asm<double, true>, (const void*)k_large_asm<float, true>,
-                         (const void*)k_bwd_S<double>, (const void*)k_bwd_S<float>};
+                         (const void*)k_large_asm<double, true>, (const void*)k_large_asm<float, true>};
     for (const void* f : fns) {
         hipFuncAttributes at{};
         r = hipFuncGetAttributes(&at, f);
@@ -2462,14 +2634,13 @@ hipError_t configure_kernels(int max_dynamic_lds) {
     template void launch_large_panel<T>(const LargeTask*, int, T*, const T*, const T*, hipStream_t);               \
     template void launch_large_dstep<T>(const DevPlan&, const LargeTask*, int, const LargeTask*, int, T*, T*, T*,  \
                                         hipStream_t);                                                              \
+    template void launch_pair_inverse<T>(const PairTask*, int, const T*, T*, hipStream_t);                         \
     template void launch_permute_in<T>(const DevPlan&, const double*, int64_t, int, T*, hipStream_t);              \
     template void launch_permute_out<T>(const DevPlan&, const T*, int, double*, int64_t, hipStream_t);             \
-    template void launch_fwd_S<T>(const DevPlan&, const int*, int, const T*, const T*, T*, T*, int, hipStream_t);  \
-    template void launch_bwd_S<T>(const DevPlan&, const int*, int, const T*, const T*, T*, int, hipStream_t);     \
-    template void launch_fwd_P<T>(const DevPlan&, const int*, int, const int*, const T*, const T*, T*, T*, T*,    \
-                                  int, hipStream_t);                                                               \
-    template void launch_bwd_P<T>(const DevPlan&, const int*, int, const T*, const T*, const T*, T*, T*,          \
-                                  const T*, int, hipStream_t);
+    template void launch_fwd<T>(bool, const PanelTask*, int, const SmallTask*, int, const int*, const T*,          \
+                                const T*, T*, T*, T*, hipStream_t);                                                \
+    template void launch_bwd<T>(bool, const PanelTask*, int, const SmallTask*, int, const int*, const T*,          \
+                                const T*, const T*, const T*, T*, T*, const T*, hipStream_t);
 
 NCL_INSTANTIATE(double)
 NCL_INSTANTIATE(float)

@@ -4,6 +4,8 @@
 
 #include <cstdint>
 
+#include "plan.hpp"
+
 
 namespace ncl {
 
@@ -11,20 +13,6 @@ constexpr int kNrhsMax = 16;   // columns per solve sweep (wider solves are chun
 constexpr int kPanel = 64;       // pivot block width of the large-front path
 constexpr int kSmallMax = 128;   // largest front order of the LDS-resident path
 constexpr int kTile = 64;        // tile order of the large-front MFMA update
-constexpr int kSolveRowsMax = 256;  // rows below a solve panel per task (fewer for wide panels)
-constexpr int kPanInts = 7;      // ints per solve panel: s, c0, w, slot0, tasks, seg0, nseg
-constexpr int kPTaskInts = 6;    // ints per solve task: panel, r0, r1, index, seg0, nseg
-// A sweep task as the kernels read it: the task, its panel and its front in
-// one record, so that one round trip brings everything the task needs.
-//   ints  0..5   the task (panel, r0, r1, index, seg0, nseg)
-//   ints  6..12  the panel (s, c0, w, slot0, tasks, seg0, nseg)
-//   ints 13..15  the front (first pivot, pivots p, order f)
-//   int64 at ints 16, 18, 20, 22: L_off, U_off, M_off, first row-list entry
-//   ints 24..27  backward: the panel this task finishes (c0, w, slot0, tasks; tasks 0: none)
-//   ints 28..31  forward: the second panel's width (0: one panel), its pivot rows' segments
-//                (first, count), 0
-constexpr int kTaskRec = 32;
-constexpr int kTaskRec64 = 16;
 constexpr int kInertiaSlots = 64;  // partial inertia counters per system (spreads the atomics)
 constexpr int kNonfiniteInput = 1;   // status bit: NaN/Inf in the assembled K (its norms)
 constexpr int kNonfiniteFactor = 4;  // status bit: NaN/Inf pivot met by the factorization
@@ -107,8 +95,6 @@ struct DevPlan {
     const int64_t* L_off;
     const int64_t* CB_off;
     const int* CB_ld;
-    const int64_t* U_off;      // in elements of one column block (times kNrhsMax applied)
-    const int64_t* M_off;      // large fronts: offset of the per-panel inverses L_kk^-1 (64 x 64 each)
     // large-front column assembly tasks (see Plan::asm_*)
     const int64_t* asm_col;
     const int* asm_fj;
@@ -192,30 +178,27 @@ template <typename T>
 void launch_large_dstep(const DevPlan& d, const LargeTask* dtasks, int nd, const LargeTask* utasks, int nu, T* F,
                         T* D, T* M, hipStream_t st);
 
+// P = -Z2 L21 Z1 of every panel pair, after the factorization.
+template <typename T>
+void launch_pair_inverse(const PairTask* tasks, int count, const T* F, T* M, hipStream_t st);
+
 // ---- solves -----------------------------------------------------------------
+// Vectors in pivot order with one value a row, or with kNrhsMax ("many", nrhs > 1;
+// unused columns zero).
 template <typename T>
 void launch_permute_in(const DevPlan& d, const double* B, int64_t ldb, int nrhs, T* Y, hipStream_t st);
 template <typename T>
-void launch_permute_out(const DevPlan& d, const T* Y, int nrhs, double* X, int64_t ldx, hipStream_t st);
-// Y: right-hand side in pivot order (updated in place by the forward sweep
-// for rows that are not yet solved); Y2: the pivots' y after the forward sweep,
-// their x after the backward sweep.  One-wave fronts (p <= 64, f <= 128):
+void launch_permute_out(const DevPlan& d, const T* X, int nrhs, double* Xo, int64_t ldx, hipStream_t st);
+// One step of a sweep: np panel tasks and ns small fronts.  Y: right-hand side
+// (updated in place for rows not yet solved), Y2: the pivots' y, X: their x, U: update
+// vectors; the backward tasks' sums go to pw, the previous step's are read from
+// pr (slots x 128 values or rows of kNrhsMax, two halves used in turn).
 template <typename T>
-void launch_fwd_S(const DevPlan& d, const int* fronts, int count, const T* F, const T* Y, T* Y2, T* U, int nrhs,
-                  hipStream_t st);
+void launch_fwd(bool many, const PanelTask* pt, int np, const SmallTask* sm, int ns, const int* gat, const T* F,
+                const T* Z, T* Y, T* Y2, T* U, hipStream_t st);
 template <typename T>
-void launch_bwd_S(const DevPlan& d, const int* fronts, int count, const T* F, const T* D, T* Y2, int nrhs,
-                  hipStream_t st);
-// The other fronts, one launch per panel step of a level (task records of
-// kTaskRec ints, contribution segments: see the sweep kernels).  Backward:
-// the step's task sums go to pw, the previous step's are read from pr (each
-// slots x kPanel x kNrhsMax, two halves used in turn).
-template <typename T>
-void launch_fwd_P(const DevPlan& d, const int* tasks, int count, const int* segs, const T* F,
-                  const T* Z, T* Y, T* Y2, T* U, int nrhs, hipStream_t st);
-template <typename T>
-void launch_bwd_P(const DevPlan& d, const int* tasks, int count, const T* F, const T* Z,
-                  const T* D, T* Y2, T* pw, const T* pr, int nrhs, hipStream_t st);
+void launch_bwd(bool many, const PanelTask* pt, int np, const SmallTask* sm, int ns, const int* rows, const T* F,
+                const T* Z, const T* D, const T* Y2, T* X, T* pw, const T* pr, hipStream_t st);
 
 // ---- refinement -------------------------------------------------------------
 // R = B - K X; per chunk of rows (all of one system) and column, kResWidth figures:

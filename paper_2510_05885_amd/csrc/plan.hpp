@@ -45,18 +45,32 @@ struct LargeStep {             // launches of the large-front path for one level
     std::vector<double> upd_flops;            // algorithmic flops of each update launch
 };
 
-// Solve schedule: a front with p <= 64 pivots and f <= 128 rows is swept by
-// one wave; every other front in panels of up to 64 pivot columns, each panel
-// split into tasks of up to 64 rows below it (one workgroup each).  Per level
-// and panel index j, one launch of the one-wave fronts (j = 0) and one of the
-// panel tasks.
+// A task of a sweep: 64 rows r0 .. r1 below a pair of panels (columns c0 .. c0 +
+// w1 + w2, w2 = 0 for a lone one) of a large front (pivots first .. first + p,
+// order f); task `index` of ntask (index -1: a record that only finishes).
+// Backward: sums go to partial slot slot0 + index; a task with fntask > 0
+// first finishes panel `which` of the pair at fc0 from its fntask sums at
+// fslot0.  gk: depth of the front's gather table at gat (0 unless c0 = 0).
+struct PanelTask {
+    int first, p, f, c0, w1, w2, r0, r1, index, ntask, slot0, gk;
+    int fc0, fw1, fw2, fslot0, fntask, which;
+    int64_t L_off, U_off, M_off, P_off, fP_off, rows_off, gat;
+};
+struct SmallTask {             // a small front's sweep (one wave)
+    int first, p, f, gk;
+    int64_t L_off, U_off, rows_off, gat;
+};
+struct PairTask {              // a panel pair whose coupling block is formed
+    int f, c0, w2, pad;
+    int64_t L_off, M_off, P_off;   // M_off: the pair's first inverse
+};
+// One launch of a sweep, in execution order.  k: pair step of the level (backward
+// partial half), -1 for the records that finish the first pairs of a level.
 struct SolveStep {
-    int level = 0, j = 0;
-    int64_t p_first = 0, p_count = 0;   // tasks in Plan::solve_p (kPTaskInts each)
-    int64_t s_first = 0, s_count = 0;   // small fronts in Plan::solve_s (one wave each)
-    int64_t f_first = 0, f_count = 0;   // j = 0 only: finish-only records in Plan::solve_p, run
-                                        // after the level's backward steps
-    double fwd_bytes = 0.0;             // algorithmic bytes of L read by the step (FP64; padding
+    int level = 0, k = 0;
+    int64_t p_first = 0, p_count = 0;   // tasks in Plan::fwd_tasks / bwd_tasks
+    int64_t s_first = 0, s_count = 0;   // small fronts in Plan::solve_small
+    double bytes = 0.0;                 // algorithmic bytes of L read by the step (FP64; padding
                                         // zeros of amalgamated fronts not counted)
 };
 
@@ -125,6 +139,7 @@ struct Plan {
     int64_t factor_elems = 0;        // factor buffer length (elements of T)
     std::vector<int64_t> U_off;      // solve: update vector of each front (c_s * nrhs_max)
     std::vector<int64_t> M_off;      // large fronts: per-panel inverses L_kk^-1 (panel^2 each)
+    std::vector<int64_t> P_off;      // large fronts: first pair's coupling block (P, P^T, panel^2 each a pair)
     int64_t M_elems = 0;
     int64_t U_elems = 0;
 
@@ -148,20 +163,12 @@ struct Plan {
     std::vector<int> large_upd;      // quads (front, k0, tile row start, tile col start); the next
                                      // panel's diagonal tile is left to large_diag
     // solve schedule
-    std::vector<SolveStep> solve_steps;
-    std::vector<int> solve_pan;      // panels (s, c0, w, slot0, tasks, seg0, nseg)
-    std::vector<int> solve_p;        // tasks (panel, r0, r1, index, seg0, nseg); index -1: finish only
-    std::vector<int> solve_fin;      // per task: the panel it finishes in the backward sweep
-                                     // (c0, w, slot0, tasks), tasks 0 if none
-    std::vector<int> solve_seg;      // (child, a0, a1): update-vector entries landing in a task
-    // forward sweep: its own steps (j = step index k of the level) and tasks
-    // (as solve_p, panel = the step's first panel), with per task (w2,
-    // seg0, nseg, 0): the second panel's width (0: one panel) and its pivot
-    // rows' contribution segments
-    std::vector<SolveStep> fsolve_steps;
-    std::vector<int> fsolve_p, fsolve_x;
-    std::vector<int> solve_s;        // small fronts (p <= 64, f <= 128) solved by one wave each
-    int64_t solve_max_slots = 0;     // tasks in the largest step (partial-sum slots)
+    std::vector<SolveStep> fwd_steps, bwd_steps;
+    std::vector<PanelTask> fwd_tasks, bwd_tasks;
+    std::vector<SmallTask> solve_small;
+    std::vector<PairTask> pairs;
+    std::vector<int> gather;         // per front gk x f offsets of update-vector entries, -1 none
+    int64_t solve_max_slots = 0;     // backward tasks in the largest step (partial-sum slots)
 
     // ---- stats ------------------------------------------------------------
     int64_t nnzL = 0;
