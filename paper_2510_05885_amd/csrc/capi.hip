@@ -106,7 +106,7 @@ struct ncl_kkt_s {
     unsigned long long* inertia_part = nullptr;
     double *F64 = nullptr, *D64 = nullptr, *Y64 = nullptr, *U64 = nullptr, *P64 = nullptr, *M64 = nullptr;
     float *F32 = nullptr, *D32 = nullptr, *Y32 = nullptr, *U32 = nullptr, *P32 = nullptr, *M32 = nullptr;
-    double *R = nullptr, *DX = nullptr, *Xp = nullptr, *partial_res = nullptr, *res_out = nullptr;
+    double *R = nullptr, *DX = nullptr, *Xp = nullptr, *Xr = nullptr, *partial_res = nullptr, *res_out = nullptr;
     double *JX = nullptr, *JL = nullptr;
     // slack elimination: J^T in CSC (row, value index per entry), Omega of the
     // last factor_k1s call; `weighted` while the factor is of K1s
@@ -324,12 +324,15 @@ void setup_device(ncl_kkt_s* h) {
     h->solve_small = upload(h, P.solve_small);
     h->pairs = upload(h, P.pairs);
     h->gather = upload(h, P.gather);
-    // row chunks (<= 256 rows, never straddling two systems)
+    // row chunks (never straddling two systems), one block each: up to 256 rows, in
+    // multiples of the 32 that a block takes at once; smaller while there are fewer
+    // than 2048 of them (eight a CU), where a block's rows one after the other set the time
     std::vector<int> c0, cn, scp(1, 0);
+    const int64_t rows = std::min<int64_t>(256, std::max<int64_t>(32, (P.N / 2048 + 31) / 32 * 32));
     for (int s = 0; s < P.S; ++s) {
-        for (int64_t r = P.sys_voff[s]; r < P.sys_voff[s + 1]; r += 256) {
+        for (int64_t r = P.sys_voff[s]; r < P.sys_voff[s + 1]; r += rows) {
             c0.push_back((int)r);
-            cn.push_back((int)std::min<int64_t>(256, P.sys_voff[s + 1] - r));
+            cn.push_back((int)std::min<int64_t>(rows, P.sys_voff[s + 1] - r));
         }
         scp.push_back((int)c0.size());
     }
@@ -372,6 +375,7 @@ void setup_device(ncl_kkt_s* h) {
     h->R = dalloc<double>(h, P.N * kNrhsMax);
     h->DX = dalloc<double>(h, P.N * kNrhsMax);
     h->Xp = dalloc<double>(h, P.N * kNrhsMax);
+    h->Xr = dalloc<double>(h, P.N * kNrhsMax);
     h->partial_res = dalloc<double>(h, (int64_t)h->nchunks * kNrhsMax * kResWidth);
     h->res_out = dalloc<double>(h, (int64_t)P.S * kNrhsMax * kResWidth);
     // adjoint structures
@@ -751,10 +755,10 @@ void sweeps(ncl_kkt_s* h, int nrhs, const T* F, const T* Z, const T* D, T* Y, T*
 }
 
 template <typename T>
-void solve_once(ncl_kkt_s* h, const double* B, int64_t ldb, double* X, int64_t ldx, int nrhs, const T* F,
+void solve_once(ncl_kkt_s* h, const double* B, int64_t si, int64_t sq, double* X, int64_t ldx, int nrhs, const T* F,
                 const T* Z, const T* D, T* Y, T* U, T* partial, hipStream_t st) {
     const DevPlan& d = h->d;
-    launch_permute_in<T>(d, B, ldb, nrhs, Y, st);
+    launch_permute_in<T>(d, B, si, sq, nrhs, Y, st);
     const int pr = std::is_same<T, float>::value ? 1 : 0;
     if (!h->opt.use_graphs || h->tm.on) {
         sweeps<T>(h, nrhs, F, Z, D, Y, U, partial, st);
@@ -774,11 +778,13 @@ void solve_once(ncl_kkt_s* h, const double* B, int64_t ldb, double* X, int64_t l
     launch_permute_out<T>(d, Y + 2 * h->P.N * (nrhs > 1 ? kNrhsMax : 1), nrhs, X, ldx, st);
 }
 
-void solve_with_factor(ncl_kkt_s* h, const double* B, int64_t ldb, double* X, int64_t ldx, int nrhs, hipStream_t st) {
+// B: column q of row i at B[i si + q sq].
+void solve_with_factor(ncl_kkt_s* h, const double* B, int64_t si, int64_t sq, double* X, int64_t ldx, int nrhs,
+                       hipStream_t st) {
     if (h->factor_prec == 1)
-        solve_once<float>(h, B, ldb, X, ldx, nrhs, h->F32, h->M32, h->D32, h->Y32, h->U32, h->P32, st);
+        solve_once<float>(h, B, si, sq, X, ldx, nrhs, h->F32, h->M32, h->D32, h->Y32, h->U32, h->P32, st);
     else
-        solve_once<double>(h, B, ldb, X, ldx, nrhs, h->F64, h->M64, h->D64, h->Y64, h->U64, h->P64, st);
+        solve_once<double>(h, B, si, sq, X, ldx, nrhs, h->F64, h->M64, h->D64, h->Y64, h->U64, h->P64, st);
 }
 
 // Backward errors of X against B, each the max over systems and columns.
@@ -793,7 +799,7 @@ Backward backward_error(ncl_kkt_s* h, const double* B, int64_t ldb, const double
     Plan& P = h->P;
     {
         Span sp(h, st, TM_RES);
-        launch_residual(h->d, h->K, B, ldb, X, ldx, h->R, nrhs, h->chunk_row0, h->chunk_rows, h->nchunks,
+        launch_residual(h->d, h->K, B, ldb, X, ldx, h->Xr, h->R, nrhs, h->chunk_row0, h->chunk_rows, h->nchunks,
                         h->partial_res, st);
         launch_reduce(h->sys_chunk_ptr, P.S, kResWidth * nrhs, kResWidth, (1u << 3) | (1u << 4), h->partial_res,
                       h->res_out, st);
@@ -827,15 +833,16 @@ bool converged(const ncl_kkt_s* h, const Backward& b) { return ir_gap(h, b) <= 1
 Backward solve_refine(ncl_kkt_s* h, const double* B, int64_t ldb, double* X, int64_t ldx, int nrhs, hipStream_t st,
                       int& steps, double& om0) {
     const int64_t N = h->P.N;
-    solve_with_factor(h, B, ldb, X, ldx, nrhs, st);
+    solve_with_factor(h, B, 1, ldb, X, ldx, nrhs, st);
     Backward om = backward_error(h, B, ldb, X, ldx, nrhs, st);
     om0 = om.omega;
     steps = 0;
     if (!h->inertia_ok) return om;
     double gap = ir_gap(h, om);
     while (gap > 1.0 && steps < h->opt.ir_max_steps) {
-        // correction from the residual left in R by backward_error
-        solve_with_factor(h, h->R, N, h->DX, N, nrhs, st);
+        // correction from the residual left in R by backward_error (row-major
+        // for several columns)
+        solve_with_factor(h, h->R, nrhs > 1 ? kNrhsMax : 1, 1, h->DX, N, nrhs, st);
         launch_copy_cols(h->Xp, N, X, ldx, N, nrhs, st);
         launch_axpy_cols(X, ldx, h->DX, N, nrhs, st);
         const Backward omn = backward_error(h, B, ldb, X, ldx, nrhs, st);

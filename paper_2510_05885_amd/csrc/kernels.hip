@@ -1169,13 +1169,15 @@ __global__ __launch_bounds__(256, 2) void k_large_dstep(DevPlan d, const LargeTa
 //   Y2  the pivots' y after the forward sweep
 //   X   the pivots' x after the backward sweep
 //   U   the fronts' update vectors (rows below the pivots)
+// B: column q of row i at B[i si + q sq].
 template <typename T, int LD>
-__global__ void k_permute_in(DevPlan d, const double* __restrict__ B, int64_t ldb, int nrhs, T* __restrict__ Y) {
+__global__ void k_permute_in(DevPlan d, const double* __restrict__ B, int64_t si, int64_t sq, int nrhs,
+                             T* __restrict__ Y) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t k = i / LD;
     const int q = (int)(i % LD);
     if (k >= d.N) return;
-    Y[i] = q < nrhs ? (T)B[d.perm[k] + q * ldb] : T(0);
+    Y[i] = q < nrhs ? (T)B[d.perm[k] * si + q * sq] : T(0);
 }
 
 template <typename T, int LD>
@@ -1365,13 +1367,13 @@ __device__ __forceinline__ void fwd_front1(const SmallTask* tk, const T* __restr
 }
 
 // np panel tasks, one workgroup each, then ns small fronts, four a workgroup.
-template <typename T>
-__global__ __launch_bounds__(256, 2) void k_fwd1(const PanelTask* __restrict__ pt, int np,
+template <typename T, bool kPanels>
+__global__ __launch_bounds__(256, kPanels ? 2 : 4) void k_fwd1(const PanelTask* __restrict__ pt, int np,
                                                  const SmallTask* __restrict__ st, int ns, const int* __restrict__ gat,
                                                  const T* __restrict__ F, const T* __restrict__ Zbuf,
                                                  T* __restrict__ Y, T* __restrict__ Y2, T* __restrict__ U) {
     const int b = blockIdx.x;
-    if (b < np) {
+    if (kPanels && b < np) {
         fwd_panels1<T>(pt + b, F, Zbuf, gat, Y, Y2, U);
     } else {
         const int t = 4 * (b - np) + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -1553,14 +1555,14 @@ __device__ __forceinline__ void bwd_front1(const SmallTask* tk, const int* __res
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256, 2) void k_bwd1(const PanelTask* __restrict__ pt, int np,
+template <typename T, bool kPanels>
+__global__ __launch_bounds__(256, kPanels ? 2 : 4) void k_bwd1(const PanelTask* __restrict__ pt, int np,
                                                  const SmallTask* __restrict__ st, int ns, const int* __restrict__ rows,
                                                  const T* __restrict__ F, const T* __restrict__ Zbuf,
                                                  const T* __restrict__ D, const T* __restrict__ Y2, T* __restrict__ X,
                                                  T* __restrict__ pw, const T* __restrict__ pr) {
     const int b = blockIdx.x;
-    if (b < np) {
+    if (kPanels && b < np) {
         bwd_panels1<T>(pt + b, rows, F, Zbuf, D, Y2, X, pw, pr);
     } else {
         __shared__ T xs[4][kSmallMax];
@@ -1643,8 +1645,11 @@ __device__ __forceinline__ void fwd_panels16(const PanelTask* tk, const T* __res
         }
         if (gk > 0) gather16<T>(a, U, gat, f, gk, i0, r1, lr, lk);
     }
-    // L of the wave's rows, in flight over the first products
-    T l1[4][4];
+    // every operand before the first product: Z1, Z2 and P for the wave's 16 rows
+    // of y, L for its rows (zero blocks past the diagonal are multiplied too:
+    // a loop up to it would wait for its loads block by block)
+    const bool two = w2 > 0;   // uniform
+    T z1[4][4], z2[4][4], pm[4][4], l1[4][4], l2[4][4];
     const T* __restrict__ Lr = L + min(i0 + lr, f - 1);
     const bool rv = i0 + lr < r1;
 #pragma unroll
@@ -1652,43 +1657,45 @@ __device__ __forceinline__ void fwd_panels16(const PanelTask* tk, const T* __res
 #pragma unroll
         for (int st = 0; st < 4; ++st) {
             const int k = 16 * kk + Mfma<T>::row(lk, st);
+            z1[kk][st] = k <= 16 * wave + lr ? G1[k * kPanel + 16 * wave + lr] : T(0);
             l1[kk][st] = rv && k < w1 ? -Lr[(int64_t)(c0 + k) * f] : T(0);
         }
-    __syncthreads();
+    if (two)
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        if (h == 1 && w2 == 0) break;   // uniform
-        const T* __restrict__ G = G1 + h * kPanel * kPanel;
-        acc_t s = {0, 0, 0, 0};
-#pragma unroll 1
-        for (int kk = 0; kk <= wave; ++kk) {
-            T z[4];
+        for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
             for (int st = 0; st < 4; ++st) {
                 const int k = 16 * kk + Mfma<T>::row(lk, st);
-                const T x = G[k * kPanel + 16 * wave + lr];
-                z[st] = k <= 16 * wave + lr ? x : T(0);
+                z2[kk][st] = k <= 16 * wave + lr ? G1[(kPanel + k) * kPanel + 16 * wave + lr] : T(0);
+                pm[kk][st] = Pm[k * kPanel + 16 * wave + lr];
+                l2[kk][st] = rv && k < w2 ? -Lr[(int64_t)(c0 + kPanel + k) * f] : T(0);
             }
-            const acc_t bb = rows16<T>(b + (64 * h + 16 * kk) * kNrhsMax, lr, lk);
-#pragma unroll
-            for (int st = 0; st < 4; ++st) s = Mfma<T>::run(z[st], bb[st], s);
-        }
-        if (h == 1)
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                T z[4];
-#pragma unroll
-                for (int st = 0; st < 4; ++st) z[st] = Pm[(16 * kk + Mfma<T>::row(lk, st)) * kPanel + 16 * wave + lr];
-                const acc_t bb = rows16<T>(b + 16 * kk * kNrhsMax, lr, lk);
-#pragma unroll
-                for (int st = 0; st < 4; ++st) s = Mfma<T>::run(z[st], bb[st], s);
-            }
+    __syncthreads();
+    auto store_y = [&](const acc_t& s, int h) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int i = 64 * h + 16 * wave + Mfma<T>::row(lk, r);
             y[i * kNrhsMax + lr] = s[r];
             if (tk->index == 0 && i < w) Y2[(int64_t)(first + c0 + i) * kNrhsMax + lr] = s[r];
         }
+    };
+    {
+        acc_t s1 = {0, 0, 0, 0}, s2 = {0, 0, 0, 0};
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+            const acc_t bb = rows16<T>(b + 16 * kk * kNrhsMax, lr, lk);
+#pragma unroll
+            for (int st = 0; st < 4; ++st) s1 = Mfma<T>::run(z1[kk][st], bb[st], s1);
+            if (two) {
+                const acc_t b2 = rows16<T>(b + (64 + 16 * kk) * kNrhsMax, lr, lk);
+#pragma unroll
+                for (int st = 0; st < 4; ++st) s2 = Mfma<T>::run(pm[kk][st], bb[st], s2);
+#pragma unroll
+                for (int st = 0; st < 4; ++st) s2 = Mfma<T>::run(z2[kk][st], b2[st], s2);
+            }
+        }
+        store_y(s1, 0);
+        if (two) store_y(s2, 1);
     }
     __syncthreads();
     if (!act) return;
@@ -1697,19 +1704,10 @@ __device__ __forceinline__ void fwd_panels16(const PanelTask* tk, const T* __res
         const acc_t yy = rows16<T>(y + 16 * kk * kNrhsMax, lr, lk);
 #pragma unroll
         for (int st = 0; st < 4; ++st) a = Mfma<T>::run(l1[kk][st], yy[st], a);
-    }
-    if (w2 > 0) {
+        if (two) {
+            const acc_t y2 = rows16<T>(y + (64 + 16 * kk) * kNrhsMax, lr, lk);
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            T l2[4];
-#pragma unroll
-            for (int st = 0; st < 4; ++st) {
-                const int k = 16 * kk + Mfma<T>::row(lk, st);
-                l2[st] = rv && k < w2 ? -Lr[(int64_t)(c0 + kPanel + k) * f] : T(0);
-            }
-            const acc_t yy = rows16<T>(y + (64 + 16 * kk) * kNrhsMax, lr, lk);
-#pragma unroll
-            for (int st = 0; st < 4; ++st) a = Mfma<T>::run(l2[st], yy[st], a);
+            for (int st = 0; st < 4; ++st) a = Mfma<T>::run(l2[kk][st], y2[st], a);
         }
     }
 #pragma unroll
@@ -1786,14 +1784,14 @@ __device__ __forceinline__ void fwd_front16(const SmallTask* tk, const T* __rest
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256, 2) void k_fwd16(const PanelTask* __restrict__ pt, int np,
+template <typename T, bool kPanels>
+__global__ __launch_bounds__(256, kPanels ? 2 : 3) void k_fwd16(const PanelTask* __restrict__ pt, int np,
                                                   const SmallTask* __restrict__ st, int ns,
                                                   const int* __restrict__ gat, const T* __restrict__ F,
                                                   const T* __restrict__ Zbuf, T* __restrict__ Y, T* __restrict__ Y2,
                                                   T* __restrict__ U) {
     const int b = blockIdx.x;
-    if (b < np) {
+    if (kPanels && b < np) {
         fwd_panels16<T>(pt + b, F, Zbuf, gat, Y, Y2, U);
     } else {
         const int t = 4 * (b - np) + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -1805,48 +1803,37 @@ __global__ __launch_bounds__(256, 2) void k_fwd16(const PanelTask* __restrict__ 
     }
 }
 
-// x pieces of a pair from v (128 x 16 in LDS): wave w forms rows 16 w .. of
-// x1 = Z1^T v1 + P^T v2 and of x2 = Z2^T v2.
+// Rows 16 w .. of one panel's x from v (128 x 16 in LDS), by wave w: x1 = Z1^T
+// v1 + P^T v2, or x2 = Z2^T v2.  The operands come loaded.
 template <typename T>
-__device__ __forceinline__ void pair_x16(const T* __restrict__ G1, const T* __restrict__ PT, const T* v, bool do1,
-                                         bool do2, int xw1, int xw2, T* __restrict__ Xp, T* xs, int xoff, int wave,
-                                         int lr, int lk) {
+struct PairOps16 {
     typedef typename Mfma<T>::acc_t acc_t;
-    for (int h = 0; h < 2; ++h) {
-        if (!(h ? do2 && xw2 > 0 : do1)) continue;   // uniform
-        const T* __restrict__ G = G1 + h * kPanel * kPanel;
-        acc_t s = {0, 0, 0, 0};
-#pragma unroll 1
-        for (int kk = wave; kk < 4; ++kk) {
-            T z[4];
+    T z[4][4], pt[4][4];
+    __device__ __forceinline__ void load(const T* __restrict__ G, const T* __restrict__ PT, bool with_p, int wave,
+                                         int lr, int lk) {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
             for (int st = 0; st < 4; ++st) {
-                const int u = 16 * kk + Mfma<T>::row(lk, st);
-                const T x = G[u * kPanel + 16 * wave + lr];   // (Z^T)[t][u] above the diagonal
-                z[st] = u >= 16 * wave + lr ? x : T(0);
+                const int u = 16 * kk + Mfma<T>::row(lk, st), t = 16 * wave + lr;
+                z[kk][st] = u >= t ? G[u * kPanel + t] : T(0);   // (Z^T)[t][u] above the diagonal
+                pt[kk][st] = with_p ? PT[u * kPanel + t] : T(0);
             }
-            const acc_t vv = rows16<T>(v + (64 * h + 16 * kk) * kNrhsMax, lr, lk);
-#pragma unroll
-            for (int st = 0; st < 4; ++st) s = Mfma<T>::run(z[st], vv[st], s);
-        }
-        if (h == 0 && xw2 > 0)
-            for (int kk = 0; kk < 4; ++kk) {
-                T z[4];
-#pragma unroll
-                for (int st = 0; st < 4; ++st) z[st] = PT[(16 * kk + Mfma<T>::row(lk, st)) * kPanel + 16 * wave + lr];
-                const acc_t vv = rows16<T>(v + (64 + 16 * kk) * kNrhsMax, lr, lk);
-#pragma unroll
-                for (int st = 0; st < 4; ++st) s = Mfma<T>::run(z[st], vv[st], s);
-            }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int i = 16 * wave + Mfma<T>::row(lk, r);
-            if (i >= (h ? xw2 : xw1)) continue;
-            Xp[(int64_t)(64 * h + i) * kNrhsMax + lr] = s[r];
-            if (xs) xs[(xoff + 64 * h + i) * kNrhsMax + lr] = s[r];
-        }
     }
-}
+    __device__ __forceinline__ acc_t apply(const T* v, int half, int lr, int lk) const {
+        acc_t s = {0, 0, 0, 0};
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+            const acc_t a = rows16<T>(v + (64 * half + 16 * kk) * kNrhsMax, lr, lk);
+            const acc_t b = rows16<T>(v + (64 + 16 * kk) * kNrhsMax, lr, lk);
+#pragma unroll
+            for (int st = 0; st < 4; ++st) s = Mfma<T>::run(z[kk][st], a[st], s);
+#pragma unroll
+            for (int st = 0; st < 4; ++st) s = Mfma<T>::run(pt[kk][st], b[st], s);
+        }
+        return s;
+    }
+};
 
 template <typename T>
 __device__ __forceinline__ void bwd_panels16(const PanelTask* tk, const int* __restrict__ rows, const T* __restrict__ F,
@@ -1864,6 +1851,25 @@ __device__ __forceinline__ void bwd_panels16(const PanelTask* tk, const int* __r
     const T* __restrict__ A = F + tk->L_off;
     const T* __restrict__ G1 = Zbuf + tk->M_off + (int64_t)(xc0 / kPanel) * (kPanel * kPanel);
     const T* __restrict__ PT = Zbuf + (fin ? tk->fP_off : tk->P_off) + kPanel * kPanel;
+    const int which = fin ? tk->which : 0;   // the panel it finishes first
+    const bool two = tk->w2 > 0;             // uniform
+    PairOps16<T> ops;
+    if (fin || self) ops.load(G1 + which * kPanel * kPanel, PT, which == 0 && xw2 > 0, wave, lr, lk);
+    // L^T operands: wave w takes columns 16 w and 64 + 16 w
+    T l1[4][4], l2[4][4];
+    if (own) {
+        const int cl = 16 * wave + lr;
+        const T* __restrict__ src = A + c0;
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+            for (int st = 0; st < 4; ++st) {
+                const int i = 16 * kk + Mfma<T>::row(lk, st);
+                const T* __restrict__ row = src + (int64_t)min(r0 + i, f - 1) * f;
+                l1[kk][st] = i < nr && cl < w ? row[cl] : T(0);
+                if (two) l2[kk][st] = i < nr && 64 + cl < w ? row[64 + cl] : T(0);
+            }
+    }
     if (own) {
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
@@ -1878,9 +1884,18 @@ __device__ __forceinline__ void bwd_panels16(const PanelTask* tk, const int* __r
 #pragma unroll
         for (int k = 0; k < 8; ++k) a[k] = T(0);
         const T* __restrict__ src = pr + (int64_t)tk->fslot0 * (128 * kNrhsMax) + tid;
-        for (int g = 0; g < tk->fntask; ++g)
+        for (int g0 = 0; g0 < tk->fntask; g0 += 4) {
+            T u[4][8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) a[k] += src[(int64_t)g * (128 * kNrhsMax) + 256 * k];
+            for (int g = 0; g < 4; ++g)
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    u[g][k] = g0 + g < tk->fntask ? src[(int64_t)(g0 + g) * (128 * kNrhsMax) + 256 * k] : T(0);
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+#pragma unroll
+                for (int k = 0; k < 8; ++k) a[k] += u[g][k];
+        }
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             const int e = tid + 256 * k, i = e >> 4;
@@ -1888,30 +1903,27 @@ __device__ __forceinline__ void bwd_panels16(const PanelTask* tk, const int* __r
                        ? Y2[(int64_t)(first + xc0) * kNrhsMax + e] * (T(1) / D[first + xc0 + i]) - a[k] : T(0);
         }
         __syncthreads();
-        pair_x16<T>(G1, PT, v, tk->which == 0, tk->which == 1, xw1, xw2, X + (int64_t)(first + xc0) * kNrhsMax,
-                    own ? xs : nullptr, xc0 - r0, wave, lr, lk);
+        const acc_t s = ops.apply(v, which, lr, lk);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 16 * wave + Mfma<T>::row(lk, r);
+            if (i >= (which ? xw2 : xw1)) continue;
+            X[(int64_t)(first + xc0 + 64 * which + i) * kNrhsMax + lr] = s[r];
+            if (own) xs[(xc0 + 64 * which + i - r0) * kNrhsMax + lr] = s[r];
+        }
     }
     if (!own) return;   // the whole workgroup
     __syncthreads();
-    // the sums: wave w takes columns 16 w and 64 + 16 w
+    // the sums
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        if (h == 1 && tk->w2 == 0) break;   // uniform
-        const int cl = 64 * h + 16 * wave + lr;
-        const T* __restrict__ src = A + c0 + min(cl, w - 1);
+        if (h == 1 && !two) break;   // uniform
         acc_t s = {0, 0, 0, 0};
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
-            T l[4];
-#pragma unroll
-            for (int st = 0; st < 4; ++st) {
-                const int i = 16 * kk + Mfma<T>::row(lk, st);
-                const T x = src[(int64_t)min(r0 + i, f - 1) * f];
-                l[st] = i < nr && cl < w ? x : T(0);
-            }
             const acc_t xx = rows16<T>(xs + 16 * kk * kNrhsMax, lr, lk);
 #pragma unroll
-            for (int st = 0; st < 4; ++st) s = Mfma<T>::run(l[st], xx[st], s);
+            for (int st = 0; st < 4; ++st) s = Mfma<T>::run(h ? l2[kk][st] : l1[kk][st], xx[st], s);
         }
         if (!self) {
 #pragma unroll
@@ -1928,8 +1940,19 @@ __device__ __forceinline__ void bwd_panels16(const PanelTask* tk, const int* __r
         }
     }
     if (!self) return;
+    if (!two)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[(64 + 16 * wave + Mfma<T>::row(lk, r)) * kNrhsMax + lr] = T(0);
     __syncthreads();
-    pair_x16<T>(G1, PT, v, true, true, xw1, xw2, X + (int64_t)(first + c0) * kNrhsMax, nullptr, 0, wave, lr, lk);
+    for (int h = 0; h < (two ? 2 : 1); ++h) {
+        if (h == 1) ops.load(G1 + kPanel * kPanel, PT, false, wave, lr, lk);
+        const acc_t s = ops.apply(v, h, lr, lk);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 64 * h + 16 * wave + Mfma<T>::row(lk, r);
+            if (i < w) X[(int64_t)(first + c0 + i) * kNrhsMax + lr] = s[r];
+        }
+    }
 }
 
 template <typename T, int NT>
@@ -1995,15 +2018,15 @@ __device__ __forceinline__ void bwd_front16(const SmallTask* tk, const int* __re
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256, 2) void k_bwd16(const PanelTask* __restrict__ pt, int np,
+template <typename T, bool kPanels>
+__global__ __launch_bounds__(256, kPanels ? 2 : 3) void k_bwd16(const PanelTask* __restrict__ pt, int np,
                                                   const SmallTask* __restrict__ st, int ns,
                                                   const int* __restrict__ rows, const T* __restrict__ F,
                                                   const T* __restrict__ Zbuf, const T* __restrict__ D,
                                                   const T* __restrict__ Y2, T* __restrict__ X, T* __restrict__ pw,
                                                   const T* __restrict__ pr) {
     const int b = blockIdx.x;
-    if (b < np) {
+    if (kPanels && b < np) {
         bwd_panels16<T>(pt + b, rows, F, Zbuf, D, Y2, X, pw, pr);
     } else {
         const int t = 4 * (b - np) + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -2081,77 +2104,139 @@ __device__ __forceinline__ double two_sum(double a, double b, double& err) {
     return s;
 }
 
-// Block per chunk of rows (one system); eight lanes share a row.  R = B - K X
-// and, per column, the chunk's kResWidth figures: max |r_i|, max |x_i|,
-// max |b_i|, sum r_i^2, sum b_i^2, and max_i |r_i| / (|K| |x| + |b|)_i (the
-// componentwise backward error; 0/0 counts as 0, r/0 as infinite).  Each row
-// sum is compensated (products split with fma, sums with two-sum: the Dot2
-// scheme of Ogita, Rump and Oishi, 2005), so r_i is accurate to about one
-// rounding of itself rather than of |K||x|_i.
+// One row of R = B - K X and its part of the chunk's figures.  Each row sum is
+// compensated (products split with fma, sums with two-sum: the Dot2 scheme of
+// Ogita, Rump and Oishi, 2005), so r_i is accurate to about one rounding of
+// itself rather than of |K||x|_i: the residual's own rounding stays near one
+// unit of |b - Kx|, and refinement is not held at the rounding floor of a
+// plain FP64 row sum.
+struct RowSum {
+    double acc = 0.0, cmp = 0.0, aacc = 0.0;
+    __device__ __forceinline__ void add(double k, double x) {
+        const double pr = k * x;
+        const double pe = fma(k, x, -pr);
+        double t;
+        acc = two_sum(acc, pr, t);
+        cmp += t + pe;
+        aacc += fabs(k) * fabs(x);
+    }
+    // r_i; v: max |r_i|, max |x_i|, max |b_i|, sum r_i^2, sum b_i^2 and max_i
+    // |r_i| / (|K| |x| + |b|)_i (the componentwise backward error; 0/0 counts
+    // as 0, r/0 as infinite)
+    __device__ __forceinline__ double finish(double b, double x, double (&v)[kResWidth]) const {
+        double t;
+        const double hi = two_sum(b, -acc, t);
+        const double rr = hi + (t - cmp);
+        const bool nan = rr != rr;
+        const double den = aacc + fabs(b);
+        const double cw = nan ? INFINITY : (den > 0.0 ? fabs(rr) / den : (rr != 0.0 ? INFINITY : 0.0));
+        v[0] = nan ? INFINITY : fmax(v[0], fabs(rr));   // NaN residual -> infinite
+        v[1] = fmax(v[1], fabs(x));
+        v[2] = fmax(v[2], fabs(b));
+        v[3] += nan ? INFINITY : rr * rr;
+        v[4] += b * b;
+        v[5] = fmax(v[5], cw);
+        return rr;
+    }
+};
 
+__device__ __forceinline__ double res_join(int k, double a, double b) { return k == 3 || k == 4 ? a + b : fmax(a, b); }
+
+// One right-hand side: block per chunk of rows (one system); eight lanes share a row.
 __global__ __launch_bounds__(256) void k_residual(DevPlan d, const double* __restrict__ K,
-                                                  const double* __restrict__ B, int64_t ldb,
-                                                  const double* __restrict__ X, int64_t ldx, double* __restrict__ R,
-                                                  int nrhs, const int* __restrict__ chunk_row0,
+                                                  const double* __restrict__ B, const double* __restrict__ x,
+                                                  double* __restrict__ R, const int* __restrict__ chunk_row0,
                                                   const int* __restrict__ chunk_rows, double* partial) {
     const int c = blockIdx.x;
     const int tid = threadIdx.x, sub = tid & 7, grp = tid >> 3;
     __shared__ double sm[kResWidth][256];
-    for (int q = 0; q < nrhs; ++q) {
-        const double* __restrict__ x = X + q * ldx;
-        double v[kResWidth] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-        for (int r = grp; r < chunk_rows[c]; r += 32) {
-            const int row = chunk_row0[c] + r;
-            // compensated dot product (sum s + c carries about twice the
-            // working precision): the residual's own rounding stays near one
-            // unit of |b - Kx|, so refinement is not held at the rounding
-            // floor of a plain FP64 row sum
-            double acc = 0.0, cmp = 0.0, aacc = 0.0;
-            for (int64_t e = d.Kp[row] + sub; e < d.Kp[row + 1]; e += 8) {
-                const double k = K[e], xv = x[d.Kj[e]];
-                const double pr = k * xv;
-                const double pe = fma(k, xv, -pr);
-                double t;
-                acc = two_sum(acc, pr, t);
-                cmp += t + pe;
-                aacc += fabs(k) * fabs(xv);
-            }
-            for (int o = 4; o > 0; o >>= 1) {
-                double t;
-                acc = two_sum(acc, __shfl_xor(acc, o, 8), t);
-                cmp += __shfl_xor(cmp, o, 8) + t;
-                aacc += __shfl_xor(aacc, o, 8);
-            }
-            if (sub == 0) {
-                const double b = B[row + q * ldb];
-                double t;
-                const double hi = two_sum(b, -acc, t);
-                const double rr = hi + (t - cmp);
-                R[row + q * d.N] = rr;
-                const bool nan = rr != rr;
-                const double den = aacc + fabs(b);
-                const double cw = nan ? INFINITY : (den > 0.0 ? fabs(rr) / den : (rr != 0.0 ? INFINITY : 0.0));
-                v[0] = nan ? INFINITY : fmax(v[0], fabs(rr));   // NaN residual -> infinite
-                v[1] = fmax(v[1], fabs(x[row]));
-                v[2] = fmax(v[2], fabs(b));
-                v[3] += nan ? INFINITY : rr * rr;
-                v[4] += b * b;
-                v[5] = fmax(v[5], cw);
-            }
+    double v[kResWidth] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int r = grp; r < chunk_rows[c]; r += 32) {
+        const int row = chunk_row0[c] + r;
+        RowSum s;
+        for (int64_t e = d.Kp[row] + sub; e < d.Kp[row + 1]; e += 8) s.add(K[e], x[d.Kj[e]]);
+        for (int o = 4; o > 0; o >>= 1) {
+            double t;
+            s.acc = two_sum(s.acc, __shfl_xor(s.acc, o, 8), t);
+            s.cmp += __shfl_xor(s.cmp, o, 8) + t;
+            s.aacc += __shfl_xor(s.aacc, o, 8);
         }
+        if (sub == 0) R[row] = s.finish(B[row], x[row], v);
+    }
 #pragma unroll
-        for (int k = 0; k < kResWidth; ++k) sm[k][tid] = v[k];
-        __syncthreads();
-        for (int o = 128; o > 0; o >>= 1) {
-            if (tid < o) {
+    for (int k = 0; k < kResWidth; ++k) sm[k][tid] = v[k];
+    __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+        if (tid < o) {
 #pragma unroll
-                for (int k = 0; k < kResWidth; ++k)
-                    sm[k][tid] = (k == 3 || k == 4) ? sm[k][tid] + sm[k][tid + o] : fmax(sm[k][tid], sm[k][tid + o]);
-            }
-            __syncthreads();
+            for (int k = 0; k < kResWidth; ++k) sm[k][tid] = res_join(k, sm[k][tid], sm[k][tid + o]);
         }
-        if (tid < kResWidth) partial[((int64_t)c * nrhs + q) * kResWidth + tid] = sm[tid][0];
         __syncthreads();
+    }
+    if (tid < kResWidth) partial[(int64_t)c * kResWidth + tid] = sm[tid][0];
+}
+
+// Several right-hand sides: 16 lanes share a row, one column each, so K is read
+// once for all of them and x (row-major, kNrhsMax a row) 16 columns at a time;
+// R is row-major too.  Column by column, K was read again for each: 537 us for
+// 16 columns at order 100k.
+__global__ __launch_bounds__(256) void k_residual16(DevPlan d, const double* __restrict__ K,
+                                                    const double* __restrict__ B, int64_t ldb,
+                                                    const double* __restrict__ Xr, double* __restrict__ R, int nrhs,
+                                                    const int* __restrict__ chunk_row0,
+                                                    const int* __restrict__ chunk_rows, double* partial) {
+    static_assert(kNrhsMax == 16, "one lane per column");
+    const int c = blockIdx.x;
+    const int tid = threadIdx.x, q = tid & 15, grp = tid >> 4;
+    __shared__ double sm[kResWidth][256];
+    double v[kResWidth] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int r = grp; r < chunk_rows[c]; r += 16) {
+        const int row = chunk_row0[c] + r;
+        RowSum s;
+        const int64_t e1 = d.Kp[row + 1];
+        for (int64_t e0 = d.Kp[row]; e0 < e1; e0 += 8) {
+            double k[8], x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int64_t e = min(e0 + u, e1 - 1);
+                k[u] = K[e];
+                x[u] = Xr[(int64_t)d.Kj[e] * kNrhsMax + q];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (e0 + u < e1) s.add(k[u], x[u]);
+        }
+        if (q < nrhs)
+            R[(int64_t)row * kNrhsMax + q] = s.finish(B[row + q * ldb], Xr[(int64_t)row * kNrhsMax + q], v);
+    }
+#pragma unroll
+    for (int k = 0; k < kResWidth; ++k) sm[k][tid] = v[k];
+    __syncthreads();
+    for (int o = 128; o >= 16; o >>= 1) {
+        if (tid < o) {
+#pragma unroll
+            for (int k = 0; k < kResWidth; ++k) sm[k][tid] = res_join(k, sm[k][tid], sm[k][tid + o]);
+        }
+        __syncthreads();
+    }
+    if (tid < nrhs)
+#pragma unroll
+        for (int k = 0; k < kResWidth; ++k) partial[((int64_t)c * nrhs + tid) * kResWidth + k] = sm[k][tid];
+}
+
+// Xr[row][q] = X[row + q ldx], zero for q >= nrhs: 64 rows a block, through LDS.
+__global__ __launch_bounds__(256) void k_to_rows(int64_t N, const double* __restrict__ X, int64_t ldx, int nrhs,
+                                                 double* __restrict__ Xr) {
+    __shared__ double t[kNrhsMax][65];
+    const int64_t r0 = (int64_t)blockIdx.x * 64;
+    for (int i = threadIdx.x; i < 64 * kNrhsMax; i += 256) {
+        const int r = i & 63, q = i >> 6;
+        t[q][r] = q < nrhs && r0 + r < N ? X[r0 + r + q * ldx] : 0.0;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < 64 * kNrhsMax; i += 256) {
+        const int q = i & (kNrhsMax - 1), r = i / kNrhsMax;
+        if (r0 + r < N) Xr[(r0 + r) * kNrhsMax + q] = t[q][r];
     }
 }
 
@@ -2528,11 +2613,12 @@ void launch_pair_inverse(const PairTask* tasks, int count, const T* F, T* M, hip
 }
 
 template <typename T>
-void launch_permute_in(const DevPlan& d, const double* B, int64_t ldb, int nrhs, T* Y, hipStream_t st) {
+void launch_permute_in(const DevPlan& d, const double* B, int64_t si, int64_t sq, int nrhs, T* Y, hipStream_t st) {
     if (nrhs == 1)
-        launch(k_permute_in<T, 1>, dim3(blocks_for(d.N, 256)), dim3(256), 0, st, d, B, ldb, nrhs, Y);
+        launch(k_permute_in<T, 1>, dim3(blocks_for(d.N, 256)), dim3(256), 0, st, d, B, si, sq, nrhs, Y);
     else
-        launch(k_permute_in<T, kNrhsMax>, dim3(blocks_for(d.N * kNrhsMax, 256)), dim3(256), 0, st, d, B, ldb, nrhs, Y);
+        launch(k_permute_in<T, kNrhsMax>, dim3(blocks_for(d.N * kNrhsMax, 256)), dim3(256), 0, st, d, B, si, sq, nrhs,
+               Y);
 }
 
 template <typename T>
@@ -2544,29 +2630,46 @@ void launch_permute_out(const DevPlan& d, const T* X, int nrhs, double* Xo, int6
                ldx);
 }
 
+// A step with panel tasks and more small fronts than this takes two launches: the
+// small fronts' own kernel keeps twice as many waves in flight, and they are then
+// bound by that rather than by the launch.
+constexpr int kSplitSmall = 1024;
+
 template <typename T>
 void launch_fwd(bool many, const PanelTask* pt, int np, const SmallTask* sm, int ns, const int* gat, const T* F,
                 const T* Z, T* Y, T* Y2, T* U, hipStream_t st) {
+    if (np > 0 && ns > kSplitSmall) {
+        launch_fwd<T>(many, pt, 0, sm, ns, gat, F, Z, Y, Y2, U, st);
+        ns = 0;
+    }
     const int grid = np + (ns + 3) / 4;
     if (grid <= 0) return;
-    if (many) launch(k_fwd16<T>, dim3(grid), dim3(256), 0, st, pt, np, sm, ns, gat, F, Z, Y, Y2, U);
-    else launch(k_fwd1<T>, dim3(grid), dim3(256), 0, st, pt, np, sm, ns, gat, F, Z, Y, Y2, U);
+    auto k = np > 0 ? (many ? k_fwd16<T, true> : k_fwd1<T, true>) : (many ? k_fwd16<T, false> : k_fwd1<T, false>);
+    launch(k, dim3(grid), dim3(256), 0, st, pt, np, sm, ns, gat, F, Z, Y, Y2, U);
 }
 
 template <typename T>
 void launch_bwd(bool many, const PanelTask* pt, int np, const SmallTask* sm, int ns, const int* rows, const T* F,
                 const T* Z, const T* D, const T* Y2, T* X, T* pw, const T* pr, hipStream_t st) {
+    if (np > 0 && ns > kSplitSmall) {
+        launch_bwd<T>(many, pt, 0, sm, ns, rows, F, Z, D, Y2, X, pw, pr, st);
+        ns = 0;
+    }
     const int grid = np + (ns + 3) / 4;
     if (grid <= 0) return;
-    if (many) launch(k_bwd16<T>, dim3(grid), dim3(256), 0, st, pt, np, sm, ns, rows, F, Z, D, Y2, X, pw, pr);
-    else launch(k_bwd1<T>, dim3(grid), dim3(256), 0, st, pt, np, sm, ns, rows, F, Z, D, Y2, X, pw, pr);
+    auto k = np > 0 ? (many ? k_bwd16<T, true> : k_bwd1<T, true>) : (many ? k_bwd16<T, false> : k_bwd1<T, false>);
+    launch(k, dim3(grid), dim3(256), 0, st, pt, np, sm, ns, rows, F, Z, D, Y2, X, pw, pr);
 }
 
 void launch_residual(const DevPlan& d, const double* K, const double* B, int64_t ldb, const double* X, int64_t ldx,
-                     double* R, int nrhs, const int* chunk_row0, const int* chunk_rows, int nchunks, double* partial,
-                     hipStream_t st) {
-    launch(k_residual, dim3(nchunks), dim3(256), 0, st, d, K, B, ldb, X, ldx, R, nrhs, chunk_row0,
-                       chunk_rows, partial);
+                     double* Xr, double* R, int nrhs, const int* chunk_row0, const int* chunk_rows, int nchunks,
+                     double* partial, hipStream_t st) {
+    if (nrhs == 1) {
+        launch(k_residual, dim3(nchunks), dim3(256), 0, st, d, K, B, X, R, chunk_row0, chunk_rows, partial);
+        return;
+    }
+    launch(k_to_rows, dim3(blocks_for(d.N, 64)), dim3(256), 0, st, d.N, X, ldx, nrhs, Xr);
+    launch(k_residual16, dim3(nchunks), dim3(256), 0, st, d, K, B, ldb, Xr, R, nrhs, chunk_row0, chunk_rows, partial);
 }
 
 void launch_axpy_cols(double* X, int64_t ldx, const double* DX, int64_t N, int nrhs, hipStream_t st) {
@@ -2635,7 +2738,7 @@ hipError_t configure_kernels(int max_dynamic_lds) {
     template void launch_large_dstep<T>(const DevPlan&, const LargeTask*, int, const LargeTask*, int, T*, T*, T*,  \
                                         hipStream_t);                                                              \
     template void launch_pair_inverse<T>(const PairTask*, int, const T*, T*, hipStream_t);                         \
-    template void launch_permute_in<T>(const DevPlan&, const double*, int64_t, int, T*, hipStream_t);              \
+    template void launch_permute_in<T>(const DevPlan&, const double*, int64_t, int64_t, int, T*, hipStream_t);     \
     template void launch_permute_out<T>(const DevPlan&, const T*, int, double*, int64_t, hipStream_t);             \
     template void launch_fwd<T>(bool, const PanelTask*, int, const SmallTask*, int, const int*, const T*,          \
                                 const T*, T*, T*, T*, hipStream_t);                                                \

@@ -185,8 +185,9 @@ void launch_pair_inverse(const PairTask* tasks, int count, const T* F, T* M, hip
 // ---- solves -----------------------------------------------------------------
 // Vectors in pivot order with one value a row, or with kNrhsMax ("many", nrhs > 1;
 // unused columns zero).
+// B: column q of row i (caller's order) at B[i si + q sq].
 template <typename T>
-void launch_permute_in(const DevPlan& d, const double* B, int64_t ldb, int nrhs, T* Y, hipStream_t st);
+void launch_permute_in(const DevPlan& d, const double* B, int64_t si, int64_t sq, int nrhs, T* Y, hipStream_t st);
 template <typename T>
 void launch_permute_out(const DevPlan& d, const T* X, int nrhs, double* Xo, int64_t ldx, hipStream_t st);
 // One step of a sweep: np panel tasks and ns small fronts.  Y: right-hand side
@@ -203,8 +204,9 @@ void launch_bwd(bool many, const PanelTask* pt, int np, const SmallTask* sm, int
 // ---- refinement -------------------------------------------------------------
 // R = B - K X; per chunk of rows (all of one system) and column, kResWidth figures:
 // max |r|, max |x|, max |b|, sum r^2, sum b^2, max |r_i| / (|K||x| + |b|)_i.
-void launch_residual(const DevPlan& d, const double* K, const double* B, int64_t ldb, const double* X,
-                     int64_t ldx, double* R, int nrhs, const int* chunk_row0, const int* chunk_rows, int nchunks,
+// nrhs > 1: R is row-major, kNrhsMax a row, and Xr (N x kNrhsMax) is scratch.
+void launch_residual(const DevPlan& d, const double* K, const double* B, int64_t ldb, const double* X, int64_t ldx,
+                     double* Xr, double* R, int nrhs, const int* chunk_row0, const int* chunk_rows, int nchunks,
                      double* partial, hipStream_t st);
 void launch_axpy_cols(double* X, int64_t ldx, const double* DX, int64_t N, int nrhs, hipStream_t st);
 void launch_copy_cols(double* dst, int64_t ldd, const double* src, int64_t lds, int64_t N, int nrhs,
