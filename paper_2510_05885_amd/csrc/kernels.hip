@@ -296,34 +296,28 @@ __device__ __forceinline__ void diag_apply(typename Mfma<T>::acc_t& acc, const T
     for (int st = 0; st < 4; ++st) acc = Mfma<T>::run(a[st], b[st], acc);
 }
 
-// Z_qq = L_qq^-1 of a 16 x 16 unit lower block by one wave: lane (g, j) builds
-// column j (the same in each 16-lane row) and holds row j of L_qq, whose
-// entries come from lane i of its row.  Waves that need Z_qq at the same time
-// each do this and write the same values.
+// Z_qq = L_qq^-1 of a 16 x 16 unit lower block by one wave: lane % 16 = row j
+// of Z, the same in each 16-lane row; step t takes L[j][t] times row t away
+// (DPP broadcast).  Waves that need Z_qq at the same time each do this and write the
+// same values.
 template <typename T>
 __device__ __forceinline__ void diag_inv16(T* B, int ld, int q, int lane) {
     const int o = 16 * q, j = lane & 15;
-    T lrow[16], z[16];
+    T z[16];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-        const T x = B[(o + j) + (o + u) * ld];
-        lrow[u] = u < j ? x : T(0);
-        z[u] = (u == j) ? T(1) : T(0);
-    }
+    for (int u = 0; u < 16; ++u) z[u] = (u == j) ? T(1) : T(0);
 #pragma unroll
-    for (int i = 1; i < 16; ++i) {
-        // Tie row i's broadcasts to z[i-1]: otherwise all 120 of them are
-        // issued up front and held in registers.
+    for (int t = 0; t < 15; ++t) {
+        const T x = B[(o + j) + (o + t) * ld];
+        const T l = j > t ? x : T(0);
 #pragma unroll
-        for (int u = 0; u < i; ++u) asm volatile("" : "+v"(lrow[u]) : "v"(z[i - 1]));
-#pragma unroll
-        for (int u = 0; u < i; ++u) z[i] = __builtin_fma(-rowbcast_n(lrow[u], i), z[u], z[i]);
+        for (int u = 0; u <= t; ++u) z[u] = __builtin_fma(-l, rowbcast_n(z[u], t), z[u]);
     }
     wave_fence();
     if (lane < 16) {
 #pragma unroll
-        for (int i = 1; i < 16; ++i)
-            if (i > j) B[(o + j) + (o + i) * ld] = z[i];
+        for (int u = 0; u < 15; ++u)
+            if (j > u) B[(o + u) + (o + j) * ld] = z[u];
     }
     wave_fence();
 }
@@ -1508,8 +1502,10 @@ __device__ __forceinline__ void bwd_panels1(const PanelTask* tk, const int* __re
 }
 
 // A small front by one wave, its 16-column sub-panels from the last: lane =
-// (column, row group g of four), the groups' sums meet by lane exchange, and
-// the sub-panel's x = Z_qq^T v (Z^T is stored above L's diagonal).
+// (column, row group g of four); the groups' sums meet by lane exchange, then
+// the sub-panel's transposed triangle is substituted within each 16-lane row.
+// A sub-panel's operands are loaded before the one after it is finished, the
+// first ones before x is gathered.
 template <typename T>
 __device__ __forceinline__ void bwd_front1(const SmallTask* tk, const int* __restrict__ rows, const T* __restrict__ F,
                                            const T* __restrict__ D, const T* __restrict__ Y2, T* __restrict__ X,
@@ -1517,36 +1513,48 @@ __device__ __forceinline__ void bwd_front1(const SmallTask* tk, const int* __res
     const int first = tk->first, p = tk->p, f = tk->f;
     const T* __restrict__ L = F + tk->L_off;
     const int t = lane & 15, g = lane >> 4;
-    for (int i = p + lane; i < f; i += 64) xs[i] = X[rows[tk->rows_off + i]];
-    wave_fence();
-    for (int kb = (p - 1) & ~15; kb >= 0; kb -= 16) {
+    T l[16], z[16], yd;   // rows base + 4 m + g below the sub-panel; its own triangle; y / d
+    auto load = [&](int kb) {
         const int bw = min(16, p - kb), c = kb + min(t, bw - 1), base = kb + bw;
         const T* __restrict__ Lc = L + (int64_t)c * f;
-        T z[16];
+#pragma unroll
+        for (int m = 0; m < 16; ++m) l[m] = Lc[min(base + 4 * m + g, f - 1)];
 #pragma unroll
         for (int u = 1; u < 16; ++u) {
-            const T x = L[c + (int64_t)(kb + min(u, bw - 1)) * f];
+            const T x = Lc[kb + min(u, bw - 1)];
             z[u] = u > t && u < bw ? x : T(0);
         }
-        const T yd = Y2[first + c] * (T(1) / D[first + c]);
-        // rows base + 4 m + g: four lanes of a column read consecutive rows
+        yd = Y2[first + c] * (T(1) / D[first + c]);
+    };
+    int kb = (p - 1) & ~15;
+    load(kb);
+    for (int i = p + lane; i < f; i += 64) xs[i] = X[rows[tk->rows_off + i]];
+    wave_fence();
+    for (; kb >= 0; kb -= 16) {
+        const int bw = min(16, p - kb), base = kb + bw;
         T acc = T(0);
-        for (int m0 = base; m0 < f; m0 += 64) {
-            T l[16];
 #pragma unroll
-            for (int m = 0; m < 16; ++m) l[m] = Lc[min(m0 + 4 * m + g, f - 1)];
+        for (int m = 0; m < 16; ++m) {
+            const int i = base + 4 * m + g;
+            acc += i < f ? l[m] * xs[min(i, kSmallMax - 1)] : T(0);
+        }
+        if (base + 64 < f) {   // uniform: orders above 64
+            const T* __restrict__ Lc = L + (int64_t)(kb + min(t, bw - 1)) * f;
+            T h[16];
+#pragma unroll
+            for (int m = 0; m < 16; ++m) h[m] = Lc[min(base + 64 + 4 * m + g, f - 1)];
 #pragma unroll
             for (int m = 0; m < 16; ++m) {
-                const int i = m0 + 4 * m + g;
-                acc += i < f ? l[m] * xs[i] : T(0);
+                const int i = base + 64 + 4 * m + g;
+                acc += i < f ? h[m] * xs[min(i, kSmallMax - 1)] : T(0);
             }
         }
         acc += __shfl_xor(acc, 16);
         acc += __shfl_xor(acc, 32);
-        const T v = yd - acc;
-        T x = v;
+        T x = yd - acc;
 #pragma unroll
-        for (int u = 1; u < 16; ++u) x += z[u] * rowbcast_n(v, u);
+        for (int u = 15; u > 0; --u) x -= z[u] * rowbcast_n(x, u);
+        if (kb > 0) load(kb - 16);
         if (lane < bw) {
             xs[kb + lane] = x;
             X[first + kb + lane] = x;
