@@ -111,8 +111,7 @@ void build_system_rows(Plan& P, const SysInput& in, int64_t vo, int64_t wo, int6
         std::sort(cols.begin(), cols.end());
         for (int c : cols) {
             P.Kj.push_back((int)(vo + c));
-            P.src_w.push_back(wsrc[c]);
-            P.src_j.push_back(jsrc[c]);
+            P.src.push_back(wsrc[c] >= 0 ? wsrc[c] : jsrc[c] >= 0 ? -2 - jsrc[c] : -1);   // never both
             P.src_flag.push_back(c == i ? diag_flag : 0);
         }
         P.Kp.push_back((int64_t)P.Kj.size());

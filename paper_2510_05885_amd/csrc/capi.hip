@@ -96,10 +96,11 @@ struct ncl_kkt_s {
     SmallTask* solve_small = nullptr;
     PairTask* pairs = nullptr;
     LargeTask *large_panel = nullptr, *large_upd = nullptr, *large_diag = nullptr;
-    int *chunk_row0 = nullptr, *chunk_rows = nullptr, *sys_chunk_ptr = nullptr;
+    RowChunk* chunks = nullptr;
+    int* sys_chunk_ptr = nullptr;
     int nchunks = 0;
     // numeric state
-    double *K = nullptr, *partial_norm = nullptr, *norms3 = nullptr, *kmax = nullptr, *kinf = nullptr,
+    double *K = nullptr, *partial_norm = nullptr, *kinf = nullptr,
            *thr = nullptr, *rho = nullptr;
     int* nonfinite = nullptr;
     unsigned long long* inertia = nullptr;
@@ -223,16 +224,10 @@ void setup_device(ncl_kkt_s* h) {
     d.n_fronts = P.nsn;
     d.form = P.form;
     h->nnzF = (int64_t)P.Kj.size();
-    std::vector<int> Krow(h->nnzF);
-    for (int64_t i = 0; i < P.N; ++i)
-        for (int64_t q = P.Kp[i]; q < P.Kp[i + 1]; ++q) Krow[q] = (int)i;
     d.Kp = upload(h, P.Kp);
     d.Kj = upload(h, P.Kj);
-    d.Krow = upload(h, Krow);
-    d.src_w = upload(h, P.src_w);
-    d.src_j = upload(h, P.src_j);
+    d.src = upload(h, P.src);
     d.src_flag = upload(h, P.src_flag);
-    d.prod_ptr = upload(h, P.prod_ptr);
     d.prod_a = upload(h, P.prod_a);
     d.prod_b = upload(h, P.prod_b);
     d.row_sys = upload(h, P.row_sys);
@@ -325,26 +320,34 @@ void setup_device(ncl_kkt_s* h) {
     h->pairs = upload(h, P.pairs);
     h->gather = upload(h, P.gather);
     // row chunks (never straddling two systems), one block each: up to 256 rows, in
-    // multiples of the 32 that a block takes at once; smaller while there are fewer
-    // than 2048 of them (eight a CU), where a block's rows one after the other set the time
-    std::vector<int> c0, cn, scp(1, 0);
-    const int64_t rows = std::min<int64_t>(256, std::max<int64_t>(32, (P.N / 2048 + 31) / 32 * 32));
+    // multiples of 8; smaller while there are fewer than 2048 of them (eight a CU),
+    // where a block's entries and rows one after the other set the time: assembly and
+    // residual 13.0 and 6.5 us with 32 rows at order 625, 8.4 and 5.7 with 8
+    std::vector<RowChunk> rc;
+    std::vector<int> scp(1, 0);
+    std::vector<unsigned int> pp(P.Kj.size());
+    const int64_t rows = std::min<int64_t>(256, std::max<int64_t>(8, (P.N / 2048 + 7) / 8 * 8));
     for (int s = 0; s < P.S; ++s) {
-        for (int64_t r = P.sys_voff[s]; r < P.sys_voff[s + 1]; r += rows) {
-            c0.push_back((int)r);
-            cn.push_back((int)std::min<int64_t>(rows, P.sys_voff[s + 1] - r));
+        for (int64_t r = P.sys_voff[s], r1; r < P.sys_voff[s + 1]; r = r1) {
+            // (a chunk's products are counted in 32 bits)
+            r1 = std::min<int64_t>(r + rows, P.sys_voff[s + 1]);
+            while (r1 > r + 1 && P.prod_ptr[P.Kp[r1]] - P.prod_ptr[P.Kp[r]] > (int64_t)UINT32_MAX) --r1;
+            RowChunk k{};
+            k.row0 = (int)r; k.rows = (int)(r1 - r); k.sys = s;
+            k.ent0 = P.Kp[r]; k.ent1 = P.Kp[r1]; k.prod0 = P.prod_ptr[k.ent0];
+            k.nprod = (unsigned int)(P.prod_ptr[k.ent1] - k.prod0);
+            for (int64_t e = k.ent0; e < k.ent1; ++e) pp[e] = (unsigned int)(P.prod_ptr[e] - k.prod0);
+            rc.push_back(k);
         }
-        scp.push_back((int)c0.size());
+        scp.push_back((int)rc.size());
     }
-    h->nchunks = (int)c0.size();
-    h->chunk_row0 = upload(h, c0);
-    h->chunk_rows = upload(h, cn);
+    h->nchunks = (int)rc.size();
+    h->chunks = upload(h, rc);
+    d.prod_ptr = upload(h, pp);
     h->sys_chunk_ptr = upload(h, scp);
     // numeric buffers
     h->K = dalloc<double>(h, h->nnzF);
     h->partial_norm = dalloc<double>(h, 3 * (int64_t)h->nchunks);
-    h->norms3 = dalloc<double>(h, 3 * P.S);
-    h->kmax = dalloc<double>(h, P.S);
     h->kinf = dalloc<double>(h, P.S);
     h->thr = dalloc<double>(h, 2 * P.S);
     h->rho = dalloc<double>(h, P.S);
@@ -690,12 +693,11 @@ int factor_impl(ncl_kkt_s* h, const double* W, const double* Sigma, const double
             const double bytes = 8.0 * ((double)P.nnzW + (double)P.nnzJ + (double)P.N + (double)P.nnz_lower);
             Span sp(h, st, TM_ASM, bytes, 3);
             if (Sigma_s) launch_k1s_omega(P.nJrows, Sigma_s, h->Jrow_sys, h->rho, h->omega, h->nonfinite, st);
-            launch_assemble(h->d, h->nnzF, W, Sigma, J, h->rho, Sigma_s ? h->omega : nullptr, h->K, st);
+            launch_assemble(h->d, h->chunks, h->nchunks, W, Sigma, J, h->rho, Sigma_s ? h->omega : nullptr, h->K,
+                            h->partial_norm, st);
             h->weighted = Sigma_s != nullptr;
-            launch_chunk_norms(h->d, h->K, h->chunk_row0, h->chunk_rows, h->nchunks, h->partial_norm, st);
-            launch_reduce(h->sys_chunk_ptr, P.S, 3, 3, 0u, h->partial_norm, h->norms3, st);
-            launch_thresholds(P.S, h->norms3, h->eps, h->pivot_mode, h->rho, h->kmax, h->kinf, h->thr, h->nonfinite,
-                              st);
+            launch_thresholds(h->sys_chunk_ptr, P.S, h->partial_norm, h->eps, h->pivot_mode, h->rho, h->kinf, h->thr,
+                              h->nonfinite, st);
         }
         HIPCHK(hipGetLastError());
         double rho_max = 0.0;
@@ -799,7 +801,7 @@ Backward backward_error(ncl_kkt_s* h, const double* B, int64_t ldb, const double
     Plan& P = h->P;
     {
         Span sp(h, st, TM_RES);
-        launch_residual(h->d, h->K, B, ldb, X, ldx, h->Xr, h->R, nrhs, h->chunk_row0, h->chunk_rows, h->nchunks,
+        launch_residual(h->d, h->K, B, ldb, X, ldx, h->Xr, h->R, nrhs, h->chunks, h->nchunks,
                         h->partial_res, st);
         launch_reduce(h->sys_chunk_ptr, P.S, kResWidth * nrhs, kResWidth, (1u << 3) | (1u << 4), h->partial_res,
                       h->res_out, st);

@@ -448,52 +448,92 @@ inline unsigned int blocks_for(int64_t n, int bs) { return (unsigned int)((n + b
 // ---------------------------------------------------------------------------
 // assembly
 // ---------------------------------------------------------------------------
-__global__ void k_assemble(DevPlan d, int64_t nnzF, const double* __restrict__ W, const double* __restrict__ Sigma,
-                           const double* __restrict__ J, const double* __restrict__ sys_rho,
-                           const double* __restrict__ omega, double* __restrict__ K) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= nnzF) return;
-    const int row = d.Krow[e];
-    const double rho = sys_rho[d.row_sys[row]];
-    double v = 0.0;
-    const int w = d.src_w[e];
-    if (w >= 0) v = W[w];
-    const uint8_t fl = d.src_flag[e];
-    if (fl & 1) v += Sigma[row];
-    const int j = d.src_j[e];
-    if (j >= 0) v += J[j];
-    const int64_t q0 = d.prod_ptr[e], q1 = d.prod_ptr[e + 1];
-    if (q1 > q0) {
-        double acc = 0.0;
-        // explicit fma in both: with every Omega_rr = 1 the K1s products
-        // round exactly like K1's
-        if (omega) {
-            // K1s: each row r of J weighted by Omega_rr
-            for (int64_t q = q0; q < q1; ++q) {
-                const int a = d.prod_a[q];
-                acc = fma(omega[d.jrow_of[a]] * J[a], J[d.prod_b[q]], acc);
-            }
-        } else {
-            for (int64_t q = q0; q < q1; ++q) acc = fma(J[d.prod_a[q]], J[d.prod_b[q]], acc);
-        }
-        v += rho * acc;
-    }
-    if (fl & 2) v += -1.0 / rho;
-    K[e] = v;
-}
-
-// Block per chunk of rows (one system): max |K_ij|, max row sum of |K|, and
-// max |K_ij| over the primal block (i, j < n_primal).  Eight lanes share a row
-// (coalesced reads of the row's entries).
-__global__ __launch_bounds__(256) void k_chunk_norms(DevPlan d, const double* __restrict__ K,
-                                                     const int* __restrict__ chunk_row0,
-                                                     const int* __restrict__ chunk_rows, double* partial) {
+// Block per chunk of rows (one system): K's entries in those rows, then max
+// |K_ij|, max row sum of |K| and max |K_ij| over the primal block (i, j <
+// n_primal), with eight lanes a row, from what the block has just written (still
+// in its L2).  A lane has two entries with two products each in flight: bound by
+// the trips to memory of lists and of the values they name, in no order (order
+// 500k: 13 M entries, 21 M products, 300 us; with one entry and one product in
+// flight 400 us, with four entries 430).  The norms in two launches of their own,
+// with each entry's row, two source indices and 64-bit list bounds read: 322 us.
+constexpr int kAsmAhead = 2, kProdAhead = 2;
+__global__ __launch_bounds__(256) void k_assemble(DevPlan d, const RowChunk* __restrict__ chunks,
+                                                  const double* __restrict__ W, const double* __restrict__ Sigma,
+                                                  const double* __restrict__ J, const double* __restrict__ sys_rho,
+                                                  const double* __restrict__ omega, double* K,
+                                                  double* __restrict__ partial) {
     const int c = blockIdx.x;
-    const int tid = threadIdx.x, sub = tid & 7, grp = tid >> 3;   // 32 row groups of 8 lanes
+    const RowChunk ch = chunks[c];
+    const int tid = threadIdx.x;
+    const double rho = sys_rho[ch.sys];
+    const int* __restrict__ pa = d.prod_a + ch.prod0;
+    const int* __restrict__ pb = d.prod_b + ch.prod0;
+    for (int64_t eb = ch.ent0 + tid; eb < ch.ent1; eb += 256 * kAsmAhead) {
+        int src[kAsmAhead];
+        uint8_t fl[kAsmAhead];
+        unsigned int q[kAsmAhead], n[kAsmAhead], most = 0;
+#pragma unroll
+        for (int u = 0; u < kAsmAhead; ++u) {
+            const int64_t e = min(eb + 256 * u, ch.ent1 - 1);
+            src[u] = d.src[e];
+            fl[u] = d.src_flag[e];
+            q[u] = d.prod_ptr[e];
+            n[u] = (e + 1 < ch.ent1 ? d.prod_ptr[e + 1] : ch.nprod) - q[u];
+        }
+        double v[kAsmAhead], acc[kAsmAhead];
+#pragma unroll
+        for (int u = 0; u < kAsmAhead; ++u) {
+            v[u] = src[u] >= 0 ? W[src[u]] : src[u] < -1 ? J[-2 - src[u]] : 0.0;
+            acc[u] = 0.0;
+            most = max(most, n[u]);
+        }
+        for (unsigned int k = 0; k < most; k += kProdAhead) {
+            int a[kAsmAhead][kProdAhead], b[kAsmAhead][kProdAhead];
+#pragma unroll
+            for (int u = 0; u < kAsmAhead; ++u)
+#pragma unroll
+                for (int t = 0; t < kProdAhead; ++t) {
+                    const bool in = k + t < n[u];
+                    a[u][t] = in ? pa[q[u] + k + t] : -1;
+                    b[u][t] = in ? pb[q[u] + k + t] : -1;
+                }
+            double ja[kAsmAhead][kProdAhead], jb[kAsmAhead][kProdAhead];
+#pragma unroll
+            for (int u = 0; u < kAsmAhead; ++u)
+#pragma unroll
+                for (int t = 0; t < kProdAhead; ++t) {
+                    ja[u][t] = jb[u][t] = 0.0;
+                    if (a[u][t] >= 0) {
+                        ja[u][t] = J[a[u][t]];
+                        jb[u][t] = J[b[u][t]];
+                        if (omega) ja[u][t] *= omega[d.jrow_of[a[u][t]]];
+                    }
+                }
+            // explicit fma: with every Omega_rr = 1 the K1s products (each row r
+            // of J weighted by Omega_rr) round exactly like K1's
+#pragma unroll
+            for (int u = 0; u < kAsmAhead; ++u)
+#pragma unroll
+                for (int t = 0; t < kProdAhead; ++t)
+                    if (k + t < n[u]) acc[u] = fma(ja[u][t], jb[u][t], acc[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < kAsmAhead; ++u) {
+            const int64_t e = eb + 256 * u;
+            if (e >= ch.ent1) break;
+            if (fl[u] & 1) v[u] += Sigma[d.Kj[e]];   // a diagonal entry: its column is its row
+            if (n[u] > 0) v[u] += rho * acc[u];
+            if (fl[u] & 2) v[u] += -1.0 / rho;
+            K[e] = v[u];
+        }
+    }
+    __syncthreads();
+    const int sub = tid & 7, grp = tid >> 3;   // 32 row groups of 8 lanes
+    const bool all_primal = d.n_primal >= d.N;
     double mx = 0.0, rsmax = 0.0, pmx = 0.0;
     bool bad = false;
-    for (int r = grp; r < chunk_rows[c]; r += 32) {
-        const int row = chunk_row0[c] + r;
+    for (int r = grp; r < ch.rows; r += 32) {
+        const int row = ch.row0 + r;
         const bool prow = row < d.n_primal;
         double rs = 0.0;
         for (int64_t e = d.Kp[row] + sub; e < d.Kp[row + 1]; e += 8) {
@@ -501,7 +541,7 @@ __global__ __launch_bounds__(256) void k_chunk_norms(DevPlan d, const double* __
             bad |= !isfinite(v);
             const double a = fabs(v);
             mx = fmax(mx, a);
-            if (prow && d.Kj[e] < d.n_primal) pmx = fmax(pmx, a);
+            if (prow && (all_primal || d.Kj[e] < d.n_primal)) pmx = fmax(pmx, a);
             rs += a;
         }
         for (int o = 4; o > 0; o >>= 1) rs += __shfl_xor(rs, o, 8);
@@ -521,11 +561,7 @@ __global__ __launch_bounds__(256) void k_chunk_norms(DevPlan d, const double* __
         }
         __syncthreads();
     }
-    if (tid == 0) {
-        partial[3 * c] = sm[0][0];
-        partial[3 * c + 1] = sm[1][0];
-        partial[3 * c + 2] = sm[2][0];
-    }
+    if (tid < 3) partial[3 * (int64_t)c + tid] = sm[tid][0];
 }
 
 // Block per (system, column group): reduction over the system's chunks of
@@ -553,19 +589,34 @@ __global__ __launch_bounds__(256) void k_reduce_partials(const int* __restrict__
     if (tid == 0) out[(int64_t)s * width + k] = sm[0];
 }
 
-// Per system, from the reduced norms (max |K_ij|, ||K||_inf, max over the
-// primal block): kmax, kinf and the two static-pivot thresholds of Sec. 3.1.
+// Block per system: the norms (max |K_ij|, ||K||_inf, max over the primal block)
+// from its chunks', then kinf and the two static-pivot thresholds of Sec. 3.1.
 // mode 0, global rule: both eps * max |K_ij|.  mode 1, block rule (stabilized
 // form): primal pivots eps * max |K_xx|, dual pivots eps / rho, the norm of
 // the -1/rho I block of Sec. 3.2, eq. K2r.  mode 2: eps itself for both (the
 // pivot epsilon of Sec. 4.3 as an absolute bound).  Non-finite norms set
 // kNonfiniteInput.
-__global__ void k_thresholds(int S, const double* norms3, double eps, int mode, const double* sys_rho,
-                             double* kmax, double* kinf, double* thr, int* nonfinite) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= S) return;
-    const double a = norms3[3 * s], b = norms3[3 * s + 1], pm = norms3[3 * s + 2];
-    kmax[s] = a;
+__global__ __launch_bounds__(256) void k_thresholds(const int* __restrict__ sys_chunk_ptr,
+                                                    const double* __restrict__ partial, double eps, int mode,
+                                                    const double* __restrict__ sys_rho, double* kinf, double* thr,
+                                                    int* nonfinite) {
+    const int s = blockIdx.x, tid = threadIdx.x;
+    double v[3] = {0.0, 0.0, 0.0};
+    for (int c = sys_chunk_ptr[s] + tid; c < sys_chunk_ptr[s + 1]; c += 256)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) v[k] = fmax(v[k], partial[3 * (int64_t)c + k]);
+    __shared__ double sm[3][4];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        for (int o = 32; o > 0; o >>= 1) v[k] = fmax(v[k], __shfl_xor(v[k], o));
+        if ((tid & 63) == 0) sm[k][tid >> 6] = v[k];
+    }
+    __syncthreads();
+    if (tid > 0) return;
+    double n[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) n[k] = fmax(fmax(sm[k][0], sm[k][1]), fmax(sm[k][2], sm[k][3]));
+    const double a = n[0], b = n[1], pm = n[2];
     kinf[s] = b;
     thr[2 * s] = mode == 2 ? eps : (mode == 1 ? pm : a) * eps;
     thr[2 * s + 1] = mode == 2 ? eps : (mode == 1 ? eps / sys_rho[s] : eps * a);
@@ -2153,14 +2204,13 @@ __device__ __forceinline__ double res_join(int k, double a, double b) { return k
 // One right-hand side: block per chunk of rows (one system); eight lanes share a row.
 __global__ __launch_bounds__(256) void k_residual(DevPlan d, const double* __restrict__ K,
                                                   const double* __restrict__ B, const double* __restrict__ x,
-                                                  double* __restrict__ R, const int* __restrict__ chunk_row0,
-                                                  const int* __restrict__ chunk_rows, double* partial) {
-    const int c = blockIdx.x;
+                                                  double* __restrict__ R, const RowChunk* __restrict__ chunks, double* partial) {
+    const int c = blockIdx.x, row0 = chunks[c].row0, rows = chunks[c].rows;
     const int tid = threadIdx.x, sub = tid & 7, grp = tid >> 3;
     __shared__ double sm[kResWidth][256];
     double v[kResWidth] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int r = grp; r < chunk_rows[c]; r += 32) {
-        const int row = chunk_row0[c] + r;
+    for (int r = grp; r < rows; r += 32) {
+        const int row = row0 + r;
         RowSum s;
         for (int64_t e = d.Kp[row] + sub; e < d.Kp[row + 1]; e += 8) s.add(K[e], x[d.Kj[e]]);
         for (int o = 4; o > 0; o >>= 1) {
@@ -2191,15 +2241,14 @@ __global__ __launch_bounds__(256) void k_residual(DevPlan d, const double* __res
 __global__ __launch_bounds__(256) void k_residual16(DevPlan d, const double* __restrict__ K,
                                                     const double* __restrict__ B, int64_t ldb,
                                                     const double* __restrict__ Xr, double* __restrict__ R, int nrhs,
-                                                    const int* __restrict__ chunk_row0,
-                                                    const int* __restrict__ chunk_rows, double* partial) {
+                                                    const RowChunk* __restrict__ chunks, double* partial) {
     static_assert(kNrhsMax == 16, "one lane per column");
-    const int c = blockIdx.x;
+    const int c = blockIdx.x, row0 = chunks[c].row0, rows = chunks[c].rows;
     const int tid = threadIdx.x, q = tid & 15, grp = tid >> 4;
     __shared__ double sm[kResWidth][256];
     double v[kResWidth] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int r = grp; r < chunk_rows[c]; r += 16) {
-        const int row = chunk_row0[c] + r;
+    for (int r = grp; r < rows; r += 16) {
+        const int row = row0 + r;
         RowSum s;
         const int64_t e1 = d.Kp[row + 1];
         for (int64_t e0 = d.Kp[row]; e0 < e1; e0 += 8) {
@@ -2496,10 +2545,10 @@ LaunchTimer* set_launch_timer(LaunchTimer* t) {
     return old;
 }
 
-void launch_assemble(const DevPlan& d, int64_t nnzF, const double* W, const double* Sigma, const double* J,
-                     const double* sys_rho, const double* omega, double* K, hipStream_t st) {
-    if (nnzF <= 0) return;
-    launch(k_assemble, dim3(blocks_for(nnzF, 256)), dim3(256), 0, st, d, nnzF, W, Sigma, J, sys_rho, omega, K);
+void launch_assemble(const DevPlan& d, const RowChunk* chunks, int nchunks, const double* W, const double* Sigma,
+                     const double* J, const double* sys_rho, const double* omega, double* K, double* partial,
+                     hipStream_t st) {
+    launch(k_assemble, dim3(nchunks), dim3(256), 0, st, d, chunks, W, Sigma, J, sys_rho, omega, K, partial);
 }
 
 void launch_k1s_omega(int64_t nrows, const double* Sigma_s, const int* Jrow_sys, const double* sys_rho, double* omega,
@@ -2556,21 +2605,15 @@ void launch_barrier_sigma(int64_t n, const double* x, const double* l, const dou
     launch(k_barrier_sigma, dim3(blocks_for(n, 256)), dim3(256), 0, st, n, x, l, u, z_l, z_u, sigma);
 }
 
-void launch_chunk_norms(const DevPlan& d, const double* K, const int* chunk_row0, const int* chunk_rows, int nchunks,
-                        double* partial, hipStream_t st) {
-    launch(k_chunk_norms, dim3(nchunks), dim3(256), 0, st, d, K, chunk_row0, chunk_rows, partial);
-}
-
 void launch_reduce(const int* sys_chunk_ptr, int S, int width, int period, unsigned int sum_mask,
                    const double* partial, double* out, hipStream_t st) {
     launch(k_reduce_partials, dim3(S, width), dim3(256), 0, st, sys_chunk_ptr, width, period, sum_mask, partial,
            out);
 }
 
-void launch_thresholds(int S, const double* norms3, double eps, int mode, const double* sys_rho, double* kmax,
-                       double* kinf, double* thr, int* nonfinite, hipStream_t st) {
-    launch(k_thresholds, dim3(blocks_for(S, 64)), dim3(64), 0, st, S, norms3, eps, mode, sys_rho, kmax, kinf, thr,
-           nonfinite);
+void launch_thresholds(const int* sys_chunk_ptr, int S, const double* partial, double eps, int mode,
+                       const double* sys_rho, double* kinf, double* thr, int* nonfinite, hipStream_t st) {
+    launch(k_thresholds, dim3(S), dim3(256), 0, st, sys_chunk_ptr, partial, eps, mode, sys_rho, kinf, thr, nonfinite);
 }
 
 template <typename T>
@@ -2670,14 +2713,14 @@ void launch_bwd(bool many, const PanelTask* pt, int np, const SmallTask* sm, int
 }
 
 void launch_residual(const DevPlan& d, const double* K, const double* B, int64_t ldb, const double* X, int64_t ldx,
-                     double* Xr, double* R, int nrhs, const int* chunk_row0, const int* chunk_rows, int nchunks,
-                     double* partial, hipStream_t st) {
+                     double* Xr, double* R, int nrhs, const RowChunk* chunks, int nchunks, double* partial,
+                     hipStream_t st) {
     if (nrhs == 1) {
-        launch(k_residual, dim3(nchunks), dim3(256), 0, st, d, K, B, X, R, chunk_row0, chunk_rows, partial);
+        launch(k_residual, dim3(nchunks), dim3(256), 0, st, d, K, B, X, R, chunks, partial);
         return;
     }
     launch(k_to_rows, dim3(blocks_for(d.N, 64)), dim3(256), 0, st, d.N, X, ldx, nrhs, Xr);
-    launch(k_residual16, dim3(nchunks), dim3(256), 0, st, d, K, B, ldb, Xr, R, nrhs, chunk_row0, chunk_rows, partial);
+    launch(k_residual16, dim3(nchunks), dim3(256), 0, st, d, K, B, ldb, Xr, R, nrhs, chunks, partial);
 }
 
 void launch_axpy_cols(double* X, int64_t ldx, const double* DX, int64_t N, int nrhs, hipStream_t st) {

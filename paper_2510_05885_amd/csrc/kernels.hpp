@@ -53,6 +53,14 @@ struct FrontPlan {
     int* nonfinite;
 };
 
+// A block's rows of K (one system) in assembly, norms and residuals: rows row0 ..
+// row0 + rows, entries ent0 .. ent1, products prod0 .. prod0 + nprod.
+struct RowChunk {
+    int row0, rows, sys;
+    unsigned int nprod;
+    int64_t ent0, ent1, prod0;
+};
+
 // Device copies of the plan (all device pointers), passed by value.
 struct DevPlan {
     int64_t N;
@@ -63,11 +71,9 @@ struct DevPlan {
     // full CSR of K with value sources
     const int64_t* Kp;
     const int* Kj;
-    const int* Krow;
-    const int* src_w;
-    const int* src_j;
+    const int* src;            // an entry's value: W's index, -2 - J's index, or -1
     const uint8_t* src_flag;
-    const int64_t* prod_ptr;
+    const unsigned int* prod_ptr;   // its first product, from the row chunk's first
     const int* prod_a;
     const int* prod_b;
     const int* row_sys;
@@ -122,8 +128,11 @@ struct LaunchTimer {
 LaunchTimer* set_launch_timer(LaunchTimer* t);   // returns the previous one
 
 // omega: per row of J, the weight of its products (K1s), or nullptr (K1, K2r).
-void launch_assemble(const DevPlan& d, int64_t nnzF, const double* W, const double* Sigma, const double* J,
-                     const double* sys_rho, const double* omega, double* K, hipStream_t st);
+// partial[3c..3c+2], per chunk: max |K_ij|, max row sum of |K|, max |K_ij| over the
+// primal block.
+void launch_assemble(const DevPlan& d, const RowChunk* chunks, int nchunks, const double* W, const double* Sigma,
+                     const double* J, const double* sys_rho, const double* omega, double* K, double* partial,
+                     hipStream_t st);
 // ---- slack elimination (K1s) and step recovery (vectors in the caller's
 // order; rows of J of all systems concatenated; rho per system) -------------
 void launch_k1s_omega(int64_t nrows, const double* Sigma_s, const int* Jrow_sys, const double* sys_rho, double* omega,
@@ -144,21 +153,17 @@ void launch_recover_dz(int64_t n, const double* x, const double* l, const double
 void launch_add_scalar(int64_t n, const double* in, double delta, double* out, hipStream_t st);
 void launch_barrier_sigma(int64_t n, const double* x, const double* l, const double* u, const double* z_l,
                           const double* z_u, double* sigma, hipStream_t st);
-// Block per chunk of rows: partial[3c..3c+2] = max |K_ij|, max row sum of |K|,
-// max |K_ij| over the primal block.
-void launch_chunk_norms(const DevPlan& d, const double* K, const int* chunk_row0, const int* chunk_rows, int nchunks,
-                        double* partial, hipStream_t st);
 // out[s*width + k] = reduction over the chunks of system s of partial[c*width + k]:
 // a sum where bit (k mod period) of sum_mask is set, else a max.  Fixed order
 // (deterministic).  1 <= period <= 32.
 void launch_reduce(const int* sys_chunk_ptr, int S, int width, int period, unsigned int sum_mask,
                    const double* partial, double* out, hipStream_t st);
-// kmax, kinf and the two static-pivot thresholds per system (thr[2s] primal,
-// thr[2s+1] dual) from the reduced norms.  mode 0: eps * max |K_ij| for both;
+// kinf and the two static-pivot thresholds per system (thr[2s] primal,
+// thr[2s+1] dual) from the chunks' norms.  mode 0: eps * max |K_ij| for both;
 // 1, block rule: primal eps * max |K_xx|, dual eps / rho; 2: eps for both.
 // Flags non-finite norms.
-void launch_thresholds(int S, const double* norms3, double eps, int mode, const double* sys_rho, double* kmax,
-                       double* kinf, double* thr, int* nonfinite, hipStream_t st);
+void launch_thresholds(const int* sys_chunk_ptr, int S, const double* partial, double eps, int mode,
+                       const double* sys_rho, double* kinf, double* thr, int* nonfinite, hipStream_t st);
 
 // ---- numeric factorization (T = double or float) --------------------------
 // One launch of small fronts of order up to fmax; strip: elements of LDS for
@@ -206,8 +211,8 @@ void launch_bwd(bool many, const PanelTask* pt, int np, const SmallTask* sm, int
 // max |r|, max |x|, max |b|, sum r^2, sum b^2, max |r_i| / (|K||x| + |b|)_i.
 // nrhs > 1: R is row-major, kNrhsMax a row, and Xr (N x kNrhsMax) is scratch.
 void launch_residual(const DevPlan& d, const double* K, const double* B, int64_t ldb, const double* X, int64_t ldx,
-                     double* Xr, double* R, int nrhs, const int* chunk_row0, const int* chunk_rows, int nchunks,
-                     double* partial, hipStream_t st);
+                     double* Xr, double* R, int nrhs, const RowChunk* chunks, int nchunks, double* partial,
+                     hipStream_t st);
 void launch_axpy_cols(double* X, int64_t ldx, const double* DX, int64_t N, int nrhs, hipStream_t st);
 void launch_copy_cols(double* dst, int64_t ldd, const double* src, int64_t lds, int64_t N, int nrhs,
                       hipStream_t st);

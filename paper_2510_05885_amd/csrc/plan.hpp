@@ -89,8 +89,7 @@ struct Plan {
     // ---- full symmetric CSR of K (unpermuted), with value sources -------
     std::vector<int64_t> Kp;         // N+1
     std::vector<int> Kj;             // nnzF column indices
-    std::vector<int> src_w;          // nnzF: W value index or -1
-    std::vector<int> src_j;          // nnzF: J value index or -1 (stabilized J / J^T blocks)
+    std::vector<int> src;            // nnzF: W value index, -2 - J value index (stabilized J / J^T blocks) or -1
     std::vector<uint8_t> src_flag;   // bit0: add Sigma[row]; bit1: add -1/rho
     std::vector<int64_t> prod_ptr;   // nnzF+1: pairs of J value indices (condensed)
     std::vector<int> prod_a, prod_b;
