@@ -103,11 +103,10 @@ struct ncl_kkt_s {
     double *K = nullptr, *partial_norm = nullptr, *kinf = nullptr,
            *thr = nullptr, *rho = nullptr;
     int* nonfinite = nullptr;
-    unsigned long long* inertia = nullptr;
     unsigned long long* inertia_part = nullptr;
     double *F64 = nullptr, *D64 = nullptr, *Y64 = nullptr, *U64 = nullptr, *P64 = nullptr, *M64 = nullptr;
     float *F32 = nullptr, *D32 = nullptr, *Y32 = nullptr, *U32 = nullptr, *P32 = nullptr, *M32 = nullptr;
-    double *R = nullptr, *DX = nullptr, *Xp = nullptr, *Xr = nullptr, *partial_res = nullptr, *res_out = nullptr;
+    double *R = nullptr, *DX = nullptr, *Xp = nullptr, *Xr = nullptr, *partial_res = nullptr;
     double *JX = nullptr, *JL = nullptr;
     // slack elimination: J^T in CSC (row, value index per entry), Omega of the
     // last factor_k1s call; `weighted` while the factor is of K1s
@@ -118,8 +117,10 @@ struct ncl_kkt_s {
     double* sigma_shift = nullptr;   // Sigma + delta of the inertia correction (allocated on first use)
     int *W_row = nullptr, *W_col = nullptr, *Jj = nullptr, *Jrow_sys = nullptr;
     int64_t *Jp = nullptr, *sys_jrow = nullptr;
-    double* host_pinned = nullptr;   // read-back staging
-    size_t host_pinned_len = 0;
+    // Pinned memory that kernels read and write: rho of each system; the figures of
+    // k_end; the backward errors.  Valid on the host after a wait for the stream.
+    double *pin_rho = nullptr, *pin_res = nullptr;
+    unsigned long long* pin_factor = nullptr;
     // host state
     std::vector<double> h_rho, h_kinf;
     std::vector<int64_t> h_inertia;   // 4 per system
@@ -352,10 +353,8 @@ void setup_device(ncl_kkt_s* h) {
     h->thr = dalloc<double>(h, 2 * P.S);
     h->rho = dalloc<double>(h, P.S);
     h->nonfinite = dalloc<int>(h, 1);
-    h->inertia = dalloc<unsigned long long>(h, 4 * P.S);
     h->inertia_part = dalloc<unsigned long long>(h, 4 * (int64_t)P.S * kInertiaSlots);
     d.sys_thr = h->thr;
-    d.inertia = h->inertia;
     d.inertia_part = h->inertia_part;
     d.nonfinite = h->nonfinite;
     h->fp.sys_thr = h->thr;
@@ -380,7 +379,6 @@ void setup_device(ncl_kkt_s* h) {
     h->Xp = dalloc<double>(h, P.N * kNrhsMax);
     h->Xr = dalloc<double>(h, P.N * kNrhsMax);
     h->partial_res = dalloc<double>(h, (int64_t)h->nchunks * kNrhsMax * kResWidth);
-    h->res_out = dalloc<double>(h, (int64_t)P.S * kNrhsMax * kResWidth);
     // adjoint structures
     if (P.form == NCL_CONDENSED) {
         h->W_row = upload(h, P.Wrow_of);
@@ -417,8 +415,12 @@ void setup_device(ncl_kkt_s* h) {
         h->JX = dalloc<double>(h, std::max<int64_t>(P.nJrows, 1) * kNrhsMax);
         h->JL = dalloc<double>(h, std::max<int64_t>(P.nJrows, 1) * kNrhsMax);
     }
-    h->host_pinned_len = (size_t)std::max<int64_t>((int64_t)P.S * kNrhsMax * kResWidth + 1, 8 * (int64_t)P.S + 8);
-    HIPCHK(hipHostMalloc((void**)&h->host_pinned, sizeof(double) * h->host_pinned_len, hipHostMallocDefault));
+    {
+        const int64_t len = P.S + 5 * (int64_t)P.S + 1 + (int64_t)P.S * kNrhsMax * kResWidth;
+        HIPCHK(hipHostMalloc((void**)&h->pin_rho, sizeof(double) * len, hipHostMallocDefault));
+        h->pin_factor = reinterpret_cast<unsigned long long*>(h->pin_rho + P.S);
+        h->pin_res = h->pin_rho + 6 * (int64_t)P.S + 1;
+    }
     HIPCHK(hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking));
     HIPCHK(hipStreamCreateWithFlags(&h->aux_stream, hipStreamNonBlocking));
     h->lvl_ev.assign(2 * (size_t)std::max(P.nlevels, 1), nullptr);
@@ -542,7 +544,6 @@ template <typename T>
 void factor_fronts(ncl_kkt_s* h, T* F, T* D, T* Mb, hipStream_t st) {
     Plan& P = h->P;
     const DevPlan& d = h->d;
-    launch_zero_u64(h->inertia_part, 4 * (int64_t)P.S * kInertiaSlots, st);
     size_t sb = 0, lb = 0;
     for (int l = 0; l < P.nlevels; ++l) {
         // Fronts of one level are independent: when the level has large fronts and
@@ -612,7 +613,7 @@ void factor_fronts(ncl_kkt_s* h, T* F, T* D, T* Mb, hipStream_t st) {
         }
     }
     launch_pair_inverse<T>(h->pairs, (int)P.pairs.size(), F, Mb, st);
-    launch_reduce_inertia(d, P.S, st);
+    launch_end(d, h->kinf, h->pin_factor, st);
 }
 
 // Runs the frontal factorization; with graphs enabled (and timing off) the
@@ -642,13 +643,10 @@ void run_factor(ncl_kkt_s* h, hipStream_t st) {
 
 int read_inertia(ncl_kkt_s* h, hipStream_t st) {
     const int S = h->P.S;
-    unsigned long long* hp = reinterpret_cast<unsigned long long*>(h->host_pinned);
-    HIPCHK(hipMemcpyAsync(hp, h->inertia, sizeof(unsigned long long) * 4 * S, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(h->host_pinned + 4 * S, h->nonfinite, sizeof(int), hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(h->host_pinned + 4 * S + 1, h->kinf, sizeof(double) * 1, hipMemcpyDeviceToHost, st));
+    const unsigned long long* hp = h->pin_factor;
     HIPCHK(hipStreamSynchronize(st));
-    int nonfin = 0;
-    std::memcpy(&nonfin, h->host_pinned + 4 * S, sizeof(int));
+    std::memcpy(h->h_kinf.data(), hp + 4 * S, sizeof(double) * S);   // of the backward error
+    const int nonfin = (int)hp[5 * S];
     h->nonfinite_bits = nonfin;
     h->inertia_ok = true;
     for (int s = 0; s < S; ++s) {
@@ -666,7 +664,7 @@ int read_inertia(ncl_kkt_s* h, hipStream_t st) {
 // assembled K (whose norms and thresholds are already on the device), and
 // remembers the rho at which FP32 was insufficient (sticky policy).
 int refactor_fp64(ncl_kkt_s* h, hipStream_t st) {
-    launch_zero_i32(h->nonfinite, 1, st);
+    launch_begin(h->P.S, nullptr, h->rho, h->nonfinite, h->inertia_part, st);
     run_factor<double>(h, st);
     h->factor_prec = 0;
     h->fell_back = true;
@@ -685,9 +683,8 @@ int factor_impl(ncl_kkt_s* h, const double* W, const double* Sigma, const double
     h->fell_back = false;
     try {
         HIPCHK(hipSetDevice(h->device));
-        for (int s = 0; s < P.S; ++s) h->host_pinned[s] = rho_host[s];
-        HIPCHK(hipMemcpyAsync(h->rho, h->host_pinned, sizeof(double) * P.S, hipMemcpyHostToDevice, st));
-        launch_zero_i32(h->nonfinite, 1, st);
+        std::memcpy(h->pin_rho, rho_host, sizeof(double) * P.S);
+        launch_begin(P.S, h->pin_rho, h->rho, h->nonfinite, h->inertia_part, st);
         {
             // algorithmic bytes: read W, Sigma, J once, write the lower triangle of K
             const double bytes = 8.0 * ((double)P.nnzW + (double)P.nnzJ + (double)P.N + (double)P.nnz_lower);
@@ -721,10 +718,7 @@ int factor_impl(ncl_kkt_s* h, const double* W, const double* Sigma, const double
             if (rc == NCL_OK || !(h->nonfinite_bits & kNonfiniteInput)) rc = refactor_fp64(h, st);
         }
         if (rc) { flush_timing(h); return rc; }
-        // host copy of ||K||_inf per system for the backward error
-        HIPCHK(hipMemcpyAsync(h->host_pinned, h->kinf, sizeof(double) * P.S, hipMemcpyDeviceToHost, st));
-        HIPCHK(hipStreamSynchronize(st));
-        for (int s = 0; s < P.S; ++s) { h->h_kinf[s] = h->host_pinned[s]; h->h_rho[s] = rho_host[s]; }
+        for (int s = 0; s < P.S; ++s) h->h_rho[s] = rho_host[s];
         flush_timing(h);
     } catch (const HipError& e) {
         return NCL_ERR_HIP;
@@ -804,16 +798,14 @@ Backward backward_error(ncl_kkt_s* h, const double* B, int64_t ldb, const double
         launch_residual(h->d, h->K, B, ldb, X, ldx, h->Xr, h->R, nrhs, h->chunks, h->nchunks,
                         h->partial_res, st);
         launch_reduce(h->sys_chunk_ptr, P.S, kResWidth * nrhs, kResWidth, (1u << 3) | (1u << 4), h->partial_res,
-                      h->res_out, st);
+                      h->pin_res, st);
     }
-    HIPCHK(hipMemcpyAsync(h->host_pinned, h->res_out, sizeof(double) * kResWidth * nrhs * P.S,
-                          hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     Backward out;
     auto upd = [](double& m, double w) { m = std::isnan(w) ? INFINITY : std::max(m, w); };
     for (int s = 0; s < P.S; ++s)
         for (int q = 0; q < nrhs; ++q) {
-            const double* v = h->host_pinned + ((int64_t)s * nrhs + q) * kResWidth;
+            const double* v = h->pin_res + ((int64_t)s * nrhs + q) * kResWidth;
             const double den = h->h_kinf[s] * v[1] + v[2];
             upd(out.omega, den > 0.0 ? v[0] / den : (v[0] > 0.0 ? INFINITY : 0.0));
             upd(out.cw, v[5]);
@@ -1238,7 +1230,7 @@ void ncl_kkt_destroy(ncl_kkt_t h) {
         (void)hipSetDevice(h->device);
         (void)hipDeviceSynchronize();
         for (void* p : h->allocs) (void)hipFree(p);
-        if (h->host_pinned) (void)hipHostFree(h->host_pinned);
+        if (h->pin_rho) (void)hipHostFree(h->pin_rho);
         for (auto& e : h->tm.pool) (void)hipEventDestroy(e);
         for (auto& g : h->g_factor) if (g) (void)hipGraphExecDestroy(g);
         for (auto& row : h->g_sweep)

@@ -2309,22 +2309,33 @@ __global__ void k_copy_cols(double* dst, int64_t ldd, const double* src, int64_t
     for (int q = 0; q < nrhs; ++q) dst[i + q * ldd] = src[i + q * lds];
 }
 
-__global__ void k_reduce_inertia(DevPlan d, int S) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= 4 * S) return;
-    const int sys = t >> 2, k = t & 3;
-    unsigned long long v = 0;
-    for (int q = 0; q < kInertiaSlots; ++q) v += d.inertia_part[4 * ((int64_t)sys * kInertiaSlots + q) + k];
-    d.inertia[t] = v;
+// Before a factorization: rho from the host's buffer (read over the bus, once;
+// nullptr: unchanged), status bits and inertia counters cleared.
+__global__ void k_begin(int S, const double* __restrict__ rho_host, double* __restrict__ rho, int* nonfinite,
+                        unsigned long long* __restrict__ part) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < 4 * (int64_t)S * kInertiaSlots) part[i] = 0ULL;
+    if (rho_host && i < S) rho[i] = rho_host[i];
+    if (i == 0) *nonfinite = 0;
 }
 
-__global__ void k_zero_u64(unsigned long long* p, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0ULL;
-}
-__global__ void k_zero_i32(int* p, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
+// After it, a block per system: the counters' sums, ||K||_inf and the status
+// bits straight into the host's buffer (4 S, S and one value).  Copied there, they
+// were three transfers behind the last kernel, and ||K||_inf a fourth after a
+// first wait: 50 us between a factorization and its solve at order 625.
+__global__ __launch_bounds__(4 * kInertiaSlots) void k_end(DevPlan d, const double* __restrict__ kinf,
+                                                           unsigned long long* host) {
+    const int s = blockIdx.x, tid = threadIdx.x;
+    __shared__ unsigned long long sm[4 * kInertiaSlots];
+    sm[tid] = d.inertia_part[4 * (int64_t)s * kInertiaSlots + tid];
+    __syncthreads();
+    for (int o = 2 * kInertiaSlots; o >= 4; o >>= 1) {
+        if (tid < o) sm[tid] += sm[tid + o];
+        __syncthreads();
+    }
+    if (tid < 4) host[4 * (int64_t)s + tid] = sm[tid];
+    if (tid == 4) host[4 * (int64_t)d.S + s] = (unsigned long long)__double_as_longlong(kinf[s]);
+    if (tid == 5 && s == 0) host[5 * (int64_t)d.S] = (unsigned long long)(unsigned int)*d.nonfinite;
 }
 
 // ---------------------------------------------------------------------------
@@ -2731,16 +2742,14 @@ void launch_copy_cols(double* dst, int64_t ldd, const double* src, int64_t lds, 
     launch(k_copy_cols, dim3(blocks_for(N, 256)), dim3(256), 0, st, dst, ldd, src, lds, N, nrhs);
 }
 
-void launch_zero_u64(unsigned long long* p, int64_t n, hipStream_t st) {
-    if (n > 0) launch(k_zero_u64, dim3(blocks_for(n, 256)), dim3(256), 0, st, p, n);
+void launch_begin(int S, const double* rho_host, double* rho, int* nonfinite, unsigned long long* part,
+                  hipStream_t st) {
+    launch(k_begin, dim3(blocks_for(4 * (int64_t)S * kInertiaSlots, 256)), dim3(256), 0, st, S, rho_host, rho, nonfinite,
+           part);
 }
 
-void launch_reduce_inertia(const DevPlan& d, int S, hipStream_t st) {
-    launch(k_reduce_inertia, dim3(blocks_for(4 * (int64_t)S, 256)), dim3(256), 0, st, d, S);
-}
-
-void launch_zero_i32(int* p, int64_t n, hipStream_t st) {
-    if (n > 0) launch(k_zero_i32, dim3(blocks_for(n, 256)), dim3(256), 0, st, p, n);
+void launch_end(const DevPlan& d, const double* kinf, unsigned long long* host, hipStream_t st) {
+    launch(k_end, dim3(d.S), dim3(4 * kInertiaSlots), 0, st, d, kinf, host);
 }
 
 void launch_adjoint(const DevPlan& d, int64_t nnzW, const int* W_row, const int* W_col, int64_t nJrows,

@@ -111,8 +111,7 @@ struct DevPlan {
     const int* asm_seg_bc;
     // per system
     const double* sys_thr;     // static-pivot thresholds, 2 per system: primal, dual pivots
-    unsigned long long* inertia;  // 4 per system: npos, nneg, nzero, nperturbed
-    unsigned long long* inertia_part;  // kInertiaSlots x 4 per system, summed into inertia
+    unsigned long long* inertia_part;  // kInertiaSlots x 4 per system: npos, nneg, nzero, nperturbed
     int* nonfinite;            // status bits kNonfiniteInput | kNonfiniteFactor
 };
 
@@ -216,9 +215,10 @@ void launch_residual(const DevPlan& d, const double* K, const double* B, int64_t
 void launch_axpy_cols(double* X, int64_t ldx, const double* DX, int64_t N, int nrhs, hipStream_t st);
 void launch_copy_cols(double* dst, int64_t ldd, const double* src, int64_t lds, int64_t N, int nrhs,
                       hipStream_t st);
-void launch_zero_u64(unsigned long long* p, int64_t n, hipStream_t st);
-void launch_zero_i32(int* p, int64_t n, hipStream_t st);
-void launch_reduce_inertia(const DevPlan& d, int S, hipStream_t st);   // inertia = sum of the partials
+// Before and after a factorization (host: pinned memory, see the kernels).
+void launch_begin(int S, const double* rho_host, double* rho, int* nonfinite, unsigned long long* part,
+                  hipStream_t st);
+void launch_end(const DevPlan& d, const double* kinf, unsigned long long* host, hipStream_t st);
 
 // Raises the dynamic-LDS limit of the LDS-resident kernels to the device maximum.
 hipError_t configure_kernels(int max_dynamic_lds);
