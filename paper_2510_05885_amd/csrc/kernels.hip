@@ -1614,8 +1614,96 @@ __device__ __forceinline__ void bwd_front1(const SmallTask* tk, const int* __res
     }
 }
 
-template <typename T, bool kPanels>
-__global__ __launch_bounds__(256, kPanels ? 2 : 4) void k_bwd1(const PanelTask* __restrict__ pt, int np,
+// The same by the four waves of a workgroup, where fronts are few: sub-panels w
+// and w + 4 belong to wave w, which loads all it needs of them at once; the rows
+// below the pivots are summed before the first is solved, and each solved
+// sub-panel's x is added to the sums above it by their waves.  One wave's loads,
+// a sub-panel at a time, were the chain: 8 to 14 us a launch of lone fronts of
+// order 65..128 (order 625), so 3.0 to 5.7.
+template <typename T>
+__device__ __forceinline__ void bwd_front1_wg(const SmallTask* tk, const int* __restrict__ rows,
+                                              const T* __restrict__ F, const T* __restrict__ D,
+                                              const T* __restrict__ Y2, T* __restrict__ X, T* xs, int tid) {
+    constexpr int kBlocks = kSmallMax / 16;
+    static_assert(kBlocks == 8, "two sub-panels a wave");
+    const int first = tk->first, p = tk->p, f = tk->f, nq = (p + 15) >> 4, nb = (f + 15) >> 4;
+    const T* __restrict__ L = F + tk->L_off;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, t = lane & 15, g = lane >> 4;
+    T l[2][kBlocks][4], z[2][16], yd[2], acc[2];   // l: rows 16 b + 4 m + g of column t
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const int q = wave + 4 * s, kb = 16 * q, bw = min(16, p - kb);
+        acc[s] = yd[s] = T(0);
+        if (q >= nq) continue;   // uniform
+        const int c = kb + min(t, bw - 1);
+        const T* __restrict__ Lc = L + (int64_t)c * f;
+#pragma unroll
+        for (int b = 0; b < kBlocks; ++b) {
+            if (b < q || b >= nb) continue;   // uniform
+#pragma unroll
+            for (int m = 0; m < 4; ++m) l[s][b][m] = Lc[min(16 * b + 4 * m + g, f - 1)];
+        }
+#pragma unroll
+        for (int u = 1; u < 16; ++u) z[s][u] = Lc[kb + min(u, bw - 1)];
+        yd[s] = Y2[first + c];
+        acc[s] = D[first + c];
+    }
+    if (tid >= p && tid < f) xs[tid] = X[rows[tk->rows_off + tid]];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const int q = wave + 4 * s, bw = min(16, p - 16 * q);
+        if (q >= nq) continue;
+        yd[s] *= T(1) / acc[s];
+        acc[s] = T(0);
+#pragma unroll
+        for (int u = 1; u < 16; ++u) z[s][u] = u > t && u < bw ? z[s][u] : T(0);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const int q = wave + 4 * s;
+        if (q >= nq) continue;
+#pragma unroll
+        for (int b = 0; b < kBlocks; ++b) {
+            if (b < nq - 1 || b >= nb) continue;   // uniform
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const int i = 16 * b + 4 * m + g;
+                acc[s] += i >= p && i < f ? l[s][b][m] * xs[i] : T(0);
+            }
+        }
+    }
+#pragma unroll
+    for (int q = kBlocks - 1; q >= 0; --q) {
+        if (q >= nq) continue;   // uniform over the workgroup
+        const int kb = 16 * q, bw = min(16, p - kb);
+        if (wave == (q & 3)) {
+            T a = acc[q >> 2];
+            a += __shfl_xor(a, 16);
+            a += __shfl_xor(a, 32);
+            T x = yd[q >> 2] - a;
+#pragma unroll
+            for (int u = 15; u > 0; --u) x -= z[q >> 2][u] * rowbcast_n(x, u);
+            if (lane < bw) {
+                xs[kb + lane] = x;
+                X[first + kb + lane] = x;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            if (wave + 4 * s >= q) continue;   // uniform
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const int i = kb + 4 * m + g;
+                acc[s] += i < p ? l[s][q][m] * xs[i] : T(0);
+            }
+        }
+    }
+}
+
+template <typename T, bool kPanels, bool kWg>
+__global__ __launch_bounds__(256, kPanels || kWg ? 2 : 4) void k_bwd1(const PanelTask* __restrict__ pt, int np,
                                                  const SmallTask* __restrict__ st, int ns, const int* __restrict__ rows,
                                                  const T* __restrict__ F, const T* __restrict__ Zbuf,
                                                  const T* __restrict__ D, const T* __restrict__ Y2, T* __restrict__ X,
@@ -1623,8 +1711,12 @@ __global__ __launch_bounds__(256, kPanels ? 2 : 4) void k_bwd1(const PanelTask* 
     const int b = blockIdx.x;
     if (kPanels && b < np) {
         bwd_panels1<T>(pt + b, rows, F, Zbuf, D, Y2, X, pw, pr);
+        return;
+    }
+    __shared__ T xs[kWg ? 1 : 4][kSmallMax];
+    if (kWg) {
+        bwd_front1_wg<T>(st + (b - np), rows, F, D, Y2, X, xs[0], threadIdx.x);
     } else {
-        __shared__ T xs[4][kSmallMax];
         const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), t = 4 * (b - np) + wave;
         if (t < ns) bwd_front1<T>(st + t, rows, F, D, Y2, X, xs[wave], threadIdx.x & 63);
     }
@@ -2696,6 +2788,9 @@ void launch_permute_out(const DevPlan& d, const T* X, int nrhs, double* Xo, int6
 // small fronts' own kernel keeps twice as many waves in flight, and they are then
 // bound by that rather than by the launch.
 constexpr int kSplitSmall = 1024;
+// Up to this many small fronts in a backward step get a workgroup each (two fit a
+// CU at once): launches of 5 to 304 fronts at order 20k 8 to 12 us by waves, 3.8 to 9.2.
+constexpr int kWgSmall = 512;
 
 template <typename T>
 void launch_fwd(bool many, const PanelTask* pt, int np, const SmallTask* sm, int ns, const int* gat, const T* F,
@@ -2717,9 +2812,11 @@ void launch_bwd(bool many, const PanelTask* pt, int np, const SmallTask* sm, int
         launch_bwd<T>(many, pt, 0, sm, ns, rows, F, Z, D, Y2, X, pw, pr, st);
         ns = 0;
     }
-    const int grid = np + (ns + 3) / 4;
+    const bool wg = !many && ns <= kWgSmall;
+    const int grid = np + (wg ? ns : (ns + 3) / 4);
     if (grid <= 0) return;
-    auto k = np > 0 ? (many ? k_bwd16<T, true> : k_bwd1<T, true>) : (many ? k_bwd16<T, false> : k_bwd1<T, false>);
+    auto k = np > 0 ? (many ? k_bwd16<T, true> : wg ? k_bwd1<T, true, true> : k_bwd1<T, true, false>)
+                    : (many ? k_bwd16<T, false> : wg ? k_bwd1<T, false, true> : k_bwd1<T, false, false>);
     launch(k, dim3(grid), dim3(256), 0, st, pt, np, sm, ns, rows, F, Z, D, Y2, X, pw, pr);
 }
 
