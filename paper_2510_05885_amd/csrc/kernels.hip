@@ -641,8 +641,6 @@ __global__ __launch_bounds__(256) void k_thresholds(const int* __restrict__ sys_
 // barriers each: 36..45 us for a lone front of order 65..128, 20 us for
 // one of 33..64 (order 20k).  Bound by latency: about six dependent trips to
 // memory, then the pivots (1.2 us per 16).
-// Z_qq = L_qq^-1 of each 16-column sub-panel goes, transposed, into the
-// strictly upper triangle of its diagonal block, for the solves.
 constexpr int kKidBatch = 4;   // children whose maps are in LDS at a time
 
 // Leading dimension of the strip: 16 mod 32 elements, see kDiagLd.
@@ -811,7 +809,6 @@ __global__ __launch_bounds__(64 * NW, NW > 1 ? 2 : 1) void k_front(FrontPlan d, 
                 const int idx = NW * t + wave, ti = tile_row<NT>(idx), tj = tile_col<NT>(idx);
                 if (tj > q && ti < nt) diag_apply<T>(acc[t], S, ld, dv, q - 1, ti, tj, lr, lk);
             }
-            if (wave == NW - 1) diag_inv16<T>(S, ld, q - 1, lane);
         }
         front_sync<NW>();
         if (q + 1 < nq) {
@@ -841,14 +838,14 @@ __global__ __launch_bounds__(64 * NW, NW > 1 ? 2 : 1) void k_front(FrontPlan d, 
             }
         }
     }
-    if (wave == NW - 1) diag_inv16<T>(S, ld, nq - 1, lane);
     if (tid == 0) {
         add_inertia(d.inertia_part, tk->sys, cnt, tk->s);
         if (bad) atomicOr(d.nonfinite, kNonfiniteFactor);
     }
     for (int k = tid; k < p; k += kThreads) D[first + k] = dv[k];
     front_sync<NW>();
-    // L with Z^T above it: column j from the top of its diagonal block
+    // column j of L from the top of its diagonal block (what is above the diagonal
+    // is not read before k_front_inverse writes it)
     T* __restrict__ L = F + tk->L_off;
     for (int j = wave; j < p; j += NW)
         for (int i = (j & ~15) + lane; i < f; i += 64) L[i + (int64_t)j * f] = S[i + j * ld];
@@ -2189,6 +2186,38 @@ __global__ __launch_bounds__(256, kPanels ? 2 : 3) void k_bwd16(const PanelTask*
     }
 }
 
+// Z_qq = L_qq^-1 of every 16-column sub-panel of the small fronts, transposed into
+// the strictly upper triangle of its diagonal block: a wave a front, 16 lanes a
+// sub-panel (lane % 16 = row of Z, as in diag_inv16).  Only the sweeps of several
+// right-hand sides apply it, so the first of them after a factorization forms it
+// (grid of 2000: 4 us); formed in k_front it took 1.3 us a sub-panel of each lone
+// front's chain, and a tenth of the launches that fill the card.
+template <typename T>
+__global__ __launch_bounds__(256) void k_front_inverse(const SmallTask* __restrict__ tasks, int n, T* __restrict__ F) {
+    const int t = 4 * blockIdx.x + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (t >= n) return;
+    const int lane = threadIdx.x & 63, j = lane & 15, p = tasks[t].p, f = tasks[t].f;
+    T* __restrict__ L = F + tasks[t].L_off;
+    for (int k0 = 0; k0 < p; k0 += 64) {
+        const int o = k0 + (lane & ~15), bw = min(16, p - o);   // <= 0: no sub-panel
+        T l[15], z[16];
+#pragma unroll
+        for (int u = 0; u < 15; ++u) {
+            const bool in = j > u && j < bw;
+            l[u] = in ? L[(o + j) + (int64_t)(o + u) * f] : T(0);
+        }
+#pragma unroll
+        for (int u = 0; u < 16; ++u) z[u] = (u == j) ? T(1) : T(0);
+#pragma unroll
+        for (int u = 0; u < 15; ++u)
+#pragma unroll
+            for (int v = 0; v <= u; ++v) z[v] = __builtin_fma(-l[u], rowbcast_n(z[v], u), z[v]);
+#pragma unroll
+        for (int u = 0; u < 15; ++u)
+            if (j > u && j < bw) L[(o + u) + (int64_t)(o + j) * f] = z[u];
+    }
+}
+
 // P = -Z2 L21 Z1 and P^T of one panel pair (64 x 64 each, column-major), by the
 // workgroup: wave w forms columns 16 w .. 16 w + 15 of L21 Z1, keeps them as the second
 // operand, and multiplies by -Z2.  One launch after the factorization, for all pairs.
@@ -2762,6 +2791,11 @@ void launch_large_dstep(const DevPlan& d, const LargeTask* dtasks, int nd, const
 }
 
 template <typename T>
+void launch_front_inverse(const SmallTask* tasks, int n, T* F, hipStream_t st) {
+    if (n > 0) launch(k_front_inverse<T>, dim3(blocks_for(n, 4)), dim3(256), 0, st, tasks, n, F);
+}
+
+template <typename T>
 void launch_pair_inverse(const PairTask* tasks, int count, const T* F, T* M, hipStream_t st) {
     if (count > 0) launch(k_pair_inverse<T>, dim3(count), dim3(256), 0, st, tasks, F, M);
 }
@@ -2894,6 +2928,7 @@ hipError_t configure_kernels(int max_dynamic_lds) {
     template void launch_large_panel<T>(const LargeTask*, int, T*, const T*, const T*, hipStream_t);               \
     template void launch_large_dstep<T>(const DevPlan&, const LargeTask*, int, const LargeTask*, int, T*, T*, T*,  \
                                         hipStream_t);                                                              \
+    template void launch_front_inverse<T>(const SmallTask*, int, T*, hipStream_t);                                 \
     template void launch_pair_inverse<T>(const PairTask*, int, const T*, T*, hipStream_t);                         \
     template void launch_permute_in<T>(const DevPlan&, const double*, int64_t, int64_t, int, T*, hipStream_t);     \
     template void launch_permute_out<T>(const DevPlan&, const T*, int, double*, int64_t, hipStream_t);             \
