@@ -666,8 +666,10 @@ __device__ __forceinline__ void front_sync() {
     else wave_fence();
 }
 
+// Waves a SIMD: without a bound the one-wave forms took 281 and 177 registers, one
+// and two waves; the launches of orders 33..64 at order 500k 312 us, so 250.
 template <typename T, int NT, int NW>
-__global__ __launch_bounds__(64 * NW, NW > 1 ? 2 : 1) void k_front(FrontPlan d, const FrontTask* __restrict__ tasks,
+__global__ __launch_bounds__(64 * NW, NW > 1 || NT > 2 ? 2 : 3) void k_front(FrontPlan d, const FrontTask* __restrict__ tasks,
                                                                const double* __restrict__ K, T* __restrict__ F,
                                                                T* __restrict__ D) {
     constexpr int kThreads = 64 * NW, kTiles = NT * (NT + 1) / 2, kSlots = (kTiles + NW - 1) / NW, kRows = 16 * NT;
