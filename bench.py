@@ -56,15 +56,15 @@ GATE_OMEGA, GATE_CW = 1e-10, 1e-14
 # counter reads for a device copy of known size (--calibrate-copy).  Valid
 # only for the kernel source they were taken on: null once kernels.hip
 # changes.  Source: profiles/pmc_traffic_opf_n500k_fp64.txt.
-TRAFFIC = {"kernels_sha1": "285e1ff0933adfa82a4a7604290efaa9c075223b", "fetch_scale": 2.00, "write_scale": 1.00,
-           "kib": {"solve_sweeps": (4396.6, 243.8),
-                   "large_update_mfma": (13925.2, 19711.9),
-                   "large_panel": (4004.2, 6316.4),
-                   "large_diag": (1686.2, 6757.1),
-                   "large_assembly": (26963.9, 51086.1),
-                   "small_fronts": (12885.4, 15669.7),
-                   "assemble": (125435.2, 25216.0),
-                   "residual": (64327.6, 2229.9)}}
+TRAFFIC = {"kernels_sha1": "812d4a708b348fe935d19ab91d42bc80eb294b73", "fetch_scale": 2.00, "write_scale": 1.00,
+           "kib": {"solve_sweeps": (6386.8, 385.7),
+                   "large_update_mfma": (13833.2, 19663.1),
+                   "large_panel": (3968.8, 6303.1),
+                   "large_diag": (2085.3, 5609.8),
+                   "large_assembly": (26964.0, 51086.0),
+                   "small_fronts": (12373.6, 19073.4),
+                   "assemble": (217160.1, 51850.0),
+                   "residual": (65643.6, 2261.4)}}
 
 
 def kernels_sha1():
@@ -424,7 +424,7 @@ def kernel_breakdown(tm, refactors):
             row["traffic_over_algorithmic"] = traffic / (alg_bytes / n[cls])
         rows.append(row)
 
-    add("small_fronts", "k_small_fronts/k_tiny_fronts<double> (LDS fronts, MFMA trailing updates)",
+    add("small_fronts", "k_front<double> (fronts of order up to 128, tiles in MFMA accumulators)",
         tm["small_flops"], "mfma", "TFLOP/s", PEAK["fp64_mfma_TFs"])
     add("large_update_mfma", "k_large_dstep<double> (trailing-update 64x64 tiles on v_mfma_f64_16x16x4, beside "
         "the next panel's diagonal blocks)", tm["update_flops"], "mfma", "TFLOP/s", PEAK["fp64_mfma_TFs"])
@@ -433,10 +433,10 @@ def kernel_breakdown(tm, refactors):
     add("large_panel", "k_large_panel<double> (panel solve, v_mfma_f64_16x16x4)", tm["panel_flops"], "mfma",
         "TFLOP/s", PEAK["fp64_mfma_TFs"])
     add("large_assembly", "k_large_asm<double> (front assembly, extend-add)", None, "hbm", "GB/s", PEAK["hbm_GBs"])
-    add("solve_sweeps", "k_fwd_P/S + k_bwd_P/S<double> (triangular sweeps: panel steps, one-wave fronts)",
+    add("solve_sweeps", "k_fwd1 + k_bwd1<double> (triangular sweeps: panel pairs, small fronts)",
         tm["solve_bytes"], "hbm", "GB/s",
         PEAK["hbm_GBs"], tm["solve_bytes"])
-    add("assemble", "k_assemble + norms (K = W + Sigma + rho J^T J)", tm["assemble_bytes"], "hbm", "GB/s",
+    add("assemble", "k_assemble (K = W + Sigma + rho J^T J, and its norms)", tm["assemble_bytes"], "hbm", "GB/s",
         PEAK["hbm_GBs"], tm["assemble_bytes"])
     add("residual", "k_residual (b - Kx, FP64)", None, "hbm", "GB/s", PEAK["hbm_GBs"])
     return rows
