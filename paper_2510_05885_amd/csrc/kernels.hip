@@ -1555,7 +1555,10 @@ __device__ __forceinline__ void bwd_panels1(const PanelTask* tk, const int* __re
 // (column, row group g of four); the groups' sums meet by lane exchange, then
 // the sub-panel's transposed triangle is substituted within each 16-lane row.
 // A sub-panel's operands are loaded before the one after it is finished, the
-// first ones before x is gathered.
+// first ones before x is gathered.  Each load takes pieces of 16 columns, 16 lines
+// of the cache, so rows and columns past the front are skipped, not clamped: with
+// 31 loads a sub-panel whatever its size the lowest levels of order 500k took 42 us a
+// launch, so 22.
 template <typename T>
 __device__ __forceinline__ void bwd_front1(const SmallTask* tk, const int* __restrict__ rows, const T* __restrict__ F,
                                            const T* __restrict__ D, const T* __restrict__ Y2, T* __restrict__ X,
@@ -1568,11 +1571,14 @@ __device__ __forceinline__ void bwd_front1(const SmallTask* tk, const int* __res
         const int bw = min(16, p - kb), c = kb + min(t, bw - 1), base = kb + bw;
         const T* __restrict__ Lc = L + (int64_t)c * f;
 #pragma unroll
-        for (int m = 0; m < 16; ++m) l[m] = Lc[min(base + 4 * m + g, f - 1)];
+        for (int m = 0; m < 16; ++m) {
+            l[m] = T(0);
+            if (base + 4 * m < f) l[m] = Lc[min(base + 4 * m + g, f - 1)];   // uniform
+        }
 #pragma unroll
         for (int u = 1; u < 16; ++u) {
-            const T x = Lc[kb + min(u, bw - 1)];
-            z[u] = u > t && u < bw ? x : T(0);
+            z[u] = T(0);
+            if (u < bw) z[u] = Lc[kb + u];   // uniform; masked where it is used
         }
         yd = Y2[first + c] * (T(1) / D[first + c]);
     };
@@ -1586,7 +1592,7 @@ __device__ __forceinline__ void bwd_front1(const SmallTask* tk, const int* __res
 #pragma unroll
         for (int m = 0; m < 16; ++m) {
             const int i = base + 4 * m + g;
-            acc += i < f ? l[m] * xs[min(i, kSmallMax - 1)] : T(0);
+            if (base + 4 * m < f) acc += i < f ? l[m] * xs[min(i, kSmallMax - 1)] : T(0);   // uniform
         }
         if (base + 64 < f) {   // uniform: orders above 64
             const T* __restrict__ Lc = L + (int64_t)(kb + min(t, bw - 1)) * f;
@@ -1603,7 +1609,7 @@ __device__ __forceinline__ void bwd_front1(const SmallTask* tk, const int* __res
         acc += __shfl_xor(acc, 32);
         T x = yd - acc;
 #pragma unroll
-        for (int u = 15; u > 0; --u) x -= z[u] * rowbcast_n(x, u);
+        for (int u = 15; u > 0; --u) x -= (u > t ? z[u] : T(0)) * rowbcast_n(x, u);
         if (kb > 0) load(kb - 16);
         if (lane < bw) {
             xs[kb + lane] = x;
