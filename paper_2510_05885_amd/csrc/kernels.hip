@@ -720,6 +720,8 @@ __global__ __launch_bounds__(64 * NW, NW > 1 || NT > 2 ? 2 : 3) void k_front(Fro
     for (int u = 0; u < kE; ++u)
         if (tid + kThreads * u < kn) S[(rc[u] & 255) + (rc[u] >> 8) * ld] = kv[u];
     for (int e = tid + kThreads * kE; e < kn; e += kThreads) S[(krc[e] & 255) + (krc[e] >> 8) * ld] = (T)K[kc[e]];
+    // K's entries come from any thread, and the owner of a tile adds to them below
+    front_sync<NW>();
     acc_t acc[kSlots];
 #pragma unroll
     for (int t = 0; t < kSlots; ++t) acc[t] = acc_t{0, 0, 0, 0};
