@@ -739,7 +739,7 @@ __global__ __launch_bounds__(64 * NW, NW > 1 || NT > 2 ? 2 : 3) void k_front(Fro
             unsigned long long ok = 0;
 #pragma unroll
             for (int t = 0; t < kSlots; ++t) {
-                const int idx = NW * t + wave;
+                const int idx = min(NW * t + wave, kTiles - 1);   // (a slot past the last tile is not used)
                 const int a = (int8_t)mrow[k][16 * tile_row<NT>(idx) + lr];   // -1: none
                 const unsigned int b4 = *reinterpret_cast<const unsigned int*>(&mcol[k][16 * tile_col<NT>(idx) + 4 * lk]);
 #pragma unroll

@@ -57,3 +57,20 @@ def test_dense_first_subpanel(order, children, precision):
     tree.add(16, mid[16:])
     tree.add(root)
     _check(tree, precision)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_ir"])
+@pytest.mark.parametrize("children", [0, 1, 4, 5])
+@pytest.mark.parametrize("order", [65, 80, 81, 96])
+def test_dense_first_subpanel_of_21_tiles(order, children, precision):
+    """The same in launches whose largest front has 65 to 96 rows: 21 tiles in the 24 slots of four waves."""
+    rng = np.random.default_rng(order + children)
+    root = 200
+    mid = np.concatenate([np.arange(16), 16 + _below(rng, root, order - 16)])
+    tree = Tree(16 + root)
+    for k in range(children):
+        tree.add(17 + k, mid[_below(rng, order, 24)])
+    tree.add(16, 16 + _below(rng, root, order - 16))
+    tree.add(16, mid[16:])
+    tree.add(root)
+    _check(tree, precision)
