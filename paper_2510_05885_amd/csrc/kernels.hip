@@ -39,26 +39,11 @@ __device__ __forceinline__ double to_d(float x) { return (double)x; }
 
 // Static-pivot thresholds of one system (Sec. 3.1): p for pivots of the
 // primal block, n for pivots of the dual block (equal unless the thresholds
-// are block-scaled); inv: the reciprocal of the replacement pivot +p or -n.
-template <typename T>
+// are block-scaled).
 struct PivThr {
     double p, n;
     __device__ PivThr(const double* sys_thr, int sys) : p(sys_thr[2 * sys]), n(sys_thr[2 * sys + 1]) {}
-    __device__ __forceinline__ T inv(int sign) const { return sign > 0 ? T(1) / (T)p : -(T(1) / (T)n); }
 };
-
-// Static-pivot rule (Sec. 3.1): returns the pivot to use; flags perturbation.
-// |d| < t (strict) with t the threshold of the pivot's block is replaced by +t
-// for a primal pivot and by -t for a dual one.
-template <typename T>
-__device__ __forceinline__ T static_pivot(T d, const PivThr<T>& th, int sign, bool& perturbed, bool& bad) {
-    const double dd = to_d(d);
-    const double t = sign > 0 ? th.p : th.n;
-    bad = !isfinite(dd);
-    perturbed = fabs(dd) < t;
-    if (perturbed) return (T)(sign > 0 ? t : -t);
-    return d;
-}
 
 // Adds a workgroup's pivot counts to one of the system's partial counters
 // (many fronts finish at once; one shared counter would serialize them).
@@ -150,107 +135,78 @@ __device__ __forceinline__ T rowbcast_n(T v, int u) {   // u: a compile-time con
     }
 }
 
-// The pivots of one 16-column sub-panel, all above the static-pivot threshold:
-// right-looking LDL^T of the 16 x 16 diagonal block with, for kExt, one more
-// row per lane below it.  rp: row lane % 16 of the diagonal block, the same in
-// each 16-lane row of the wave, so that the pivot and the multipliers of the
-// other columns come from lane t and u of the lane's own row by DPP (one
-// instruction, against two readlanes through scalar registers); x: the lane's
-// own row below.  On return both hold L, and dk the pivot of row lane % 16.
-// The next pivot's column is updated first, so that its reciprocal runs under
-// the other columns' updates.  The chain was bound by the issue of ~45
-// instructions per pivot (290 cycles, against ~65 of dependent latency); the
-// threshold test is left to the caller, once for all 16 pivots.
+// The pivots of one 16-column sub-panel: right-looking LDL^T of the 16 x 16
+// diagonal block with one more row per lane below it, by the static-pivot rule of
+// Sec. 3.1: a pivot |d| < t (strict), t the threshold of its block, becomes +t for a
+// primal pivot and -t for a dual one (bit t of dual).  rp: row lane % 16 of the
+// diagonal block, the same in each 16-lane row of the wave, so that the pivots'
+// reciprocals and the multipliers of the other columns come from lane t and u of the
+// lane's own row by DPP (one instruction, against two readlanes through scalar
+// registers); x: the lane's own row below.  On return both hold L, dk the pivot of
+// row lane % 16 and pk whether it was replaced.  The next pivot's column is updated
+// first, so that its reciprocal runs under the other columns' updates.
+// The chain is bound by the issue of ~45 instructions per pivot (290 cycles, against
+// ~65 of dependent latency), so each lane applies the rule to its own row's pivot
+// with its own threshold: one comparison and a select before the broadcast.  (One
+// test after all 16 pivots, against the larger threshold, and a sub-panel that failed
+// it done again pivot by pivot in LDS: a stabilized OPF factorization of order 8k
+// took 927 us with the absolute rule, 1618 with the block rule and 1568 with the
+// global one, so 909, 913 and 909.  The rule on the broadcast pivot, with the
+// thresholds in scalar registers: 2.5 to 5 per cent longer factorizations.)
 // Pivots t >= bw are skipped.
-template <typename T, bool kExt>
-__device__ __forceinline__ void pivots16(T (&rp)[16], T (&x)[16], T& dk, int bw, int li) {
-    T d = rowbcast_n(rp[0], 0);
-    T inv = fast_rcp(d);
+template <typename T>
+__device__ __forceinline__ void pivots16(T (&rp)[16], T (&x)[16], T& dk, bool& pk, int bw, PivThr thr,
+                                         unsigned int dual, int li) {
+    const bool n = dual >> li & 1u;
+    const double tl = n ? thr.n : thr.p;
+    const T rl = (T)(n ? -tl : tl), il = T(1) / rl;
+    auto reciprocal = [&](T d) {
+        const T r = fast_rcp(d);
+        return fabs(to_d(d)) < tl ? il : r;
+    };
+    T inv = rowbcast_n(reciprocal(rp[0]), 0);
     dk = T(1);
 #pragma unroll
     for (int t = 0; t < 16; ++t) {
         if (t >= bw) continue;   // uniform
-        const T dt = d;
         const T l = rp[t] * inv;
-        const T lx = kExt ? x[t] * inv : T(0);
+        const T lx = x[t] * inv;
         if (t + 1 < 16) {
             const T c = rowbcast_n(rp[t], t + 1);
             rp[t + 1] -= l * c;
-            if (kExt) x[t + 1] -= lx * c;
-            d = rowbcast_n(rp[t + 1], t + 1);
-            inv = fast_rcp(d);
+            x[t + 1] -= lx * c;
+            inv = rowbcast_n(reciprocal(rp[t + 1]), t + 1);
         }
 #pragma unroll
         for (int u = t + 2; u < 16; ++u) {
             const T c = rowbcast_n(rp[t], u);
             rp[u] -= l * c;
-            if (kExt) x[u] -= lx * c;
+            x[u] -= lx * c;
         }
-        dk = li == t ? dt : dk;
+        dk = li == t ? rp[t] : dk;
         rp[t] = l;
-        if (kExt) x[t] = lx;
-    }
-    // x is updated here, not where the caller comes to use it: that would hold
-    // all 120 broadcasts in registers until then
-    if (kExt)
+        x[t] = lx;
+        // x is updated here, not where the caller comes to use it: that would hold
+        // all 120 broadcasts in registers until then
+        if ((t & 3) == 3)
 #pragma unroll
-        for (int t = 0; t < 16; ++t) asm volatile("" : "+v"(x[t]));
-}
-
-// Whether every pivot dk of a sub-panel's first bw (lane % 16 < bw) is finite
-// and at or above the larger threshold, so that the static-pivot rule of
-// Sec. 3.1 keeps them all; and their counts (positive, negative, zero).
-template <typename T>
-__device__ __forceinline__ bool pivots_plain(T dk, const PivThr<T>& thr, int bw, int lane, unsigned int* n3) {
-    const double a = fabs(to_d(dk));
-    const bool in = lane < bw;
-    const bool ok = a >= thr.p && a >= thr.n && isfinite(a);
-    if (__ballot(in && !ok) != 0ULL) return false;
-    n3[0] = __popcll(__ballot(in && to_d(dk) > 0.0));
-    n3[1] = __popcll(__ballot(in && to_d(dk) < 0.0));
-    n3[2] = __popcll(__ballot(in && to_d(dk) == 0.0));
-    return true;
-}
-
-// A sub-panel with a pivot that the static-pivot rule replaces (or a
-// non-finite one), by one wave straight in LDS, pivot by pivot: columns kb ..
-// kb + bw of the rows kb .. f - 1 of A.  Bit t of neg: pivot t takes the
-// negative sign.  Each entry takes the operations of pivots16 in the same
-// order.  Rolled on purpose: it is rare, and must not set the register budget
-// of the kernels around it.  Counts pivots t < bcount.
-template <typename T>
-__device__ __forceinline__ void subpanel_by_pivot(T* A, int lda, int f, int kb, int bw, int bcount, unsigned int neg,
-                                                  T* dv, const PivThr<T>& thr, int lane, unsigned int* cnt,
-                                                  bool& bad_any) {
-#pragma unroll 1
-    for (int t = 0; t < bw; ++t) {
-        T* col = A + (kb + t) * lda;
-        bool pert, bad;
-        const int sg = (neg >> t & 1u) ? -1 : 1;
-        const T draw = col[kb + t];
-        const T inv0 = fast_rcp(draw);
-        const T dk = static_pivot(draw, thr, sg, pert, bad);
-        const T inv = pert ? thr.inv(sg) : inv0;
-#pragma unroll 1
-        for (int i = kb + t + 1 + lane; i < f; i += 64) {
-            const T l = col[i] * inv;
-#pragma unroll 1
-            for (int u = t + 1; u < bw && kb + u <= i; ++u) A[i + (kb + u) * lda] -= l * col[kb + u];
-        }
-        wave_fence();   // every row has taken the unscaled column
-#pragma unroll 1
-        for (int i = kb + t + 1 + lane; i < f; i += 64) col[i] *= inv;
-        if (lane == 0) {
-            col[kb + t] = dk;
-            dv[kb + t] = dk;
-            if (t < bcount) {
-                const double dd = to_d(dk);
-                cnt[0] += dd > 0.0; cnt[1] += dd < 0.0; cnt[2] += dd == 0.0; cnt[3] += pert;
-                bad_any |= bad;
-            }
-        }
-        wave_fence();
+            for (int u = 0; u < 16; ++u) asm volatile("" : "+v"(x[u]));
     }
+#pragma unroll
+    for (int t = 0; t < 16; ++t) asm volatile("" : "+v"(x[t]));   // (bw < 16)
+    pk = fabs(to_d(dk)) < tl;
+    dk = pk ? rl : dk;
+}
+
+// Counts of a sub-panel's first bw pivots (lane % 16 < bw): positive, negative,
+// zero, replaced; and whether one is not finite.
+template <typename T>
+__device__ __forceinline__ void count_pivots(T dk, bool pk, int bw, int lane, unsigned int* cnt, bool& bad) {
+    const bool in = lane < bw;
+    const unsigned int a = __popcll(__ballot(in && to_d(dk) > 0.0)), b = __popcll(__ballot(in && to_d(dk) < 0.0)),
+                       c = __popcll(__ballot(in && to_d(dk) == 0.0)), e = __popcll(__ballot(in && pk));
+    bad |= __ballot(in && !isfinite(to_d(dk))) != 0ULL;
+    cnt[0] += a; cnt[1] += b; cnt[2] += c; cnt[3] += e;
 }
 
 // ---- one diagonal block of a large front ---------------------------------
@@ -361,7 +317,7 @@ __device__ __forceinline__ void diag_zrow(const typename Mfma<T>::acc_t& S, T* B
 // free on entry; ends with a barrier.
 template <typename T>
 __device__ __forceinline__ void diag_factor(typename Mfma<T>::acc_t (&acc)[3], T* B, T* dv,
-                                            unsigned long long negmask, int w, const PivThr<T>& thr,
+                                            unsigned long long negmask, int w, PivThr thr,
                                             unsigned int* cnt, bool& bad_out, int tid) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int lr = lane & 15, lk = lane >> 4;
@@ -392,30 +348,24 @@ __device__ __forceinline__ void diag_factor(typename Mfma<T>::acc_t (&acc)[3], T
             const int row = kb + 16 + lane;
             const int rowc = min(row, kPanel - 1);
             T rp[16], x[16], dk;
+            bool pk;
 #pragma unroll
             for (int t = 0; t < 16; ++t) {
                 rp[t] = B[(kb + lr) + (kb + t) * kDiagLd];
                 x[t] = B[rowc + (kb + t) * kDiagLd];
             }
-            pivots16<T, true>(rp, x, dk, 16, lr);
-            unsigned int n3[3];
-            if (pivots_plain(dk, thr, min(16, w - kb), lane, n3)) {
-                // the diagonal block's upper triangle takes scratch values: it
-                // is written as Z before it is read
-                if (row < kPanel)
+            pivots16(rp, x, dk, pk, 16, thr, (unsigned int)(negmask >> kb) & 0xffffu, lr);
+            // the diagonal block's upper triangle takes scratch values: it
+            // is written as Z before it is read
+            if (row < kPanel)
 #pragma unroll
-                    for (int t = 0; t < 16; ++t) B[row + (kb + t) * kDiagLd] = x[t];
-                if (lane < 16) {
+                for (int t = 0; t < 16; ++t) B[row + (kb + t) * kDiagLd] = x[t];
+            if (lane < 16) {
 #pragma unroll
-                    for (int t = 0; t < 16; ++t) B[(kb + lane) + (kb + t) * kDiagLd] = rp[t];
-                    dv[kb + lane] = dk;
-                }
-                if (lane == 0)
-                    for (int k = 0; k < 3; ++k) cnt[k] += n3[k];
-            } else {
-                subpanel_by_pivot(B, kDiagLd, kPanel, kb, 16, w - kb, (unsigned int)(negmask >> kb) & 0xffffu, dv,
-                                  thr, lane, cnt, bad_any);
+                for (int t = 0; t < 16; ++t) B[(kb + lane) + (kb + t) * kDiagLd] = rp[t];
+                dv[kb + lane] = dk;
             }
+            count_pivots(dk, pk, min(16, w - kb), lane, cnt, bad_any);
         } else if (q > 0) {
 #pragma unroll
             for (int t = 0; t < 3; ++t)
@@ -674,6 +624,7 @@ __global__ __launch_bounds__(64 * NW, NW > 1 || NT > 2 ? 2 : 3) void k_front(Fro
                                                                T* __restrict__ D) {
     constexpr int kThreads = 64 * NW, kTiles = NT * (NT + 1) / 2, kSlots = (kTiles + NW - 1) / NW, kRows = 16 * NT;
     constexpr int kE = NW > 1 ? 2 : NT;   // K entries a thread holds from the start
+    constexpr int kSigns = NT > 4 ? 2 : 1;
     typedef typename Mfma<T>::acc_t acc_t;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     T* S = reinterpret_cast<T*>(smem_raw);
@@ -696,7 +647,11 @@ __global__ __launch_bounds__(64 * NW, NW > 1 || NT > 2 ? 2 : 3) void k_front(Fro
         rc[u] = krc[ec];
         kv[u] = (T)K[kc[ec]];
     }
-    const PivThr<T> thr(d.sys_thr, tk->sys);
+    const PivThr thr(d.sys_thr, tk->sys);
+    // the pivots' signs, 64 a word (the last pivot's repeated)
+    int8_t sg[kSigns];
+#pragma unroll
+    for (int u = 0; u < kSigns; ++u) sg[u] = d.piv_sign[first + min(64 * u + lane, p - 1)];
     // the maps of children kid .. kid + kKidBatch - 1; columns in the order in
     // which a lane's accumulator items take them
     auto load_maps = [&](int kid) {
@@ -757,11 +712,15 @@ __global__ __launch_bounds__(64 * NW, NW > 1 || NT > 2 ? 2 : 3) void k_front(Fro
                 for (int r = 0; r < 4; ++r) acc[t][r] += (ok >> (4 * t + r) & 1ULL) ? v[t][r] : T(0);
         }
     }
+    unsigned long long negs[kSigns];
+#pragma unroll
+    for (int u = 0; u < kSigns; ++u) negs[u] = __ballot(sg[u] < 0);
     unsigned int cnt[4] = {0, 0, 0, 0};
     bool bad = false;
 #pragma unroll 1
     for (int q = 0; q < nq; ++q) {
         const int kb = 16 * q, bw = min(16, p - kb);
+        const unsigned int neg = (unsigned int)(negs[kb < 64 ? 0 : kSigns - 1] >> (kb & 63)) & 0xffffu;
 #pragma unroll
         for (int t = 0; t < kSlots; ++t) {
             const int idx = NW * t + wave, ti = tile_row<NT>(idx);
@@ -777,6 +736,7 @@ __global__ __launch_bounds__(64 * NW, NW > 1 || NT > 2 ? 2 : 3) void k_front(Fro
         const int row = kb + 16 + 64 * wave + lane, rowc = min(row, rows - 1);
         const bool act = wave == 0 || (wave == 1 && two);
         T rp[16], x[16], dk = T(0);
+        bool pk;
         if (act) {
 #pragma unroll
             for (int t = 0; t < 16; ++t) {
@@ -786,25 +746,16 @@ __global__ __launch_bounds__(64 * NW, NW > 1 || NT > 2 ? 2 : 3) void k_front(Fro
         }
         if (NW > 1 && two) __syncthreads();   // wave 1 has read the diagonal block that wave 0 overwrites
         if (act) {
-            pivots16<T, true>(rp, x, dk, bw, lr);
-            unsigned int n3[3];
-            if (pivots_plain(dk, thr, bw, lane, n3)) {
+            pivots16(rp, x, dk, pk, bw, thr, neg, lr);
 #pragma unroll
-                for (int t = 0; t < 16; ++t) {
-                    if (t >= bw) continue;   // uniform: columns past the last pivot stay zero
-                    if (row < rows) S[row + (kb + t) * ld] = x[t];
-                    if (wave == 0 && lane < 16) S[(kb + lane) + (kb + t) * ld] = rp[t];
-                }
-                if (wave == 0) {
-                    if (lane < 16) dv[kb + lane] = lane < bw ? dk : T(0);
-                    if (lane == 0)
-                        for (int k = 0; k < 3; ++k) cnt[k] += n3[k];
-                }
-            } else if (wave == 0) {
-                const int8_t sg = lane < bw ? d.piv_sign[first + kb + lane] : 1;
-                if (lane < 16) dv[kb + lane] = T(0);
-                wave_fence();
-                subpanel_by_pivot(S, ld, f, kb, bw, bw, (unsigned int)__ballot(sg < 0), dv, thr, lane, cnt, bad);
+            for (int t = 0; t < 16; ++t) {
+                if (t >= bw) continue;   // uniform: columns past the last pivot stay zero
+                if (row < rows) S[row + (kb + t) * ld] = x[t];
+                if (wave == 0 && lane < 16) S[(kb + lane) + (kb + t) * ld] = rp[t];
+            }
+            if (wave == 0) {
+                if (lane < 16) dv[kb + lane] = lane < bw ? dk : T(0);
+                count_pivots(dk, pk, bw, lane, cnt, bad);
             }
         }
         if (q > 0) {
@@ -1019,7 +970,7 @@ __device__ __forceinline__ void diag_body(const DevPlan& d, const LargeTask* tk,
     const int lr = lane & 15, lk = lane >> 4;
     __builtin_amdgcn_s_setprio(3);   // the launch waits for this chain, not for the tiles beside it
     const int8_t sg = lane < w ? d.piv_sign[first + k0 + lane] : 1;
-    const PivThr<T> thr(d.sys_thr, tk->sys);
+    const PivThr thr(d.sys_thr, tk->sys);
     typename Mfma<T>::acc_t acc[3];
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
