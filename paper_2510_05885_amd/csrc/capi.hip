@@ -94,7 +94,6 @@ struct ncl_kkt_s {
     int *level_list = nullptr, *large_asm = nullptr, *gather = nullptr;
     PanelTask *fwd_tasks = nullptr, *bwd_tasks = nullptr;
     SmallTask* solve_small = nullptr;
-    bool front_z = false;   // k_front_inverse has run on the factor in use
     PairTask* pairs = nullptr;
     LargeTask *large_panel = nullptr, *large_upd = nullptr, *large_diag = nullptr;
     RowChunk* chunks = nullptr;
@@ -626,7 +625,6 @@ void run_factor(ncl_kkt_s* h, hipStream_t st) {
     T* F = pr ? (T*)h->F32 : (T*)h->F64;
     T* D = pr ? (T*)h->D32 : (T*)h->D64;
     T* Mb = pr ? (T*)h->M32 : (T*)h->M64;
-    h->front_z = false;
     if (!h->opt.use_graphs || h->tm.on) {
         factor_fronts<T>(h, F, D, Mb, st);
         return;
@@ -753,14 +751,9 @@ void sweeps(ncl_kkt_s* h, int nrhs, const T* F, const T* Z, const T* D, T* Y, T*
 }
 
 template <typename T>
-void solve_once(ncl_kkt_s* h, const double* B, int64_t si, int64_t sq, double* X, int64_t ldx, int nrhs, T* F,
+void solve_once(ncl_kkt_s* h, const double* B, int64_t si, int64_t sq, double* X, int64_t ldx, int nrhs, const T* F,
                 const T* Z, const T* D, T* Y, T* U, T* partial, hipStream_t st) {
     const DevPlan& d = h->d;
-    if (nrhs > 1 && !h->front_z) {
-        Span sp(h, st, TM_SMALL);
-        launch_front_inverse<T>(h->solve_small, (int)h->P.solve_small.size(), F, st);
-        h->front_z = true;
-    }
     launch_permute_in<T>(d, B, si, sq, nrhs, Y, st);
     const int pr = std::is_same<T, float>::value ? 1 : 0;
     if (!h->opt.use_graphs || h->tm.on) {

@@ -800,7 +800,7 @@ __global__ __launch_bounds__(64 * NW, NW > 1 || NT > 2 ? 2 : 3) void k_front(Fro
     for (int k = tid; k < p; k += kThreads) D[first + k] = dv[k];
     front_sync<NW>();
     // column j of L from the top of its diagonal block (what is above the diagonal
-    // is not read before k_front_inverse writes it)
+    // is not used)
     T* __restrict__ L = F + tk->L_off;
     for (int j = wave; j < p; j += NW)
         for (int i = (j & ~15) + lane; i < f; i += 64) L[i + (int64_t)j * f] = S[i + j * ld];
@@ -1692,16 +1692,17 @@ __device__ __forceinline__ typename Mfma<T>::acc_t rows16(const T* V, int lr, in
     return a;
 }
 
-// Adds the children's update vectors to rows i0 .. i0 + 15 (those < iend) of a front.
-template <typename T>
+// Adds the children's update vectors to rows i0 .. i0 + 15 (those < iend) of a
+// front; row(r): the row of item r, from i0.
+template <typename T, typename Row>
 __device__ __forceinline__ void gather16(typename Mfma<T>::acc_t& a, const T* __restrict__ U,
-                                         const int* __restrict__ gat, int f, int gk, int i0, int iend, int lr, int lk) {
+                                         const int* __restrict__ gat, int f, int gk, int i0, int iend, int lr, Row row) {
     for (int k = 0; k < gk; ++k) {
         int o[4];
         T u[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int i = i0 + Mfma<T>::row(lk, r);
+            const int i = i0 + row(r);
             o[r] = i < iend ? gat[k * f + i] : -1;
         }
 #pragma unroll
@@ -1738,7 +1739,7 @@ __device__ __forceinline__ void fwd_panels16(const PanelTask* tk, const T* __res
             const int i = l0 + Mfma<T>::row(lk, r);
             if (i < w) a[r] = Y[(int64_t)(first + c0 + i) * kNrhsMax + lr];
         }
-        if (gk > 0) gather16<T>(a, U, gat, f, gk, c0 + l0, c0 + w, lr, lk);
+        if (gk > 0) gather16<T>(a, U, gat, f, gk, c0 + l0, c0 + w, lr, [&](int r) { return Mfma<T>::row(lk, r); });
 #pragma unroll
         for (int r = 0; r < 4; ++r) b[(l0 + Mfma<T>::row(lk, r)) * kNrhsMax + lr] = a[r];
     }
@@ -1752,7 +1753,7 @@ __device__ __forceinline__ void fwd_panels16(const PanelTask* tk, const T* __res
                 else if (c0 > 0) a[r] = Us[(int64_t)(i - p) * kNrhsMax + lr];
             }
         }
-        if (gk > 0) gather16<T>(a, U, gat, f, gk, i0, r1, lr, lk);
+        if (gk > 0) gather16<T>(a, U, gat, f, gk, i0, r1, lr, [&](int r) { return Mfma<T>::row(lk, r); });
     }
     // every operand before the first product: Z1, Z2 and P for the wave's 16 rows
     // of y, L for its rows (zero blocks past the diagonal are multiplied too:
@@ -1828,13 +1829,85 @@ __device__ __forceinline__ void fwd_panels16(const PanelTask* tk, const T* __res
     }
 }
 
-// A small front of order up to 16 NT by one wave, all of it in registers.
+// Small fronts hold their pieces in one order for both types: item r of a lane is
+// row 4 r + lk.  The f32 products give it when the lane's row of the first operand
+// is the (4, 4)-transposed one (an involution), and step st contracts rows 4 st + lk.
+template <typename T>
+__device__ __forceinline__ int op_row(int lr) { return sizeof(T) == 8 ? lr : 4 * (lr & 3) + (lr >> 2); }
+
+// The four 16-lane rows of v, each spread over the wave (lane % 16 kept): gfx950's
+// row swaps, a few cycles each against an LDS permute's hundred.
+__device__ __forceinline__ void spread_rows(unsigned int v, unsigned int (&o)[4]) {
+    const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);          // rows 0 0 2 2 and 1 1 3 3
+    const auto b = __builtin_amdgcn_permlane32_swap(a[0], a[0], false, false);    // 0 and 2
+    const auto c = __builtin_amdgcn_permlane32_swap(a[1], a[1], false, false);    // 1 and 3
+    o[0] = b[0]; o[1] = c[0]; o[2] = b[1]; o[3] = c[1];
+}
+__device__ __forceinline__ void spread_rows(float v, float (&o)[4]) {
+    unsigned int u[4];
+    spread_rows(__builtin_bit_cast(unsigned int, v), u);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) o[k] = __builtin_bit_cast(float, u[k]);
+}
+__device__ __forceinline__ void spread_rows(double v, double (&o)[4]) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    unsigned int lo[4], hi[4];
+    spread_rows((unsigned int)b, lo);
+    spread_rows((unsigned int)(b >> 32), hi);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) o[k] = __builtin_bit_cast(double, (unsigned long long)hi[k] << 32 | lo[k]);
+}
+
+// Substitution with a 16 x 16 unit triangle for 16 columns: a (item r: row 4 r + lk)
+// becomes L^-1 a, or, kBack, L^-T a.  Four rows at a time, by every lane for its
+// column, then one product takes them to the other rows.  d: step st's first
+// operand, forward d[st] = L[op_row][4 st + lk], backward d[st] = L[4 st + lk][op_row],
+// zero on and above the diagonal.  With the triangle's explicit inverse (four products
+// a triangle; a solve of 16 columns at order 500k 3710 us, so 3775) the residuals of an
+// OPF of order 625 to 2000 were 1.22 to 1.59 times those of one column at a time, so
+// 1.07 to 1.13.
+template <typename T, bool kBack>
+__device__ __forceinline__ void substitute16(typename Mfma<T>::acc_t& a, const T (&d)[4], int lr, int lk) {
+    const int m = op_row<T>(lr);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int r = kBack ? 3 - q : q;
+        T l[4][4], v[4];   // l: the 4 x 4 triangle, from the lane that holds each entry
+#pragma unroll
+        for (int i = 1; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < i; ++j)
+                l[i][j] = kBack ? bcast(d[r], 16 * i + op_row<T>(4 * r + j)) : bcast(d[r], 16 * j + op_row<T>(4 * r + i));
+        spread_rows(a[r], v);
+        if (!kBack) {
+            v[1] -= l[1][0] * v[0];
+            v[2] -= l[2][0] * v[0];
+            v[3] -= l[3][0] * v[0];
+            v[2] -= l[2][1] * v[1];
+            v[3] -= l[3][1] * v[1];
+            v[3] -= l[3][2] * v[2];
+        } else {
+            v[2] -= l[3][2] * v[3];
+            v[1] -= l[3][1] * v[3];
+            v[0] -= l[3][0] * v[3];
+            v[1] -= l[2][1] * v[2];
+            v[0] -= l[2][0] * v[2];
+            v[0] -= l[1][0] * v[1];
+        }
+        a[r] = lk == 0 ? v[0] : lk == 1 ? v[1] : lk == 2 ? v[2] : v[3];
+        if (q < 3) a = Mfma<T>::run((kBack ? m < 4 * r : m > 4 * r + 3) ? -d[r] : T(0), a[r], a);
+    }
+}
+
+// A small front of order up to 16 NT by one wave, all of it in registers.  Each
+// sub-panel's products are summed from zero before they are added to a piece: added
+// one after the other to a large value they are rounded to its last place each time.
 template <typename T, int NT>
 __device__ __forceinline__ void fwd_front16(const SmallTask* tk, const T* __restrict__ F, const int* __restrict__ gatab,
                                             const T* __restrict__ Y, T* __restrict__ Y2, T* __restrict__ U, int lane) {
     typedef typename Mfma<T>::acc_t acc_t;
     const int first = tk->first, p = tk->p, f = tk->f, gk = tk->gk;
-    const int lr = lane & 15, lk = lane >> 4;
+    const int lr = lane & 15, lk = lane >> 4, m = op_row<T>(lr);
     const T* __restrict__ L = F + tk->L_off;
     T* __restrict__ Us = U + tk->U_off * kNrhsMax;
     acc_t a[NT];
@@ -1843,51 +1916,46 @@ __device__ __forceinline__ void fwd_front16(const SmallTask* tk, const T* __rest
         a[ti] = acc_t{0, 0, 0, 0};
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int i = 16 * ti + Mfma<T>::row(lk, r);
+            const int i = 16 * ti + 4 * r + lk;
             if (i < p) a[ti][r] = Y[(int64_t)(first + i) * kNrhsMax + lr];
         }
-        if (gk > 0) gather16<T>(a[ti], U, gatab + tk->gat, f, gk, 16 * ti, f, lr, lk);
+        if (gk > 0) gather16<T>(a[ti], U, gatab + tk->gat, f, gk, 16 * ti, f, lr, [&](int r) { return 4 * r + lk; });
     }
 #pragma unroll
     for (int q = 0; q < NT; ++q) {
         const int kb = 16 * q, bw = min(16, p - kb);
         if (bw <= 0) break;   // uniform
-        // y = Z_qq b, on the sub-panel's pivots only
-        T z[4];
-#pragma unroll
-        for (int st = 0; st < 4; ++st) {
-            const int k = Mfma<T>::row(lk, st);
-            const T x = L[(kb + min(k, bw - 1)) + (int64_t)(kb + min(lr, bw - 1)) * f];
-            z[st] = lr < bw && k <= lr ? (k == lr ? T(1) : x) : T(0);
-        }
-        acc_t y = {0, 0, 0, 0};
-#pragma unroll
-        for (int st = 0; st < 4; ++st) y = Mfma<T>::run(z[st], a[q][st], y);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int i = Mfma<T>::row(lk, r);
-            if (i < bw) Y2[(int64_t)(first + kb + i) * kNrhsMax + lr] = y[r];
-        }
+        T l[4];
 #pragma unroll
         for (int ti = q; ti < NT; ++ti) {
-            T l[4];
-            const int i = 16 * ti + lr;
+            const int i = 16 * ti + m;
             const T* __restrict__ Li = L + min(i, f - 1);
 #pragma unroll
             for (int st = 0; st < 4; ++st) {
-                const int k = Mfma<T>::row(lk, st);
+                const int k = 4 * st + lk;
                 const T x = Li[(int64_t)(kb + min(k, bw - 1)) * f];
-                l[st] = k < bw && i < f && i >= kb + bw ? -x : T(0);
+                l[st] = k < bw && i < f && (ti > q || m > k) ? x : T(0);
             }
+            if (ti == q) {
+                substitute16<T, false>(a[q], l, lr, lk);
+                continue;
+            }
+            acc_t s = {0, 0, 0, 0};
 #pragma unroll
-            for (int st = 0; st < 4; ++st) a[ti] = Mfma<T>::run(l[st], y[st], a[ti]);
+            for (int st = 0; st < 4; ++st) s = Mfma<T>::run(l[st], a[q][st], s);
+            a[ti] -= s;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 4 * r + lk;
+            if (i < bw) Y2[(int64_t)(first + kb + i) * kNrhsMax + lr] = a[q][r];
         }
     }
 #pragma unroll
     for (int ti = 0; ti < NT; ++ti) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int i = 16 * ti + Mfma<T>::row(lk, r);
+            const int i = 16 * ti + 4 * r + lk;
             if (i >= p && i < f) Us[(int64_t)(i - p) * kNrhsMax + lr] = a[ti][r];
         }
     }
@@ -2070,7 +2138,7 @@ __device__ __forceinline__ void bwd_front16(const SmallTask* tk, const int* __re
                                             int lane) {
     typedef typename Mfma<T>::acc_t acc_t;
     const int first = tk->first, p = tk->p, f = tk->f;
-    const int lr = lane & 15, lk = lane >> 4;
+    const int lr = lane & 15, lk = lane >> 4, m = op_row<T>(lr);
     const T* __restrict__ L = F + tk->L_off;
     acc_t x[NT];
 #pragma unroll
@@ -2078,7 +2146,7 @@ __device__ __forceinline__ void bwd_front16(const SmallTask* tk, const int* __re
         x[ti] = acc_t{0, 0, 0, 0};
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int i = 16 * ti + Mfma<T>::row(lk, r);
+            const int i = 16 * ti + 4 * r + lk;
             if (i >= p && i < f) x[ti][r] = X[(int64_t)rows[tk->rows_off + i] * kNrhsMax + lr];
         }
     }
@@ -2087,15 +2155,17 @@ __device__ __forceinline__ void bwd_front16(const SmallTask* tk, const int* __re
         const int kb = 16 * q, bw = min(16, p - kb);
         if (bw <= 0) continue;   // uniform
         acc_t s = {0, 0, 0, 0};
-        const T* __restrict__ Lc = L + (int64_t)(kb + min(lr, bw - 1)) * f;
+        const T* __restrict__ Lc = L + (int64_t)(kb + min(m, bw - 1)) * f;
+        T d[4];   // the sub-panel's own triangle
 #pragma unroll
         for (int ti = q; ti < NT; ++ti) {
             T l[4];
 #pragma unroll
             for (int st = 0; st < 4; ++st) {
-                const int i = 16 * ti + Mfma<T>::row(lk, st);
+                const int i = 16 * ti + 4 * st + lk;
                 const T e = Lc[min(i, f - 1)];
-                l[st] = lr < bw && i < f && i >= kb + bw ? e : T(0);
+                l[st] = m < bw && i < f && i >= kb + bw ? e : T(0);
+                if (ti == q) d[st] = 4 * st + lk < bw && 4 * st + lk > m ? e : T(0);
             }
 #pragma unroll
             for (int st = 0; st < 4; ++st) s = Mfma<T>::run(l[st], x[ti][st], s);
@@ -2103,25 +2173,16 @@ __device__ __forceinline__ void bwd_front16(const SmallTask* tk, const int* __re
         acc_t v;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int i = kb + min(Mfma<T>::row(lk, r), bw - 1);
-            v[r] = Y2[(int64_t)(first + i) * kNrhsMax + lr] * (T(1) / D[first + i]) - s[r];
+            const int i = 4 * r + lk, ic = kb + min(i, bw - 1);
+            v[r] = i < bw ? Y2[(int64_t)(first + ic) * kNrhsMax + lr] * (T(1) / D[first + ic]) - s[r] : T(0);
         }
-        T z[4];
-#pragma unroll
-        for (int st = 0; st < 4; ++st) {
-            const int u = Mfma<T>::row(lk, st);
-            const T e = L[(kb + min(lr, bw - 1)) + (int64_t)(kb + min(u, bw - 1)) * f];
-            z[st] = lr < bw && u < bw && u >= lr ? (u == lr ? T(1) : e) : T(0);
-        }
-        acc_t xq = {0, 0, 0, 0};
-#pragma unroll
-        for (int st = 0; st < 4; ++st) xq = Mfma<T>::run(z[st], v[st], xq);
+        substitute16<T, true>(v, d, lr, lk);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int i = Mfma<T>::row(lk, r);
+            const int i = 4 * r + lk;
             if (i < bw) {
-                X[(int64_t)(first + kb + i) * kNrhsMax + lr] = xq[r];
-                x[q][r] = xq[r];
+                X[(int64_t)(first + kb + i) * kNrhsMax + lr] = v[r];
+                x[q][r] = v[r];
             }
         }
     }
@@ -2144,38 +2205,6 @@ __global__ __launch_bounds__(256, kPanels ? 2 : 3) void k_bwd16(const PanelTask*
         if (st[t].f <= 32) bwd_front16<T, 2>(st + t, rows, F, D, Y2, X, lane);
         else if (st[t].f <= 64) bwd_front16<T, 4>(st + t, rows, F, D, Y2, X, lane);
         else bwd_front16<T, 8>(st + t, rows, F, D, Y2, X, lane);
-    }
-}
-
-// Z_qq = L_qq^-1 of every 16-column sub-panel of the small fronts, transposed into
-// the strictly upper triangle of its diagonal block: a wave a front, 16 lanes a
-// sub-panel (lane % 16 = row of Z, as in diag_inv16).  Only the sweeps of several
-// right-hand sides apply it, so the first of them after a factorization forms it
-// (grid of 2000: 4 us); formed in k_front it took 1.3 us a sub-panel of each lone
-// front's chain, and a tenth of the launches that fill the card.
-template <typename T>
-__global__ __launch_bounds__(256) void k_front_inverse(const SmallTask* __restrict__ tasks, int n, T* __restrict__ F) {
-    const int t = 4 * blockIdx.x + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    if (t >= n) return;
-    const int lane = threadIdx.x & 63, j = lane & 15, p = tasks[t].p, f = tasks[t].f;
-    T* __restrict__ L = F + tasks[t].L_off;
-    for (int k0 = 0; k0 < p; k0 += 64) {
-        const int o = k0 + (lane & ~15), bw = min(16, p - o);   // <= 0: no sub-panel
-        T l[15], z[16];
-#pragma unroll
-        for (int u = 0; u < 15; ++u) {
-            const bool in = j > u && j < bw;
-            l[u] = in ? L[(o + j) + (int64_t)(o + u) * f] : T(0);
-        }
-#pragma unroll
-        for (int u = 0; u < 16; ++u) z[u] = (u == j) ? T(1) : T(0);
-#pragma unroll
-        for (int u = 0; u < 15; ++u)
-#pragma unroll
-            for (int v = 0; v <= u; ++v) z[v] = __builtin_fma(-l[u], rowbcast_n(z[v], u), z[v]);
-#pragma unroll
-        for (int u = 0; u < 15; ++u)
-            if (j > u && j < bw) L[(o + u) + (int64_t)(o + j) * f] = z[u];
     }
 }
 
@@ -2758,11 +2787,6 @@ void launch_large_dstep(const DevPlan& d, const LargeTask* dtasks, int nd, const
 }
 
 template <typename T>
-void launch_front_inverse(const SmallTask* tasks, int n, T* F, hipStream_t st) {
-    if (n > 0) launch(k_front_inverse<T>, dim3(blocks_for(n, 4)), dim3(256), 0, st, tasks, n, F);
-}
-
-template <typename T>
 void launch_pair_inverse(const PairTask* tasks, int count, const T* F, T* M, hipStream_t st) {
     if (count > 0) launch(k_pair_inverse<T>, dim3(4 * count), dim3(256), 0, st, tasks, F, M);
 }
@@ -2895,7 +2919,6 @@ hipError_t configure_kernels(int max_dynamic_lds) {
     template void launch_large_panel<T>(const LargeTask*, int, T*, const T*, const T*, hipStream_t);               \
     template void launch_large_dstep<T>(const DevPlan&, const LargeTask*, int, const LargeTask*, int, T*, T*, T*,  \
                                         hipStream_t);                                                              \
-    template void launch_front_inverse<T>(const SmallTask*, int, T*, hipStream_t);                                 \
     template void launch_pair_inverse<T>(const PairTask*, int, const T*, T*, hipStream_t);                         \
     template void launch_permute_in<T>(const DevPlan&, const double*, int64_t, int64_t, int, T*, hipStream_t);     \
     template void launch_permute_out<T>(const DevPlan&, const T*, int, double*, int64_t, hipStream_t);             \

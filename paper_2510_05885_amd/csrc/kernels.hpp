@@ -183,9 +183,6 @@ void launch_large_dstep(const DevPlan& d, const LargeTask* dtasks, int nd, const
                         T* D, T* M, hipStream_t st);
 
 // P = -Z2 L21 Z1 of every panel pair, after the factorization.
-// Sub-panel inverses of all small fronts, for the sweeps of several right-hand sides.
-template <typename T>
-void launch_front_inverse(const SmallTask* tasks, int n, T* F, hipStream_t st);
 template <typename T>
 void launch_pair_inverse(const PairTask* tasks, int count, const T* F, T* M, hipStream_t st);
 

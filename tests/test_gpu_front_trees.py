@@ -74,3 +74,19 @@ def test_dense_first_subpanel_of_21_tiles(order, children, precision):
     tree.add(16, mid[16:])
     tree.add(root)
     _check(tree, precision)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_ir"])
+@pytest.mark.parametrize("children", [0, 1, 4, 5, 9])
+@pytest.mark.parametrize("root", [33, 64, 65, 80, 96, 97, 128, 193])
+def test_star(root, children, precision):
+    """A root of every class (one wave, four waves, panels) under leaves whose pivots and rows are no multiples
+    of 16, with 1, 3 and 16 right-hand sides: more children than maps in LDS at a time, several entries a row in
+    the sweeps' gather tables, contribution blocks and rows of ancestors at every offset."""
+    rng = np.random.default_rng(root + children)
+    tree = Tree(root)
+    for k in range(children):
+        # (with enough pivots not to be merged into the root)
+        tree.add([15, 16, 17, 31, 33, 47, 48, 49, 65][k], _below(rng, root, [14, 13, 15, 17, 30, 16, 9, 25, 21][k]))
+    tree.add(root)
+    _check(tree, precision, columns=(1, 3, 16), passes=2)
