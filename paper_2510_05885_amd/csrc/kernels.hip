@@ -237,7 +237,9 @@ __device__ __forceinline__ T zget(const T* B, int u, int t) {
 }
 
 // acc (a tile at block (ti, tj), transposed) -= L_ti D L_tj^T of sub-panel q,
-// L in LDS with leading dimension ld.
+// L in LDS with leading dimension ld.  The 16 products are summed from zero: added
+// one by one to the tile, each was rounded to its last place (unrefined residuals of
+// an OPF of order 2000 up to 1.35 times as large, the same time).
 template <typename T>
 __device__ __forceinline__ void diag_apply(typename Mfma<T>::acc_t& acc, const T* B, int ld, const T* dv, int q, int ti,
                                            int tj, int lr, int lk) {
@@ -248,8 +250,10 @@ __device__ __forceinline__ void diag_apply(typename Mfma<T>::acc_t& acc, const T
         a[st] = B[(16 * tj + lr) + t * ld] * -dv[t];
         b[st] = B[(16 * ti + lr) + t * ld];
     }
+    typename Mfma<T>::acc_t sum = {0, 0, 0, 0};
 #pragma unroll
-    for (int st = 0; st < 4; ++st) acc = Mfma<T>::run(a[st], b[st], acc);
+    for (int st = 0; st < 4; ++st) sum = Mfma<T>::run(a[st], b[st], sum);
+    acc += sum;
 }
 
 // Z_qq = L_qq^-1 of a 16 x 16 unit lower block by one wave: lane % 16 = row j
@@ -1346,14 +1350,19 @@ __device__ __forceinline__ void fwd_front1(const SmallTask* tk, const T* __restr
     }
     for (int kb = 0; kb < p; kb += kC) {
         if (kb > 0) load(kb);
+        // rows below the sub-panel sum its products from zero
+        const bool own0 = lane < kb + kC, own1 = lane + 64 < kb + kC;
+        T w0 = own0 ? v0 : T(0), w1 = own1 ? v1 : T(0);
 #pragma unroll
         for (int t = 0; t < kC; ++t) {
             const int k = kb + t;
             if (k >= p) continue;   // uniform
-            const T yk = !kHi || k < 64 ? bcast(v0, k) : bcast(v1, k - 64);
-            v0 -= (lane > k ? l0[t] : T(0)) * yk;
-            if (kHi) v1 -= (lane + 64 > k ? l1[t] : T(0)) * yk;
+            const T yk = !kHi || k < 64 ? bcast(w0, k) : bcast(w1, k - 64);
+            w0 -= (lane > k ? l0[t] : T(0)) * yk;
+            if (kHi) w1 -= (lane + 64 > k ? l1[t] : T(0)) * yk;
         }
+        v0 = own0 ? w0 : v0 + w0;
+        if (kHi) v1 = own1 ? w1 : v1 + w1;
     }
     if (lane < p) Y2[first + lane] = v0;
     else if (lane < f) Us[lane - p] = v0;
@@ -1809,17 +1818,19 @@ __device__ __forceinline__ void fwd_panels16(const PanelTask* tk, const T* __res
     }
     __syncthreads();
     if (!act) return;
+    acc_t s1 = {0, 0, 0, 0}, s2 = {0, 0, 0, 0};   // summed from zero, see diag_apply
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
         const acc_t yy = rows16<T>(y + 16 * kk * kNrhsMax, lr, lk);
 #pragma unroll
-        for (int st = 0; st < 4; ++st) a = Mfma<T>::run(l1[kk][st], yy[st], a);
+        for (int st = 0; st < 4; ++st) s1 = Mfma<T>::run(l1[kk][st], yy[st], s1);
         if (two) {
             const acc_t y2 = rows16<T>(y + (64 + 16 * kk) * kNrhsMax, lr, lk);
 #pragma unroll
-            for (int st = 0; st < 4; ++st) a = Mfma<T>::run(l2[kk][st], y2[st], a);
+            for (int st = 0; st < 4; ++st) s2 = Mfma<T>::run(l2[kk][st], y2[st], s2);
         }
     }
+    a += s1 + s2;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int i = i0 + Mfma<T>::row(lk, r);

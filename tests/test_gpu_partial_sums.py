@@ -1,0 +1,68 @@
+"""Rounding of the FP32 factor and its sweeps: products are summed 16 at a time from zero before they meet the
+value they are subtracted from, so that value takes one rounding per 16 columns.  Reference: the same elimination
+in numpy's float32, 16 columns at a time."""
+import numpy as np
+import pytest
+
+from paper_2510_05885_amd import ncl_kkt as nk
+from paper_2510_05885_amd import synth
+
+from gpu_util import colmajor, dev
+
+pytestmark = pytest.mark.gpu
+F = np.float32
+
+
+def _blocked_solve(A, B):
+    n = len(A)
+    W, x = A.astype(F), B.astype(F)
+    for k in range(0, n, 16):
+        e = min(n, k + 16)
+        for t in range(k, e):
+            W[t + 1:, t] /= W[t, t]
+            for u in range(t + 1, e):
+                W[u:, u] -= W[u:, t] * (W[t, t] * W[u, t])
+        W[e:, e:] -= W[e:, k:e] @ (W[e:, k:e] * np.diag(W)[k:e]).T
+    L = np.tril(W, -1)
+    for k in range(0, n, 16):
+        e = min(n, k + 16)
+        for t in range(k, e):
+            x[t + 1:e] -= np.outer(L[t + 1:e, t], x[t])
+        x[e:] -= L[e:, k:e] @ x[k:e]
+    x /= np.diag(W)[:, None]
+    for k in range((n - 1) // 16 * 16, -1, -16):
+        e = min(n, k + 16)
+        x[k:e] -= L[e:, k:e].T @ x[e:]
+        for t in range(e - 1, k, -1):
+            x[k:t] -= np.outer(L[t, k:t], x[t])
+    return x
+
+
+def _rms(A, X, B):
+    return np.sqrt(np.mean(((B - A @ X.astype(np.float64)) / (np.abs(A) @ np.abs(X.astype(np.float64)))) ** 2))
+
+
+@pytest.mark.parametrize("columns", [1, 16])
+@pytest.mark.parametrize("n", [64, 96, 128, 320])   # one wave, four waves, panels
+def test_rounding_of_an_fp32_factor(n, columns):
+    colptr = np.concatenate([[0], np.cumsum(np.arange(n, 0, -1))]).astype(np.int32)
+    rowidx = np.concatenate([np.arange(j, n) for j in range(n)]).astype(np.int32)
+    errs = []
+    for seed in range(12):
+        rng = np.random.default_rng(seed)
+        # products of about a hundredth of the entries that they are subtracted from
+        A = 1.0 + 0.1 * rng.uniform(-1.0, 1.0, (n, n))
+        A = (A + A.T) / 2 + np.diag(rng.uniform(50.0, 150.0, n))
+        B = A @ rng.uniform(0.5, 1.5, (n, columns))
+        inp = synth.KKTInput(n, 0, colptr, rowidx, np.concatenate([A[j:, j] for j in range(n)]), np.zeros(n),
+                             np.zeros(1, np.int32), np.zeros(0, np.int32), np.zeros(0), 1.0)
+        kkt = nk.KKT.from_input(inp, precision="fp32_ir", ordering="natural", ir_tol=1e-2)
+        assert kkt.factor(dev(inp.W_val), dev(inp.Sigma), None, 1.0) == 0
+        X, info = kkt.solve(colmajor(B))
+        assert info.ir_steps == 0 and not info.fell_back_fp64
+        errs.append((_rms(A, X.cpu().numpy().reshape(B.shape), B), _rms(A, _blocked_solve(A, B), B)))
+        kkt.close()
+    gpu, ref = np.sqrt(np.mean(np.square(errs), 0))
+    print(f"n {n} columns {columns}: rms row error {gpu:.3g}, reference {ref:.3g}")
+    # the same roundings up to their order; added one by one they would be 1.5 to 3 times as large
+    assert gpu <= 1.25 * ref
