@@ -688,16 +688,12 @@ int build_plan(Plan& P, int form, const std::vector<SysInput>& sys, int ordering
         }
         P.U_elems = std::max<int64_t>(uoff, 32);
         P.M_off.assign(nsn, -1);   // -1: small front (no panel inverses)
-        P.P_off.assign(nsn, 0);
         int64_t moff = 0;
         for (int s = 0; s < nsn; ++s) {
             if (!P.sn_large[s]) continue;
             const int64_t p = P.sn_first[s + 1] - P.sn_first[s];
             P.M_off[s] = moff;
-            // one block per panel, then P and P^T per pair of panels
-            const int64_t npan = (p + cfg.panel - 1) / cfg.panel, blk = (int64_t)cfg.panel * cfg.panel;
-            P.P_off[s] = moff + npan * blk;
-            moff += (npan + 2 * (npan / 2)) * blk;
+            moff += ((p + cfg.panel - 1) / cfg.panel) * (int64_t)cfg.panel * cfg.panel;
         }
         P.M_elems = std::max<int64_t>(moff, 32);
 
@@ -837,7 +833,6 @@ int build_plan(Plan& P, int form, const std::vector<SysInput>& sys, int ordering
                 t.w1 = std::min(PW, t.p - c0);
                 t.w2 = std::min(PW, t.p - c0 - t.w1);
                 t.L_off = P.L_off[s]; t.U_off = P.U_off[s]; t.M_off = P.M_off[s]; t.rows_off = P.sn_rowptr[s];
-                t.P_off = t.w2 > 0 ? P.P_off[s] + (int64_t)(c0 / (2 * PW)) * 2 * PW * PW : 0;
                 t.gat = gat[s]; t.gk = c0 == 0 ? gk[s] : 0;
                 t.ntask = std::max(1, (t.f - c0 - t.w1 - t.w2 + 63) / 64);
                 return t;
@@ -856,10 +851,6 @@ int build_plan(Plan& P, int form, const std::vector<SysInput>& sys, int ordering
                     const int s = P.level_list[k], p = pivots(s), f = order(s);
                     if (P.sn_large[s]) {
                         npair = std::max(npair, (p + 2 * PW - 1) / (2 * PW));
-                        for (int c0 = 0; c0 + PW < p; c0 += 2 * PW)
-                            P.pairs.push_back(PairTask{f, c0, std::min(PW, p - c0 - PW), 0, P.L_off[s],
-                                                       P.M_off[s] + (int64_t)(c0 / PW) * PW * PW,
-                                                       P.P_off[s] + (int64_t)(c0 / (2 * PW)) * 2 * PW * PW});
                     } else {
                         P.solve_small.push_back(SmallTask{P.sn_first[s], p, f, gk[s], P.L_off[s], P.U_off[s],
                                                           P.sn_rowptr[s], gat[s]});
@@ -909,7 +900,7 @@ int build_plan(Plan& P, int form, const std::vector<SysInput>& sys, int ordering
                             if (fin.ntask == 1) fin.ntask = 0;
                         }
                         auto finishes = [&](PanelTask& t, int which) {
-                            t.fc0 = fin.c0; t.fw1 = fin.w1; t.fw2 = fin.w2; t.fP_off = fin.P_off;
+                            t.fc0 = fin.c0; t.fw1 = fin.w1; t.fw2 = fin.w2;
                             t.fslot0 = slot_of[a]; t.fntask = fin.ntask; t.which = which;
                         };
                         const int nfin = fin.ntask == 0 ? 0 : (fin.w2 > 0 ? 2 : 1);

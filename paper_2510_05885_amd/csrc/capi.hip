@@ -94,7 +94,6 @@ struct ncl_kkt_s {
     int *level_list = nullptr, *large_asm = nullptr, *gather = nullptr;
     PanelTask *fwd_tasks = nullptr, *bwd_tasks = nullptr;
     SmallTask* solve_small = nullptr;
-    PairTask* pairs = nullptr;
     LargeTask *large_panel = nullptr, *large_upd = nullptr, *large_diag = nullptr;
     RowChunk* chunks = nullptr;
     int* sys_chunk_ptr = nullptr;
@@ -318,7 +317,6 @@ void setup_device(ncl_kkt_s* h) {
     h->fwd_tasks = upload(h, P.fwd_tasks);
     h->bwd_tasks = upload(h, P.bwd_tasks);
     h->solve_small = upload(h, P.solve_small);
-    h->pairs = upload(h, P.pairs);
     h->gather = upload(h, P.gather);
     // row chunks (never straddling two systems), one block each: up to 256 rows, in
     // multiples of 8; smaller while there are fewer than 2048 of them (eight a CU),
@@ -612,7 +610,6 @@ void factor_fronts(ncl_kkt_s* h, T* F, T* D, T* Mb, hipStream_t st) {
             HIPCHK(hipStreamWaitEvent(st, h->lvl_ev[2 * l + 1], 0));
         }
     }
-    launch_pair_inverse<T>(h->pairs, (int)P.pairs.size(), F, Mb, st);
     launch_end(d, h->kinf, h->pin_factor, st);
 }
 

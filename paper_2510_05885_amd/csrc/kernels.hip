@@ -1196,10 +1196,14 @@ __global__ void k_permute_out(DevPlan d, const T* __restrict__ X, int nrhs, doub
 // [c0, c0 + w1) and [c0 + w1, c0 + w1 + w2) (w1 = 64 when w2 > 0), through
 //   G1, G2  the inverses Z = L_kk^-1 of their diagonal blocks (unit lower,
 //           with Z^T in the strictly upper triangle) and
-//   P       = -Z2 L21 Z1, the coupling block of the pair's inverse (and P^T),
-// so that every result is one product with what the launch starts from:
-//   forward:  y1 = Z1 b1, y2 = Z2 b2 + P b1, rows below -= L1 y1 + L2 y2
-//   backward: v = y / d - L^T x (rows below), x2 = Z2^T v2, x1 = Z1^T v1 + P^T v2
+//   L21     the second panel's rows of the first:
+//   forward:  y1 = Z1 b1, y2 = Z2 (b2 - L21 y1), rows below -= L1 y1 + L2 y2
+//   backward: v = y / d - L^T x (rows below), x2 = Z2^T v2, x1 = Z1^T (v1 - L21^T x2)
+// (Through the inverse of the pair's whole triangle, with P = -Z2 L21 Z1 formed after
+// the factorization, every result was one product with what the launch starts from:
+// a solve of one column at order 500k 1332 us, so 1385, a factorization 5685, so 5652.
+// But its rounding was 1.1 times as large for one column and 1.3 to 1.45 times for
+// several, FP32 fronts of order 320 and 576.)
 // The rows below are split into tasks of 64.
 //   forward:  every task forms the pair's y itself; task 0 stores it.
 //   backward: a pair with one task is finished by it.  The tasks of any other
@@ -1230,18 +1234,41 @@ __device__ __forceinline__ T gather1(const T* __restrict__ U, const int* __restr
 }
 
 // ---- one right-hand side ----------------------------------------------------
+// The waves' shares of a 64-vector: wave q4's entry `lane` at part[64 q4 + lane].
+template <typename T>
+__device__ __forceinline__ T share_sum(const T* part, int lane) {
+    return (part[lane] + part[64 + lane]) + (part[128 + lane] + part[192 + lane]);
+}
+// A wave's copy of a vector whose entry `lane` is x, for its reads of 16 entries
+// (xw: 64 values of its own; its LDS accesses are in order).
+template <typename T>
+__device__ __forceinline__ const T* wave_copy(T* xw, T x, int lane) {
+    wave_fence();
+    xw[lane] = x;
+    wave_fence();
+    return xw;
+}
+template <typename T>
+__device__ __forceinline__ T dot16(const T (&a)[16], const T* x) {
+    T s = T(0);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) s += a[j] * x[j];
+    return s;
+}
+
+// A wave holds 16 columns of every operand; each product's four shares meet in LDS
+// and every wave sums them for itself, so a product costs one barrier.
 template <typename T>
 __device__ __forceinline__ void fwd_panels1(const PanelTask* tk, const T* __restrict__ F, const T* __restrict__ Zbuf,
                                             const int* __restrict__ gatab, T* __restrict__ Y, T* __restrict__ Y2,
                                             T* __restrict__ U) {
-    __shared__ T v[128], y[128], rw[64], part[2][256];
+    __shared__ T v[128], rw[64], part[2][256], xw[4][64];
     const int first = tk->first, p = tk->p, f = tk->f, c0 = tk->c0, w1 = tk->w1, w2 = tk->w2;
     const int r0 = tk->r0, nr = tk->r1 - r0;
     const int tid = threadIdx.x, lane = tid & 63, q4 = tid >> 6;
     const T* __restrict__ L = F + tk->L_off;
     const T* __restrict__ G1 = Zbuf + tk->M_off + (int64_t)(c0 / kPanel) * (kPanel * kPanel);
     const T* __restrict__ G2 = G1 + kPanel * kPanel;
-    const T* __restrict__ Pm = Zbuf + tk->P_off;
     T* __restrict__ Us = U + tk->U_off;
     // right-hand side: the pair's pivots, then the task's rows
     if (tid < 192) {
@@ -1255,7 +1282,7 @@ __device__ __forceinline__ void fwd_panels1(const PanelTask* tk, const T* __rest
         }
         (tid < 128 ? v[tid] : rw[tid - 128]) = b;
     }
-    T z1[16], z2[16], pm[16], l1[16], l2[16];
+    T z1[16], z2[16], lb[16], l1[16], l2[16];
     const bool rv = lane < nr;
     const T* __restrict__ Lr = L + r0 + (rv ? lane : 0);
 #pragma unroll
@@ -1265,56 +1292,43 @@ __device__ __forceinline__ void fwd_panels1(const PanelTask* tk, const T* __rest
         l1[j] = (rv && k < w1) ? Lr[(int64_t)(c0 + k) * f] : T(0);
     }
     if (w2 > 0) {
+        const T* __restrict__ L21 = L + c0 + kPanel + min(lane, w2 - 1);
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             const int k = 16 * q4 + j;
-            pm[j] = Pm[k * kPanel + lane];
+            lb[j] = L21[(int64_t)(c0 + k) * f];
             z2[j] = G2[k * kPanel + lane];
             l2[j] = (rv && k < w2) ? Lr[(int64_t)(c0 + kPanel + k) * f] : T(0);
         }
     }
     __syncthreads();
-    {
-        const T* v1 = v + 16 * q4;
-        T a1 = T(0);
 #pragma unroll
-        for (int j = 0; j < 16; ++j) a1 += (16 * q4 + j <= lane ? z1[j] : T(0)) * v1[j];
-        part[0][tid] = a1;
-        if (w2 > 0) {
-            T a2 = T(0);
-#pragma unroll
-            for (int j = 0; j < 16; ++j) a2 += pm[j] * v1[j] + (16 * q4 + j <= lane ? z2[j] : T(0)) * v1[64 + j];
-            part[1][tid] = a2;
-        }
-    }
+    for (int j = 0; j < 16; ++j) z1[j] = 16 * q4 + j <= lane ? z1[j] : T(0);   // Z^T lies above
+    part[0][tid] = dot16(z1, v + 16 * q4);
     __syncthreads();
-    if (tid < w1 + w2) {
-        const T* pp = part[tid >> 6] + (tid & 63);
-        const T s = (pp[0] + pp[64]) + (pp[128] + pp[192]);
-        y[tid] = s;
-        if (tk->index == 0) Y2[first + c0 + tid] = s;
-    } else if (tid < 128) {
-        y[tid] = T(0);
+    const T y1 = share_sum(part[0], lane);   // (zero beyond w1)
+    if (tid < w1 && tk->index == 0) Y2[first + c0 + tid] = y1;
+    const T* x = wave_copy(xw[q4], y1, lane) + 16 * q4;
+    T a = dot16(l1, x);
+    if (w2 > 0) {
+        part[1][tid] = dot16(lb, x);
+        __syncthreads();
+        const T b2 = lane < w2 ? v[64 + lane] - share_sum(part[1], lane) : T(0);
+        x = wave_copy(xw[q4], b2, lane) + 16 * q4;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) z2[j] = 16 * q4 + j <= lane ? z2[j] : T(0);
+        part[0][tid] = dot16(z2, x);
+        __syncthreads();
+        const T y2 = share_sum(part[0], lane);
+        if (tid < w2 && tk->index == 0) Y2[first + c0 + kPanel + tid] = y2;
+        x = wave_copy(xw[q4], y2, lane) + 16 * q4;
+        a += dot16(l2, x);
     }
     if (nr == 0) return;   // the whole workgroup
-    __syncthreads();
-    {
-        const T* y1 = y + 16 * q4;
-        T a = T(0);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) a += l1[j] * y1[j];
-        if (w2 > 0) {
-            T b = T(0);
-#pragma unroll
-            for (int j = 0; j < 16; ++j) b += l2[j] * y1[64 + j];
-            a += b;
-        }
-        part[0][tid] = a;
-    }
+    part[1][tid] = a;
     __syncthreads();
     if (tid < nr) {
-        const T* pp = part[0] + tid;
-        const T val = rw[tid] - ((pp[0] + pp[64]) + (pp[128] + pp[192]));
+        const T val = rw[tid] - share_sum(part[1], tid);
         const int gi = r0 + tid;
         if (gi < p) Y[first + gi] = val;
         else Us[gi - p] = val;
@@ -1389,27 +1403,42 @@ __global__ __launch_bounds__(256, kPanels ? 2 : 4) void k_fwd1(const PanelTask* 
     }
 }
 
-// One panel of a pair from v = y / d - sums (v: 128 in LDS): x1 = Z1^T v1 +
-// P^T v2, or x2 = Z2^T v2.  The operands come loaded (wave q4 takes rows
-// 16 q4 .. 16 q4 + 15); the waves' shares go to part.
+// A pair's x from v = y / d - sums (v: 128 in LDS, zero beyond its columns): x2 =
+// Z2^T v2, then, with `one`, x1 = Z1^T (v1 - L21^T x2).  Wave q4 takes rows 16 q4 ..
+// of each product; entry `lane` of x1 and x2 in every wave.
 template <typename T>
 struct PairOps {
-    T z[16], pt[16];
-    __device__ __forceinline__ void load(const T* __restrict__ G, const T* __restrict__ PT, bool with_p, int lane,
-                                         int q4) {
+    T z1[16], z2[16], lb[16];
+    // A: the front; (c0, w2): the pair's first column and its second panel's width
+    __device__ __forceinline__ void load(const T* __restrict__ G1, const T* __restrict__ A, int f, int c0, int w2,
+                                         bool one, int lane, int q4) {
+        const T* __restrict__ G2 = G1 + kPanel * kPanel;
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             const int u = 16 * q4 + j;
-            z[j] = u >= lane ? G[u * kPanel + lane] : T(0);   // Z^T is upper
-            pt[j] = with_p ? PT[u * kPanel + lane] : T(0);
+            z1[j] = one && u >= lane ? G1[u * kPanel + lane] : T(0);   // Z^T is upper
+            z2[j] = w2 > 0 && u >= lane ? G2[u * kPanel + lane] : T(0);
+            lb[j] = one && u < w2 ? A[c0 + lane + (int64_t)(c0 + kPanel + u) * f] : T(0);   // L^T lies above
         }
     }
-    __device__ __forceinline__ void apply(const T* v, int half, T* part, int lane, int q4) const {
-        const T* vq = v + 16 * q4;
-        T a = T(0);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) a += z[j] * vq[64 * half + j] + pt[j] * vq[64 + j];
-        part[64 * q4 + lane] = a;
+    // part: 2 x 256, xw: the wave's 64
+    __device__ __forceinline__ void apply(const T* v, bool two, bool one, T (*part)[256], T* xw, int lane, int q4,
+                                          T& x1, T& x2) const {
+        const int tid = 64 * q4 + lane;
+        T v1 = v[lane];
+        x2 = T(0);
+        if (two) {
+            part[0][tid] = dot16(z2, v + 64 + 16 * q4);
+            __syncthreads();
+            x2 = share_sum(part[0], lane);
+            if (!one) return;
+            part[1][tid] = dot16(lb, wave_copy(xw, x2, lane) + 16 * q4);
+            __syncthreads();
+            v1 -= share_sum(part[1], lane);
+        }
+        part[0][tid] = dot16(z1, wave_copy(xw, v1, lane) + 16 * q4);
+        __syncthreads();
+        x1 = share_sum(part[0], lane);
     }
 };
 
@@ -1418,14 +1447,14 @@ __device__ __forceinline__ void bwd_panels1(const PanelTask* tk, const int* __re
                                             const T* __restrict__ Zbuf, const T* __restrict__ D,
                                             const T* __restrict__ Y2, T* __restrict__ X, T* __restrict__ pw,
                                             const T* __restrict__ pr) {
-    __shared__ T v[128], xs[64], part[2][256];
+    __shared__ T v[128], xs[64], part[2][256], xw[4][64];
     const int first = tk->first, p = tk->p, f = tk->f, c0 = tk->c0, w = tk->w1 + tk->w2;
     const int r0 = tk->r0, nr = tk->r1 - r0;
     const int tid = threadIdx.x, lane = tid & 63, q4 = tid >> 6;
     const bool own = tk->index >= 0;                 // else a finish-only record
     const bool fin = tk->fntask > 0, self = own && tk->ntask == 1;
     const int xc0 = fin ? tk->fc0 : c0, xw1 = fin ? tk->fw1 : tk->w1, xw2 = fin ? tk->fw2 : tk->w2;
-    const int which = fin ? tk->which : 0;           // the panel it finishes first
+    const int which = fin ? tk->which : 0;           // the panel it finishes
     const T* __restrict__ A = F + tk->L_off;
     // L^T operands (a large front keeps L^T above its diagonal): one panel: 64
     // columns in four groups of 16 rows, two: 128 in two of 32
@@ -1443,10 +1472,8 @@ __device__ __forceinline__ void bwd_panels1(const PanelTask* tk, const int* __re
             for (int m = 16; m < 32; ++m) lv[m] = m < n ? src[(int64_t)m * f] : T(0);
     }
     PairOps<T> ops;
-    const T* __restrict__ G1 = Zbuf + tk->M_off + (int64_t)(xc0 / kPanel) * (kPanel * kPanel);
     if (fin || self)
-        ops.load(G1 + which * kPanel * kPanel, Zbuf + (fin ? tk->fP_off : tk->P_off) + kPanel * kPanel,
-                 which == 0 && xw2 > 0, lane, q4);
+        ops.load(Zbuf + tk->M_off + (int64_t)(xc0 / kPanel) * (kPanel * kPanel), A, f, xc0, xw2, which == 0, lane, q4);
     T yd = T(0);   // y / d of the pair to finish
     if (tid < xw1 + xw2 && (fin || self)) yd = Y2[first + xc0 + tid] * (T(1) / D[first + xc0 + tid]);
     if (own && tid < 64) {
@@ -1469,11 +1496,10 @@ __device__ __forceinline__ void bwd_panels1(const PanelTask* tk, const int* __re
         __syncthreads();
         if (tid < 128) v[tid] = tid < xw1 + xw2 ? yd - (part[0][tid] + part[0][tid + 128]) : T(0);
         __syncthreads();
-        ops.apply(v, which, part[0], lane, q4);
-        __syncthreads();
-        const T* pp = part[0] + lane;
+        T x1, x2;
+        ops.apply(v, xw2 > 0, which == 0, part, xw[q4], lane, q4, x1, x2);
         if (tid < (which ? xw2 : xw1)) {
-            const T x = (pp[0] + pp[64]) + (pp[128] + pp[192]);
+            const T x = which ? x2 : x1;
             const int gi = xc0 + 64 * which + tid;
             X[first + gi] = x;
             if (own) xs[gi - r0] = x;
@@ -1489,28 +1515,21 @@ __device__ __forceinline__ void bwd_panels1(const PanelTask* tk, const int* __re
         if (two)
 #pragma unroll
             for (int m = 16; m < 32; ++m) b += lv[m] * xr[m];
-        part[0][tid] = a + b;
+        part[1][tid] = a + b;
     }
     __syncthreads();
-    if (tid < cols) {
-        const T* pp = part[0] + tid;
-        const T s = two ? pp[0] + pp[128] : (pp[0] + pp[64]) + (pp[128] + pp[192]);
-        if (!self) pw[(int64_t)(tk->slot0 + tk->index) * 128 + tid] = s;
-        else v[tid] = tid < w ? yd - s : T(0);
+    if (tid < 128) {
+        const T* pp = part[1] + tid;
+        const T s = tid >= cols ? T(0) : two ? pp[0] + pp[128] : (pp[0] + pp[64]) + (pp[128] + pp[192]);
+        if (self) v[tid] = tid < w ? yd - s : T(0);
+        else if (tid < cols) pw[(int64_t)(tk->slot0 + tk->index) * 128 + tid] = s;
     }
     if (!self) return;
-    if (!two && tid >= 64 && tid < 128) v[tid] = T(0);
     __syncthreads();
-    ops.apply(v, 0, part[0], lane, q4);
-    if (two) {
-        ops.load(G1 + kPanel * kPanel, nullptr, false, lane, q4);
-        ops.apply(v, 1, part[1], lane, q4);
-    }
-    __syncthreads();
-    if (tid < w) {
-        const T* pp = part[tid >> 6] + lane;
-        X[first + c0 + tid] = (pp[0] + pp[64]) + (pp[128] + pp[192]);
-    }
+    T x1, x2;
+    ops.apply(v, two, true, part, xw[q4], lane, q4, x1, x2);
+    if (tid < tk->w1) X[first + c0 + tid] = x1;
+    if (tid < tk->w2) X[first + c0 + kPanel + tid] = x2;
 }
 
 // A small front by one wave, its 16-column sub-panels from the last: lane =
@@ -1701,6 +1720,22 @@ __device__ __forceinline__ typename Mfma<T>::acc_t rows16(const T* V, int lr, in
     return a;
 }
 
+// 16 rows of a product with a 64 x 16 piece V: op[kk][st] the lane's operands for
+// rows 16 kk + row(lk, st) of V.  Four chains from zero, one per 16 rows, as the sums
+// of one column are taken.
+template <typename T>
+__device__ __forceinline__ typename Mfma<T>::acc_t product16(const T (&op)[4][4], const T* V, int lr, int lk) {
+    typename Mfma<T>::acc_t c[4];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+        const typename Mfma<T>::acc_t b = rows16<T>(V + 16 * kk * kNrhsMax, lr, lk);
+        c[kk] = typename Mfma<T>::acc_t{0, 0, 0, 0};
+#pragma unroll
+        for (int st = 0; st < 4; ++st) c[kk] = Mfma<T>::run(op[kk][st], b[st], c[kk]);
+    }
+    return (c[0] + c[1]) + (c[2] + c[3]);
+}
+
 // Adds the children's update vectors to rows i0 .. i0 + 15 (those < iend) of a
 // front; row(r): the row of item r, from i0.
 template <typename T, typename Row>
@@ -1733,7 +1768,6 @@ __device__ __forceinline__ void fwd_panels16(const PanelTask* tk, const T* __res
     const int lr = lane & 15, lk = lane >> 4;
     const T* __restrict__ L = F + tk->L_off;
     const T* __restrict__ G1 = Zbuf + tk->M_off + (int64_t)(c0 / kPanel) * (kPanel * kPanel);
-    const T* __restrict__ Pm = Zbuf + tk->P_off;
     T* __restrict__ Us = U + tk->U_off * kNrhsMax;
     const int* __restrict__ gat = gatab + tk->gat;
     const int i0 = r0 + 16 * wave;   // the wave's 16 rows
@@ -1764,12 +1798,13 @@ __device__ __forceinline__ void fwd_panels16(const PanelTask* tk, const T* __res
         }
         if (gk > 0) gather16<T>(a, U, gat, f, gk, i0, r1, lr, [&](int r) { return Mfma<T>::row(lk, r); });
     }
-    // every operand before the first product: Z1, Z2 and P for the wave's 16 rows
+    // every operand before the first product: Z1, Z2 and L21 for the wave's 16 rows
     // of y, L for its rows (zero blocks past the diagonal are multiplied too:
     // a loop up to it would wait for its loads block by block)
     const bool two = w2 > 0;   // uniform
-    T z1[4][4], z2[4][4], pm[4][4], l1[4][4], l2[4][4];
+    T z1[4][4], z2[4][4], lb[4][4], l1[4][4], l2[4][4];
     const T* __restrict__ Lr = L + min(i0 + lr, f - 1);
+    const T* __restrict__ L21 = L + min(c0 + kPanel + 16 * wave + lr, f - 1);
     const bool rv = i0 + lr < r1;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
@@ -1777,7 +1812,7 @@ __device__ __forceinline__ void fwd_panels16(const PanelTask* tk, const T* __res
         for (int st = 0; st < 4; ++st) {
             const int k = 16 * kk + Mfma<T>::row(lk, st);
             z1[kk][st] = k <= 16 * wave + lr ? G1[k * kPanel + 16 * wave + lr] : T(0);
-            l1[kk][st] = rv && k < w1 ? -Lr[(int64_t)(c0 + k) * f] : T(0);
+            l1[kk][st] = rv && k < w1 ? Lr[(int64_t)(c0 + k) * f] : T(0);
         }
     if (two)
 #pragma unroll
@@ -1786,10 +1821,11 @@ __device__ __forceinline__ void fwd_panels16(const PanelTask* tk, const T* __res
             for (int st = 0; st < 4; ++st) {
                 const int k = 16 * kk + Mfma<T>::row(lk, st);
                 z2[kk][st] = k <= 16 * wave + lr ? G1[(kPanel + k) * kPanel + 16 * wave + lr] : T(0);
-                pm[kk][st] = Pm[k * kPanel + 16 * wave + lr];
-                l2[kk][st] = rv && k < w2 ? -Lr[(int64_t)(c0 + kPanel + k) * f] : T(0);
+                lb[kk][st] = 16 * wave + lr < w2 ? L21[(int64_t)(c0 + k) * f] : T(0);
+                l2[kk][st] = rv && k < w2 ? Lr[(int64_t)(c0 + kPanel + k) * f] : T(0);
             }
     __syncthreads();
+    // the wave's 16 rows of panel h's y
     auto store_y = [&](const acc_t& s, int h) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -1798,39 +1834,19 @@ __device__ __forceinline__ void fwd_panels16(const PanelTask* tk, const T* __res
             if (tk->index == 0 && i < w) Y2[(int64_t)(first + c0 + i) * kNrhsMax + lr] = s[r];
         }
     };
-    {
-        acc_t s1 = {0, 0, 0, 0}, s2 = {0, 0, 0, 0};
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            const acc_t bb = rows16<T>(b + 16 * kk * kNrhsMax, lr, lk);
-#pragma unroll
-            for (int st = 0; st < 4; ++st) s1 = Mfma<T>::run(z1[kk][st], bb[st], s1);
-            if (two) {
-                const acc_t b2 = rows16<T>(b + (64 + 16 * kk) * kNrhsMax, lr, lk);
-#pragma unroll
-                for (int st = 0; st < 4; ++st) s2 = Mfma<T>::run(pm[kk][st], bb[st], s2);
-#pragma unroll
-                for (int st = 0; st < 4; ++st) s2 = Mfma<T>::run(z2[kk][st], b2[st], s2);
-            }
-        }
-        store_y(s1, 0);
-        if (two) store_y(s2, 1);
-    }
+    store_y(product16<T>(z1, b, lr, lk), 0);
     __syncthreads();
-    if (!act) return;
-    acc_t s1 = {0, 0, 0, 0}, s2 = {0, 0, 0, 0};   // summed from zero, see diag_apply
+    if (two) {
+        const acc_t s = product16<T>(lb, y, lr, lk);
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-        const acc_t yy = rows16<T>(y + 16 * kk * kNrhsMax, lr, lk);
-#pragma unroll
-        for (int st = 0; st < 4; ++st) s1 = Mfma<T>::run(l1[kk][st], yy[st], s1);
-        if (two) {
-            const acc_t y2 = rows16<T>(y + (64 + 16 * kk) * kNrhsMax, lr, lk);
-#pragma unroll
-            for (int st = 0; st < 4; ++st) s2 = Mfma<T>::run(l2[kk][st], y2[st], s2);
-        }
+        for (int r = 0; r < 4; ++r) b[(64 + 16 * wave + Mfma<T>::row(lk, r)) * kNrhsMax + lr] -= s[r];
+        __syncthreads();
+        store_y(product16<T>(z2, b + 64 * kNrhsMax, lr, lk), 1);
+        __syncthreads();
     }
-    a += s1 + s2;
+    if (!act) return;
+    a -= product16<T>(l1, y, lr, lk);
+    if (two) a -= product16<T>(l2, y + 64 * kNrhsMax, lr, lk);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int i = i0 + Mfma<T>::row(lk, r);
@@ -1991,35 +2007,44 @@ __global__ __launch_bounds__(256, kPanels ? 2 : 3) void k_fwd16(const PanelTask*
     }
 }
 
-// Rows 16 w .. of one panel's x from v (128 x 16 in LDS), by wave w: x1 = Z1^T
-// v1 + P^T v2, or x2 = Z2^T v2.  The operands come loaded.
+// A pair's x from v (128 x 16 in LDS, zero beyond its columns): x2 = Z2^T v2, then,
+// with `one`, x1 = Z1^T (v1 - L21^T x2); wave w's 16 rows of each.  x2 takes v2's
+// place, v1 - L21^T x2 that of v1.
 template <typename T>
 struct PairOps16 {
     typedef typename Mfma<T>::acc_t acc_t;
-    T z[4][4], pt[4][4];
-    __device__ __forceinline__ void load(const T* __restrict__ G, const T* __restrict__ PT, bool with_p, int wave,
-                                         int lr, int lk) {
+    T z1[4][4], z2[4][4], lb[4][4];
+    __device__ __forceinline__ void load(const T* __restrict__ G1, const T* __restrict__ A, int f, int c0, int w2,
+                                         bool one, int wave, int lr, int lk) {
+        const T* __restrict__ G2 = G1 + kPanel * kPanel;
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
             for (int st = 0; st < 4; ++st) {
                 const int u = 16 * kk + Mfma<T>::row(lk, st), t = 16 * wave + lr;
-                z[kk][st] = u >= t ? G[u * kPanel + t] : T(0);   // (Z^T)[t][u] above the diagonal
-                pt[kk][st] = with_p ? PT[u * kPanel + t] : T(0);
+                z1[kk][st] = one && u >= t ? G1[u * kPanel + t] : T(0);   // (Z^T)[t][u] above the diagonal
+                z2[kk][st] = w2 > 0 && u >= t ? G2[u * kPanel + t] : T(0);
+                lb[kk][st] = one && u < w2 ? A[c0 + t + (int64_t)(c0 + kPanel + u) * f] : T(0);
             }
     }
-    __device__ __forceinline__ acc_t apply(const T* v, int half, int lr, int lk) const {
-        acc_t s = {0, 0, 0, 0};
+    __device__ __forceinline__ void apply(T* v, bool two, bool one, int wave, int lr, int lk, acc_t& x1,
+                                          acc_t& x2) const {
+        if (two) {
+            x2 = product16<T>(z2, v + 64 * kNrhsMax, lr, lk);
+            if (!one) return;
+            __syncthreads();   // v2 has been read
+            put(v + 64 * kNrhsMax, x2, wave, lr, lk);
+            __syncthreads();
+            const acc_t s = product16<T>(lb, v + 64 * kNrhsMax, lr, lk);
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            const acc_t a = rows16<T>(v + (64 * half + 16 * kk) * kNrhsMax, lr, lk);
-            const acc_t b = rows16<T>(v + (64 + 16 * kk) * kNrhsMax, lr, lk);
-#pragma unroll
-            for (int st = 0; st < 4; ++st) s = Mfma<T>::run(z[kk][st], a[st], s);
-#pragma unroll
-            for (int st = 0; st < 4; ++st) s = Mfma<T>::run(pt[kk][st], b[st], s);
+            for (int r = 0; r < 4; ++r) v[(16 * wave + Mfma<T>::row(lk, r)) * kNrhsMax + lr] -= s[r];
+            __syncthreads();
         }
-        return s;
+        x1 = product16<T>(z1, v, lr, lk);
+    }
+    static __device__ __forceinline__ void put(T* v, const acc_t& x, int wave, int lr, int lk) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[(16 * wave + Mfma<T>::row(lk, r)) * kNrhsMax + lr] = x[r];
     }
 };
 
@@ -2037,12 +2062,12 @@ __device__ __forceinline__ void bwd_panels16(const PanelTask* tk, const int* __r
     const bool own = tk->index >= 0, fin = tk->fntask > 0, self = own && tk->ntask == 1;
     const int xc0 = fin ? tk->fc0 : c0, xw1 = fin ? tk->fw1 : tk->w1, xw2 = fin ? tk->fw2 : tk->w2;
     const T* __restrict__ A = F + tk->L_off;
-    const T* __restrict__ G1 = Zbuf + tk->M_off + (int64_t)(xc0 / kPanel) * (kPanel * kPanel);
-    const T* __restrict__ PT = Zbuf + (fin ? tk->fP_off : tk->P_off) + kPanel * kPanel;
-    const int which = fin ? tk->which : 0;   // the panel it finishes first
+    const int which = fin ? tk->which : 0;   // the panel it finishes
     const bool two = tk->w2 > 0;             // uniform
     PairOps16<T> ops;
-    if (fin || self) ops.load(G1 + which * kPanel * kPanel, PT, which == 0 && xw2 > 0, wave, lr, lk);
+    if (fin || self)
+        ops.load(Zbuf + tk->M_off + (int64_t)(xc0 / kPanel) * (kPanel * kPanel), A, f, xc0, xw2, which == 0, wave, lr,
+                 lk);
     // L^T operands: wave w takes columns 16 w and 64 + 16 w
     T l1[4][4], l2[4][4];
     if (own) {
@@ -2091,7 +2116,9 @@ __device__ __forceinline__ void bwd_panels16(const PanelTask* tk, const int* __r
                        ? Y2[(int64_t)(first + xc0) * kNrhsMax + e] * (T(1) / D[first + xc0 + i]) - a[k] : T(0);
         }
         __syncthreads();
-        const acc_t s = ops.apply(v, which, lr, lk);
+        acc_t x1, x2;
+        ops.apply(v, xw2 > 0, which == 0, wave, lr, lk, x1, x2);
+        const acc_t s = which ? x2 : x1;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int i = 16 * wave + Mfma<T>::row(lk, r);
@@ -2106,13 +2133,7 @@ __device__ __forceinline__ void bwd_panels16(const PanelTask* tk, const int* __r
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         if (h == 1 && !two) break;   // uniform
-        acc_t s = {0, 0, 0, 0};
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            const acc_t xx = rows16<T>(xs + 16 * kk * kNrhsMax, lr, lk);
-#pragma unroll
-            for (int st = 0; st < 4; ++st) s = Mfma<T>::run(h ? l2[kk][st] : l1[kk][st], xx[st], s);
-        }
+        const acc_t s = product16<T>(h ? l2 : l1, xs, lr, lk);
         if (!self) {
 #pragma unroll
             for (int r = 0; r < 4; ++r)
@@ -2128,18 +2149,14 @@ __device__ __forceinline__ void bwd_panels16(const PanelTask* tk, const int* __r
         }
     }
     if (!self) return;
-    if (!two)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[(64 + 16 * wave + Mfma<T>::row(lk, r)) * kNrhsMax + lr] = T(0);
     __syncthreads();
-    for (int h = 0; h < (two ? 2 : 1); ++h) {
-        if (h == 1) ops.load(G1 + kPanel * kPanel, PT, false, wave, lr, lk);
-        const acc_t s = ops.apply(v, h, lr, lk);
+    acc_t x1, x2;
+    ops.apply(v, two, true, wave, lr, lk, x1, x2);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int i = 64 * h + 16 * wave + Mfma<T>::row(lk, r);
-            if (i < w) X[(int64_t)(first + c0 + i) * kNrhsMax + lr] = s[r];
-        }
+    for (int r = 0; r < 4; ++r) {
+        const int i = 16 * wave + Mfma<T>::row(lk, r);
+        if (i < tk->w1) X[(int64_t)(first + c0 + i) * kNrhsMax + lr] = x1[r];
+        if (i < tk->w2) X[(int64_t)(first + c0 + kPanel + i) * kNrhsMax + lr] = x2[r];
     }
 }
 
@@ -2216,66 +2233,6 @@ __global__ __launch_bounds__(256, kPanels ? 2 : 3) void k_bwd16(const PanelTask*
         if (st[t].f <= 32) bwd_front16<T, 2>(st + t, rows, F, D, Y2, X, lane);
         else if (st[t].f <= 64) bwd_front16<T, 4>(st + t, rows, F, D, Y2, X, lane);
         else bwd_front16<T, 8>(st + t, rows, F, D, Y2, X, lane);
-    }
-}
-
-// P = -Z2 L21 Z1 and P^T of one panel pair (64 x 64 each, column-major): four
-// workgroups a pair, 16 columns w each, a wave per 16 rows; L21 Z1 goes through LDS
-// to be the second operand of the product with -Z2.  One launch after the
-// factorization, for all pairs: a chain of trips to memory, so all operands are
-// loaded at once.  A workgroup a pair, loading 16 columns of operands a step:
-// 16.6 us for the 9 pairs of the grid of 2000, so 5.7.
-template <typename T>
-__global__ __launch_bounds__(256) void k_pair_inverse(const PairTask* __restrict__ tasks, const T* __restrict__ F,
-                                                      T* __restrict__ Zbuf) {
-    typedef typename Mfma<T>::acc_t acc_t;
-    __shared__ T M[4][4][64];
-    const PairTask* tk = tasks + (blockIdx.x >> 2);
-    const int f = tk->f, c0 = tk->c0, w2 = tk->w2, w = blockIdx.x & 3;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int lr = lane & 15, lk = lane >> 4, r = 16 * wave + lr, c = 16 * w + lr;
-    const T* __restrict__ A = F + tk->L_off + (c0 + kPanel) + (int64_t)c0 * f;   // L21
-    const T* __restrict__ G1 = Zbuf + tk->M_off;
-    const T* __restrict__ G2 = G1 + kPanel * kPanel;
-    T z[4][4], l[4][4], g[4][4];
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-        for (int st = 0; st < 4; ++st) {
-            const int k = 16 * kk + Mfma<T>::row(lk, st);
-            z[kk][st] = G1[c * kPanel + k];
-            l[kk][st] = A[min(r, w2 - 1) + (int64_t)k * f];
-            g[kk][st] = G2[k * kPanel + r];
-        }
-    acc_t m = {0, 0, 0, 0}, s = {0, 0, 0, 0};   // rows 16 wave .., columns 16 w .. of L21 Z1 and of P
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-        if (kk < w) continue;   // uniform: Z1 is lower, rows k >= its column
-#pragma unroll
-        for (int st = 0; st < 4; ++st) {
-            const int k = 16 * kk + Mfma<T>::row(lk, st);
-            m = Mfma<T>::run(r < w2 ? l[kk][st] : T(0), k >= c ? z[kk][st] : T(0), m);
-        }
-    }
-#pragma unroll
-    for (int st = 0; st < 4; ++st) M[wave][st][lane] = m[st];
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-        if (kk > wave) continue;   // uniform
-#pragma unroll
-        for (int st = 0; st < 4; ++st) {
-            const int k = 16 * kk + Mfma<T>::row(lk, st);
-            s = Mfma<T>::run(r >= k ? -g[kk][st] : T(0), M[kk][st][lane], s);
-        }
-    }
-    T* __restrict__ P = Zbuf + tk->P_off;
-    T* __restrict__ PT = P + kPanel * kPanel;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const int u = 16 * wave + Mfma<T>::row(lk, t);
-        P[u + c * kPanel] = s[t];
-        PT[c + u * kPanel] = s[t];
     }
 }
 
@@ -2798,11 +2755,6 @@ void launch_large_dstep(const DevPlan& d, const LargeTask* dtasks, int nd, const
 }
 
 template <typename T>
-void launch_pair_inverse(const PairTask* tasks, int count, const T* F, T* M, hipStream_t st) {
-    if (count > 0) launch(k_pair_inverse<T>, dim3(4 * count), dim3(256), 0, st, tasks, F, M);
-}
-
-template <typename T>
 void launch_permute_in(const DevPlan& d, const double* B, int64_t si, int64_t sq, int nrhs, T* Y, hipStream_t st) {
     if (nrhs == 1)
         launch(k_permute_in<T, 1>, dim3(blocks_for(d.N, 256)), dim3(256), 0, st, d, B, si, sq, nrhs, Y);
@@ -2930,7 +2882,6 @@ hipError_t configure_kernels(int max_dynamic_lds) {
     template void launch_large_panel<T>(const LargeTask*, int, T*, const T*, const T*, hipStream_t);               \
     template void launch_large_dstep<T>(const DevPlan&, const LargeTask*, int, const LargeTask*, int, T*, T*, T*,  \
                                         hipStream_t);                                                              \
-    template void launch_pair_inverse<T>(const PairTask*, int, const T*, T*, hipStream_t);                         \
     template void launch_permute_in<T>(const DevPlan&, const double*, int64_t, int64_t, int, T*, hipStream_t);     \
     template void launch_permute_out<T>(const DevPlan&, const T*, int, double*, int64_t, hipStream_t);             \
     template void launch_fwd<T>(bool, const PanelTask*, int, const SmallTask*, int, const int*, const T*,          \

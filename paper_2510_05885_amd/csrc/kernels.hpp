@@ -182,10 +182,6 @@ template <typename T>
 void launch_large_dstep(const DevPlan& d, const LargeTask* dtasks, int nd, const LargeTask* utasks, int nu, T* F,
                         T* D, T* M, hipStream_t st);
 
-// P = -Z2 L21 Z1 of every panel pair, after the factorization.
-template <typename T>
-void launch_pair_inverse(const PairTask* tasks, int count, const T* F, T* M, hipStream_t st);
-
 // ---- solves -----------------------------------------------------------------
 // Vectors in pivot order with one value a row, or with kNrhsMax ("many", nrhs > 1;
 // unused columns zero).

@@ -54,15 +54,11 @@ struct LargeStep {             // launches of the large-front path for one level
 struct PanelTask {
     int first, p, f, c0, w1, w2, r0, r1, index, ntask, slot0, gk;
     int fc0, fw1, fw2, fslot0, fntask, which;
-    int64_t L_off, U_off, M_off, P_off, fP_off, rows_off, gat;
+    int64_t L_off, U_off, M_off, rows_off, gat;
 };
 struct SmallTask {             // a small front's sweep (one wave)
     int first, p, f, gk;
     int64_t L_off, U_off, rows_off, gat;
-};
-struct PairTask {              // a panel pair whose coupling block is formed
-    int f, c0, w2, pad;
-    int64_t L_off, M_off, P_off;   // M_off: the pair's first inverse
 };
 // One launch of a sweep, in execution order.  k: pair step of the level (backward
 // partial half), -1 for the records that finish the first pairs of a level.
@@ -138,7 +134,6 @@ struct Plan {
     int64_t factor_elems = 0;        // factor buffer length (elements of T)
     std::vector<int64_t> U_off;      // solve: update vector of each front (c_s * nrhs_max)
     std::vector<int64_t> M_off;      // large fronts: per-panel inverses L_kk^-1 (panel^2 each)
-    std::vector<int64_t> P_off;      // large fronts: first pair's coupling block (P, P^T, panel^2 each a pair)
     int64_t M_elems = 0;
     int64_t U_elems = 0;
 
@@ -165,7 +160,6 @@ struct Plan {
     std::vector<SolveStep> fwd_steps, bwd_steps;
     std::vector<PanelTask> fwd_tasks, bwd_tasks;
     std::vector<SmallTask> solve_small;
-    std::vector<PairTask> pairs;
     std::vector<int> gather;         // per front gk x f offsets of update-vector entries, -1 none
     int64_t solve_max_slots = 0;     // backward tasks in the largest step (partial-sum slots)
 

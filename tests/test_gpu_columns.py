@@ -12,7 +12,7 @@ from gpu_util import colmajor, dev
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("nodes,rho", [(125, 1e2), (125, 1e6), (400, 1e4), (400, 1e6)])
+@pytest.mark.parametrize("nodes,rho", [(125, 1e2), (125, 1e6), (400, 1e4), (400, 1e6), (1500, 1e4)])
 def test_several_columns_are_as_accurate_as_one(nodes, rho):
     inp = synth.opf_network(N=nodes, seed=2)
     kkt = nk.KKT.from_input(inp, pivot_scale="absolute", pivot_eps=1e-12, ir_max_steps=0)

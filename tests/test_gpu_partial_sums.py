@@ -43,7 +43,7 @@ def _rms(A, X, B):
 
 
 @pytest.mark.parametrize("columns", [1, 16])
-@pytest.mark.parametrize("n", [64, 96, 128, 320])   # one wave, four waves, panels
+@pytest.mark.parametrize("n", [64, 96, 128, 320, 576])   # one wave, four waves, panels (pairs and a lone one)
 def test_rounding_of_an_fp32_factor(n, columns):
     colptr = np.concatenate([[0], np.cumsum(np.arange(n, 0, -1))]).astype(np.int32)
     rowidx = np.concatenate([np.arange(j, n) for j in range(n)]).astype(np.int32)
@@ -64,5 +64,6 @@ def test_rounding_of_an_fp32_factor(n, columns):
         kkt.close()
     gpu, ref = np.sqrt(np.mean(np.square(errs), 0))
     print(f"n {n} columns {columns}: rms row error {gpu:.3g}, reference {ref:.3g}")
-    # the same roundings up to their order; added one by one they would be 1.5 to 3 times as large
-    assert gpu <= 1.25 * ref
+    # the same roundings up to their order; added one by one they were 1.26 to 1.98 times as large.  Panels, each by
+    # its own triangle's inverse: through the inverse of a pair's whole triangle 1.07 and 1.09 times (one column)
+    assert gpu <= (1.25 if n <= 128 else 1.05) * ref
