@@ -774,6 +774,10 @@ void solve_once(ncl_kkt_s* h, const double* B, int64_t si, int64_t sq, double* X
 // B: column q of row i at B[i si + q sq].
 void solve_with_factor(ncl_kkt_s* h, const double* B, int64_t si, int64_t sq, double* X, int64_t ldx, int nrhs,
                        hipStream_t st) {
+    if (nrhs > 1 && nrhs < kManyColumns) {
+        for (int q = 0; q < nrhs; ++q) solve_with_factor(h, B + q * sq, si, sq, X + q * ldx, ldx, 1, st);
+        return;
+    }
     if (h->factor_prec == 1)
         solve_once<float>(h, B, si, sq, X, ldx, nrhs, h->F32, h->M32, h->D32, h->Y32, h->U32, h->P32, st);
     else
@@ -832,8 +836,9 @@ Backward solve_refine(ncl_kkt_s* h, const double* B, int64_t ldb, double* X, int
     double gap = ir_gap(h, om);
     while (gap > 1.0 && steps < h->opt.ir_max_steps) {
         // correction from the residual left in R by backward_error (row-major
-        // for several columns)
-        solve_with_factor(h, h->R, nrhs > 1 ? kNrhsMax : 1, 1, h->DX, N, nrhs, st);
+        // from kManyColumns columns)
+        const bool many = nrhs >= kManyColumns;
+        solve_with_factor(h, h->R, many ? kNrhsMax : 1, many ? 1 : N, h->DX, N, nrhs, st);
         launch_copy_cols(h->Xp, N, X, ldx, N, nrhs, st);
         launch_axpy_cols(X, ldx, h->DX, N, nrhs, st);
         const Backward omn = backward_error(h, B, ldb, X, ldx, nrhs, st);

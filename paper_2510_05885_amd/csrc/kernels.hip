@@ -2287,9 +2287,11 @@ struct RowSum {
 __device__ __forceinline__ double res_join(int k, double a, double b) { return k == 3 || k == 4 ? a + b : fmax(a, b); }
 
 // One right-hand side: block per chunk of rows (one system); eight lanes share a row.
+// The chunk's figures go to partial[stride c ..].
 __global__ __launch_bounds__(256) void k_residual(DevPlan d, const double* __restrict__ K,
                                                   const double* __restrict__ B, const double* __restrict__ x,
-                                                  double* __restrict__ R, const RowChunk* __restrict__ chunks, double* partial) {
+                                                  double* __restrict__ R, const RowChunk* __restrict__ chunks, double* partial,
+                                                  int stride) {
     const int c = blockIdx.x, row0 = chunks[c].row0, rows = chunks[c].rows;
     const int tid = threadIdx.x, sub = tid & 7, grp = tid >> 3;
     __shared__ double sm[kResWidth][256];
@@ -2316,7 +2318,7 @@ __global__ __launch_bounds__(256) void k_residual(DevPlan d, const double* __res
         }
         __syncthreads();
     }
-    if (tid < kResWidth) partial[(int64_t)c * kResWidth + tid] = sm[tid][0];
+    if (tid < kResWidth) partial[(int64_t)c * stride + tid] = sm[tid][0];
 }
 
 // Several right-hand sides: 16 lanes share a row, one column each, so K is read
@@ -2811,8 +2813,10 @@ void launch_bwd(bool many, const PanelTask* pt, int np, const SmallTask* sm, int
 void launch_residual(const DevPlan& d, const double* K, const double* B, int64_t ldb, const double* X, int64_t ldx,
                      double* Xr, double* R, int nrhs, const RowChunk* chunks, int nchunks, double* partial,
                      hipStream_t st) {
-    if (nrhs == 1) {
-        launch(k_residual, dim3(nchunks), dim3(256), 0, st, d, K, B, X, R, chunks, partial);
+    if (nrhs < kManyColumns) {
+        for (int q = 0; q < nrhs; ++q)
+            launch(k_residual, dim3(nchunks), dim3(256), 0, st, d, K, B + q * ldb, X + q * ldx, R + q * d.N, chunks,
+                   partial + q * kResWidth, nrhs * kResWidth);
         return;
     }
     launch(k_to_rows, dim3(blocks_for(d.N, 64)), dim3(256), 0, st, d.N, X, ldx, nrhs, Xr);

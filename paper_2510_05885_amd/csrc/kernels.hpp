@@ -10,6 +10,10 @@
 namespace ncl {
 
 constexpr int kNrhsMax = 16;   // columns per solve sweep (wider solves are chunked)
+// Columns from which sweeps and residuals take kNrhsMax at a time.  That costs the same
+// for any number of them (a solve at order 100k 1240 us, at 500k 3140, with one column 552
+// and 1392), so two go one by one: 1062 and 2733 us; three would take 1600 and 4100.
+constexpr int kManyColumns = 3;
 constexpr int kPanel = 64;       // pivot block width of the large-front path
 constexpr int kSmallMax = 128;   // largest front order of the LDS-resident path
 constexpr int kTile = 64;        // tile order of the large-front MFMA update
@@ -204,7 +208,8 @@ void launch_bwd(bool many, const PanelTask* pt, int np, const SmallTask* sm, int
 // ---- refinement -------------------------------------------------------------
 // R = B - K X; per chunk of rows (all of one system) and column, kResWidth figures:
 // max |r|, max |x|, max |b|, sum r^2, sum b^2, max |r_i| / (|K||x| + |b|)_i.
-// nrhs > 1: R is row-major, kNrhsMax a row, and Xr (N x kNrhsMax) is scratch.
+// From kManyColumns columns R is row-major, kNrhsMax a row, and Xr (N x kNrhsMax) is
+// scratch; with fewer R is N x nrhs by columns.
 void launch_residual(const DevPlan& d, const double* K, const double* B, int64_t ldb, const double* X, int64_t ldx,
                      double* Xr, double* R, int nrhs, const RowChunk* chunks, int nchunks, double* partial,
                      hipStream_t st);
