@@ -594,20 +594,13 @@ int build_plan(Plan& P, int form, const std::vector<SysInput>& sys, int ordering
 
         // ---------------- extend-add maps -----------------------------------
         P.rel_ptr.assign(nsn + 1, 0);
-        P.inv_ptr.assign(nsn + 1, 0);
         for (int s = 0; s < nsn; ++s) {
             const int np = P.sn_first[s + 1] - P.sn_first[s];
             const int64_t f = P.sn_rowptr[s + 1] - P.sn_rowptr[s];
             const int64_t c = f - np;
             P.rel_ptr[s + 1] = P.rel_ptr[s] + c;
-            const int par = P.sn_parent[s];
-            if (par >= 0 && P.sn_large[par])
-                P.inv_ptr[s + 1] = P.inv_ptr[s] + (P.sn_rowptr[par + 1] - P.sn_rowptr[par]);
-            else
-                P.inv_ptr[s + 1] = P.inv_ptr[s];
         }
         P.rel.resize(P.rel_ptr[nsn]);
-        P.inv.assign(P.inv_ptr[nsn], -1);
         for (int s = 0; s < nsn; ++s) {
             const int par = P.sn_parent[s];
             if (par < 0) continue;
@@ -625,7 +618,6 @@ int build_plan(Plan& P, int form, const std::vector<SysInput>& sys, int ordering
                     lr = (int)(it - pb);
                 }
                 P.rel[P.rel_ptr[s] + a] = lr;
-                if (P.sn_large[par]) P.inv[P.inv_ptr[s] + lr] = (int)a;
             }
         }
 
@@ -642,14 +634,9 @@ int build_plan(Plan& P, int form, const std::vector<SysInput>& sys, int ordering
         for (int s = 0; s < nsn; ++s) P.level_ptr[P.sn_level[s] + 1]++;
         for (int l = 0; l < P.nlevels; ++l) P.level_ptr[l + 1] += P.level_ptr[l];
         P.level_list.resize(nsn);
-        P.level_fmax.assign(P.nlevels, 0);
         {
             std::vector<int> f(P.level_ptr.begin(), P.level_ptr.end() - 1);
-            for (int s = 0; s < nsn; ++s) {
-                P.level_list[f[P.sn_level[s]]++] = s;
-                P.level_fmax[P.sn_level[s]] =
-                    std::max<int>(P.level_fmax[P.sn_level[s]], (int)(P.sn_rowptr[s + 1] - P.sn_rowptr[s]));
-            }
+            for (int s = 0; s < nsn; ++s) P.level_list[f[P.sn_level[s]]++] = s;
         }
 
         // ---------------- storage -------------------------------------------
@@ -735,13 +722,23 @@ int build_plan(Plan& P, int form, const std::vector<SysInput>& sys, int ordering
             if (large.empty()) continue;
             LargeStep st;
             st.level = l;
-            st.asm_first = (int64_t)P.large_asm.size() / 2;
+            st.asm_first = (int64_t)P.asm_col.size();
             for (int s : large) {
                 const int f = (int)(P.sn_rowptr[s + 1] - P.sn_rowptr[s]);
                 const int np = P.sn_first[s + 1] - P.sn_first[s];
                 st.asm_fmax = std::max(st.asm_fmax, f);
+                // the children's columns by the column j that they land on: (child, its column)
+                std::vector<int64_t> at(f + 1, 0);
+                for (int k = P.child_ptr[s]; k < P.child_ptr[s + 1]; ++k)
+                    for (int64_t q = P.rel_ptr[P.child_list[k]]; q < P.rel_ptr[P.child_list[k] + 1]; ++q) at[P.rel[q] + 1]++;
+                for (int j = 0; j < f; ++j) at[j + 1] += at[j];
+                std::vector<std::pair<int, int>> seg(at[f]);
+                for (int k = P.child_ptr[s]; k < P.child_ptr[s + 1]; ++k) {
+                    const int ch = P.child_list[k];
+                    for (int64_t q = P.rel_ptr[ch]; q < P.rel_ptr[ch + 1]; ++q)
+                        seg[at[P.rel[q]]++] = {ch, (int)(q - P.rel_ptr[ch])};
+                }
                 for (int j = 0; j < f; ++j) {
-                    P.large_asm.push_back(s); P.large_asm.push_back(j);
                     if (P.asm_seg_ptr.empty()) P.asm_seg_ptr.push_back(0);
                     P.asm_col.push_back(P.L_off[s] + (int64_t)j * f);
                     P.asm_fj.push_back(f); P.asm_fj.push_back(j);
@@ -751,10 +748,8 @@ int build_plan(Plan& P, int form, const std::vector<SysInput>& sys, int ordering
                     } else {
                         P.asm_kr.push_back(0); P.asm_kr.push_back(0);
                     }
-                    for (int k = P.child_ptr[s]; k < P.child_ptr[s + 1]; ++k) {
-                        const int ch = P.child_list[k];
-                        const int b = P.inv[P.inv_ptr[ch] + j];
-                        if (b < 0) continue;
+                    for (int64_t q = j > 0 ? at[j - 1] : 0; q < at[j]; ++q) {   // (at[j]: now its end)
+                        const int ch = seg[q].first, b = seg[q].second;
                         const int cc = (int)(P.sn_rowptr[ch + 1] - P.sn_rowptr[ch]) - (P.sn_first[ch + 1] - P.sn_first[ch]);
                         P.asm_seg_cb.push_back(P.CB_off[ch] + (int64_t)b * P.CB_ld[ch]);
                         P.asm_seg_rel.push_back(P.rel_ptr[ch]);
@@ -763,7 +758,7 @@ int build_plan(Plan& P, int form, const std::vector<SysInput>& sys, int ordering
                     P.asm_seg_ptr.push_back((int64_t)P.asm_seg_cb.size());
                 }
             }
-            st.asm_count = (int64_t)P.large_asm.size() / 2 - st.asm_first;
+            st.asm_count = (int64_t)P.asm_col.size() - st.asm_first;
             int maxp = 0;
             for (int s : large) maxp = std::max(maxp, P.sn_first[s + 1] - P.sn_first[s]);
             for (int k0 = 0; k0 < maxp; k0 += nb) {

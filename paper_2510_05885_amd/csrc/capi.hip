@@ -91,7 +91,7 @@ struct ncl_kkt_s {
     // schedule arrays (device)
     FrontTask* small_tasks = nullptr;
     FrontPlan fp{};
-    int *level_list = nullptr, *large_asm = nullptr, *gather = nullptr;
+    int* gather = nullptr;
     PanelTask *fwd_tasks = nullptr, *bwd_tasks = nullptr;
     SmallTask* solve_small = nullptr;
     LargeTask *large_panel = nullptr, *large_upd = nullptr, *large_diag = nullptr;
@@ -221,8 +221,6 @@ void setup_device(ncl_kkt_s* h) {
     d.N = P.N;
     d.n_primal = P.form == NCL_STABILIZED ? P.sys_n[0] : P.N;
     d.S = P.S;
-    d.n_fronts = P.nsn;
-    d.form = P.form;
     h->nnzF = (int64_t)P.Kj.size();
     d.Kp = upload(h, P.Kp);
     d.Kj = upload(h, P.Kj);
@@ -231,32 +229,16 @@ void setup_device(ncl_kkt_s* h) {
     d.prod_a = upload(h, P.prod_a);
     d.prod_b = upload(h, P.prod_b);
     d.row_sys = upload(h, P.row_sys);
-    d.row_sign = upload(h, P.row_sign);
     d.perm = upload(h, P.perm);
     {
         std::vector<int8_t> ps(P.N);
         for (int64_t k = 0; k < P.N; ++k) ps[k] = P.row_sign[P.perm[k]];
         d.piv_sign = upload(h, ps);
     }
-    d.sn_first = upload(h, P.sn_first);
-    d.sn_rowptr = upload(h, P.sn_rowptr);
     d.sn_rows = upload(h, P.sn_rows);
-    d.child_ptr = upload(h, P.child_ptr);
-    d.child_list = upload(h, P.child_list);
-    d.sn_sys = upload(h, P.sn_sys);
-    d.sn_parent = upload(h, P.sn_parent);
-    d.kent_ptr = upload(h, P.kent_ptr);
     d.kent_csr = upload(h, P.kent_csr);
     d.kent_pos = upload(h, P.kent_pos);
-    d.kcol_ptr = upload(h, P.kcol_ptr);
-    d.kcol_base = upload(h, P.kcol_base);
-    d.rel_ptr = upload(h, P.rel_ptr);
     d.rel = upload(h, P.rel);
-    d.inv_ptr = upload(h, P.inv_ptr);
-    d.inv = upload(h, P.inv);
-    d.L_off = upload(h, P.L_off);
-    d.CB_off = upload(h, P.CB_off);
-    d.CB_ld = upload(h, P.CB_ld);
     d.asm_col = upload(h, P.asm_col);
     d.asm_fj = upload(h, P.asm_fj);
     d.asm_kr = upload(h, P.asm_kr);
@@ -295,8 +277,6 @@ void setup_device(ncl_kkt_s* h) {
         h->fp.kent_csr = d.kent_csr;
         h->fp.piv_sign = d.piv_sign;
     }
-    h->level_list = upload(h, P.level_list);
-    h->large_asm = upload(h, P.large_asm);
     {
         // tasks of `width` ints (front, panel, then first row, column) as records
         auto records = [&](const std::vector<int>& v, int width) {

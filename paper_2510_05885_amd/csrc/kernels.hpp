@@ -70,8 +70,6 @@ struct DevPlan {
     int64_t N;
     int64_t n_primal;          // rows [0, n_primal) form the primal block (N for the condensed form)
     int S;
-    int form;
-    int n_fronts;              // supernodes (fronts)
     // full CSR of K with value sources
     const int64_t* Kp;
     const int* Kj;
@@ -81,30 +79,14 @@ struct DevPlan {
     const int* prod_a;
     const int* prod_b;
     const int* row_sys;
-    const int8_t* row_sign;
     const int* perm;
-    const int8_t* piv_sign;    // row_sign in pivot order
+    const int8_t* piv_sign;    // per pivot: +1 primal, -1 dual
     // supernodes
-    const int* sn_first;
-    const int64_t* sn_rowptr;
     const int* sn_rows;
-    const int* child_ptr;
-    const int* child_list;
-    const int* sn_sys;
-    const int* sn_parent;      // parent supernode or -1
     const int* jrow_of;        // row of J of each stored J entry (condensed form)
-    const int64_t* kent_ptr;
     const int64_t* kent_csr;
     const int* kent_pos;
-    const int64_t* kcol_ptr;
-    const int64_t* kcol_base;
-    const int64_t* rel_ptr;
     const int* rel;
-    const int64_t* inv_ptr;
-    const int* inv;
-    const int64_t* L_off;
-    const int64_t* CB_off;
-    const int* CB_ld;
     // large-front column assembly tasks (see Plan::asm_*)
     const int64_t* asm_col;
     const int* asm_fj;

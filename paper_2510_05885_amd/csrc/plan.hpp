@@ -36,7 +36,7 @@ struct LevelBatch {            // one launch of the small-front kernel
 
 struct LargeStep {             // launches of the large-front path for one level
     int level = 0;
-    int64_t asm_first = 0, asm_count = 0;     // (front, column) tasks in large_asm
+    int64_t asm_first = 0, asm_count = 0;     // (front, column) tasks in Plan::asm_*
     int asm_fmax = 0;                         // largest front of the level (column buffer size)
     // per panel step k: diagonal-block, panel (TRSM) and update tasks
     std::vector<int64_t> diag_first, diag_count;
@@ -123,9 +123,6 @@ struct Plan {
     // extend-add maps: child CB row a -> local row in the parent front
     std::vector<int64_t> rel_ptr;    // nsn+1 (length c_s)
     std::vector<int> rel;
-    // large parents: for each child, parent local row -> child CB index or -1
-    std::vector<int64_t> inv_ptr;    // nsn+1 (length f_parent when the parent is large)
-    std::vector<int> inv;
 
     // ---- storage ---------------------------------------------------------
     std::vector<int64_t> L_off;      // offset of front s's L (ld = f) in the factor buffer
@@ -143,17 +140,15 @@ struct Plan {
     std::vector<LevelBatch> small_batches;
     std::vector<int> level_ptr;      // nlevels+1 into level_list (all fronts by level)
     std::vector<int> level_list;
-    std::vector<int> level_fmax;     // largest front of each level
     std::vector<LargeStep> large_steps;
     // large-front tasks
-    std::vector<int> large_asm;      // pairs (front, column)
-    // per large_asm task: column base in the factor buffer, (f, j), K-entry
-    // range, and its contribution segments (children whose CB has a column
+    // assembly tasks (front, column j): column base in the factor buffer, (f, j),
+    // K-entry range, and its contribution segments (children whose CB has a column
     // mapping to j): CB column offset, relative-index offset, (first row, rows)
     std::vector<int64_t> asm_col, asm_kr, asm_seg_ptr, asm_seg_cb, asm_seg_rel;
     std::vector<int> asm_fj, asm_seg_bc;
     std::vector<int> large_diag;     // pairs (front, k0): diagonal block update, factorization, inverse
-    std::vector<int> large_panel;    // triples (front, k0, 32-row block start >= k0 + panel)
+    std::vector<int> large_panel;    // triples (front, k0, 32-row block start >= min(k0 + panel, pivots))
     std::vector<int> large_upd;      // quads (front, k0, tile row start, tile col start); the next
                                      // panel's diagonal tile is left to large_diag
     // solve schedule
