@@ -795,26 +795,47 @@ int build_plan(Plan& P, int form, const std::vector<SysInput>& sys, int ordering
         // ---------------- solve schedule -----------------------------------
         {
             const int PW = cfg.panel;
-            // gather tables: row i of front s takes the update-vector entries
-            // gather[gat[s] + k f + i], k = 0 .. gk[s] - 1, in the children's order
+            // gather tables, see Plan::gather.  A table as deep as its deepest row would take
+            // blocks x border entries for many blocks with a border row in common: the
+            // table has at most 16 entries a row or eight per entry it holds, the rest
+            // is a list.
             std::vector<int64_t> gat(nsn, 0);
-            std::vector<int> gk(nsn, 0), depth;
-            if (P.U_elems >= (int64_t)1 << 31) throw AnalyzeError(-3, "update vectors beyond 2^31 entries");
+            std::vector<int> gk(nsn, 0), deep(nsn, 0), depth;
             for (int s = 0; s < nsn; ++s) {
                 const int f = (int)(P.sn_rowptr[s + 1] - P.sn_rowptr[s]);
                 depth.assign(f, 0);
+                int64_t total = 0;
                 for (int k = P.child_ptr[s]; k < P.child_ptr[s + 1]; ++k) {
                     const int ch = P.child_list[k];
                     for (int64_t q = P.rel_ptr[ch]; q < P.rel_ptr[ch + 1]; ++q) gk[s] = std::max(gk[s], ++depth[P.rel[q]]);
+                    total += P.rel_ptr[ch + 1] - P.rel_ptr[ch];
                 }
+                const int64_t cap = std::max<int64_t>(16, 8 * total / f);
                 gat[s] = (int64_t)P.gather.size();
-                P.gather.resize(P.gather.size() + (size_t)gk[s] * f, -1);
+                std::vector<int64_t> next;   // a deep row's next place in the list
+                if (gk[s] > cap) {
+                    gk[s] = (int)cap;
+                    deep[s] = 1;
+                    const int64_t list = gat[s] + cap * f + f + 1;
+                    next.resize(f);
+                    P.gather.resize(list, -1);
+                    int64_t at = 0;
+                    for (int i = 0; i < f; ++i) {
+                        P.gather[gat[s] + cap * f + i] = (int)at;
+                        next[i] = list + at;
+                        at += std::max<int64_t>(0, depth[i] - cap);
+                    }
+                    P.gather[list - 1] = (int)at;
+                    P.gather.resize(list + at, -1);
+                } else {
+                    P.gather.resize(P.gather.size() + (size_t)gk[s] * f, -1);
+                }
                 std::fill(depth.begin(), depth.end(), 0);
                 for (int k = P.child_ptr[s]; k < P.child_ptr[s + 1]; ++k) {
                     const int ch = P.child_list[k];
                     for (int64_t q = P.rel_ptr[ch], a = 0; q < P.rel_ptr[ch + 1]; ++q, ++a) {
-                        const int i = P.rel[q];
-                        P.gather[gat[s] + (int64_t)depth[i]++ * f + i] = (int)(P.U_off[ch] + a);
+                        const int i = P.rel[q], k = depth[i]++;
+                        P.gather[k < gk[s] ? gat[s] + (int64_t)k * f + i : next[i]++] = (int)(P.U_off[ch] + a);
                     }
                 }
             }
@@ -828,7 +849,7 @@ int build_plan(Plan& P, int form, const std::vector<SysInput>& sys, int ordering
                 t.w1 = std::min(PW, t.p - c0);
                 t.w2 = std::min(PW, t.p - c0 - t.w1);
                 t.L_off = P.L_off[s]; t.U_off = P.U_off[s]; t.M_off = P.M_off[s]; t.rows_off = P.sn_rowptr[s];
-                t.gat = gat[s]; t.gk = c0 == 0 ? gk[s] : 0;
+                t.gat = gat[s]; t.gk = c0 == 0 ? gk[s] : 0; t.deep = deep[s];
                 t.ntask = std::max(1, (t.f - c0 - t.w1 - t.w2 + 63) / 64);
                 return t;
             };
@@ -847,7 +868,7 @@ int build_plan(Plan& P, int form, const std::vector<SysInput>& sys, int ordering
                     if (P.sn_large[s]) {
                         npair = std::max(npair, (p + 2 * PW - 1) / (2 * PW));
                     } else {
-                        P.solve_small.push_back(SmallTask{P.sn_first[s], p, f, gk[s], P.L_off[s], P.U_off[s],
+                        P.solve_small.push_back(SmallTask{P.sn_first[s], p, f, gk[s], deep[s], 0, P.L_off[s], P.U_off[s],
                                                           P.sn_rowptr[s], gat[s]});
                         sm.bytes += 8.0 * ((double)p * f - (double)p * (p - 1) / 2.0) * P.sn_nnz_ratio[s];
                     }

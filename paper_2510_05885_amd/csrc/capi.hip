@@ -297,6 +297,7 @@ void setup_device(ncl_kkt_s* h) {
     h->fwd_tasks = upload(h, P.fwd_tasks);
     h->bwd_tasks = upload(h, P.bwd_tasks);
     h->solve_small = upload(h, P.solve_small);
+    if (P.U_elems >= (int64_t)1 << 31) throw std::bad_alloc();   // (its offsets; 256 GiB of update vectors)
     h->gather = upload(h, P.gather);
     // row chunks (never straddling two systems), one block each: up to 256 rows, in
     // multiples of 8; smaller while there are fewer than 2048 of them (eight a CU),

@@ -1212,23 +1212,37 @@ __global__ void k_permute_out(DevPlan d, const T* __restrict__ X, int nrhs, doub
 //     with the two panels, or, for a front's first pair, two records of their
 //     own after the level's last step.  No task waits for another of its launch.
 // Children's update vectors come through a table: row i of the front takes
-// U[gat[k f + i]], k = 0 .. gk - 1 in the children's order (-1: none).
+// U[gat[k f + i]], k = 0 .. gk - 1 in the children's order (-1: none), and then,
+// where rows have more (deep), those of its list, see Plan::gather.
 // The sweeps are bound by the latency of their chain of launches; panel by
 // panel, with the one-wave fronts forked to a second stream, a forward step
 // took 10 us, a backward one 6 and the fork and join 9 (order 20k).
 
 // Values of a pair's pivots and of the task's rows before the step.
 template <typename T>
-__device__ __forceinline__ T gather1(const T* __restrict__ U, const int* __restrict__ gat, int f, int gk, int i, T v) {
+__device__ __forceinline__ T gather1(const T* __restrict__ U, const int* __restrict__ gat, int f, int gk, bool deep,
+                                    int i, T v) {
     for (int k0 = 0; k0 < gk; k0 += 4) {
         int o[4];
         T u[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) o[k] = k0 + k < gk ? gat[(k0 + k) * f + i] : -1;
+        for (int k = 0; k < 4; ++k) o[k] = k0 + k < gk ? gat[(int64_t)(k0 + k) * f + i] : -1;
 #pragma unroll
         for (int k = 0; k < 4; ++k) u[k] = U[max(o[k], 0)];
 #pragma unroll
         for (int k = 0; k < 4; ++k) v += o[k] >= 0 ? u[k] : T(0);
+    }
+    if (deep) {   // uniform
+        const int* __restrict__ start = gat + (int64_t)gk * f;
+        const int* __restrict__ list = start + f + 1;
+        const int q1 = start[i + 1];
+        for (int q = start[i]; q < q1; q += 8) {
+            T u[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) u[k] = U[list[min(q + k, q1 - 1)]];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v += q + k < q1 ? u[k] : T(0);
+        }
     }
     return v;
 }
@@ -1278,7 +1292,7 @@ __device__ __forceinline__ void fwd_panels1(const PanelTask* tk, const T* __rest
         if (in) {
             if (gi < p) b = Y[first + gi];
             else if (c0 > 0) b = Us[gi - p];
-            if (tk->gk > 0) b = gather1(U, gatab + tk->gat, f, tk->gk, gi, b);
+            if (tk->gk > 0) b = gather1(U, gatab + tk->gat, f, tk->gk, tk->deep != 0, gi, b);
         }
         (tid < 128 ? v[tid] : rw[tid - 128]) = b;
     }
@@ -1359,8 +1373,8 @@ __device__ __forceinline__ void fwd_front1(const SmallTask* tk, const T* __restr
     T v0 = lane < p ? Y[first + lane] : T(0);
     T v1 = kHi && lane + 64 < p ? Y[first + lane + 64] : T(0);
     if (gk > 0) {
-        v0 = gather1(U, gat, f, gk, i0, v0);
-        if (kHi) v1 = gather1(U, gat, f, gk, i1, v1);
+        v0 = gather1(U, gat, f, gk, tk->deep != 0, i0, v0);
+        if (kHi) v1 = gather1(U, gat, f, gk, tk->deep != 0, i1, v1);
     }
     for (int kb = 0; kb < p; kb += kC) {
         if (kb > 0) load(kb);
@@ -1740,19 +1754,37 @@ __device__ __forceinline__ typename Mfma<T>::acc_t product16(const T (&op)[4][4]
 // front; row(r): the row of item r, from i0.
 template <typename T, typename Row>
 __device__ __forceinline__ void gather16(typename Mfma<T>::acc_t& a, const T* __restrict__ U,
-                                         const int* __restrict__ gat, int f, int gk, int i0, int iend, int lr, Row row) {
+                                         const int* __restrict__ gat, int f, int gk, bool deep, int i0, int iend,
+                                         int lr, Row row) {
     for (int k = 0; k < gk; ++k) {
         int o[4];
         T u[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int i = i0 + row(r);
-            o[r] = i < iend ? gat[k * f + i] : -1;
+            o[r] = i < iend ? gat[(int64_t)k * f + i] : -1;
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) u[r] = U[(int64_t)max(o[r], 0) * kNrhsMax + lr];
 #pragma unroll
         for (int r = 0; r < 4; ++r) a[r] += o[r] >= 0 ? u[r] : T(0);
+    }
+    if (deep) {   // uniform
+        const int* __restrict__ start = gat + (int64_t)gk * f;
+        const int* __restrict__ list = start + f + 1;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = i0 + row(r);
+            if (i >= iend) continue;
+            const int q1 = start[i + 1];
+            for (int q = start[i]; q < q1; q += 8) {
+                T u[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) u[k] = U[(int64_t)list[min(q + k, q1 - 1)] * kNrhsMax + lr];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) a[r] += q + k < q1 ? u[k] : T(0);
+            }
+        }
     }
 }
 
@@ -1782,7 +1814,7 @@ __device__ __forceinline__ void fwd_panels16(const PanelTask* tk, const T* __res
             const int i = l0 + Mfma<T>::row(lk, r);
             if (i < w) a[r] = Y[(int64_t)(first + c0 + i) * kNrhsMax + lr];
         }
-        if (gk > 0) gather16<T>(a, U, gat, f, gk, c0 + l0, c0 + w, lr, [&](int r) { return Mfma<T>::row(lk, r); });
+        if (gk > 0) gather16<T>(a, U, gat, f, gk, tk->deep != 0, c0 + l0, c0 + w, lr, [&](int r) { return Mfma<T>::row(lk, r); });
 #pragma unroll
         for (int r = 0; r < 4; ++r) b[(l0 + Mfma<T>::row(lk, r)) * kNrhsMax + lr] = a[r];
     }
@@ -1796,7 +1828,7 @@ __device__ __forceinline__ void fwd_panels16(const PanelTask* tk, const T* __res
                 else if (c0 > 0) a[r] = Us[(int64_t)(i - p) * kNrhsMax + lr];
             }
         }
-        if (gk > 0) gather16<T>(a, U, gat, f, gk, i0, r1, lr, [&](int r) { return Mfma<T>::row(lk, r); });
+        if (gk > 0) gather16<T>(a, U, gat, f, gk, tk->deep != 0, i0, r1, lr, [&](int r) { return Mfma<T>::row(lk, r); });
     }
     // every operand before the first product: Z1, Z2 and L21 for the wave's 16 rows
     // of y, L for its rows (zero blocks past the diagonal are multiplied too:
@@ -1946,7 +1978,7 @@ __device__ __forceinline__ void fwd_front16(const SmallTask* tk, const T* __rest
             const int i = 16 * ti + 4 * r + lk;
             if (i < p) a[ti][r] = Y[(int64_t)(first + i) * kNrhsMax + lr];
         }
-        if (gk > 0) gather16<T>(a[ti], U, gatab + tk->gat, f, gk, 16 * ti, f, lr, [&](int r) { return 4 * r + lk; });
+        if (gk > 0) gather16<T>(a[ti], U, gatab + tk->gat, f, gk, tk->deep != 0, 16 * ti, f, lr, [&](int r) { return 4 * r + lk; });
     }
 #pragma unroll
     for (int q = 0; q < NT; ++q) {

@@ -50,14 +50,14 @@ struct LargeStep {             // launches of the large-front path for one level
 // order f); task `index` of ntask (index -1: a record that only finishes).
 // Backward: sums go to partial slot slot0 + index; a task with fntask > 0
 // first finishes panel `which` of the pair at fc0 from its fntask sums at
-// fslot0.  gk: depth of the front's gather table at gat (0 unless c0 = 0).
+// fslot0.  gat, gk, deep: the front's gather table (gk = 0 unless c0 = 0).
 struct PanelTask {
-    int first, p, f, c0, w1, w2, r0, r1, index, ntask, slot0, gk;
+    int first, p, f, c0, w1, w2, r0, r1, index, ntask, slot0, gk, deep;
     int fc0, fw1, fw2, fslot0, fntask, which;
     int64_t L_off, U_off, M_off, rows_off, gat;
 };
 struct SmallTask {             // a small front's sweep (one wave)
-    int first, p, f, gk;
+    int first, p, f, gk, deep, pad;
     int64_t L_off, U_off, rows_off, gat;
 };
 // One launch of a sweep, in execution order.  k: pair step of the level (backward
@@ -155,7 +155,10 @@ struct Plan {
     std::vector<SolveStep> fwd_steps, bwd_steps;
     std::vector<PanelTask> fwd_tasks, bwd_tasks;
     std::vector<SmallTask> solve_small;
-    std::vector<int> gather;         // per front gk x f offsets of update-vector entries, -1 none
+    // Gather tables of the update vectors: row i of a front takes entries gather[gat +
+    // k f + i], k = 0 .. gk - 1 (-1: none), in the children's order; where a row takes
+    // more (`deep`), f + 1 starts and the further entries by rows follow the table.
+    std::vector<int> gather;
     int64_t solve_max_slots = 0;     // backward tasks in the largest step (partial-sum slots)
 
     // ---- stats ------------------------------------------------------------

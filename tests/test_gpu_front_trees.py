@@ -90,3 +90,16 @@ def test_star(root, children, precision):
         tree.add([15, 16, 17, 31, 33, 47, 48, 49, 65][k], _below(rng, root, [14, 13, 15, 17, 30, 16, 9, 25, 21][k]))
     tree.add(root)
     _check(tree, precision, columns=(1, 3, 16), passes=2)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_ir"])
+@pytest.mark.parametrize("root", [30, 64, 128, 193])
+def test_many_children_on_one_row(root, precision):
+    """60 leaves with the root's first row in common: that row's update entries go beyond the sweeps' gather table
+    into its list, with 1, 3 and 16 right-hand sides."""
+    rng = np.random.default_rng(root)
+    tree = Tree(root)
+    for _ in range(60):
+        tree.add(25, _below(rng, root, 3))
+    tree.add(root)
+    _check(tree, precision, columns=(1, 3, 16), passes=2)

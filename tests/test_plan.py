@@ -3,6 +3,8 @@ the symbolic plan (ordering, supernodes, front row lists) against a brute-force
 dense symbolic factorization.  No GPU needed (ncl_kkt_analyze_host)."""
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -150,3 +152,31 @@ def test_user_permutation_is_kept_up_to_equivalent_reordering():
     nz_user = int(_symbolic_L(K, up).sum())
     nz_plan = int(_symbolic_L(K, k.perm()).sum())
     assert nz_plan == nz_user
+
+
+def test_block_arrow_plan_is_linear_in_its_rows():
+    """20,000 blocks under one border of 3,000 with its first row in common: the sweeps' gather table has as many
+    entries as the blocks' rows and a few per border row, not blocks x border (240 MB)."""
+    code = """
+import resource, numpy as np
+from paper_2510_05885_amd import ncl_kkt as nk, synth
+nb, B, w = 20000, 3000, 4
+n = nb * w + B
+cols = []
+for b in range(nb):
+    for j in range(w):
+        cols.append(np.array([b * w + k for k in range(j, w)] + [nb * w, nb * w + 1 + (7 * b + 3) % (B - 1)]))
+cols += [np.array([nb * w + j]) for j in range(B)]
+colptr = np.concatenate([[0], np.cumsum([len(c) for c in cols])]).astype(np.int32)
+rowidx = np.concatenate(cols).astype(np.int32)
+inp = synth.KKTInput(n, 0, colptr, rowidx, np.zeros(len(rowidx)), np.zeros(n), np.zeros(1, np.int32),
+                     np.zeros(0, np.int32), np.zeros(0), 1.0)
+k0 = nk.KKT.from_input(synth.random_system(30, 5), host_only=True)
+before = resource.getrusage(resource.RUSAGE_SELF).ru_maxrss
+kkt = nk.KKT.from_input(inp, host_only=True, ordering="natural")
+after = resource.getrusage(resource.RUSAGE_SELF).ru_maxrss
+print(len(kkt.supernodes()[1]), (after - before) // 1024)
+"""
+    out = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, check=True).stdout
+    fronts, grown = (int(v) for v in out.split())
+    assert fronts > 15_000 and grown < 160, out
