@@ -413,15 +413,6 @@ void setup_device(ncl_kkt_s* h) {
     h->host_only = false;
 }
 
-int pick_small_max(int& fmax_out) {
-    int dev = 0, lds = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return NCL_ERR_HIP;
-    if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) return NCL_ERR_HIP;
-    int f = (int)std::floor(std::sqrt((double)lds / 8.0));
-    fmax_out = std::min(f, 128);
-    return NCL_OK;
-}
-
 void fill_defaults(ncl_kkt_options* o) {
     o->form = NCL_CONDENSED;
     o->precision = NCL_FP64;
@@ -462,10 +453,9 @@ int do_analyze(ncl_kkt_t* out, const ncl_kkt_options* o, const std::vector<SysIn
     if (h->opt.persistent > 0) { delete h; return NCL_ERR_ARG; }
     PlanConfig cfg;
     if (!host_only) {
-        int fm = 90;
-        int rc = pick_small_max(fm);
-        if (rc) { delete h; return rc; }
-        cfg.small_front_max = fm;
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess) { delete h; return NCL_ERR_HIP; }
+        cfg.small_front_max = kSmallMax;
     }
     if (h->opt.small_front_max > 0) {
         if (h->opt.small_front_max > cfg.small_front_max && !host_only) { delete h; return NCL_ERR_ARG; }

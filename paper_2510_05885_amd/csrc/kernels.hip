@@ -2,22 +2,23 @@
 //
 //   assembly   K = W + Sigma + rho J^T J (Sec. 3.3, eq. K1) or the stabilized
 //              [[W + Sigma, J^T], [J, -1/rho I]] (Sec. 3.2, eq. K2r) on the
-//              fixed pattern, one thread per stored entry, FP64; row and
-//              system norms by two-stage deterministic reductions.
+//              fixed pattern in FP64, a block per chunk of rows, which also
+//              takes the rows' norms.
 //   factor     supernodal multifrontal LDL^T with the static-pivot rule of
 //              Sec. 3.1 (|d| < thr -> d = sign * thr, sign of the pivot's
 //              block before reordering); fronts processed level by level:
-//                * small fronts: one workgroup per front, the whole front in
-//                  LDS (assembly, extend-add of the children's contribution
-//                  blocks, partial factorization, write-out);
+//                * small fronts: one or four waves per front, its tiles in
+//                  MFMA accumulators (children's contribution blocks gathered
+//                  into them), its pivot columns in LDS;
 //                * large fronts: the front lives in the factor buffer; one
 //                  launch assembles it column by column, then per pivot panel
-//                  a one-wave diagonal-block factor, a panel solve, and a
-//                  trailing update on MFMA (v_mfma_f64_16x16x4 / f32).
+//                  a diagonal-block factor and its inverse by four waves, a
+//                  panel solve, and a trailing update on MFMA
+//                  (v_mfma_f64_16x16x4 / f32) beside the next diagonal block.
 //   solve      level-scheduled multifrontal forward sweep (children's
 //              update vectors pulled by the parent: no atomics), D^-1, and
-//              backward sweep; right-hand sides chunked through LDS.
-//   refinement residual b - K x with per-system max norms.
+//              backward sweep, for one right-hand side or, on MFMA, sixteen.
+//   refinement residual b - K x with per-system backward errors.
 // All reductions are deterministic; integer atomics only count inertia.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
@@ -1163,8 +1164,8 @@ __global__ __launch_bounds__(256, 2) void k_large_dstep(DevPlan d, const LargeTa
 // ---------------------------------------------------------------------------
 // solves
 // ---------------------------------------------------------------------------
-// Vectors in pivot order, `ld` values per row: 1 for one right-hand side,
-// kNrhsMax (unused columns zero) for several, so that a row's columns are
+// Vectors in pivot order: one value a row for one right-hand side, kNrhsMax
+// (unused columns zero) for several, so that a row's columns are
 // contiguous and a 16-row, 16-column piece is one MFMA operand.
 //   Y   the right-hand side, updated in place for rows not yet solved
 //   Y2  the pivots' y after the forward sweep
@@ -1192,7 +1193,7 @@ __global__ void k_permute_out(DevPlan d, const T* __restrict__ X, int nrhs, doub
 
 // One launch per step of a level holds the tasks of its large fronts (one
 // workgroup each) and, in the level's first step, its small fronts (one wave
-// each).  A large front's panels are taken two at a time, columns
+// each, or a workgroup each in a backward step of few).  A large front's panels are taken two at a time, columns
 // [c0, c0 + w1) and [c0 + w1, c0 + w1 + w2) (w1 = 64 when w2 > 0), through
 //   G1, G2  the inverses Z = L_kk^-1 of their diagonal blocks (unit lower,
 //           with Z^T in the strictly upper triangle) and
@@ -2458,9 +2459,6 @@ __global__ __launch_bounds__(4 * kInertiaSlots) void k_end(DevPlan d, const doub
 }
 
 // ---------------------------------------------------------------------------
-// adjoint (condensed form)
-// ---------------------------------------------------------------------------
-// ---------------------------------------------------------------------------
 // slack elimination (K1s) and the recovery of the rest of the Newton step
 // ---------------------------------------------------------------------------
 // Every row r of J carries Sigma_s[r] >= 0 (its slack's barrier term) or
@@ -2573,6 +2571,9 @@ __global__ void k_barrier_sigma(int64_t n, const double* __restrict__ x, const d
     sigma[i] = z_l[i] / (x[i] - l[i]) + z_u[i] / (u[i] - x[i]);
 }
 
+// ---------------------------------------------------------------------------
+// adjoint (condensed form)
+// ---------------------------------------------------------------------------
 __global__ void k_jmul(int64_t nrows, const int64_t* __restrict__ Jp, const int* __restrict__ Jj,
                        const double* __restrict__ Jv, const double* __restrict__ X, const double* __restrict__ Lam,
                        int64_t ld, int nrhs, double* JX, double* JL) {

@@ -169,7 +169,7 @@ void launch_large_dstep(const DevPlan& d, const LargeTask* dtasks, int nd, const
                         T* D, T* M, hipStream_t st);
 
 // ---- solves -----------------------------------------------------------------
-// Vectors in pivot order with one value a row, or with kNrhsMax ("many", nrhs > 1;
+// Vectors in pivot order with one value a row (nrhs = 1), or with kNrhsMax ("many";
 // unused columns zero).
 // B: column q of row i (caller's order) at B[i si + q sq].
 template <typename T>

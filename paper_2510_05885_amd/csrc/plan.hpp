@@ -10,11 +10,8 @@
 
 namespace ncl {
 
-// Fronts of order above this bound use the global-memory path.  The LDS path
-// stores a full front x front tile of T; the bound is set per plan from the
-// device's LDS limit and the element size.
 struct PlanConfig {
-    int small_front_max = 90;   // fronts with f <= this run in one workgroup in LDS
+    int small_front_max = 90;   // fronts with f <= this run in one workgroup (at most kSmallMax)
     int panel = 64;             // pivot block width of the large-front path
     int tile = 64;              // tile order of the large-front update
     int nd_leaf = 64;           // nested-dissection leaf size (compressed vertices)
@@ -56,7 +53,7 @@ struct PanelTask {
     int fc0, fw1, fw2, fslot0, fntask, which;
     int64_t L_off, U_off, M_off, rows_off, gat;
 };
-struct SmallTask {             // a small front's sweep (one wave)
+struct SmallTask {             // a small front's sweep
     int first, p, f, gk, deep, pad;
     int64_t L_off, U_off, rows_off, gat;
 };
