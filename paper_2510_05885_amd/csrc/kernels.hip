@@ -317,8 +317,8 @@ __device__ __forceinline__ void diag_zrow(const typename Mfma<T>::acc_t& S, T* B
 // Factors the block whose tiles are in acc (first w pivots; entries beyond are
 // taken as the identity), leaving L strictly below the diagonal of B, Z
 // transposed above it (rows past the last sub-panel unwritten) and the pivots
-// in dv.  Bit c of negmask: pivot c takes the negative sign; lane 0 of wave 0
-// adds the counts of the w pivots to cnt[4].  Called by all 256 threads; B is
+// in dv.  Bit c of negmask: pivot c takes the negative sign; wave 0 adds the
+// counts of the w pivots to its cnt[4].  Called by all 256 threads; B is
 // free on entry; ends with a barrier.
 template <typename T>
 __device__ __forceinline__ void diag_factor(typename Mfma<T>::acc_t (&acc)[3], T* B, T* dv,
