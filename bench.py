@@ -56,15 +56,15 @@ GATE_OMEGA, GATE_CW = 1e-10, 1e-14
 # counter reads for a device copy of known size (--calibrate-copy).  Valid
 # only for the kernel source they were taken on: null once kernels.hip
 # changes.  Source: profiles/pmc_traffic_opf_n500k_fp64.txt.
-TRAFFIC = {"kernels_sha1": "d00f3bb70444df4194ff439f88ef812cb1dddd8e", "fetch_scale": 2.00, "write_scale": 1.00,
-           "kib": {"solve_sweeps": (6349.8, 223.4),
-                   "large_update_mfma": (13833.3, 19663.8),
-                   "large_panel": (3968.8, 6303.7),
-                   "large_diag": (2085.3, 5609.8),
-                   "large_assembly": (26964.1, 51086.0),
-                   "small_fronts": (12373.6, 19073.3),
-                   "assemble": (217298.0, 51849.0),
-                   "residual": (65730.6, 2263.8)}}
+TRAFFIC = {"kernels_sha1": "67b0837004cf61d7553504bba63089651a6c12c6", "fetch_scale": 2.00, "write_scale": 1.00,
+           "kib": {"solve_sweeps": (6334.1, 223.4),
+                   "large_update_mfma": (13836.1, 19662.5),
+                   "large_panel": (3966.8, 6303.5),
+                   "large_diag": (2077.7, 5609.8),
+                   "large_assembly": (26963.5, 51086.0),
+                   "small_fronts": (12483.4, 19073.3),
+                   "assemble": (216891.6, 51851.0),
+                   "residual": (65815.6, 2262.0)}}
 
 
 def kernels_sha1():
